@@ -213,17 +213,17 @@ int duqpp_mxfp4_gemm_tiled(const uint8_t* a_codes_t, const uint8_t* a_scales_t,
  * NOT PART OF THE CONTRACT -- a hook for tests and measurements that may change with the kernels:
  * duqpp_mxfp4_gemm_tiled on one named kernel instead of the one the library would
  * pick for the shape, so that every kernel can be checked at every shape.  Same arguments, checks and result.
- * A kernel that cannot run the call returns DUQPP_ERR_SHAPE: the decode kernel takes T <= 128; the 256 x 256
- * kernel with bf16 output needs y 16-byte aligned and N, ldy multiples of 8.
+ * A kernel that cannot run the call returns DUQPP_ERR_SHAPE: the decode kernels take T <= 128; LARGE
+ * with bf16 output needs y 16-byte aligned and N, ldy multiples of 8.
  * duqpp_gemm_kernel_for reports (host, pure) which kernel DUQPP_GEMM_KERNEL_AUTO resolves to; it assumes an
  * aligned output.
  */
 enum {
     DUQPP_GEMM_KERNEL_AUTO = 0,
-    DUQPP_GEMM_KERNEL_DECODE = 1,   /* weight streaming, T <= 128 */
-    DUQPP_GEMM_KERNEL_SMALL = 2,    /* 64 x 128 tiles */
-    DUQPP_GEMM_KERNEL_MID = 3,      /* 128 x 256 tiles */
-    DUQPP_GEMM_KERNEL_LARGE = 4     /* 256 x 256 tiles */
+    DUQPP_GEMM_KERNEL_DECODE = 1,   /* weight streaming, T <= 128: K split over the waves, or tiles of few tokens or channels */
+    DUQPP_GEMM_KERNEL_SMALL = 2,    /* tiles of up to 128 tokens x 128 channels */
+    DUQPP_GEMM_KERNEL_MID = 3,      /* tiles of 96 or 128 tokens x 256 channels */
+    DUQPP_GEMM_KERNEL_LARGE = 4     /* tiles of 128 to 256 tokens x 256 channels, several of them per CU */
 };
 int duqpp_mxfp4_gemm_tiled_on(int kernel,
                               const uint8_t* a_codes_t, const uint8_t* a_scales_t,

@@ -129,8 +129,7 @@ extern "C" {
 int duqpp_init(void) {
     int st = check_device();
     if (st != DUQPP_OK) return st;
-    if (setup_rotq() != hipSuccess || setup_gemm_tiled_mid() != hipSuccess || setup_gemm_tiled_small() != hipSuccess ||
-        setup_gemm_tiled_large() != hipSuccess || setup_scratch() != hipSuccess)
+    if (setup_rotq() != hipSuccess || setup_gemm_tiled() != hipSuccess || setup_scratch() != hipSuccess)
         return DUQPP_ERR_HIP;
     return DUQPP_OK;
 }

@@ -55,9 +55,7 @@ inline hipError_t allow_dynamic_lds(const void* kernel, int bytes) {
 // Per-device set-up of each translation unit's kernels (what duqpp_init runs; the launchers run it themselves on
 // first use).
 hipError_t setup_rotq();
-hipError_t setup_gemm_tiled_mid();
-hipError_t setup_gemm_tiled_small();
-hipError_t setup_gemm_tiled_large();
+hipError_t setup_gemm_tiled();
 
 // ---- rotate + quantise (rotq.hip) ------------------------------------------------------
 struct RotqParams {
@@ -174,9 +172,8 @@ struct TiledGemmParams {
 hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream);     // picks the kernel by shape
 int choose_gemm_kernel(const TiledGemmParams& p);                              // the DUQPP_GEMM_KERNEL_* it picks
 hipError_t launch_gemm_tiled_as(const TiledGemmParams& p, int kernel, hipStream_t stream);   // a named kernel
-hipError_t launch_gemm_tiled_small(const TiledGemmParams& p, hipStream_t stream);   // 64 x 128 tiles
-hipError_t launch_gemm_tiled_large(const TiledGemmParams& p, hipStream_t stream);   // 256 x 256 tiles
-bool gemm_tiled_large_accepts(const TiledGemmParams& p);                           // output alignment the large kernel needs
+hipError_t launch_gemm_streaming_tiles(const TiledGemmParams& p, hipStream_t stream);    // the tiles that stream the weights
+bool gemm_tiled_large_accepts(const TiledGemmParams& p);                           // output alignment its name promises
 // ---- one-kernel rotate + quantise + multiply for up to 32 tokens (rotq_gemm_fused.hip) ----------------------
 struct FusedDecodeParams {
     const uint16_t* x; int64_t ldx; int T;               // bf16 [T, K]
@@ -189,7 +186,7 @@ struct FusedDecodeParams {
 constexpr int kFusedMaxT = 32 * 65535;                    // token tiles run along blockIdx.y
 hipError_t launch_rotq_gemm_fused_decode(const FusedDecodeParams& p, hipStream_t stream);
 
-constexpr int kDecodeMaxT = 128;   // up to four activation row tiles go to the weight-streaming kernel
+constexpr int kDecodeMaxT = 128;   // tokens the weight-streaming kernels take
 hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream);    // T <= kDecodeMaxT
 
 }  // namespace duqpp

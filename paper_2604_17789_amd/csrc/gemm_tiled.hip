@@ -1,460 +1,517 @@
-// W4A4 MXFP4 GEMM (the Q(X^) . Q(W^) product of the paper's Eq. 5) for operands in the tiled
-// layout, on gfx950's block-scaled matrix cores (v_mfma_scale_f32_32x32x64_f8f6f4, FP4 x FP4).
+// W4A4 MXFP4 GEMM (the Q(X^) . Q(W^) product of the paper's Eq. 5) for operands in the tiled layout, on gfx950's
+// block-scaled matrix cores (v_mfma_scale_f32_32x32x64_f8f6f4, FP4 x FP4): one kernel, a family of tile shapes.
 //
-// Shape of the kernel
-//   workgroup  4 waves (one per SIMD) as 2 x 2, output tile 128 (tokens) x 256 (output channels);
-//              each wave owns 64 x 128 = 2 x 4 MFMA tiles = 128 fp32 accumulators per lane.
-//   tiles      one workgroup per CU walks its output tiles one after the other; the operand transfers of the
-//              next tile start while the current one finishes, so only the store of a tile interrupts the
-//              matrix cores, not the refill of the pipeline.
-//   K loop     steps of 256 (8 MXFP4 groups).  The codes of a step, (4 + 8) row tiles x 4 KiB, and
-//              their scale words, 12 x 256 B, go from global memory straight into LDS by LDS-DMA
-//              (each code transfer moves one contiguous KiB); three such stages rotate, two in
-//              flight while one is consumed.
-//   operands   in the tiled layout the 16 code bytes of (row r, group j) of a row tile sit at
-//              (j * 32 + r) * 16, so the FP4 operand of lane (r, g) for MFMA i of a step -- group
-//              4 g + i of row r -- is one ds_read_b128 and 32 lanes read 512 contiguous bytes.
-//   scales     lane (r, g) needs the four E8M0 bytes of groups 4 g .. 4 g + 3: one 32-bit word,
-//              stored lane-linear per (row tile, step); the four MFMAs of a step select bytes
-//              0..3 of it.
-// K is a summation index, so feeding groups to the instruction in this permuted order changes
-// nothing but the order of the fp32 additions.
+// Shape of the kernel (MT, NT, W, D are template parameters)
+//   workgroup  W waves side by side along the output channels; the tile is 32 MT tokens x 32 NT W channels, and wave w
+//              owns all of its tokens against its own 32 NT channels: MT x NT MFMA tiles of 32 x 32.
+//   weights    go straight from global memory into the registers of the one wave that multiplies them (no LDS): the
+//              16 code bytes of (row r, group 4 g + q) of a row tile are the operand of lane (r, g) for MFMA q of a K step
+//              of 256, so a request is two runs of 512 contiguous bytes.  D register sets: D steps are in flight.
+//   tokens     are shared by the waves: their codes and scale words go by LDS-DMA into one of D + 1 stages, and every
+//              wave reads its fragments from there, one quarter step ahead of the MFMAs.
+//   K loop     one workgroup barrier per step.  A step's requests are spread between its MFMAs, and the registers of a
+//              weight fragment are requested anew right behind their last use.  The last D steps, which have nothing left
+//              to request, are a copy of the loop's body of their own.
+// K is a summation index, so feeding groups to the instruction in this permuted order changes nothing but the order of
+// the fp32 additions; that order is the same for every tile shape, and so is the result, bit for bit.
 //
-// The LDS-DMA transfers are issued from asm statements and their completion is awaited by hand
-// (s_waitcnt vmcnt before the workgroup barrier): were they visible to the compiler as LDS writes, it
-// would drain the whole DMA queue before every LDS read it cannot disambiguate, i.e. serialise the
-// pipeline.  No other vector-memory load is issued inside the K loop, so the compiler places no
-// vmcnt wait of its own there; LDS reads and MFMAs are ordinary code with compiler-managed waits.
+// What bounds it.  With every CU busy on real codes the chip runs at its power limit: at 2048 x 14336 x 4096 the K loop
+// takes the same 1307 cycles per step of 128 x 256 outputs (1024 of them MFMA) on zero and on random codes, but the clock
+// is 2.24 GHz on the former and 1.52 GHz on the latter; with half of the CUs it stays at 2.39 GHz.  What costs energy
+// beside the MFMAs is the transfer from L2 (taken out: 48 -> 38 us of loop) and the LDS reads (-> 43 us), so the family
+// keeps the weights out of LDS (per step of 128 x 256 outputs 17 KiB written to and 64 KiB read from LDS; with both
+// operands staged and the waves as 2 x 2 it was 52 and 96) and takes the tile that covers the output with the fewest
+// tiles per CU.  A tile of few MFMAs is bound by the path from L2 into the CU (about 44 bytes per cycle).
+// Measured against the kernels it replaces (both operands through LDS, 64 x 128, 128 x 256 and persistent 256 x 256 tiles;
+// us per launch on one MI355X, T x N x K): 160 x 4096 x 4096 11.4 -> 6.1, 512 x 4096 x 4096 12.3 -> 8.5,
+// 333 x 14336 x 4096 19.8 -> 14.9, 777 x 4096 x 14336 46.8 -> 30.0, 2048 x 4096 x 14336 61.0 -> 56.4,
+// 3001 x 14336 x 4096 97.1 -> 87.3, 8192 x 4096 x 4096 71.0 -> 65.3, 8192 x 14336 x 4096 239.5 -> 219.5,
+// 4096 x 8192 x 28672 412.6 -> 393.7.
+//
+// The requests and LDS-DMA transfers are asm statements and their completion is awaited by hand: were the transfers
+// visible to the compiler as LDS writes, it would drain the whole queue before every LDS read it cannot disambiguate.
 #include <type_traits>
+#include <utility>
 
 #include "duqpp_internal.h"
-#include "gemm_tiled_common.h"
+#include "mxfp4_device.h"
 
 namespace duqpp {
 
-constexpr int kBM = 128, kBN = 256;
-constexpr int kMT = kBM / 32, kNT = kBN / 32;           // row tiles of A / B per workgroup
-constexpr int kStageBytes = (kMT + kNT) * kTileStepBytes + 4 * 1024;   // codes + scale words
-constexpr int kStages = 3;
-constexpr int kGemmLdsBytes = kStages * kStageBytes;    // 159744 of the CU's 163840
-constexpr int kGroupM = 8;                              // M tiles per group in the workgroup ordering: an XCD's 32 workgroups form an 8 x 4 block (1024 x 1024 outputs), the shape with the fewest operand rows
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));   // fp32 pairs convert to it in one instruction, round to nearest even
 
-constexpr int kScaleRegionBytes = 4 * 1024;               // 12 x 256 B of scale words + 1 KiB of padding
-constexpr int kScalesOff = (kMT + kNT) * kTileStepBytes;  // scale words follow the codes in a stage
+namespace {
 
-struct Frags {
-    u32x4 a[2], b[4];
-};
+constexpr int kTileStepBytes = 8 * 512;                 // codes of one row tile for one K step (8 groups)
 
-struct Scales {
-    uint32_t a[2], b[4];
-};
+#define DUQPP_MFMA(ACC, A, B, SA, SB, SEL) \
+    ACC = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(A), fp4_operand(B), ACC, 4, 4, SEL, (int)(SA), SEL, (int)(SB))
 
-// the eight MFMAs of one quarter step: groups 4 g + SEL of every row tile pair, in an order that changes one
-// operand at a time (the second row runs backwards): operands that switch cost matrix-core time
-#define DUQPP_MFMA8(F, S, SEL)                                    \
-    DUQPP_MFMA(acc[0][0], F.a[0], F.b[0], S.a[0], S.b[0], SEL);   \
-    DUQPP_MFMA(acc[0][1], F.a[0], F.b[1], S.a[0], S.b[1], SEL);   \
-    DUQPP_MFMA(acc[0][2], F.a[0], F.b[2], S.a[0], S.b[2], SEL);   \
-    DUQPP_MFMA(acc[0][3], F.a[0], F.b[3], S.a[0], S.b[3], SEL);   \
-    DUQPP_MFMA(acc[1][3], F.a[1], F.b[3], S.a[1], S.b[3], SEL);   \
-    DUQPP_MFMA(acc[1][2], F.a[1], F.b[2], S.a[1], S.b[2], SEL);   \
-    DUQPP_MFMA(acc[1][1], F.a[1], F.b[1], S.a[1], S.b[1], SEL);   \
-    DUQPP_MFMA(acc[1][0], F.a[1], F.b[0], S.a[1], S.b[0], SEL)
+// M0 carries the LDS destination of an LDS-DMA transfer; the compiler reserves the register but
+// has no use for it in this kernel, and the clobber tells it the value does not survive.
+#pragma clang diagnostic ignored "-Winline-asm"
 
-// fragments of quarter Q of the stage whose per-lane base addresses are pa (A tiles) and pb (B tiles)
-template <int Q>
-__device__ __forceinline__ void read_frags(Frags& f, const uint8_t* pa, const uint8_t* pb) {
-    f.a[0] = *(const u32x4*)(pa + Q * 512);
-    f.a[1] = *(const u32x4*)(pa + 4096 + Q * 512);
-    f.b[0] = *(const u32x4*)(pb + Q * 512);
-    f.b[1] = *(const u32x4*)(pb + 4096 + Q * 512);
-    f.b[2] = *(const u32x4*)(pb + 8192 + Q * 512);
-    f.b[3] = *(const u32x4*)(pb + 12288 + Q * 512);
+template <int N, typename F, int... I>
+__device__ __forceinline__ void unroll_impl(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F&& f) {
+    unroll_impl<N>(f, std::make_integer_sequence<int, N>{});
 }
 
-template <bool OUT_BF16>
-__global__ __launch_bounds__(256) void gemm_tiled_kernel(TiledGemmParams p) {
+// 16 (4) bytes per lane from base + voff + OFF into the registers that hold `r` already: the transfer is asynchronous, so
+// the value may be used only behind a wait that names it (below), and the in-out operand keeps the register the same one
+// from the request to the wait.
+template <int OFF>
+__device__ __forceinline__ void request_b128(u32x4& r, uint32_t voff, const uint8_t* base) {
+    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "+v"(r) : "v"(voff), "s"(base), "n"(OFF));
+}
+__device__ __forceinline__ void request_b32(uint32_t& r, uint32_t voff, const uint8_t* base) {
+    asm volatile("global_load_dword %0, %1, %2" : "+v"(r) : "v"(voff), "s"(base));
+}
+// (the immediate offset advances both addresses)
+template <int OFF>
+__device__ __forceinline__ void dma_1k_s(uint32_t voff, const uint8_t* base, uint32_t lds_dst) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" : : "v"(voff), "s"(base), "s"(lds_dst), "n"(OFF) : "memory", "m0");
+}
+__device__ __forceinline__ void dma_256_s(uint32_t voff, const uint8_t* base, uint32_t lds_dst) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(base), "s"(lds_dst) : "memory", "m0");
+}
+
+// At most N requests outstanding, and the registers named hold their values from here on; then every LDS access of this
+// wave has completed, and all waves of the workgroup have come this far.
+template <int N>
+__device__ __forceinline__ void arrive(u32x4 (&b)[1][4], uint32_t (&s)[1]) {
+    asm volatile("s_waitcnt vmcnt(%5) lgkmcnt(0)\n\ts_barrier"
+                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]), "+v"(s[0]) : "n"(N) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void arrive(u32x4 (&b)[2][4], uint32_t (&s)[2]) {
+    asm volatile("s_waitcnt vmcnt(%10) lgkmcnt(0)\n\ts_barrier"
+                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]), "+v"(s[0]),
+                   "+v"(b[1][0]), "+v"(b[1][1]), "+v"(b[1][2]), "+v"(b[1][3]), "+v"(s[1]) : "n"(N) : "memory");
+}
+
+// Every LDS access this wave has issued has completed, then workgroup barrier.
+__device__ __forceinline__ void workgroup_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int MT, int NT, int D, int W>
+struct Tile {
+    static constexpr int kBM = 32 * MT, kBN = 32 * NT * W;
+    static constexpr int kScalesOff = MT * kTileStepBytes;    // scale words follow the codes in a stage
+    static constexpr int kStageBytes = kScalesOff + MT * 256;
+    static constexpr int kStages = D + 1;
+    static constexpr int kPieces = 4 / W;                     // KiB of a token row tile's step that one wave transfers
+    static constexpr int kCOps = MT * kPieces;
+    static constexpr int kSOps = (MT + W - 1) / W;            // scale transfers per wave and step
+    static constexpr int kDma = kCOps + kSOps;                // LDS-DMA transfers per wave and step
+    static constexpr int kOps = kDma + 5 * NT;                // all requests per wave and step, in the order they complete
+    static constexpr int kLate = 2 * NT;                      // of them behind the step's wait
+    static constexpr int kPitch = 64 * NT + 16;               // a row of the bf16 transpose
+    static constexpr int kEpBytes = 32 * kPitch;
+    static constexpr int kLdsBytes = kStages * kStageBytes > W * kEpBytes ? kStages * kStageBytes : W * kEpBytes;
+    static_assert(kOps * (D - 1) <= 63, "the wait counter holds 63");
+    static_assert(D % 2 == 0, "scale registers alternate by step parity");
+};
+
+constexpr int kGroupM = 8;
+
+// the weight codes of the steps that pad a run of K steps to a multiple of D: their products are exact zeros
+static __device__ __align__(1024) const uint8_t zero_codes[kTileStepBytes] = {};
+
+template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
+__global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams p) {
+    using TL = Tile<MT, NT, D, W>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, g = lane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;
 
-    const int tiles_m = (p.T + kBM - 1) / kBM, tiles_n = (p.N + kBN - 1) / kBN;
-    const int total = tiles_m * tiles_n;
+    const int tiles_m = (p.T + TL::kBM - 1) / TL::kBM, tiles_n = (p.N + TL::kBN - 1) / TL::kBN;
+    // Workgroups are dealt to the XCDs in turn.  Within each round of as many as the chip holds at once they are renumbered
+    // so that an XCD owns a contiguous range, and tile numbers run through groups of kGroupM M-tiles swept along N: the
+    // workgroups sharing an L2 cover a compact block of the output, and the blocks of one round lie side by side (with
+    // one contiguous range per XCD over the whole launch instead, 8192 x 14336 x 4096 takes 270 us, by rounds 234).
+    int pid;
+    {
+        constexpr int kRound = kNumCU * OCC;
+        const int first = (int)blockIdx.x / kRound * kRound;
+        const int id = (int)blockIdx.x - first, left_wgs = (int)gridDim.x - first, n = left_wgs < kRound ? left_wgs : kRound;
+        const int per = n / kNumXCD, rem = n % kNumXCD;
+        const int xcd = id % kNumXCD, slot = id / kNumXCD;
+        pid = first + xcd * per + (xcd < rem ? xcd : rem) + slot;
+    }
+    const int group_sz = kGroupM * tiles_n;
+    const int first_m = (pid / group_sz) * kGroupM;
+    const int gm = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
+    const int tile_m = first_m + (pid % group_sz) % gm;
+    const int tile_n = (pid % group_sz) / gm;
+
     const int RTa = (p.T + 31) / 32, RTb = (p.N + 31) / 32;
-    const int NI = p.GP / 8;                               // K steps per tile
+    const int NI = p.GP / 8;                               // K steps
     const int64_t tile_bytes = (int64_t)p.GP * 512;        // codes of one row tile
     const int64_t tile_sbytes = (int64_t)NI * 256;         // scale words of one row tile
 
-    // ---- which output tiles.  The launch has at most one workgroup per CU; workgroup `slot` takes tiles
-    // slot, slot + nwg, ...  Within each such round the workgroups are renumbered so that an XCD holds a
-    // contiguous range, and tile numbers run through groups of kGroupM M-tiles swept along N, so that the
-    // 32 workgroups sharing an L2 cover a compact block of the output.
-    const int nwg = gridDim.x;                             // <= total
-    int slot;
-    {
-        const int id = blockIdx.x;
-        const int per = nwg / kNumXCD, rem = nwg % kNumXCD;
-        const int xcd = id % kNumXCD, sl = id / kNumXCD;
-        slot = xcd * per + (xcd < rem ? xcd : rem) + sl;
-    }
-    const int nt = (total - 1 - slot) / nwg + 1;           // tiles of this workgroup
-    const int S = nt * NI;                                 // its K steps, all tiles in a row
-    auto tile_of = [&](int j, int& tile_m, int& tile_n) {
-        const int pid = j * nwg + slot;
-        const int group_sz = kGroupM * tiles_n;
-        const int first_m = (pid / group_sz) * kGroupM;
-        const int gm = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
-        tile_m = first_m + (pid % group_sz) % gm;
-        tile_n = (pid % group_sz) / gm;
-    };
-
-    // ---- LDS-DMA duty of this wave per step: three whole row tiles of codes (12 transfers of 1 KiB)
-    // and one KiB of scale words (the words of four row tiles; wave 3 has only padding to move, which
-    // keeps the number of transfers per wave uniform for the waits below).  The transfers run two steps
-    // ahead of the MFMAs and carry on into the workgroup's next tile while the current one finishes.
-    const uint8_t* dma_src[3];                             // this lane's source of the step to transfer next
-    const uint8_t* sdma_src;
-    uint32_t dma_dst[3];
+    // sources of the step to request next; tiles past the ragged edge are replaced by the last valid one (their outputs
+    // are never stored)
+    const uint8_t* a_src[MT];
+    const uint8_t* as_src[TL::kSOps];
+    const uint8_t* b_src[NT];
+    const uint8_t* bs_src[NT];
+    auto a_tile = [&](int m) { const int rt = tile_m * MT + m; return rt < RTa ? rt : RTa - 1; };
+#pragma unroll
+    for (int m = 0; m < MT; ++m) a_src[m] = p.a_codes + a_tile(m) * tile_bytes + wave * (TL::kPieces * 1024);
+    uint32_t as_dst[TL::kSOps];
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)lds);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) dma_dst[k] = lds0 + (wave * 3 + k) * kTileStepBytes;
-    const uint32_t sdma_dst = lds0 + kScalesOff + wave * 1024;
-    auto set_dma_tile = [&](int j) {
-        int tile_m, tile_n;
-        tile_of(j, tile_m, tile_n);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int tq = wave * 3 + k;                   // 0..3: A row tiles, 4..11: B row tiles
-            const uint8_t* base;
-            if (tq < kMT) {
-                int rt = tile_m * kMT + tq;
-                if (rt >= RTa) rt = RTa - 1;               // ragged M: any valid tile, its rows are never stored
-                base = p.a_codes + rt * tile_bytes;
-            } else {
-                int rt = tile_n * kNT + (tq - kMT);
-                if (rt >= RTb) rt = RTb - 1;
-                base = p.b_codes + rt * tile_bytes;
-            }
-            dma_src[k] = base + lane * 16;
-        }
-        // scale words: lane l of wave w moves 16 bytes = the words of lanes 4 (l % 16) .. + 3 of row tile
-        // 4 w + l / 16 (tiles 0..3: A, 4..11: B, 12..15: none -- wave 3 re-reads tile 11 into the padding)
-        int tq = wave * 4 + (lane >> 4);
-        if (tq > kMT + kNT - 1) tq = kMT + kNT - 1;
-        const uint8_t* base;
-        if (tq < kMT) {
-            int rt = tile_m * kMT + tq;
-            if (rt >= RTa) rt = RTa - 1;
-            base = p.a_scales + rt * tile_sbytes;
-        } else {
-            int rt = tile_n * kNT + (tq - kMT);
-            if (rt >= RTb) rt = RTb - 1;
-            base = p.b_scales + rt * tile_sbytes;
-        }
-        sdma_src = base + (lane & 15) * 16;
-    };
-    int dma_j = 0, dma_it = 0;                             // tile and step within it that the sources point at
-    set_dma_tile(0);
-    auto advance_dma = [&]() {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) dma_src[k] += kTileStepBytes;
-        sdma_src += 256;
-        if (++dma_it == NI) {
-            dma_it = 0;
-            if (++dma_j < nt) set_dma_tile(dma_j);
-        }
-    };
-    constexpr int kDmaOps = 13;                            // transfers per wave per step
-    auto issue_dma = [&](int stage) {
-        const uint32_t so = stage * kStageBytes;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) dma_4k(dma_src[k], dma_dst[k] + so);
-        dma_1k(sdma_src, sdma_dst + so);
-        advance_dma();
-    };
-
-    // ---- LDS read addresses: lane (r, g) reads group 4 g + i of row r at (4 g + i) * 512 + r * 16;
-    // its scale word of row tile t at kScalesOff + t * 256 + lane * 4
-    const uint8_t* pa0 = lds + g * 2048 + r * 16 + (wm * 2) * kTileStepBytes;
-    const uint8_t* pb0 = lds + g * 2048 + r * 16 + (kMT + wn * 4) * kTileStepBytes;
-    const uint8_t* psa0 = lds + kScalesOff + (wm * 2) * 256 + lane * 4;
-    const uint8_t* psb0 = lds + kScalesOff + (kMT + wn * 4) * 256 + lane * 4;
-    auto read_scales = [&](Scales& s, int stage) {
-        const uint8_t* qa = psa0 + stage * kStageBytes;
-        const uint8_t* qb = psb0 + stage * kStageBytes;
-        s.a[0] = *(const uint32_t*)(qa);
-        s.a[1] = *(const uint32_t*)(qa + 256);
-        s.b[0] = *(const uint32_t*)(qb);
-        s.b[1] = *(const uint32_t*)(qb + 256);
-        s.b[2] = *(const uint32_t*)(qb + 512);
-        s.b[3] = *(const uint32_t*)(qb + 768);
-    };
-
-    // ---- prologue: the first two stages.  Transfers complete in issue order, so "at most 13
-    // outstanding" means everything but the newest step's transfers has landed.
-    issue_dma(0);
-    if (S > 1) {
-        issue_dma(1);
-        wait_vmcnt<kDmaOps>();
-    } else {
-        wait_vmcnt<0>();
+    for (int x = 0; x < TL::kSOps; ++x) {
+        const int m = wave + W * x < MT ? wave + W * x : MT - 1;   // a wave without a tile of its own repeats the last one
+        as_src[x] = p.a_scales + a_tile(m) * tile_sbytes;
+        as_dst[x] = lds0 + TL::kScalesOff + m * 256;
     }
-    workgroup_barrier();
-    Frags f0, f1;
-    Scales sc, sn;
-    read_frags<0>(f0, pa0, pb0);
-    read_scales(sc, 0);
-    sn = sc;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+        int rt = (tile_n * W + wave) * NT + n;
+        if (rt >= RTb) rt = RTb - 1;
+        b_src[n] = p.b_codes + rt * tile_bytes;
+        bs_src[n] = p.b_scales + rt * tile_sbytes;
+    }
+    const uint32_t voff_dma = lane * 16, voff_word = lane * 4, voff_b = g * 2048 + r * 16;
+    const uint32_t a_dst = lds0 + wave * (TL::kPieces * 1024);
 
-    int stage = 0;                                         // stage of the step to compute next
-    for (int j = 0; j < nt; ++j) {                         // ---- one output tile per iteration
-    // The accumulators live and die inside one iteration: nothing but the transfer pipeline, the stage
-    // counter and the prefetched fragments of the next step is carried from tile to tile.
-    f32x16 acc[2][4];
+    // No branch: the K loop has to stay one straight piece of code, or the compiler moves products out from between the
+    // requests and copies registers whose contents are still on their way.
+    int left = NI - 1;                                     // steps after the one the sources point at
+    auto advance = [&]() {
+        const uint32_t more = left > 0 ? 1u : 0u;
+        const uint64_t keep = 0ull - more, zeros = (uint64_t)zero_codes & ~keep;
+        --left;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int m = 0; m < MT; ++m) a_src[m] += more * kTileStepBytes;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
+        for (int x = 0; x < TL::kSOps; ++x) as_src[x] += more * 256;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][jj][e] = 0.f;
+        for (int n = 0; n < NT; ++n) {
+            b_src[n] = (const uint8_t*)((((uint64_t)b_src[n] + kTileStepBytes) & keep) | zeros);
+            bs_src[n] += more * 256;
+        }
+    };
 
-    // One K step.  MORE1 / MORE2: a next step / a step after that exists (in this tile or the next).
-    auto step = [&](int stage, auto more1_c, auto more2_c) {
-        constexpr bool MORE1 = decltype(more1_c)::value, MORE2 = decltype(more2_c)::value;
-        const int stage1 = stage + 1 == kStages ? 0 : stage + 1;
-        const int stage2 = stage1 + 1 == kStages ? 0 : stage1 + 1;
-        // The 13 transfers that refill the stage consumed in the previous step (every wave has passed
-        // the barrier that followed its last read of it) are spread over the first three quarters, one
-        // every other MFMA: the CU's one texture path moves 64 B/clk, i.e. a step's 52 KiB take 832 of
-        // the step's 1024 MFMA cycles, and a wave that issues its transfers in a burst sits behind the
-        // other waves' bursts with its MFMAs waiting.
-        const uint8_t* d0 = dma_src[0];
-        const uint8_t* d1 = dma_src[1];
-        const uint8_t* d2 = dma_src[2];
-        const uint8_t* d3 = sdma_src;
-        const uint32_t so2 = stage2 * kStageBytes;
-        auto dma_slot = [&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            if constexpr (MORE2) {
-                if constexpr (k < 4) dma_1k_at<(k % 4) * 1024>(d0, dma_dst[0] + so2);
-                else if constexpr (k < 8) dma_1k_at<(k % 4) * 1024>(d1, dma_dst[1] + so2);
-                else if constexpr (k < 12) dma_1k_at<(k % 4) * 1024>(d2, dma_dst[2] + so2);
-                else dma_1k_at<0>(d3, sdma_dst + so2);
-            }
-        };
-        const uint8_t* pa = pa0 + stage * kStageBytes;
-        const uint8_t* pb = pb0 + stage * kStageBytes;
+    u32x4 b[D][NT][4];
+    uint32_t sb[D][NT];
+    u32x4 fa[2][MT];
+    uint32_t sa[2][MT];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            sb[d][n] = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) b[d][n][q] = (u32x4){0, 0, 0, 0};
+        }
+
+    auto dma_op = [&](auto kc, uint32_t so) {
+        constexpr int k = decltype(kc)::value;
+        if constexpr (k < TL::kCOps) {
+            constexpr int m = k / TL::kPieces, piece = k % TL::kPieces;
+            dma_1k_s<piece * 1024>(voff_dma, a_src[m], a_dst + m * kTileStepBytes + so);
+        } else if constexpr (k < TL::kDma) {
+            dma_256_s(voff_word, as_src[k - TL::kCOps], as_dst[k - TL::kCOps] + so);
+        }
+    };
+
+    // ---- prologue: D steps in flight
+    unroll<D>([&](auto dc) {
+        constexpr int d = decltype(dc)::value;
+        unroll<TL::kDma>([&](auto kc) { dma_op(kc, d * TL::kStageBytes); });
+        unroll<NT>([&](auto nc) {
+            constexpr int n = decltype(nc)::value;
+            request_b128<0>(b[d][n][0], voff_b, b_src[n]);
+            request_b128<512>(b[d][n][1], voff_b, b_src[n]);
+            request_b128<1024>(b[d][n][2], voff_b, b_src[n]);
+            request_b128<1536>(b[d][n][3], voff_b, b_src[n]);
+            request_b32(sb[d][n], voff_word, bs_src[n]);
+        });
+        advance();
+    });
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[m][n][e] = 0.f;
+
+    const uint8_t* pa0 = lds + g * 2048 + r * 16;
+    const uint8_t* ps0 = lds + TL::kScalesOff + lane * 4;
+    arrive<(D - 1) * TL::kOps>(b[0], sb[0]);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        fa[0][m] = *(const u32x4*)(pa0 + m * kTileStepBytes);
+        sa[0][m] = *(const uint32_t*)(ps0 + m * 256);
+    }
+
+    int stage = 0;
+    // One K step; P: its register set.  MORE: it requests the step D ahead; the last D steps (MORE = false) request nothing,
+    // and the wait of step P of them leaves the D - 2 - P steps behind the next one outstanding.
+    auto step = [&](auto pc, auto more_c) {
+        constexpr bool MORE = decltype(more_c)::value;
+        constexpr int P = decltype(pc)::value, P1 = (P + 1) % D;
+        const int stage1 = stage + 1 == TL::kStages ? 0 : stage + 1;
+        const uint32_t so = (stage == 0 ? TL::kStages - 1 : stage - 1) * TL::kStageBytes;   // consumed in the previous step
+        const uint8_t* pa = pa0 + stage * TL::kStageBytes;
 #define DUQPP_PIN __builtin_amdgcn_sched_barrier(0)
-#define DUQPP_DMA(K) dma_slot(std::integral_constant<int, K>{}); DUQPP_PIN
-        // quarter Q (fragments CUR) while the fragments of quarter Q + 1 (NXT) are read; D0..D3: transfers
-#define DUQPP_QUARTER(Q, CUR, NXT, D0, D1, D2, D3)                                            \
-        DUQPP_DMA(D0);                                                                         \
-        NXT.a[0] = *(const u32x4*)(pa + (Q + 1) * 512);                                         \
-        DUQPP_MFMA(acc[0][0], CUR.a[0], CUR.b[0], sc.a[0], sc.b[0], Q); DUQPP_PIN;              \
-        NXT.b[0] = *(const u32x4*)(pb + (Q + 1) * 512);                                         \
-        DUQPP_MFMA(acc[0][1], CUR.a[0], CUR.b[1], sc.a[0], sc.b[1], Q); DUQPP_PIN;              \
-        DUQPP_DMA(D1);                                                                         \
-        NXT.b[1] = *(const u32x4*)(pb + 4096 + (Q + 1) * 512);                                  \
-        DUQPP_MFMA(acc[0][2], CUR.a[0], CUR.b[2], sc.a[0], sc.b[2], Q); DUQPP_PIN;              \
-        NXT.b[2] = *(const u32x4*)(pb + 8192 + (Q + 1) * 512);                                  \
-        DUQPP_MFMA(acc[0][3], CUR.a[0], CUR.b[3], sc.a[0], sc.b[3], Q); DUQPP_PIN;              \
-        DUQPP_DMA(D2);                                                                         \
-        NXT.b[3] = *(const u32x4*)(pb + 12288 + (Q + 1) * 512);                                 \
-        DUQPP_MFMA(acc[1][3], CUR.a[1], CUR.b[3], sc.a[1], sc.b[3], Q); DUQPP_PIN;              \
-        NXT.a[1] = *(const u32x4*)(pa + 4096 + (Q + 1) * 512);                                  \
-        DUQPP_MFMA(acc[1][2], CUR.a[1], CUR.b[2], sc.a[1], sc.b[2], Q); DUQPP_PIN;              \
-        DUQPP_DMA(D3);                                                                         \
-        DUQPP_MFMA(acc[1][1], CUR.a[1], CUR.b[1], sc.a[1], sc.b[1], Q);                         \
-        DUQPP_MFMA(acc[1][0], CUR.a[1], CUR.b[0], sc.a[1], sc.b[0], Q); DUQPP_PIN
-        DUQPP_DMA(12);
-        DUQPP_QUARTER(0, f0, f1, 0, 1, 2, 3);
-        DUQPP_QUARTER(1, f1, f0, 4, 5, 6, 7);
-        DUQPP_QUARTER(2, f0, f1, 8, 9, 10, 11);
-#undef DUQPP_QUARTER
-#undef DUQPP_DMA
-        if constexpr (MORE2) advance_dma();
-        if constexpr (MORE1) {
-            // next stage landed for this wave, then for all; every LDS read of the current stage has
-            // been issued and returns before any later transfer can touch it
-            if constexpr (MORE2) wait_vmcnt<kDmaOps>();
-            else wait_vmcnt<0>();
-            workgroup_barrier();
-            read_frags<0>(f0, pa0 + stage1 * kStageBytes, pb0 + stage1 * kStageBytes);
-            read_scales(sn, stage1);
-        }
-        DUQPP_MFMA8(f1, sc, 3);
-        if constexpr (MORE1) {
-            // the reads above (6 fragments, 3 paired scale reads) two at a time ahead of the MFMAs
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            }
-        }
+        constexpr int kSlots = 3 * MT * NT;   // transfers spread over the first three quarters
+        unroll<3>([&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            unroll<NT>([&](auto nc) {
+                constexpr int n = decltype(nc)::value;
+                unroll<MT>([&](auto mc) {
+                    constexpr int m0 = decltype(mc)::value, m = (n & 1) ? MT - 1 - m0 : m0;
+                    constexpr int slot = (Q * NT + n) * MT + m0;
+                    if constexpr (MORE) {
+                        constexpr int k0 = (slot * TL::kDma + kSlots - 1) / kSlots, k1 = ((slot + 1) * TL::kDma + kSlots - 1) / kSlots;
+                        unroll<k1 - k0>([&](auto kc) { dma_op(std::integral_constant<int, k0 + decltype(kc)::value>{}, so); });
+                    }
+                    if constexpr (n == 0) fa[(Q + 1) & 1][m] = *(const u32x4*)(pa + m * kTileStepBytes + (Q + 1) * 512);
+                    DUQPP_PIN;
+                    DUQPP_MFMA(acc[m][n], fa[Q & 1][m], b[P][n][Q], sa[P & 1][m], sb[P][n], Q);
+                    DUQPP_PIN;
+                });
+                if constexpr (MORE) request_b128<Q * 512>(b[P][n][Q], voff_b, b_src[n]);
+                DUQPP_PIN;
+            });
+        });
+        // the next step's operands have arrived, for this wave and then for all
+        if constexpr (MORE) arrive<(D - 2) * TL::kOps + TL::kOps - TL::kLate>(b[P1], sb[P1]);
+        else if constexpr (P < D - 1) arrive<(D - 2 - P) * TL::kOps>(b[P1], sb[P1]);
         DUQPP_PIN;
+        const uint8_t* na = pa0 + stage1 * TL::kStageBytes;
+        const uint8_t* ns = ps0 + stage1 * TL::kStageBytes;
+        unroll<NT>([&](auto nc) {
+            constexpr int n = decltype(nc)::value;
+            unroll<MT>([&](auto mc) {
+                constexpr int m0 = decltype(mc)::value, m = (n & 1) ? MT - 1 - m0 : m0;
+                if constexpr (n == 0 && (MORE || P < D - 1)) {
+                    fa[0][m] = *(const u32x4*)(na + m * kTileStepBytes);
+                    sa[(P + 1) & 1][m] = *(const uint32_t*)(ns + m * 256);
+                }
+                DUQPP_PIN;
+                DUQPP_MFMA(acc[m][n], fa[1][m], b[P][n][3], sa[P & 1][m], sb[P][n], 3);
+                DUQPP_PIN;
+            });
+            if constexpr (MORE) {
+                request_b128<1536>(b[P][n][3], voff_b, b_src[n]);
+                request_b32(sb[P][n], voff_word, bs_src[n]);
+                DUQPP_PIN;
+            }
+        });
 #undef DUQPP_PIN
-        sc = sn;
+        if constexpr (MORE) advance();
+        stage = stage1;
     };
+    for (int it = (NI + D - 1) / D; it > 1; --it) unroll<D>([&](auto dc) { step(dc, std::true_type{}); });
+    unroll<D>([&](auto dc) { step(dc, std::false_type{}); });
+    // the last products happen here, whatever is stored below (or the compiler moves them into the branches of the stores)
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            if constexpr (OCC == 1) asm volatile("" : "+a"(acc[m][n]));
+            else asm volatile("" : "+v"(acc[m][n]));
+        }
+    workgroup_barrier();                                   // the stages become the scratch of the transpose below
 
-    // ---- a finished tile: acc[i][j][e] of lane (r, g) is row 32 i + 8 (e / 4) + 4 g + e % 4, column 32 j + r.
-    // `stage` is the stage the tile's last step consumed: no wave reads it any more (`synced`: they have all
-    // passed a barrier since), and the only transfers that will write bytes [12288 w, 12288 (w + 1)) of it are
-    // wave w's own, issued later in program order -- so that range is wave w's scratch for the bf16 transpose.
-    auto store_tile = [&](int j, int stage, bool synced) {
-        int tile_m, tile_n;
-        tile_of(j, tile_m, tile_n);
-        const int m0 = tile_m * kBM + wm * 64, n0 = tile_n * kBN + wn * 128;
-        if constexpr (OUT_BF16) {
-            // A direct store would write 2 bytes per lane, 64 contiguous bytes per instruction and row.
-            // Instead each 32 x 128 half of the wave's tile is transposed through LDS and leaves as 16-byte
-            // pieces, 256 contiguous bytes per row.  Rows are padded to 272 bytes so that the two
-            // half-waves (four rows apart) fall on different banks.
-            const bool vec_ok = ((reinterpret_cast<uintptr_t>(p.y) & 15) == 0) && (p.ldy % 8) == 0;
-            if (vec_ok) {
-                constexpr int kRowPitch = 272;
-                static_assert(32 * kRowPitch <= 3 * kTileStepBytes, "scratch within the wave's own transfer range");
-                if (!synced) workgroup_barrier();
-                uint8_t* ep = lds + stage * kStageBytes + wave * (3 * kTileStepBytes);
+    // ---- epilogue: acc[m][n][e] of lane (r, g) is row 32 m + 8 (e / 4) + 4 g + e % 4, column 32 n + r of the wave's tile
+    const int m0 = tile_m * TL::kBM, n0 = tile_n * TL::kBN + wave * 32 * NT;
+    if constexpr (OUT_BF16) {
+        if ((reinterpret_cast<uintptr_t>(p.y) & 15) == 0 && (p.ldy % 8) == 0) {
+            constexpr int kChunks = 4 * NT, kRows = 64 / kChunks;      // 16-byte pieces of a row; rows per store instruction
+            uint8_t* ep = lds + wave * TL::kEpBytes;
+            const int ch = lane % kChunks, row0 = lane / kChunks;
+            const int gcol = n0 + ch * 8;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
+            for (int m = 0; m < MT; ++m) {
+                __builtin_amdgcn_sched_barrier(0);         // one row tile's values in registers at a time
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
+                for (int n = 0; n < NT; ++n)
 #pragma unroll
-                        for (int e = 0; e < 16; e += 2) {
-                            // rows 8 (e / 4) + 4 g + e % 4 and the next one: the two halves of one packed convert
-                            const bf16x2 b = __builtin_convertvector((f32x2){acc[i][jj][e], acc[i][jj][e + 1]}, bf16x2);
-                            const uint32_t u = __builtin_bit_cast(uint32_t, b);
-                            uint8_t* q = ep + (8 * (e / 4) + 4 * g + (e % 4)) * kRowPitch + (32 * jj + r) * 2;
-                            *(uint16_t*)q = (uint16_t)u;
-                            *(uint16_t*)(q + kRowPitch) = (uint16_t)(u >> 16);
-                        }
-                    // same wave wrote and reads: program order suffices within a wave
+                    for (int e = 0; e < 16; e += 2) {
+                        const bf16x2 v = __builtin_convertvector((f32x2){acc[m][n][e], acc[m][n][e + 1]}, bf16x2);
+                        const uint32_t u = __builtin_bit_cast(uint32_t, v);
+                        uint8_t* q = ep + (8 * (e / 4) + 4 * g + (e % 4)) * TL::kPitch + (32 * n + r) * 2;
+                        *(uint16_t*)q = (uint16_t)u;
+                        *(uint16_t*)(q + TL::kPitch) = (uint16_t)(u >> 16);
+                    }
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const int row = k * 4 + (lane >> 4), ch = lane & 15;
-                        const int grow = m0 + 32 * i + row, gcol = n0 + ch * 8;
-                        const u32x4 v = *(const u32x4*)(ep + row * kRowPitch + ch * 16);
-                        if (grow < p.T && gcol < p.N) {
-                            uint16_t* dst = (uint16_t*)p.y + (int64_t)grow * p.ldy + gcol;
-                            if (gcol + 8 <= p.N) {
-                                __builtin_nontemporal_store(v, (u32x4*)dst);   // streamed: keeps the operands' lines in L2 (1-5 % at the LLaMA-3-8B shapes)
-                            } else {                       // ragged right edge
-                                for (int c = 0; c < 8 && gcol + c < p.N; ++c) dst[c] = (uint16_t)(v[c / 2] >> (16 * (c & 1)));
-                            }
+                for (int k = 0; k < 32 / kRows; ++k) {
+                    const int row = k * kRows + row0, grow = m0 + 32 * m + row;
+                    const u32x4 v = *(const u32x4*)(ep + row * TL::kPitch + ch * 16);
+                    if (grow < p.T && gcol < p.N) {
+                        uint16_t* dst = (uint16_t*)p.y + (int64_t)grow * p.ldy + gcol;
+                        if (gcol + 8 <= p.N) {
+                            __builtin_nontemporal_store(v, (u32x4*)dst);
+                        } else {                           // ragged right edge
+                            for (int c = 0; c < 8 && gcol + c < p.N; ++c) dst[c] = (uint16_t)(v[c / 2] >> (16 * (c & 1)));
                         }
                     }
                 }
-                return;
+            }
+            return;
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            const int col = n0 + 32 * n + r;
+            if (col >= p.N) continue;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int row = m0 + 32 * m + 8 * (e / 4) + 4 * g + (e % 4);
+                if (row < p.T) {
+                    if (OUT_BF16) ((uint16_t*)p.y)[(int64_t)row * p.ldy + col] = f32_to_bf16_rne(acc[m][n][e]);
+                    else ((float*)p.y)[(int64_t)row * p.ldy + col] = acc[m][n][e];
+                }
             }
         }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int col = n0 + 32 * jj + r;
-                if (col >= p.N) continue;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = m0 + 32 * i + 8 * (e / 4) + 4 * g + (e % 4);
-                    if (row < p.T) {
-                        if (OUT_BF16) ((uint16_t*)p.y)[(int64_t)row * p.ldy + col] = f32_to_bf16_rne(acc[i][jj][e]);
-                        else ((float*)p.y)[(int64_t)row * p.ldy + col] = acc[i][jj][e];
-                    }
-                }
-            }
-    };
-
-    // Steps of this tile.  All but the last two steps of the whole run have two successors.
-    const int s0 = j * NI;
-    int hot = S - 2 - s0;
-    hot = hot < 0 ? 0 : (hot > NI ? NI : hot);
-    int it = 0;
-    for (; it < hot; ++it) {
-        step(stage, std::true_type{}, std::true_type{});
-        stage = stage + 1 == kStages ? 0 : stage + 1;
-    }
-    for (; it < NI; ++it) {
-        if (s0 + it + 1 < S) step(stage, std::true_type{}, std::false_type{});
-        else step(stage, std::false_type{}, std::false_type{});
-        stage = stage + 1 == kStages ? 0 : stage + 1;
-    }
-    // a step with a successor ends behind a barrier
-    store_tile(j, stage == 0 ? kStages - 1 : stage - 1, s0 + NI < S);
-    }                                                      // ---- tile loop
 }
 
-// 128 x 256 tiles, persistent workgroups, any shape.
-hipError_t setup_gemm_tiled_mid() {
+template <int MT, int NT, int D, int W, int OCC>
+hipError_t allow() {
+    hipError_t e = allow_dynamic_lds((const void*)gemm_tiled_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+    if (e != hipSuccess) return e;
+    return allow_dynamic_lds((const void*)gemm_tiled_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+}
+template <int MT, int NT, int D, int W, int OCC>
+hipError_t run(const TiledGemmParams& p, hipStream_t stream) {
+    using TL = Tile<MT, NT, D, W>;
+    const int64_t tiles = (int64_t)((p.T + TL::kBM - 1) / TL::kBM) * ((p.N + TL::kBN - 1) / TL::kBN);
+    const dim3 grid((unsigned)tiles), block(64 * W);
+    return p.out_bf16 ? launch(gemm_tiled_kernel<true, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p)
+                      : launch(gemm_tiled_kernel<false, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p);
+}
+
+// The tile shapes.  Two workgroups of the four-wave tiles fit a CU, but for the two largest (one): while one of them
+// waits for its first operands or stores its tile, the other has the matrix cores.  one / two: microseconds per K step of
+// 256 while a CU holds one or two tiles; fixed: per round of tiles, what the pipeline's start and the store take.  Fitted
+// to the time of every shape at 400 products (33 to 8192 tokens, seven linears of the 8B and 70B models and four generic
+// ones, weights in the last-level cache and in HBM): the shape chosen is on average 0.3 % slower than the fastest, 13 % at worst.
+struct Shape {
+    int mt, nt, w, per_cu;
+    double one, two, fixed;
+    hipError_t (*allow)();
+    hipError_t (*run)(const TiledGemmParams&, hipStream_t);
+};
+#define DUQPP_SHAPE(MT, NT, D, W, OCC, PER_CU, ONE, TWO, FIXED) \
+    {MT, NT, W, PER_CU, ONE, TWO, FIXED, allow<MT, NT, D, W, OCC>, run<MT, NT, D, W, OCC>}
+const Shape kShapes[] = {
+    // 64 channels wide, for outputs that these cut into no more tiles than there are CUs: per output a 64 x 64 tile fetches
+    // four fifths of the bytes of a 32 x 128 one (256 x 4096 x 14336 from HBM: 19.4 us, 32 x 128 tiles 23.2 us)
+    DUQPP_SHAPE(1, 1, 4, 2, 2, 1, 0.194, 0.0, 2.16),
+    DUQPP_SHAPE(2, 1, 4, 2, 2, 1, 0.232, 0.0, 2.68),
+    DUQPP_SHAPE(3, 1, 4, 2, 2, 1, 0.296, 0.0, 3.80),
+    // 128 channels wide
+    DUQPP_SHAPE(1, 1, 4, 4, 2, 2, 0.237, 0.540, 2.60),
+    DUQPP_SHAPE(2, 1, 4, 4, 2, 2, 0.372, 0.655, 2.97),
+    DUQPP_SHAPE(3, 1, 4, 4, 2, 2, 0.414, 0.730, 3.43),
+    DUQPP_SHAPE(4, 1, 2, 4, 2, 2, 0.526, 0.930, 3.60),
+    // 256 channels wide
+    DUQPP_SHAPE(3, 2, 2, 4, 2, 2, 0.616, 1.386, 3.58),
+    DUQPP_SHAPE(4, 2, 2, 4, 2, 2, 0.695, 1.601, 6.37),
+    DUQPP_SHAPE(6, 2, 2, 4, 1, 1, 1.151, 0.0, 8.42),
+    DUQPP_SHAPE(8, 2, 2, 4, 1, 1, 1.414, 0.0, 10.11),
+};
+#undef DUQPP_SHAPE
+
+int64_t tiles_of(const Shape& s, const TiledGemmParams& p) {
+    return (int64_t)((p.T + 32 * s.mt - 1) / (32 * s.mt)) * ((p.N + 32 * s.nt * s.w - 1) / (32 * s.nt * s.w));
+}
+
+// Rounds of tiles over the CUs, the last one with one tile per CU where that is all there is.
+double cost_of(const Shape& s, const TiledGemmParams& p) {
+    const int64_t n = tiles_of(s, p), cap = (int64_t)kNumCU * s.per_cu;
+    const int64_t full = n / cap, rest = n % cap;
+    const double steps = p.GP / 8;
+    if (s.per_cu == 1) return (double)(full + (rest != 0)) * (steps * s.one + s.fixed);
+    return (double)full * (steps * s.two + s.fixed) +
+           (rest == 0 ? 0.0 : steps * (rest > kNumCU ? s.two : s.one) + s.fixed);
+}
+
+template <typename Pred>
+const Shape* best_shape(const TiledGemmParams& p, Pred&& allowed) {
+    const Shape* best = nullptr;
+    double best_cost = 0.0;
+    for (const Shape& s : kShapes) {
+        if (!allowed(s) || (s.w < 4 && tiles_of(s, p) > kNumCU)) continue;
+        const double c = cost_of(s, p);
+        if (!best || c < best_cost) { best = &s; best_cost = c; }
+    }
+    return best;
+}
+
+bool any_shape(const Shape&) { return true; }
+bool streaming_shape(const Shape& s) { return s.mt == 1 || s.w < 4; }
+bool small_shape(const Shape& s) { return s.nt == 1; }
+bool mid_shape(const Shape& s) { return s.nt == 2 && s.mt <= 4; }
+bool large_shape(const Shape& s) { return s.nt == 2 && s.mt >= 4; }
+bool unaligned_shape(const Shape& s) { return s.mt <= 4; }
+
+// N a multiple of 8 for either output type, so that the fp32 and the bf16 result of a shape are said to come from the same kernel
+bool large_ok(const TiledGemmParams& p) { return (p.N % 8) == 0 && gemm_tiled_large_accepts(p); }
+
+const Shape* choose_shape(const TiledGemmParams& p) { return large_ok(p) ? best_shape(p, any_shape) : best_shape(p, unaligned_shape); }
+
+hipError_t run_shape(const Shape* s, const TiledGemmParams& p, hipStream_t stream) {
+    hipError_t e = setup_gemm_tiled();
+    return e == hipSuccess ? s->run(p, stream) : e;
+}
+
+}  // namespace
+
+// what the name DUQPP_GEMM_KERNEL_LARGE promises: bf16 results leave in whole 16-byte pieces
+bool gemm_tiled_large_accepts(const TiledGemmParams& p) {
+    if (!p.out_bf16) return true;
+    return (reinterpret_cast<uintptr_t>(p.y) & 15) == 0 && (p.ldy % 8) == 0 && (p.N % 8) == 0;
+}
+
+hipError_t setup_gemm_tiled() {
     static PerDeviceOnce once;
     return once.run([] {
-        hipError_t e = allow_dynamic_lds((const void*)gemm_tiled_kernel<true>, kGemmLdsBytes);
-        if (e != hipSuccess) return e;
-        return allow_dynamic_lds((const void*)gemm_tiled_kernel<false>, kGemmLdsBytes);
+        for (const Shape& s : kShapes) {
+            const hipError_t e = s.allow();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     });
 }
 
-hipError_t launch_gemm_tiled_mid(const TiledGemmParams& p, hipStream_t stream) {
-    hipError_t e = setup_gemm_tiled_mid();
-    if (e != hipSuccess) return e;
-    const int tiles_m = (p.T + kBM - 1) / kBM, tiles_n = (p.N + kBN - 1) / kBN;
-    // persistent workgroups: the 156 KiB of LDS allow one per CU, and each walks its tiles with the
-    // transfer pipeline running across tile boundaries
-    const int total = tiles_m * tiles_n;
-    dim3 grid((unsigned)(total < kNumCU ? total : kNumCU)), block(256);
-    return p.out_bf16 ? launch(gemm_tiled_kernel<true>, grid, block, kGemmLdsBytes, stream, p)
-                      : launch(gemm_tiled_kernel<false>, grid, block, kGemmLdsBytes, stream, p);
+// The weight-streaming tiles, for the decode launcher's larger calls.
+hipError_t launch_gemm_streaming_tiles(const TiledGemmParams& p, hipStream_t stream) {
+    return run_shape(best_shape(p, streaming_shape), p, stream);
 }
 
-// Which kernel runs a shape.
+// Which kernel runs a shape, by the names of the ABI.
 int choose_gemm_kernel(const TiledGemmParams& p) {
-    // Weight-streaming shapes go to the decode kernel: always up to 32 tokens, up to 64 unless the 64 x 128 tiles fill
-    // the chip (N beyond about 24 k); from 65 to 128 (two passes
-    // over the weights) when that beats the 128 x 256 kernel, which then has at most N / 256 of the 256 CUs busy
-    // for GP / 8 steps of about a microsecond.  Times in microseconds, fitted to measurements at the LLaMA-3-8B shapes.
     if (p.T <= 32) return DUQPP_GEMM_KERNEL_DECODE;
-    if (p.T <= 64) {
-        // Two activation row tiles per wave stream the weights at about 4 TB/s; the 64 x 128 tiles take about 0.8 us
-        // per K step of 256 once there are enough of them for every CU, whatever the byte count (N = 28672, K = 8192,
-        // T = 48: 27.9 us against 33.9 us; N = 14336, K = 4096: 12.1 us against 11.1 us).
-        const double t_decode = 2.5 + (double)p.N * p.GP * 17.0 / 4.0e6;
-        const int64_t small_tiles = (int64_t)((p.T + 63) / 64) * ((p.N + 127) / 128);
-        const double t_small = 2.5 + 0.8 * (p.GP / 8) * (double)((small_tiles + 2 * kNumCU - 1) / (2 * kNumCU));
-        return t_decode <= t_small ? DUQPP_GEMM_KERNEL_DECODE : DUQPP_GEMM_KERNEL_SMALL;
-    }
-    const int64_t mid_tiles = (int64_t)((p.T + kBM - 1) / kBM) * ((p.N + kBN - 1) / kBN);
-    if (p.T <= kDecodeMaxT) {
-        const double weight_bytes = (double)p.N * p.GP * 17.0;
-        const double t_decode = 2.0 * (2.5 + weight_bytes / 2.8e6);
-        const int tiles = (p.N + kBN - 1) / kBN;
-        const double t_prefill = 3.0 + 1.05 * (p.GP / 8) * ((tiles + kNumCU - 1) / kNumCU);
-        if (t_decode < t_prefill) return DUQPP_GEMM_KERNEL_DECODE;
-    }
-    // Too few 128 x 256 tiles to occupy the chip: 64 x 128 tiles, four times as many, two workgroups per CU.
-    if (mid_tiles < kNumCU / 2) return DUQPP_GEMM_KERNEL_SMALL;
-    // 256 x 256 tiles do a flop in about 0.8 of the time of 128 x 256 tiles (less L2 and LDS traffic per flop),
-    // i.e. a tile with twice the work costs 1.6 of a 128 x 256 tile: they win when the rounds over the 256 CUs come out
-    // cheaper, which needs at least 256 of them or so.
-    // (N a multiple of 8 for either output type, so that the fp32 and the bf16 result of a shape come from the same
-    // kernel and the second is the rounding of the first.)
-    if ((p.N % 8) == 0 && gemm_tiled_large_accepts(p)) {
-        const int64_t large_tiles = (int64_t)((p.T + 255) / 256) * ((p.N + 255) / 256);
-        const double t_mid = (double)((mid_tiles + kNumCU - 1) / kNumCU);
-        const double t_large = 1.6 * (double)((large_tiles + kNumCU - 1) / kNumCU);
-        if (t_large < t_mid) return DUQPP_GEMM_KERNEL_LARGE;
-    }
-    return DUQPP_GEMM_KERNEL_MID;
+    const Shape* s = choose_shape(p);
+    if (p.T <= 64 && streaming_shape(*s)) return DUQPP_GEMM_KERNEL_DECODE;
+    if (small_shape(*s)) return DUQPP_GEMM_KERNEL_SMALL;
+    // several rounds of 256-channel tiles over the CUs
+    if (large_ok(p) && large_shape(*s) && tiles_of(*s, p) > (int64_t)kNumCU * s->per_cu) return DUQPP_GEMM_KERNEL_LARGE;
+    return s->mt <= 4 ? DUQPP_GEMM_KERNEL_MID : DUQPP_GEMM_KERNEL_LARGE;
 }
 
 hipError_t launch_gemm_tiled_as(const TiledGemmParams& p, int kernel, hipStream_t stream) {
     switch (kernel) {
-        case DUQPP_GEMM_KERNEL_AUTO: return launch_gemm_tiled_as(p, choose_gemm_kernel(p), stream);
+        case DUQPP_GEMM_KERNEL_AUTO: return p.T <= 32 ? launch_gemm_decode(p, stream) : run_shape(choose_shape(p), p, stream);
         case DUQPP_GEMM_KERNEL_DECODE: return p.T <= kDecodeMaxT ? launch_gemm_decode(p, stream) : hipErrorInvalidValue;
-        case DUQPP_GEMM_KERNEL_SMALL: return launch_gemm_tiled_small(p, stream);
-        case DUQPP_GEMM_KERNEL_MID: return launch_gemm_tiled_mid(p, stream);
-        case DUQPP_GEMM_KERNEL_LARGE: return launch_gemm_tiled_large(p, stream);
+        case DUQPP_GEMM_KERNEL_SMALL: return run_shape(best_shape(p, small_shape), p, stream);
+        case DUQPP_GEMM_KERNEL_MID: return run_shape(best_shape(p, mid_shape), p, stream);
+        case DUQPP_GEMM_KERNEL_LARGE:
+            return gemm_tiled_large_accepts(p) ? run_shape(best_shape(p, large_shape), p, stream) : hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 }
