@@ -8,6 +8,20 @@
 
 namespace duqpp {
 
+namespace {
+
+constexpr int kErrWaves = 4;            // waves per workgroup, two groups each
+constexpr int kErrWorkgroups = 512;     // aimed at: two per CU (1024: 11.1 us at 2048 x 4096, 512: 9.3, 256: 10.0)
+// From this many ratios on the mean is formed from the partial sums of the workgroups that compute them.
+constexpr int64_t kPartialsFrom = 65536;
+
+struct ErrPlan {
+    int chunks, runs;                   // workgroups: column chunks x token runs
+    int ntiles;                         // token tiles of 32 in play
+    int64_t keep_from, keep_to;         // ratios stored: their place in err, in floats
+    int partials;                       // err's first floats receive each workgroup's partial sum and count
+};
+
 // value of an E2M1 code (sign, two exponent bits, one mantissa bit): 0, 0.5, 1, 1.5, 2, 3, 4, 6
 __device__ __forceinline__ double e2m1_value(uint32_t nib) {
     const uint32_t e = (nib >> 1) & 3u, m = nib & 1u;
@@ -15,61 +29,173 @@ __device__ __forceinline__ double e2m1_value(uint32_t nib) {
     return (nib & 8u) ? -mag : mag;
 }
 
-// One wave per (tile of 32 tokens, group): lane (c, h) holds 16 of token c's 32 values, as in rotate_tile.
-__global__ __launch_bounds__(64) void group_error_kernel(GroupErrorParams p) {
-    const int lane = threadIdx.x, c = lane & 31, h = lane >> 5;
-    const int j = blockIdx.x;
-    const int token = blockIdx.y * 32 + c;
-    const int tl = token < p.rows ? token : p.rows - 1;      // rows past the end: a valid row, never stored
-    const uint16_t* xr = p.x + (int64_t)tl * p.ldx + 32 * j;
-    f32x16 acc;
-    if (p.R) {
-        RotOperand op;
-        load_rot_operand(p.R + (int64_t)j * p.r_stride, c, h, op);
-        u32x4 xv[2];
-        xv[0] = *(const u32x4*)(xr + 8 * h);
-        xv[1] = *(const u32x4*)(xr + 8 * h + 16);
-        acc = rotate_tile(op, xv);
-    } else {
-        // no rotation: acc[i] is channel 8 (i / 4) + 4 h + i % 4 of the group, the layout rotate_tile would give
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint2 v = *(const uint2*)(xr + 8 * q + 4 * h);
-            acc[4 * q + 0] = __uint_as_float(v.x << 16);
-            acc[4 * q + 1] = __uint_as_float(v.x & 0xFFFF0000u);
-            acc[4 * q + 2] = __uint_as_float(v.y << 16);
-            acc[4 * q + 3] = __uint_as_float(v.y & 0xFFFF0000u);
-        }
-    }
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// This lane's 16 of a token's 32 values: sums of (Q(y) - y)^2 and of y^2.
+__device__ __forceinline__ void error_sums(const f32x16& acc, double& num, double& den) {
     uint32_t p0, p1;
     const uint32_t byte = quantize_lane(acc, p0, p1);
-    // 2^(byte - 127) as a double (the fp32 form of 2^-127 would be subnormal)
-    const double scale = __longlong_as_double((long long)(byte + 896u) << 52);
-    double num = 0.0, den = 0.0;
+    num = 0.0;
+    den = 0.0;
+    if (__any(byte < 32u)) {
+        // a group near the bottom of fp32's range: in fp64 throughout (2^(byte - 127) as a double: the fp32 form of 2^-127
+        // would be subnormal)
+        const double scale = __longlong_as_double((long long)(byte + 896u) << 52);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const uint32_t nib = ((i < 8 ? p0 : p1) >> (4 * (i & 7))) & 15u;
-        const double y = (double)acc[i];
-        const double d = e2m1_value(nib) * scale - y;
-        num += d * d;
-        den += y * y;
+        for (int i = 0; i < 16; ++i) {
+            const double y = (double)acc[i];
+            const double d = e2m1_value(((i < 8 ? p0 : p1) >> (4 * (i & 7))) & 15u) * scale - y;
+            num += d * d;
+            den += y * y;
+        }
+        return;
     }
-    num += __shfl_xor(num, 32);
-    den += __shfl_xor(den, 32);
-    if (h == 0 && token < p.rows) p.err[(int64_t)token * p.G + j] = den > 0.0 ? (float)sqrt(num / den) : -1.0f;
+    // Q(y) - y is exact in fp32: Q(y) and y are multiples of the last place of y, and their difference is no larger than y.
+    const float sc = __uint_as_float(byte << 23);
+    auto two = [&](float y0, float y1, const f32x2& q) {
+        const double d0 = (double)(q[0] - y0), d1 = (double)(q[1] - y1);
+        num += d0 * d0;
+        den += (double)y0 * (double)y0;
+        num += d1 * d1;
+        den += (double)y1 * (double)y1;
+    };
+    two(acc[0], acc[1], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p0, sc, 0));
+    two(acc[2], acc[3], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p0, sc, 1));
+    two(acc[4], acc[5], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p0, sc, 2));
+    two(acc[6], acc[7], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p0, sc, 3));
+    two(acc[8], acc[9], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p1, sc, 0));
+    two(acc[10], acc[11], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p1, sc, 1));
+    two(acc[12], acc[13], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p1, sc, 2));
+    two(acc[14], acc[15], __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p1, sc, 3));
 }
 
-// Mean of the ratios over the groups that have one (err >= 0), summed in a fixed order: thread t takes elements
-// t, t + 1024, ..., then a tree over the 1024 partial sums.
+// v0 summed over the lane pair (c, c + 32) in the lower half of the wave, v1 in the upper half.
+__device__ __forceinline__ double pair_sums(double v0, double v1) {
+    const unsigned long long a = (unsigned long long)__double_as_longlong(v0), b = (unsigned long long)__double_as_longlong(v1);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+// A wave takes two adjacent groups (one 128-byte line per token row) and walks its run of 32-token tiles with their
+// rotation blocks in registers and the next tile's line requested ahead.  Lane (c, h) computes half of token c's values
+// of both groups, then the ratio of group h: one division and square root per lane.
+// Bound by the fp64 sums and the start (rotation blocks, first tiles), a third of it by reading x.  2048 x 4096 on one
+// MI355X: 13.2 -> 9.3 us against a wave per (tile, group) that formed the codes' values in fp64; the mean 86 -> 6.3 us (2.4 from
+// the partial sums, 3.9 to compute the first ratios again) against one workgroup with one load in flight per thread.
+template <bool ROTATED>
+__global__ __launch_bounds__(64 * kErrWaves) void group_error_kernel(GroupErrorParams p, ErrPlan e) {
+    __shared__ double sums[kErrWaves][2];
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int chunk = blockIdx.x % e.chunks, run = blockIdx.x / e.chunks;
+    const int j0 = (chunk * kErrWaves + wave) * 2;
+    double sum = 0.0, count = 0.0;
+    if (j0 < p.G) {
+        const int j1 = j0 + 1 < p.G ? j0 + 1 : j0;           // an odd last group: computed twice, stored once
+        RotOperand op0, op1;
+        if constexpr (ROTATED) {
+            load_rot_operand(p.R + (int64_t)j0 * p.r_stride, c, h, op0);
+            load_rot_operand(p.R + (int64_t)j1 * p.r_stride, c, h, op1);
+        }
+        const int step1 = 32 * (j1 - j0);
+        auto load = [&](u32x4 (&v)[4], int tile) {
+            const int token = tile * 32 + c;
+            const uint16_t* xr = p.x + (int64_t)(token < p.rows ? token : p.rows - 1) * p.ldx + 32 * j0;   // past the end: a valid row
+            if constexpr (ROTATED) {
+                v[0] = *(const u32x4*)(xr + 8 * h);
+                v[1] = *(const u32x4*)(xr + 8 * h + 16);
+                v[2] = *(const u32x4*)(xr + step1 + 8 * h);
+                v[3] = *(const u32x4*)(xr + step1 + 8 * h + 16);
+            } else {
+                // channels 8 q + 4 h .. + 3 of each group, the layout rotate_tile would give
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint2 a = *(const uint2*)(xr + 8 * q + 4 * h), b = *(const uint2*)(xr + step1 + 8 * q + 4 * h);
+                    v[q / 2][2 * (q & 1)] = a.x;
+                    v[q / 2][2 * (q & 1) + 1] = a.y;
+                    v[2 + q / 2][2 * (q & 1)] = b.x;
+                    v[2 + q / 2][2 * (q & 1) + 1] = b.y;
+                }
+            }
+        };
+        auto values = [&](const u32x4* v, const RotOperand& op) {
+            if constexpr (ROTATED) {
+                const u32x4 xv[2] = {v[0], v[1]};
+                return rotate_tile(op, xv);
+            } else {
+                f32x16 acc;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t w = v[i / 4][i % 4];
+                    acc[2 * i] = __uint_as_float(w << 16);
+                    acc[2 * i + 1] = __uint_as_float(w & 0xFFFF0000u);
+                }
+                return acc;
+            }
+        };
+        u32x4 x[4], nx[4];
+        if (run < e.ntiles) load(x, run);
+        for (int tile = run; tile < e.ntiles; tile += e.runs) {
+            const int ahead = tile + e.runs < e.ntiles ? tile + e.runs : tile;
+            load(nx, ahead);
+            double n0, d0, n1, d1;
+            error_sums(values(x, op0), n0, d0);
+            error_sums(values(x + 2, op1), n1, d1);
+            const double num = pair_sums(n0, n1), den = pair_sums(d0, d1);
+            const int token = tile * 32 + c;
+            if (token < p.rows && j0 + h < p.G) {
+                const float r = den > 0.0 ? (float)sqrt(num / den) : -1.0f;
+                const int64_t at = (int64_t)token * p.G + j0 + h;
+                if (at >= e.keep_from && at < e.keep_to) p.err[at] = r;
+                if (r >= 0.f) { sum += (double)r; count += 1.0; }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[k] = nx[k];
+        }
+    }
+    if (!e.partials) return;
+    for (int off = 32; off > 0; off >>= 1) {
+        sum += __shfl_xor(sum, off);
+        count += __shfl_xor(count, off);
+    }
+    if (lane == 0) { sums[wave][0] = sum; sums[wave][1] = count; }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+        for (int k = 0; k < kErrWaves; ++k) t += sums[k][threadIdx.x];
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(t);
+        uint32_t* out = (uint32_t*)p.err + (int64_t)blockIdx.x * 4 + 2 * threadIdx.x;      // err is aligned to a float only
+        out[0] = (uint32_t)bits;
+        out[1] = (uint32_t)(bits >> 32);
+    }
+}
+
+// Mean of the ratios over the groups that have one (err >= 0), summed in a fixed order: each thread its elements or partial
+// sums in order, then a tree over the 1024 threads.
+template <bool PARTIALS>
 __global__ __launch_bounds__(1024) void group_error_mean_kernel(GroupErrorMeanParams p) {
-    const float* err = p.err;
-    const int64_t n = p.n;
     __shared__ double ssum[1024];
     __shared__ double scnt[1024];
     double s = 0.0, cnt = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) {
-        const float e = err[i];
-        if (e >= 0.f) { s += (double)e; cnt += 1.0; }
+    if constexpr (PARTIALS) {
+        const uint32_t* w = (const uint32_t*)p.err;
+        for (int64_t i = threadIdx.x; i < p.n; i += 1024) {
+            const uint32_t* q = w + 4 * i;
+            s += __longlong_as_double((long long)(((unsigned long long)q[1] << 32) | q[0]));
+            cnt += __longlong_as_double((long long)(((unsigned long long)q[3] << 32) | q[2]));
+        }
+    } else {
+        // eight elements in flight per thread: one workgroup reads at what a CU takes in
+        for (int64_t i = threadIdx.x; i < p.n; i += 8 * 1024) {
+            float e[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) e[k] = i + k * 1024 < p.n ? p.err[i + k * 1024] : -1.f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (e[k] >= 0.f) { s += (double)e[k]; cnt += 1.0; }
+        }
     }
     ssum[threadIdx.x] = s;
     scnt[threadIdx.x] = cnt;
@@ -84,13 +210,45 @@ __global__ __launch_bounds__(1024) void group_error_mean_kernel(GroupErrorMeanPa
     if (threadIdx.x == 0) *p.mean = scnt[0] > 0.0 ? ssum[0] / scnt[0] : 0.0;
 }
 
+}  // namespace
+
 hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream) {
     const int64_t tiles = ((int64_t)p.rows + 31) / 32;
     if (p.G < 1 || p.rows < 1 || tiles > kGroupErrorMaxTiles) return hipErrorInvalidValue;
-    hipError_t e = launch(group_error_kernel, dim3((unsigned)p.G, (unsigned)tiles), dim3(64), 0, stream, p);
-    if (e != hipSuccess || !p.mean) return e;
-    const GroupErrorMeanParams m{p.err, (int64_t)p.rows * p.G, p.mean};
-    return launch(group_error_mean_kernel, dim3(1), dim3(1024), 0, stream, m);
+    const int64_t n = (int64_t)p.rows * p.G;
+    const int per_chunk = 2 * kErrWaves;
+    auto plan = [&](int ntiles) {
+        ErrPlan e{};
+        e.chunks = (p.G + per_chunk - 1) / per_chunk;
+        e.runs = kErrWorkgroups / e.chunks;
+        e.runs = e.runs < 1 ? 1 : (e.runs > ntiles ? ntiles : e.runs);
+        e.ntiles = ntiles;
+        e.keep_to = n;
+        return e;
+    };
+    auto run = [&](const ErrPlan& e) {
+        const dim3 grid((unsigned)(e.chunks * e.runs)), block(64 * kErrWaves);
+        return p.R ? launch(group_error_kernel<true>, grid, block, 0, stream, p, e)
+                   : launch(group_error_kernel<false>, grid, block, 0, stream, p, e);
+    };
+    ErrPlan e = plan((int)tiles);
+    const int64_t workgroups = (int64_t)e.chunks * e.runs, held = 4 * workgroups;   // floats the partial sums take
+    if (!p.mean || n < kPartialsFrom || held > n) {
+        const hipError_t st = run(e);
+        if (st != hipSuccess || !p.mean) return st;
+        return launch(group_error_mean_kernel<false>, dim3(1), dim3(1024), 0, stream, GroupErrorMeanParams{p.err, n, p.mean});
+    }
+    // The partial sums need a place until the mean is formed, and the call has no scratch: they take the first floats of err,
+    // whose ratios (at most a few token tiles) are computed once more afterwards.
+    e.partials = 1;
+    e.keep_from = held;
+    hipError_t st = run(e);
+    if (st != hipSuccess) return st;
+    st = launch(group_error_mean_kernel<true>, dim3(1), dim3(1024), 0, stream, GroupErrorMeanParams{p.err, workgroups, p.mean});
+    if (st != hipSuccess) return st;
+    ErrPlan again = plan((int)(((held + p.G - 1) / p.G + 31) / 32));
+    again.keep_to = held;
+    return run(again);
 }
 
 }  // namespace duqpp
