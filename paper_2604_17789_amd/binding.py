@@ -103,12 +103,20 @@ def _check(status, what):
         raise DuqppError(status, what)
 
 
+# What a call costs on the host counts: two launches take 4.4 us there, and everything below has to stay small beside them
+# (rotq_gemm_tiled_packed with its buffers given: 13.0 us per call with a torch.cuda.Stream object built for every call and
+# the layout's sizes fetched through the C call, 9.1 us without).
+_current_device = torch._C._cuda_getDevice
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device as the integer the C calls take."""
+    return _raw_stream(_current_device())
 
 
 def _dev(t, dtype, what):
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype):
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype):
         raise TypeError(f"{what} must be a cuda tensor of {dtype}")
     return t
 
@@ -261,11 +269,22 @@ def group_error(x, R=None, return_mean=True):
 
 
 # ---------------------------------------------------------------- tiled operand layout
+_MOST = 1 << 30                                              # rows and K the library takes
+
+
 def tiled_bytes(rows, K):
     """(codes bytes, scales bytes) of the tiled form of a [rows, K] operand."""
+    if 1 <= rows <= _MOST and 32 <= K <= _MOST and K % 32 == 0:
+        n = (rows + 31) // 32 * ((K + 255) // 256)           # row tiles x runs of 8 groups: 4096 code and 256 scale bytes each
+        return n * 4096, n * 256
     cb, sb = ctypes.c_size_t(0), ctypes.c_size_t(0)
     _check(lib.duqpp_tiled_bytes(rows, K, ctypes.byref(cb), ctypes.byref(sb)), "duqpp_tiled_bytes")
     return int(cb.value), int(sb.value)
+
+
+def _tiled_workspace(T, K, device):
+    cb, sb = tiled_bytes(T, K)
+    return torch.empty(((cb + 255) // 256 + (sb + 255) // 256) * 256, dtype=torch.uint8, device=device)
 
 
 def _tiled_buffers(rows, K, device, out=None):
@@ -363,9 +382,8 @@ def rotq_gemm_tiled_packed(x, R_packed, b_codes_t, b_scales_t, N, out_dtype=F32,
     if (b_codes_t.numel(), b_scales_t.numel()) != tiled_bytes(N, K):
         raise ValueError("weight operand sizes disagree with N, K")
     y = _out(T, N, out_dtype, x.device, out)
-    cb, sb = tiled_bytes(T, K)
     if workspace is None:
-        workspace = torch.empty(((cb + 255) // 256 + (sb + 255) // 256) * 256, dtype=torch.uint8, device=x.device)
+        workspace = _tiled_workspace(T, K, x.device)
     _check(lib.duqpp_rotq_gemm_tiled_packed(x.data_ptr(), x.stride(0), R_packed.data_ptr(), _n_packed(R_packed),
                                             b_codes_t.data_ptr(), b_scales_t.data_ptr(), T, N, K, y.data_ptr(), out_dtype,
                                             y.stride(0), workspace.data_ptr(), workspace.numel(), _stream()),
@@ -427,10 +445,8 @@ def rotq_gemm_tiled(x, R, b_codes_t, b_scales_t, N, out_dtype=F32, out=None, wor
     if (b_codes_t.numel(), b_scales_t.numel()) != tiled_bytes(N, K):
         raise ValueError("weight operand sizes disagree with N, K")
     y = _out(T, N, out_dtype, x.device, out)
-    cb, sb = tiled_bytes(T, K)
-    need = ((cb + 255) // 256 + (sb + 255) // 256) * 256
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+        workspace = _tiled_workspace(T, K, x.device)
     _check(lib.duqpp_rotq_gemm_tiled(x.data_ptr(), x.stride(0), R.data_ptr(), _n_rblocks(R), b_codes_t.data_ptr(),
                                      b_scales_t.data_ptr(), T, N, K, y.data_ptr(), out_dtype, y.stride(0),
                                      workspace.data_ptr(), workspace.numel(), _stream()), "duqpp_rotq_gemm_tiled")
