@@ -60,10 +60,11 @@ int validate_rows_K(int64_t rows, int64_t K, int64_t ld, int64_t n_rblocks) {
     return DUQPP_OK;
 }
 
-// R: fp32 blocks, or with `packed` the blocks in the form duqpp_pack_rotation writes (tiled output only).
+// R: fp32 blocks, or with `packed` the blocks in the form duqpp_pack_rotation writes (tiled output only).  `weights`
+// (tiled output, fp32 blocks) is a row-major operand to be put into the tiled layout by the same launch.
 int rotate_quantize_impl(const void* x, int64_t rows, int64_t K, int64_t ldx, const void* R, int64_t n_rblocks,
                          uint8_t* codes, uint8_t* scales, float* ydbg, void* stream, bool tiled = false,
-                         bool packed = false) {
+                         bool packed = false, const LayoutParams* weights = nullptr) {
     int st = duqpp_validate_rotate_quantize(x, rows, K, ldx, static_cast<const float*>(R), n_rblocks, codes, scales);
     if (st != DUQPP_OK) return st;
     if (ydbg && !aligned_to(ydbg, 16)) return DUQPP_ERR_ALIGN;
@@ -85,7 +86,8 @@ int rotate_quantize_impl(const void* x, int64_t rows, int64_t K, int64_t ldx, co
     p.tiled = tiled ? 1 : 0;
     p.GP = (int)tiled_groups(K / 32);
     plan_rotq(p);
-    return launch_rotq(p, static_cast<hipStream_t>(stream)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
+    const hipStream_t hs = static_cast<hipStream_t>(stream);
+    return (weights ? launch_rotq_and_tile(p, *weights, hs) : launch_rotq(p, hs)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
 }
 
 // Scratch of the row-major GEMM calls: both operands in the tiled layout, each part rounded up to 256 bytes:
@@ -227,7 +229,7 @@ int duqpp_mxfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const uint
     const int G = (int)(K / 32), GP = (int)tiled_groups(G);
     LayoutParams la{a_codes, a_scales, ws + w.a_codes, ws + w.a_scales, (int)T, G, GP};
     LayoutParams lb{b_codes, b_scales, ws + w.b_codes, ws + w.b_scales, (int)N, G, GP};
-    if (launch_tile(la, hs) != hipSuccess || launch_tile(lb, hs) != hipSuccess) return DUQPP_ERR_HIP;
+    if (launch_tile(la, lb, hs) != hipSuccess) return DUQPP_ERR_HIP;
     TiledGemmParams p{ws + w.a_codes, ws + w.a_scales, ws + w.b_codes, ws + w.b_scales, (int)T, (int)N, GP,
                       y, ldy, out_dtype == DUQPP_BF16};
     return launch_gemm_tiled(p, hs) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
@@ -245,15 +247,14 @@ int duqpp_rotq_gemm(const void* x_bf16, int64_t ldx, const float* R, int64_t n_r
     if (st != DUQPP_OK) return st;
     st = check_device();
     if (st != DUQPP_OK) return st;
-    // activations are rotated and quantised straight into the tiled layout; the row-major weights are re-tiled
+    // one launch rotates and quantises the activations straight into the tiled layout and re-tiles the row-major weights
     hipStream_t hs = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     const TiledScratch w = tiled_scratch(T, N, K);
     const int G = (int)(K / 32), GP = (int)tiled_groups(G);
-    st = rotate_quantize_impl(x_bf16, T, K, ldx, R, n_rblocks, ws + w.a_codes, ws + w.a_scales, nullptr, stream, true);
+    const LayoutParams lb{b_codes, b_scales, ws + w.b_codes, ws + w.b_scales, (int)N, G, GP};
+    st = rotate_quantize_impl(x_bf16, T, K, ldx, R, n_rblocks, ws + w.a_codes, ws + w.a_scales, nullptr, stream, true, false, &lb);
     if (st != DUQPP_OK) return st;
-    LayoutParams lb{b_codes, b_scales, ws + w.b_codes, ws + w.b_scales, (int)N, G, GP};
-    if (launch_tile(lb, hs) != hipSuccess) return DUQPP_ERR_HIP;
     TiledGemmParams p{ws + w.a_codes, ws + w.a_scales, ws + w.b_codes, ws + w.b_scales, (int)T, (int)N, GP,
                       y, ldy, out_dtype == DUQPP_BF16};
     return launch_gemm_tiled(p, hs) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;

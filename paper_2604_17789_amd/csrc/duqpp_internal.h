@@ -142,6 +142,8 @@ struct LayoutParams {
     int rows, G, GP;
 };
 hipError_t launch_tile(const LayoutParams& p, hipStream_t stream);     // row-major -> tiled (writes the padding too)
+hipError_t launch_tile(const LayoutParams& a, const LayoutParams& b, hipStream_t stream);   // two operands in one launch
+hipError_t launch_rotq_and_tile(const RotqParams& p, const LayoutParams& w, hipStream_t stream);   // independent of each other
 hipError_t launch_untile(const LayoutParams& p, hipStream_t stream);   // tiled -> row-major
 
 // ---- smoothing merged into the rotation blocks (smooth.hip) ---------------------------------

@@ -1,0 +1,52 @@
+// Device code shared by the kernels that put a row-major MXFP4 operand into the tiled layout (layout.hip, rotq.hip).
+#ifndef DUQPP_LAYOUT_DEVICE_H
+#define DUQPP_LAYOUT_DEVICE_H
+
+#include "duqpp_internal.h"
+
+namespace duqpp {
+
+// A unit of work is one row tile x 8 groups: 4 KiB of codes and 256 bytes of scales, moved by one wave.
+__host__ __device__ inline int64_t tile_units(const LayoutParams& p) { return (int64_t)((p.rows + 31) / 32) * (p.GP / 8); }
+
+// Codes: lane (row % 8, group) of four loads reads 16 bytes, so that a row's 128 bytes are one run, and stores them at
+// group * 512 + row * 16, where eight rows are a run of 128 bytes again: both sides move whole lines without LDS.  (With a
+// thread per (group, row) in the order of the tiled layout the reads were 16 bytes out of every row's line.)  Rows and
+// groups of the padding read a valid place and are replaced, so that no branch stands between the loads.
+__device__ __forceinline__ void tile_unit(const LayoutParams& p, int64_t unit, int lane) {
+    const int NI = p.GP / 8;
+    const int64_t rt = unit / NI;
+    const int q8 = (int)(unit % NI);
+    const int ch = lane & 7, r8 = lane >> 3;
+    const int j = 8 * q8 + ch, jl = j < p.G ? j : p.G - 1;
+    uint4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t row = 32 * rt + 8 * i + r8, rl = row < p.rows ? row : p.rows - 1;
+        v[i] = *(const uint4*)(p.src_codes + (rl * p.G + jl) * 16);
+    }
+    const int r = lane & 31, h = lane >> 5, j0 = 8 * q8 + 4 * h;
+    const int64_t srow = 32 * rt + r;
+    const uint8_t* sr = p.src_scales + (srow < p.rows ? srow : p.rows - 1) * p.G;
+    uint32_t s = 0;
+    if ((p.G & 3) == 0 && ((uintptr_t)p.src_scales & 3) == 0) {            // the rows of scales are whole words
+        s = *(const uint32_t*)(sr + (j0 < p.G ? j0 : 0));
+        if (j0 >= p.G || srow >= p.rows) s = 0x7F7F7F7Fu;
+    } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t one = sr[j0 + b < p.G ? j0 + b : 0];
+            s |= (j0 + b < p.G && srow < p.rows ? one : 127u) << (8 * b);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool pad = 32 * rt + 8 * i + r8 >= p.rows || j >= p.G;
+        if (pad) v[i] = make_uint4(0, 0, 0, 0);
+        *(uint4*)(p.dst_codes + (rt * p.GP + j) * 512 + (8 * i + r8) * 16) = v[i];
+    }
+    *(uint32_t*)(p.dst_scales + unit * 256 + lane * 4) = s;
+}
+
+}  // namespace duqpp
+#endif

@@ -13,6 +13,7 @@
 // nearest even, saturates at 6, keeps the sign of zero and divides by the power of two held
 // in the exponent field of its scale operand (field 0 meaning 2^-127).
 #include "duqpp_internal.h"
+#include "layout_device.h"
 #include "rotq_device.h"
 
 namespace duqpp {
@@ -26,10 +27,10 @@ constexpr int kBlocksPerWG = kRotqWaves * kBlocksPerWave;
 // less time per launch at the prefill shapes)
 constexpr int kStreamedLoad = 2;
 
-__device__ __forceinline__ void logical_workgroup(int& logical) {
-    // Workgroups are dealt round-robin to the 8 XCDs; renumber so that each XCD gets a
-    // contiguous range of logical workgroups.
-    int id = blockIdx.x, n = gridDim.x;
+__device__ __forceinline__ void logical_workgroup(int& logical, int n) {
+    // Workgroups are dealt round-robin to the 8 XCDs; renumber the n that rotate so that each XCD
+    // gets a contiguous range of logical workgroups.
+    int id = blockIdx.x;
     int per = n / kNumXCD, rem = n % kNumXCD;
     int xcd = id % kNumXCD, slot = id / kNumXCD;
     logical = xcd * per + (xcd < rem ? xcd : rem) + slot;
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(WAVES * 64) void rotq_kernel(RotqParams p) {
     using TL = RotqTile<WAVES, STAGES>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     int logical;
-    logical_workgroup(logical);
+    logical_workgroup(logical, gridDim.x);
     const int chunk = logical % p.nchunks;                   // neighbours on an XCD: neighbouring columns, same rows
     const int tg = logical / p.nchunks;
     const int lane = threadIdx.x & 63;
@@ -313,10 +314,9 @@ __device__ __forceinline__ void issue_wave_tile(const RotqParams& p, uint32_t ld
 }
 
 template <int STAGES, bool PACKED>
-__global__ __launch_bounds__(512) void rotq_wave_kernel(RotqParams p) {
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+__device__ __forceinline__ void rotq_wave(const RotqParams& p, uint8_t* lds, int workgroups) {
     int logical;
-    logical_workgroup(logical);
+    logical_workgroup(logical, workgroups);
     // Which workgroups share an XCD (the renumbering keeps consecutive logical ones together):
     //  - by_columns: an XCD owns a few column chunks for all token runs, so each rotation block is fetched into one
     //    L2 only, and (token tiles being dealt to the runs in turn, below) its workgroups read neighbouring rows of
@@ -405,6 +405,29 @@ __global__ __launch_bounds__(512) void rotq_wave_kernel(RotqParams p) {
     }
 }
 
+template <int STAGES, bool PACKED>
+__global__ __launch_bounds__(512) void rotq_wave_kernel(RotqParams p) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    rotq_wave<STAGES, PACKED>(p, lds, gridDim.x);
+}
+
+// The same in the first workgroups, and in those behind them a row-major operand put into the tiled layout: the two
+// have nothing to do with each other, and each alone leaves the chip waiting for its first loads for most of its time.
+// 512 tokens and 4096 x 4096 weights on one MI355X: 5.0 and 5.5 us as two launches, 7.2 us as one.
+template <int STAGES>
+__global__ __launch_bounds__(512) void rotq_wave_and_tile_kernel(RotqParams p, LayoutParams w) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    const int rotating = p.nchunks * p.ngroups;
+    if ((int)blockIdx.x < rotating) {
+        rotq_wave<STAGES, false>(p, lds, rotating);
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t units = tile_units(w), stride = (int64_t)((int)gridDim.x - rotating) * p.waves;
+    for (int64_t unit = (int64_t)((int)blockIdx.x - rotating) * p.waves + wave; unit < units; unit += stride) tile_unit(w, unit, lane);
+}
+
 constexpr int kRotqStages = 4;             // 3 tiles in flight, one in use
 
 constexpr int kWaveStages = 2;             // per-wave ring of the tiled-output kernel: 2 tiles of 4 KiB in flight, or
@@ -483,7 +506,11 @@ hipError_t setup_rotq() {
         constexpr int kDeepLdsMax = 8 * kWaveStagesDeep * kWaveTileBytes;
         e = allow_dynamic_lds((const void*)rotq_wave_kernel<kWaveStagesDeep, false>, kDeepLdsMax);
         if (e != hipSuccess) return e;
-        return allow_dynamic_lds((const void*)rotq_wave_kernel<kWaveStagesDeep, true>, kDeepLdsMax);
+        e = allow_dynamic_lds((const void*)rotq_wave_kernel<kWaveStagesDeep, true>, kDeepLdsMax);
+        if (e != hipSuccess) return e;
+        e = allow_dynamic_lds((const void*)rotq_wave_and_tile_kernel<kWaveStages>, kWaveLdsMax);
+        if (e != hipSuccess) return e;
+        return allow_dynamic_lds((const void*)rotq_wave_and_tile_kernel<kWaveStagesDeep>, kDeepLdsMax);
     });
 }
 
@@ -505,6 +532,21 @@ hipError_t launch_rotq(const RotqParams& p, hipStream_t stream) {
     }
     if (p.r_packed) return hipErrorInvalidValue;             // the packed blocks feed the tiled-output kernel only
     return launch(rotq_kernel<kRotqWaves, kRotqStages, false>, grid, dim3(kRotqWaves * 64), TL::kLdsBytes, stream, p);
+}
+
+constexpr int64_t kTileWorkgroups = 8192;  // beyond these a wave takes several units
+
+hipError_t launch_rotq_and_tile(const RotqParams& p, const LayoutParams& w, hipStream_t stream) {
+    hipError_t e = setup_rotq();
+    if (e != hipSuccess) return e;
+    if (!p.tiled || p.r_packed || p.waves < 1 || p.waves > 8) return hipErrorInvalidValue;
+    if (p.stages != kWaveStages && p.stages != kWaveStagesDeep) return hipErrorInvalidValue;
+    const int64_t need = (tile_units(w) + p.waves - 1) / p.waves;
+    const dim3 grid((unsigned)((int64_t)p.nchunks * p.ngroups + (need < kTileWorkgroups ? need : kTileWorkgroups)));
+    const dim3 block(p.waves * 64);
+    const size_t lds = (size_t)p.waves * p.stages * kWaveTileBytes;
+    return p.stages == kWaveStagesDeep ? launch(rotq_wave_and_tile_kernel<kWaveStagesDeep>, grid, block, lds, stream, p, w)
+                                       : launch(rotq_wave_and_tile_kernel<kWaveStages>, grid, block, lds, stream, p, w);
 }
 
 // Offline: the rotation blocks in the packed form load_rot_operand_packed reads.  One wave per block; the pieces are
