@@ -189,6 +189,7 @@ constexpr int kFusedMaxT = 32 * 65535;                    // token tiles run alo
 hipError_t launch_rotq_gemm_fused_decode(const FusedDecodeParams& p, hipStream_t stream);
 
 constexpr int kDecodeMaxT = 128;   // tokens the weight-streaming kernels take
+bool decode_takes_two_row_tiles(const TiledGemmParams& p);
 hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream);    // T <= kDecodeMaxT
 
 }  // namespace duqpp

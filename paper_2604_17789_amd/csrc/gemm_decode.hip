@@ -1,6 +1,6 @@
-// Decode-shape W4A4 MXFP4 GEMM (Eq. 5 with a handful of tokens): up to 32 tokens are one activation row tile and the
-// product is bound by streaming the weights from HBM (N * K * 17/32 bytes).  Tiled operand layout, same instruction and
-// K permutation as the prefill kernel.
+// Decode-shape W4A4 MXFP4 GEMM (Eq. 5 with a handful of tokens): up to 32 tokens are one activation row tile, in some
+// calls up to 64 are two (MT), and the product is bound by streaming the weights from HBM (N * K * 17/32 bytes).  Tiled
+// operand layout, same instruction and K permutation as the prefill kernel.
 //
 // One workgroup of 8 waves per ROWS = 32 or 16 output channels of a weight row tile: the streaming rate
 // a single CU sustains is a small fraction of the chip's, so the launch wants at least one workgroup per
@@ -22,33 +22,39 @@ constexpr int kDecWaves = 8;
 #define DUQPP_DEC_MFMA(ACC, A, B, SA, SB, SEL) \
     ACC = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(A), fp4_operand(B), ACC, 4, 4, SEL, (int)(SA), SEL, (int)(SB))
 
+template <int MT>
 struct DecStep {
-    u32x4 a[4], b[4];
-    uint32_t sa, sb;
+    u32x4 a[MT][4], b[4];
+    uint32_t sa[MT], sb;
 };
 
 // One K step's fragments.  No lane is switched off: a branch around a load makes the compiler wait for every
 // outstanding load at the join (s_waitcnt vmcnt(0)), i.e. for the step just requested as well as for the one about
 // to be multiplied, and the two steps in flight collapse into one.  Lanes without a token of their own re-read
-// row 0 (lane_code_a / lane4_a of such a lane point there): the same cache lines as lane 0, so
+// row 0 of the first activation tile (a_off / a_soff of such a lane point there): the same cache lines as lane 0, so
 // no extra traffic -- fetching all 32 rows of a tile that holds a handful of tokens would be more traffic into the CU
 // than the weights -- and their results fall on tokens >= T and are never stored.  Likewise the lanes beyond a
 // half-tile workgroup's 16 rows re-read rows 0..15 (lane_code_b is built from r % ROWS).
-__device__ __forceinline__ void dec_load(DecStep& d, const uint8_t* a_codes, const uint8_t* a_scales,
-                                         const uint8_t* b_codes, const uint8_t* b_scales, int step, int lane_code_a,
-                                         int lane4_a, int lane_code_b, int lane4_b) {
-    const uint8_t* pa = a_codes + (int64_t)step * 4096 + lane_code_a;
+template <int ROWS, int MT>
+__device__ __forceinline__ void dec_load(DecStep<MT>& d, const uint8_t* a_codes, const uint8_t* a_scales,
+                                         const int64_t (&a_off)[MT], const int64_t (&a_soff)[MT],
+                                         const uint8_t* b_codes, const uint8_t* b_scales, int step, int lane_code_b,
+                                         int lane4_b) {
     const uint8_t* pb = b_codes + (int64_t)step * 4096 + lane_code_b;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) d.a[i] = *(const u32x4*)(pa + i * 512);
-    d.sa = *(const uint32_t*)(a_scales + (int64_t)step * 256 + lane4_a);
+    for (int m = 0; m < MT; ++m) {
+        const uint8_t* pa = a_codes + a_off[m] + (int64_t)step * 4096;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d.a[m][i] = *(const u32x4*)(pa + i * 512);
+        d.sa[m] = *(const uint32_t*)(a_scales + a_soff[m] + (int64_t)step * 256);
+    }
     // weights are read once
 #pragma unroll
     for (int i = 0; i < 4; ++i) d.b[i] = __builtin_nontemporal_load((const u32x4*)(pb + i * 512));
     d.sb = *(const uint32_t*)(b_scales + (int64_t)step * 256 + lane4_b);
 }
 
-template <bool OUT_BF16, int ROWS>
+template <bool OUT_BF16, int ROWS, int MT>
 __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmParams p) {
     static_assert(ROWS == 32 || ROWS == 16, "a row tile is cut into 1 or 2 workgroups");
     __shared__ float part[kDecWaves][16][64];              // [wave][accumulator register][lane]
@@ -66,34 +72,50 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmPa
 
     const uint8_t* b_codes = p.b_codes + (int64_t)rt * p.GP * 512;
     const uint8_t* b_scales = p.b_scales + (int64_t)rt * NI * 256;
+    const int64_t a_tile_bytes = (int64_t)p.GP * 512, a_tile_sbytes = (int64_t)NI * 256;
+    // this workgroup's activation row tiles: MT of them from m0; one past the last tile is all zeros
+    // (its results fall on tokens >= T and are dropped)
+    const int RTa = (p.T + 31) / 32;
+    const int m0 = blockIdx.y * MT;
     // A operand (activations): group 4 g + i of row r sits at (4 g + i) * 512 + r * 16, its scale word at
-    // (32 g + r) * 4, r the lane's token row or row 0 when it has none; B operand (weights): the same with row rb
-    const int ra = r < p.T ? r : 0;
-    const int lane_code_a = g * 2048 + ra * 16, lane_code_b = g * 2048 + rb * 16;
-    const int lane4_a = (g * 32 + ra) * 4, lane4_b = (g * 32 + rb) * 4;
-    auto load = [&](DecStep& d, int step) {
-        dec_load(d, p.a_codes, p.a_scales, b_codes, b_scales, step, lane_code_a, lane4_a, lane_code_b, lane4_b);
-    };
-
-    f32x16 acc;
+    // (32 g + r) * 4; B operand (weights): the same with row rb
+    const int lane_code = g * 2048 + r * 16, lane_code_b = g * 2048 + rb * 16;
+    const int lane4 = lane * 4, lane4_b = (g * 32 + rb) * 4;
+    // per activation row tile: this lane's token row, or row 0 of the first tile when it has none
+    int64_t a_off[MT], a_soff[MT];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    for (int m = 0; m < MT; ++m) {
+        const int mt = m0 + m;
+        const bool own = mt < RTa && r < p.T - 32 * mt;
+        a_off[m] = own ? mt * a_tile_bytes + lane_code : (int64_t)g * 2048;
+        a_soff[m] = own ? mt * a_tile_sbytes + lane4 : (int64_t)g * 128;
+    }
+
+    f32x16 acc[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[m][e] = 0.f;
 
     // The loads of step s + 1 are issued before the MFMAs of step s.
-    auto mfmas = [&](const DecStep& d) {
-        DUQPP_DEC_MFMA(acc, d.a[0], d.b[0], d.sa, d.sb, 0);
-        DUQPP_DEC_MFMA(acc, d.a[1], d.b[1], d.sa, d.sb, 1);
-        DUQPP_DEC_MFMA(acc, d.a[2], d.b[2], d.sa, d.sb, 2);
-        DUQPP_DEC_MFMA(acc, d.a[3], d.b[3], d.sa, d.sb, 3);
+    auto mfmas = [&](const DecStep<MT>& d) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            DUQPP_DEC_MFMA(acc[m], d.a[m][0], d.b[0], d.sa[m], d.sb, 0);
+            DUQPP_DEC_MFMA(acc[m], d.a[m][1], d.b[1], d.sa[m], d.sb, 1);
+            DUQPP_DEC_MFMA(acc[m], d.a[m][2], d.b[2], d.sa[m], d.sb, 2);
+            DUQPP_DEC_MFMA(acc[m], d.a[m][3], d.b[3], d.sa[m], d.sb, 3);
+        }
     };
-    if constexpr (ROWS == 32) {
-        // Whole row tiles: a wave has few steps (two at K = 4096), and the plain loop measured
+    if constexpr (ROWS == 32 && MT == 1) {
+        // Whole row tiles, one activation tile: a wave has few steps (two at K = 4096), and the plain loop measured
         // 1-4 % faster than the two-set form below (8192 x 8192, T = 32: 8.7 against 9.0 us).
         if (s0 < s1) {
-            DecStep cur, nxt;
-            load(cur, s0);
+            DecStep<MT> cur, nxt;
+            dec_load<ROWS, MT>(cur, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s0, lane_code_b, lane4_b);
             for (int s = s0; s < s1; ++s) {
-                if (s + 1 < s1) load(nxt, s + 1);
+                if (s + 1 < s1)
+                    dec_load<ROWS, MT>(nxt, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
                 mfmas(cur);
                 cur = nxt;
             }
@@ -102,46 +124,50 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmPa
         // Two register sets taking turns, two steps per round and no branch in the round: with a branch around a
         // load, or a copy from one set to the other, the compiler's wait covers the loads just issued as well and
         // only one step is ever in flight.
-        DecStep even, odd;
-        load(even, s0);
+        DecStep<MT> even, odd;
+        dec_load<ROWS, MT>(even, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s0, lane_code_b, lane4_b);
         int s = s0;
         for (; s + 2 < s1; s += 2) {
             // (the barriers keep the scheduler from gathering all loads of the round at its top, which again ends
             // every round with nothing in flight)
-            load(odd, s + 1);
+            dec_load<ROWS, MT>(odd, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(even);
             __builtin_amdgcn_sched_barrier(0);
-            load(even, s + 2);
+            dec_load<ROWS, MT>(even, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 2, lane_code_b, lane4_b);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(odd);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (s + 1 < s1) {
-            load(odd, s + 1);
+            dec_load<ROWS, MT>(odd, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
             mfmas(even);
             mfmas(odd);
         } else {
             mfmas(even);
         }
     }
-    // the eight partial tiles through LDS, summed in a fixed order
+    // per activation row tile: the eight partial tiles through LDS, summed in a fixed order
 #pragma unroll
-    for (int e = 0; e < 16; ++e) part[wave][e][lane] = acc[e];
-    __syncthreads();
-    // acc[e] of lane (r, g): token 8 (e / 4) + 4 g + e % 4, output channel 32 rt + rb (lanes r < ROWS).
-    // 1024 outputs, 512 threads: thread t sums register e = t / 64 and e + 8 of lane t % 64 over the waves.
+    for (int m = 0; m < MT; ++m) {
+        if (m > 0) __syncthreads();                        // the previous tile's partials have been read
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int e = (threadIdx.x >> 6) + 8 * h;
-        float sum = 0.f;
+        for (int e = 0; e < 16; ++e) part[wave][e][lane] = acc[m][e];
+        __syncthreads();
+        // acc[e] of lane (r, g): token 32 (m0 + m) + 8 (e / 4) + 4 g + e % 4, output channel 32 rt + rb (lanes r < ROWS).
+        // 1024 outputs, 512 threads: thread t sums register e = t / 64 and e + 8 of lane t % 64 over the waves.
 #pragma unroll
-        for (int w = 0; w < kDecWaves; ++w) sum += part[w][e][lane];
-        const int tok = 8 * (e / 4) + 4 * g + (e % 4);
-        const int col = rt * 32 + rb;
-        if (r < ROWS && tok < p.T && col < p.N) {
-            if (OUT_BF16) ((uint16_t*)p.y)[(int64_t)tok * p.ldy + col] = f32_to_bf16_rne(sum);
-            else ((float*)p.y)[(int64_t)tok * p.ldy + col] = sum;
+        for (int h = 0; h < 2; ++h) {
+            const int e = (threadIdx.x >> 6) + 8 * h;
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < kDecWaves; ++w) sum += part[w][e][lane];
+            const int tok = 32 * (m0 + m) + 8 * (e / 4) + 4 * g + (e % 4);
+            const int col = rt * 32 + rb;
+            if (r < ROWS && tok < p.T && col < p.N) {
+                if (OUT_BF16) ((uint16_t*)p.y)[(int64_t)tok * p.ldy + col] = f32_to_bf16_rne(sum);
+                else ((float*)p.y)[(int64_t)tok * p.ldy + col] = sum;
+            }
         }
     }
 }
@@ -238,11 +264,20 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode16_kernel(TiledGemm
     }
 }
 
-template <int ROWS>
+template <int ROWS, int MT>
 static hipError_t launch_decode_rows(const TiledGemmParams& p, unsigned tiles, hipStream_t stream) {
     dim3 grid(tiles * (32 / ROWS)), block(kDecWaves * 64);
-    return p.out_bf16 ? launch(gemm_decode_kernel<true, ROWS>, grid, block, 0, stream, p)
-                      : launch(gemm_decode_kernel<false, ROWS>, grid, block, 0, stream, p);
+    return p.out_bf16 ? launch(gemm_decode_kernel<true, ROWS, MT>, grid, block, 0, stream, p)
+                      : launch(gemm_decode_kernel<false, ROWS, MT>, grid, block, 0, stream, p);
+}
+
+// 33 to 64 tokens against a long K and about one weight row tile per CU: the tiles of gemm_tiled.hip would be one small
+// workgroup per CU or fewer, waiting for 112 steps from HBM one after the other, where eight waves share them here (whole
+// call, N = 8192, K = 28672: T = 48 39.0 us with those tiles, 31.8 here; T = 64 38.7 and 34.0).  With K = 14336 or less, or
+// half the row tiles, the tiles are as fast or faster (T = 64, N = 4096, K = 14336 13.3 us, 16.3 here).
+bool decode_takes_two_row_tiles(const TiledGemmParams& p) {
+    const int tiles = (p.N + 31) / 32;
+    return p.T > 32 && p.T <= 64 && p.GP > 512 && tiles >= kNumCU && tiles < 320;
 }
 
 hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream) {
@@ -254,6 +289,7 @@ hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream) {
     // cannot keep enough requests in flight and splitting K over eight waves wins (N = 4096, K = 14336: T = 32 11.6
     // against 15.6; N = K = 4096: 5.1 against 6.2; from 33 tokens on 6.3 against 6.2 and 14.2 against 15.5 there, and
     // 13.3 against 10.3 with the weights in the last-level cache).
+    if (decode_takes_two_row_tiles(p)) return launch_decode_rows<32, 2>(p, tiles, stream);
     if (p.T > 32 || (p.T > 16 && tiles >= 320)) return launch_gemm_streaming_tiles(p, stream);
     // Fewer row tiles than CUs: half tiles, twice the workgroups (whole tiles on
     // half the CUs are slower from 9 tokens on).  Quartering the tiles, 16 waves per workgroup or register rings three
@@ -265,7 +301,7 @@ hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream) {
         return p.out_bf16 ? launch(gemm_decode16_kernel<true>, grid, block, 0, stream, p)
                           : launch(gemm_decode16_kernel<false>, grid, block, 0, stream, p);
     }
-    return tiles < (unsigned)kNumCU ? launch_decode_rows<16>(p, tiles, stream) : launch_decode_rows<32>(p, tiles, stream);
+    return tiles < (unsigned)kNumCU ? launch_decode_rows<16, 1>(p, tiles, stream) : launch_decode_rows<32, 1>(p, tiles, stream);
 }
 
 }  // namespace duqpp

@@ -495,7 +495,7 @@ hipError_t launch_gemm_streaming_tiles(const TiledGemmParams& p, hipStream_t str
 
 // Which kernel runs a shape, by the names of the ABI.
 int choose_gemm_kernel(const TiledGemmParams& p) {
-    if (p.T <= 32) return DUQPP_GEMM_KERNEL_DECODE;
+    if (p.T <= 32 || decode_takes_two_row_tiles(p)) return DUQPP_GEMM_KERNEL_DECODE;
     const Shape* s = choose_shape(p);
     if (p.T <= 64 && streaming_shape(*s)) return DUQPP_GEMM_KERNEL_DECODE;
     if (small_shape(*s)) return DUQPP_GEMM_KERNEL_SMALL;
@@ -506,7 +506,8 @@ int choose_gemm_kernel(const TiledGemmParams& p) {
 
 hipError_t launch_gemm_tiled_as(const TiledGemmParams& p, int kernel, hipStream_t stream) {
     switch (kernel) {
-        case DUQPP_GEMM_KERNEL_AUTO: return p.T <= 32 ? launch_gemm_decode(p, stream) : run_shape(choose_shape(p), p, stream);
+        case DUQPP_GEMM_KERNEL_AUTO:
+            return p.T <= 32 || decode_takes_two_row_tiles(p) ? launch_gemm_decode(p, stream) : run_shape(choose_shape(p), p, stream);
         case DUQPP_GEMM_KERNEL_DECODE: return p.T <= kDecodeMaxT ? launch_gemm_decode(p, stream) : hipErrorInvalidValue;
         case DUQPP_GEMM_KERNEL_SMALL: return run_shape(best_shape(p, small_shape), p, stream);
         case DUQPP_GEMM_KERNEL_MID: return run_shape(best_shape(p, mid_shape), p, stream);
