@@ -28,8 +28,10 @@
 // 3001 x 14336 x 4096 97.1 -> 87.3, 8192 x 4096 x 4096 71.0 -> 65.3, 8192 x 14336 x 4096 239.5 -> 219.5,
 // 4096 x 8192 x 28672 412.6 -> 393.7.
 //
-// The requests and LDS-DMA transfers are asm statements and their completion is awaited by hand: were the transfers
-// visible to the compiler as LDS writes, it would drain the whole queue before every LDS read it cannot disambiguate.
+// Requests and LDS-DMA transfers are builtins, so that the compiler knows which registers are still being written and counts
+// every transfer in its waits for them.  Its waits for the transfers themselves would drain the whole queue before every LDS
+// read, so gemm_tile is given the LDS twice, as the destination of the transfers and as what is read, each restrict: the
+// compiler leaves that order to arrive(), which counts on the order of the requests (hence the sched_barriers).
 #include <type_traits>
 #include <utility>
 
@@ -48,10 +50,6 @@ constexpr int kTileStepBytes = 8 * 512;                 // codes of one row tile
 #define DUQPP_MFMA(ACC, A, B, SA, SB, SEL) \
     ACC = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand(A), fp4_operand(B), ACC, 4, 4, SEL, (int)(SA), SEL, (int)(SB))
 
-// M0 carries the LDS destination of an LDS-DMA transfer; the compiler reserves the register but
-// has no use for it in this kernel, and the clobber tells it the value does not survive.
-#pragma clang diagnostic ignored "-Winline-asm"
-
 template <int N, typename F, int... I>
 __device__ __forceinline__ void unroll_impl(F&& f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, I>{}), ...);
@@ -61,37 +59,36 @@ __device__ __forceinline__ void unroll(F&& f) {
     unroll_impl<N>(f, std::make_integer_sequence<int, N>{});
 }
 
-// 16 (4) bytes per lane from base + voff + OFF into the registers that hold `r` already: the transfer is asynchronous, so
-// the value may be used only behind a wait that names it (below), and the in-out operand keeps the register the same one
-// from the request to the wait.
+// 16 (4) bytes per lane from base + voff + OFF.  Ordinary loads: the compiler knows which registers are still being written
+// and waits for them itself ahead of their use.
+typedef const __attribute__((address_space(1))) uint8_t* GlobalBytes;
 template <int OFF>
-__device__ __forceinline__ void request_b128(u32x4& r, uint32_t voff, const uint8_t* base) {
-    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "+v"(r) : "v"(voff), "s"(base), "n"(OFF));
+__device__ __forceinline__ u32x4 request_b128(uint32_t voff, const uint8_t* base) {
+    asm("" : "+v"(voff));   // keeps the lane's offset a 32-bit register: widened ahead of the loop it would cost an addition per request
+    return *(const __attribute__((address_space(1))) u32x4*)((GlobalBytes)base + voff + OFF);
 }
-__device__ __forceinline__ void request_b32(uint32_t& r, uint32_t voff, const uint8_t* base) {
-    asm volatile("global_load_dword %0, %1, %2" : "+v"(r) : "v"(voff), "s"(base));
+__device__ __forceinline__ uint32_t request_b32(uint32_t voff, const uint8_t* base) {
+    asm("" : "+v"(voff));
+    return *(const __attribute__((address_space(1))) uint32_t*)((GlobalBytes)base + voff);
 }
-// (the immediate offset advances both addresses)
-template <int OFF>
-__device__ __forceinline__ void dma_1k_s(uint32_t voff, const uint8_t* base, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" : : "v"(voff), "s"(base), "s"(lds_dst), "n"(OFF) : "memory", "m0");
-}
-__device__ __forceinline__ void dma_256_s(uint32_t voff, const uint8_t* base, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(base), "s"(lds_dst) : "memory", "m0");
+// 16 (4) bytes per lane from base + soff + voff + OFF to dst + OFF + 16 (4) * lane in LDS.  The form with a buffer descriptor: the
+// compiler takes the one with a plain address for an access to LDS as well and drains the whole queue at the next wait.
+typedef __attribute__((address_space(3))) uint8_t* LdsBytes;
+typedef __attribute__((address_space(3))) uint16_t* LdsU16;
+typedef const __attribute__((address_space(3))) uint32_t* LdsU32;
+typedef const __attribute__((address_space(3))) u32x4* LdsU32x4;
+template <int BYTES, int OFF>
+__device__ __forceinline__ void dma(const uint8_t* base, uint32_t soff, uint32_t voff, LdsBytes dst) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xFFFFFFFF, 0x00020000);
+    const auto to = (__attribute__((address_space(3))) void*)dst;
+    if constexpr (BYTES == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, to, 16, voff, soff, OFF, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, to, 4, voff, soff, OFF, 0);
 }
 
-// At most N requests outstanding, and the registers named hold their values from here on; then every LDS access of this
-// wave has completed, and all waves of the workgroup have come this far.
+// At most N requests outstanding, every LDS access of this wave completed, and all waves of the workgroup come this far.
 template <int N>
-__device__ __forceinline__ void arrive(u32x4 (&b)[1][4], uint32_t (&s)[1]) {
-    asm volatile("s_waitcnt vmcnt(%5) lgkmcnt(0)\n\ts_barrier"
-                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]), "+v"(s[0]) : "n"(N) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void arrive(u32x4 (&b)[2][4], uint32_t (&s)[2]) {
-    asm volatile("s_waitcnt vmcnt(%10) lgkmcnt(0)\n\ts_barrier"
-                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]), "+v"(s[0]),
-                   "+v"(b[1][0]), "+v"(b[1][1]), "+v"(b[1][2]), "+v"(b[1][3]), "+v"(s[1]) : "n"(N) : "memory");
+__device__ __forceinline__ void arrive() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
 // Every LDS access this wave has issued has completed, then workgroup barrier.
@@ -122,9 +119,8 @@ constexpr int kGroupM = 8;
 static __device__ __align__(1024) const uint8_t zero_codes[kTileStepBytes] = {};
 
 template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
-__global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams p) {
+__device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged, LdsBytes __restrict__ lds) {
     using TL = Tile<MT, NT, D, W>;
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, g = lane >> 5;
@@ -156,20 +152,21 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
 
     // sources of the step to request next; tiles past the ragged edge are replaced by the last valid one (their outputs
     // are never stored)
-    const uint8_t* a_src[MT];
-    const uint8_t* as_src[TL::kSOps];
     const uint8_t* b_src[NT];
     const uint8_t* bs_src[NT];
-    auto a_tile = [&](int m) { const int rt = tile_m * MT + m; return rt < RTa ? rt : RTa - 1; };
+    // tokens: the tile's first row tile, and the others' distance from it (below 4 GiB: best_shape)
+    const uint8_t* a_src = p.a_codes + (int64_t)(tile_m * MT) * tile_bytes;
+    const uint8_t* as_src = p.a_scales + (int64_t)(tile_m * MT) * tile_sbytes;
+    auto valid = [&](int m) { return (uint32_t)(tile_m * MT + m < RTa ? m : RTa - 1 - tile_m * MT); };
+    uint32_t a_off[MT], as_off[TL::kSOps];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) a_src[m] = p.a_codes + a_tile(m) * tile_bytes + wave * (TL::kPieces * 1024);
-    uint32_t as_dst[TL::kSOps];
-    const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)lds);
+    for (int m = 0; m < MT; ++m) a_off[m] = valid(m) * (uint32_t)tile_bytes;
+    LdsBytes as_dst[TL::kSOps];
 #pragma unroll
     for (int x = 0; x < TL::kSOps; ++x) {
         const int m = wave + W * x < MT ? wave + W * x : MT - 1;   // a wave without a tile of its own repeats the last one
-        as_src[x] = p.a_scales + a_tile(m) * tile_sbytes;
-        as_dst[x] = lds0 + TL::kScalesOff + m * 256;
+        as_off[x] = valid(m) * (uint32_t)tile_sbytes;
+        as_dst[x] = staged + TL::kScalesOff + m * 256;
     }
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
@@ -178,20 +175,18 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
         b_src[n] = p.b_codes + rt * tile_bytes;
         bs_src[n] = p.b_scales + rt * tile_sbytes;
     }
-    const uint32_t voff_dma = lane * 16, voff_word = lane * 4, voff_b = g * 2048 + r * 16;
-    const uint32_t a_dst = lds0 + wave * (TL::kPieces * 1024);
+    const uint32_t voff_dma = wave * (TL::kPieces * 1024) + lane * 16, voff_word = lane * 4, voff_b = g * 2048 + r * 16;
+    const LdsBytes a_dst = staged + wave * (TL::kPieces * 1024);
 
     // No branch: the K loop has to stay one straight piece of code, or the compiler moves products out from between the
-    // requests and copies registers whose contents are still on their way.
+    // requests and copies registers whose contents are still on their way (waiting for them first).
     int left = NI - 1;                                     // steps after the one the sources point at
     auto advance = [&]() {
         const uint32_t more = left > 0 ? 1u : 0u;
         const uint64_t keep = 0ull - more, zeros = (uint64_t)zero_codes & ~keep;
         --left;
-#pragma unroll
-        for (int m = 0; m < MT; ++m) a_src[m] += more * kTileStepBytes;
-#pragma unroll
-        for (int x = 0; x < TL::kSOps; ++x) as_src[x] += more * 256;
+        a_src += more * kTileStepBytes;
+        as_src += more * 256;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
             b_src[n] = (const uint8_t*)((((uint64_t)b_src[n] + kTileStepBytes) & keep) | zeros);
@@ -203,22 +198,14 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
     uint32_t sb[D][NT];
     u32x4 fa[2][MT];
     uint32_t sa[2][MT];
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            sb[d][n] = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) b[d][n][q] = (u32x4){0, 0, 0, 0};
-        }
 
     auto dma_op = [&](auto kc, uint32_t so) {
         constexpr int k = decltype(kc)::value;
         if constexpr (k < TL::kCOps) {
             constexpr int m = k / TL::kPieces, piece = k % TL::kPieces;
-            dma_1k_s<piece * 1024>(voff_dma, a_src[m], a_dst + m * kTileStepBytes + so);
+            dma<16, piece * 1024>(a_src, a_off[m], voff_dma, a_dst + m * kTileStepBytes + so);
         } else if constexpr (k < TL::kDma) {
-            dma_256_s(voff_word, as_src[k - TL::kCOps], as_dst[k - TL::kCOps] + so);
+            dma<4, 0>(as_src, as_off[k - TL::kCOps], voff_word, as_dst[k - TL::kCOps] + so);
         }
     };
 
@@ -228,13 +215,14 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
         unroll<TL::kDma>([&](auto kc) { dma_op(kc, d * TL::kStageBytes); });
         unroll<NT>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
-            request_b128<0>(b[d][n][0], voff_b, b_src[n]);
-            request_b128<512>(b[d][n][1], voff_b, b_src[n]);
-            request_b128<1024>(b[d][n][2], voff_b, b_src[n]);
-            request_b128<1536>(b[d][n][3], voff_b, b_src[n]);
-            request_b32(sb[d][n], voff_word, bs_src[n]);
+            b[d][n][0] = request_b128<0>(voff_b, b_src[n]);
+            b[d][n][1] = request_b128<512>(voff_b, b_src[n]);
+            b[d][n][2] = request_b128<1024>(voff_b, b_src[n]);
+            b[d][n][3] = request_b128<1536>(voff_b, b_src[n]);
+            sb[d][n] = request_b32(voff_word, bs_src[n]);
         });
         advance();
+        __builtin_amdgcn_sched_barrier(0);                 // the waits count on the steps' order
     });
     f32x16 acc[MT][NT];
 #pragma unroll
@@ -244,13 +232,13 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[m][n][e] = 0.f;
 
-    const uint8_t* pa0 = lds + g * 2048 + r * 16;
-    const uint8_t* ps0 = lds + TL::kScalesOff + lane * 4;
-    arrive<(D - 1) * TL::kOps>(b[0], sb[0]);
+    const LdsBytes pa0 = lds + g * 2048 + r * 16;
+    const LdsBytes ps0 = lds + TL::kScalesOff + lane * 4;
+    arrive<(D - 1) * TL::kOps>();
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-        fa[0][m] = *(const u32x4*)(pa0 + m * kTileStepBytes);
-        sa[0][m] = *(const uint32_t*)(ps0 + m * 256);
+        fa[0][m] = *(LdsU32x4)(pa0 + m * kTileStepBytes);
+        sa[0][m] = *(LdsU32)(ps0 + m * 256);
     }
 
     int stage = 0;
@@ -261,7 +249,7 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
         constexpr int P = decltype(pc)::value, P1 = (P + 1) % D;
         const int stage1 = stage + 1 == TL::kStages ? 0 : stage + 1;
         const uint32_t so = (stage == 0 ? TL::kStages - 1 : stage - 1) * TL::kStageBytes;   // consumed in the previous step
-        const uint8_t* pa = pa0 + stage * TL::kStageBytes;
+        const LdsBytes pa = pa0 + stage * TL::kStageBytes;
 #define DUQPP_PIN __builtin_amdgcn_sched_barrier(0)
         constexpr int kSlots = 3 * MT * NT;   // transfers spread over the first three quarters
         unroll<3>([&](auto qc) {
@@ -275,36 +263,36 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
                         constexpr int k0 = (slot * TL::kDma + kSlots - 1) / kSlots, k1 = ((slot + 1) * TL::kDma + kSlots - 1) / kSlots;
                         unroll<k1 - k0>([&](auto kc) { dma_op(std::integral_constant<int, k0 + decltype(kc)::value>{}, so); });
                     }
-                    if constexpr (n == 0) fa[(Q + 1) & 1][m] = *(const u32x4*)(pa + m * kTileStepBytes + (Q + 1) * 512);
+                    if constexpr (n == 0) fa[(Q + 1) & 1][m] = *(LdsU32x4)(pa + m * kTileStepBytes + (Q + 1) * 512);
                     DUQPP_PIN;
                     DUQPP_MFMA(acc[m][n], fa[Q & 1][m], b[P][n][Q], sa[P & 1][m], sb[P][n], Q);
                     DUQPP_PIN;
                 });
-                if constexpr (MORE) request_b128<Q * 512>(b[P][n][Q], voff_b, b_src[n]);
+                if constexpr (MORE) b[P][n][Q] = request_b128<Q * 512>(voff_b, b_src[n]);
                 DUQPP_PIN;
             });
         });
         // the next step's operands have arrived, for this wave and then for all
-        if constexpr (MORE) arrive<(D - 2) * TL::kOps + TL::kOps - TL::kLate>(b[P1], sb[P1]);
-        else if constexpr (P < D - 1) arrive<(D - 2 - P) * TL::kOps>(b[P1], sb[P1]);
+        if constexpr (MORE) arrive<(D - 2) * TL::kOps + TL::kOps - TL::kLate>();
+        else if constexpr (P < D - 1) arrive<(D - 2 - P) * TL::kOps>();
         DUQPP_PIN;
-        const uint8_t* na = pa0 + stage1 * TL::kStageBytes;
-        const uint8_t* ns = ps0 + stage1 * TL::kStageBytes;
+        const LdsBytes na = pa0 + stage1 * TL::kStageBytes;
+        const LdsBytes ns = ps0 + stage1 * TL::kStageBytes;
         unroll<NT>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
             unroll<MT>([&](auto mc) {
                 constexpr int m0 = decltype(mc)::value, m = (n & 1) ? MT - 1 - m0 : m0;
                 if constexpr (n == 0 && (MORE || P < D - 1)) {
-                    fa[0][m] = *(const u32x4*)(na + m * kTileStepBytes);
-                    sa[(P + 1) & 1][m] = *(const uint32_t*)(ns + m * 256);
+                    fa[0][m] = *(LdsU32x4)(na + m * kTileStepBytes);
+                    sa[(P + 1) & 1][m] = *(LdsU32)(ns + m * 256);
                 }
                 DUQPP_PIN;
                 DUQPP_MFMA(acc[m][n], fa[1][m], b[P][n][3], sa[P & 1][m], sb[P][n], 3);
                 DUQPP_PIN;
             });
             if constexpr (MORE) {
-                request_b128<1536>(b[P][n][3], voff_b, b_src[n]);
-                request_b32(sb[P][n], voff_word, bs_src[n]);
+                b[P][n][3] = request_b128<1536>(voff_b, b_src[n]);
+                sb[P][n] = request_b32(voff_word, bs_src[n]);
                 DUQPP_PIN;
             }
         });
@@ -329,7 +317,7 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
     if constexpr (OUT_BF16) {
         if ((reinterpret_cast<uintptr_t>(p.y) & 15) == 0 && (p.ldy % 8) == 0) {
             constexpr int kChunks = 4 * NT, kRows = 64 / kChunks;      // 16-byte pieces of a row; rows per store instruction
-            uint8_t* ep = lds + wave * TL::kEpBytes;
+            const LdsBytes ep = lds + wave * TL::kEpBytes;
             const int ch = lane % kChunks, row0 = lane / kChunks;
             const int gcol = n0 + ch * 8;
 #pragma unroll
@@ -341,14 +329,14 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
                     for (int e = 0; e < 16; e += 2) {
                         const bf16x2 v = __builtin_convertvector((f32x2){acc[m][n][e], acc[m][n][e + 1]}, bf16x2);
                         const uint32_t u = __builtin_bit_cast(uint32_t, v);
-                        uint8_t* q = ep + (8 * (e / 4) + 4 * g + (e % 4)) * TL::kPitch + (32 * n + r) * 2;
-                        *(uint16_t*)q = (uint16_t)u;
-                        *(uint16_t*)(q + TL::kPitch) = (uint16_t)(u >> 16);
+                        const LdsBytes q = ep + (8 * (e / 4) + 4 * g + (e % 4)) * TL::kPitch + (32 * n + r) * 2;
+                        *(LdsU16)q = (uint16_t)u;
+                        *(LdsU16)(q + TL::kPitch) = (uint16_t)(u >> 16);
                     }
 #pragma unroll
                 for (int k = 0; k < 32 / kRows; ++k) {
                     const int row = k * kRows + row0, grow = m0 + 32 * m + row;
-                    const u32x4 v = *(const u32x4*)(ep + row * TL::kPitch + ch * 16);
+                    const u32x4 v = *(LdsU32x4)(ep + row * TL::kPitch + ch * 16);
                     if (grow < p.T && gcol < p.N) {
                         uint16_t* dst = (uint16_t*)p.y + (int64_t)grow * p.ldy + gcol;
                         if (gcol + 8 <= p.N) {
@@ -377,6 +365,12 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
                 }
             }
         }
+}
+
+template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
+__global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams p) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    gemm_tile<OUT_BF16, MT, NT, D, W, OCC>(p, (LdsBytes)lds, (LdsBytes)lds);
 }
 
 template <int MT, int NT, int D, int W, int OCC>
@@ -446,6 +440,7 @@ const Shape* best_shape(const TiledGemmParams& p, Pred&& allowed) {
     double best_cost = 0.0;
     for (const Shape& s : kShapes) {
         if (!allowed(s) || (s.w < 4 && tiles_of(s, p) > kNumCU)) continue;
+        if ((int64_t)(s.mt - 1) * p.GP * 512 >= (int64_t)0xFFFFE000) continue;   // distances within a tile's tokens are 32-bit
         const double c = cost_of(s, p);
         if (!best || c < best_cost) { best = &s; best_cost = c; }
     }
@@ -465,6 +460,7 @@ bool large_ok(const TiledGemmParams& p) { return (p.N % 8) == 0 && gemm_tiled_la
 const Shape* choose_shape(const TiledGemmParams& p) { return large_ok(p) ? best_shape(p, any_shape) : best_shape(p, unaligned_shape); }
 
 hipError_t run_shape(const Shape* s, const TiledGemmParams& p, hipStream_t stream) {
+    if (!s) return hipErrorInvalidValue;
     hipError_t e = setup_gemm_tiled();
     return e == hipSuccess ? s->run(p, stream) : e;
 }
