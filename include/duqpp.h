@@ -214,17 +214,24 @@ int duqpp_mxfp4_gemm_tiled(const uint8_t* a_codes_t, const uint8_t* a_scales_t,
  * duqpp_mxfp4_gemm_tiled on one named kernel instead of the one the library would
  * pick for the shape, so that every kernel can be checked at every shape.  Same arguments, checks and result.
  * A kernel that cannot run the call returns DUQPP_ERR_SHAPE: the decode kernels take T <= 128; LARGE
- * with bf16 output needs y 16-byte aligned and N, ldy multiples of 8.
+ * with bf16 output needs y 16-byte aligned and N, ldy multiples of 8; tiles of 32 m tokens need (m - 1) * K * 16 bytes
+ * below 4 GiB.  The result's fp32 additions are in the same order for every tile.
  * duqpp_gemm_kernel_for reports (host, pure) which kernel DUQPP_GEMM_KERNEL_AUTO resolves to; it assumes an
- * aligned output.
+ * aligned output.  duqpp_gemm_tile_for reports which tile `kernel` (any of these values) runs a call with, as its index
+ * 0, 1, ..., or DUQPP_GEMM_SPLIT_K where the waves of a workgroup share K instead, and where tokens, channels are not null
+ * that tile's size; duqpp_gemm_tiles is how many tiles there are.
  */
 enum {
     DUQPP_GEMM_KERNEL_AUTO = 0,
     DUQPP_GEMM_KERNEL_DECODE = 1,   /* weight streaming, T <= 128: K split over the waves, or tiles of few tokens or channels */
     DUQPP_GEMM_KERNEL_SMALL = 2,    /* tiles of up to 128 tokens x 128 channels */
     DUQPP_GEMM_KERNEL_MID = 3,      /* tiles of 96 or 128 tokens x 256 channels */
-    DUQPP_GEMM_KERNEL_LARGE = 4     /* tiles of 128 to 256 tokens x 256 channels, several of them per CU */
+    DUQPP_GEMM_KERNEL_LARGE = 4,    /* tiles of 192 or 256 tokens x 256 channels */
+    DUQPP_GEMM_KERNEL_TILE = 16     /* + i: tile i */
 };
+#define DUQPP_GEMM_SPLIT_K 1000
+int duqpp_gemm_tiles(void);
+int duqpp_gemm_tile_for(int kernel, int64_t T, int64_t N, int64_t K, int out_dtype, int* tokens, int* channels);
 int duqpp_mxfp4_gemm_tiled_on(int kernel,
                               const uint8_t* a_codes_t, const uint8_t* a_scales_t,
                               const uint8_t* b_codes_t, const uint8_t* b_scales_t,

@@ -10,6 +10,8 @@ _LIB_NAME = "libduqpp.so"
 F32, BF16 = 0, 1
 # kernels of the tiled GEMM (the DUQPP_GEMM_KERNEL_* values of the header)
 KERNEL_AUTO, KERNEL_DECODE, KERNEL_SMALL, KERNEL_MID, KERNEL_LARGE = 0, 1, 2, 3, 4
+KERNEL_TILE = 16                                             # + i: tile i
+SPLIT_K = 1000                                               # gemm_tile_for where no tile runs the call
 
 
 class DuqppError(RuntimeError):
@@ -52,6 +54,10 @@ def _load():
     L.duqpp_mxfp4_gemm_tiled_on.restype = ci
     L.duqpp_gemm_kernel_for.argtypes = [i64, i64, i64, ci]
     L.duqpp_gemm_kernel_for.restype = ci
+    L.duqpp_gemm_tiles.argtypes = []
+    L.duqpp_gemm_tiles.restype = ci
+    L.duqpp_gemm_tile_for.argtypes = [ci, i64, i64, i64, ci, ctypes.POINTER(ci), ctypes.POINTER(ci)]
+    L.duqpp_gemm_tile_for.restype = ci
     L.duqpp_rotq_gemm_tiled.argtypes = [vp, i64, fp, i64, u8p, u8p, i64, i64, i64, vp, ci, i64, vp, sz, vp]
     L.duqpp_fold_smoothing.argtypes = [fp, i64, fp, i64, fp, fp, vp]
     L.duqpp_construct_rotation_workspace_bytes.argtypes = [i64, ci]
@@ -416,6 +422,19 @@ def gemm_kernel_for(T, N, K, out_dtype=F32):
     if k < 0:
         _check(k, "duqpp_gemm_kernel_for")
     return k
+
+
+def gemm_tiles():
+    return int(lib.duqpp_gemm_tiles())
+
+
+def gemm_tile_for(T, N, K, out_dtype=F32, kernel=KERNEL_AUTO):
+    """(index, tokens, channels) of the tile that runs a call, (SPLIT_K, 0, 0) where the waves share K instead."""
+    tokens, channels = ctypes.c_int(0), ctypes.c_int(0)
+    i = lib.duqpp_gemm_tile_for(kernel, T, N, K, out_dtype, ctypes.byref(tokens), ctypes.byref(channels))
+    if i < 0:
+        _check(i, "duqpp_gemm_tile_for")
+    return i, tokens.value, channels.value
 
 
 def mxfp4_gemm_tiled(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, out_dtype=F32, out=None, kernel=KERNEL_AUTO):

@@ -108,6 +108,11 @@ TiledScratch tiled_scratch(int64_t T, int64_t N, int64_t K) {
     return w;
 }
 
+bool is_gemm_kernel(int kernel) {
+    return (kernel >= DUQPP_GEMM_KERNEL_AUTO && kernel <= DUQPP_GEMM_KERNEL_LARGE) ||
+           (kernel >= DUQPP_GEMM_KERNEL_TILE && kernel < DUQPP_GEMM_KERNEL_TILE + gemm_tiles());
+}
+
 // The fused call on tiled weights with the activation operand in a_codes / a_scales (256-byte aligned scratch of
 // the sizes duqpp_tiled_bytes reports): every argument of both stages is checked before the first launch.
 int rotq_gemm_tiled_impl(const void* x_bf16, int64_t ldx, const void* R, int64_t n_rblocks, uint8_t* a_codes,
@@ -356,7 +361,7 @@ int duqpp_mxfp4_gemm_tiled(const uint8_t* a_codes_t, const uint8_t* a_scales_t, 
 int duqpp_mxfp4_gemm_tiled_on(int kernel, const uint8_t* a_codes_t, const uint8_t* a_scales_t,
                               const uint8_t* b_codes_t, const uint8_t* b_scales_t, int64_t T, int64_t N, int64_t K,
                               void* y, int out_dtype, int64_t ldy, void* stream) {
-    if (kernel < DUQPP_GEMM_KERNEL_AUTO || kernel > DUQPP_GEMM_KERNEL_LARGE) return DUQPP_ERR_SHAPE;
+    if (!is_gemm_kernel(kernel)) return DUQPP_ERR_SHAPE;
     int st = duqpp_validate_mxfp4_gemm(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, y, out_dtype, ldy,
                                        nullptr, 0, 2);
     if (st != DUQPP_OK) return st;
@@ -365,8 +370,7 @@ int duqpp_mxfp4_gemm_tiled_on(int kernel, const uint8_t* a_codes_t, const uint8_
         return DUQPP_ERR_ALIGN;
     TiledGemmParams p{a_codes_t, a_scales_t, b_codes_t, b_scales_t, (int)T, (int)N, (int)tiled_groups(K / 32),
                       y, ldy, out_dtype == DUQPP_BF16};
-    if (kernel == DUQPP_GEMM_KERNEL_DECODE && T > kDecodeMaxT) return DUQPP_ERR_SHAPE;
-    if (kernel == DUQPP_GEMM_KERNEL_LARGE && !gemm_tiled_large_accepts(p)) return DUQPP_ERR_SHAPE;
+    if (gemm_tile_for(p, kernel, nullptr, nullptr) < 0) return DUQPP_ERR_SHAPE;
     st = check_device();
     if (st != DUQPP_OK) return st;
     return launch_gemm_tiled_as(p, kernel, static_cast<hipStream_t>(stream)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
@@ -379,6 +383,17 @@ int duqpp_gemm_kernel_for(int64_t T, int64_t N, int64_t K, int out_dtype) {
     TiledGemmParams p{nullptr, nullptr, nullptr, nullptr, (int)T, (int)N, (int)tiled_groups(K / 32),
                       nullptr, N, out_dtype == DUQPP_BF16};
     return choose_gemm_kernel(p);
+}
+
+int duqpp_gemm_tiles(void) { return gemm_tiles(); }
+
+int duqpp_gemm_tile_for(int kernel, int64_t T, int64_t N, int64_t K, int out_dtype, int* tokens, int* channels) {
+    const int st = duqpp_gemm_kernel_for(T, N, K, out_dtype);
+    if (st < 0) return st;
+    TiledGemmParams p{nullptr, nullptr, nullptr, nullptr, (int)T, (int)N, (int)tiled_groups(K / 32),
+                      nullptr, N, out_dtype == DUQPP_BF16};
+    const int tile = is_gemm_kernel(kernel) ? gemm_tile_for(p, kernel, tokens, channels) : -1;
+    return tile < 0 ? DUQPP_ERR_SHAPE : tile;
 }
 
 int duqpp_rotq_gemm_tiled(const void* x_bf16, int64_t ldx, const float* R, int64_t n_rblocks,

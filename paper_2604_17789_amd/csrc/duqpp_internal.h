@@ -174,7 +174,8 @@ struct TiledGemmParams {
 hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream);     // picks the kernel by shape
 int choose_gemm_kernel(const TiledGemmParams& p);                              // the DUQPP_GEMM_KERNEL_* it picks
 hipError_t launch_gemm_tiled_as(const TiledGemmParams& p, int kernel, hipStream_t stream);   // a named kernel
-hipError_t launch_gemm_streaming_tiles(const TiledGemmParams& p, hipStream_t stream);    // the tiles that stream the weights
+int gemm_tiles();                                                              // tiles of the kernel
+int gemm_tile_for(const TiledGemmParams& p, int kernel, int* tokens, int* channels);   // duqpp_gemm_tile_for; -1: cannot run it
 bool gemm_tiled_large_accepts(const TiledGemmParams& p);                           // output alignment its name promises
 // ---- one-kernel rotate + quantise + multiply for up to 32 tokens (rotq_gemm_fused.hip) ----------------------
 struct FusedDecodeParams {
@@ -189,7 +190,7 @@ constexpr int kFusedMaxT = 32 * 65535;                    // token tiles run alo
 hipError_t launch_rotq_gemm_fused_decode(const FusedDecodeParams& p, hipStream_t stream);
 
 constexpr int kDecodeMaxT = 128;   // tokens the weight-streaming kernels take
-bool decode_takes_two_row_tiles(const TiledGemmParams& p);
-hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream);    // T <= kDecodeMaxT
+bool decode_splits_k(const TiledGemmParams& p);                                // the kernels of gemm_decode.hip run the call
+hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream);
 
 }  // namespace duqpp

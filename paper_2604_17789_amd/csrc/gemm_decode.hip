@@ -275,22 +275,26 @@ static hipError_t launch_decode_rows(const TiledGemmParams& p, unsigned tiles, h
 // workgroup per CU or fewer, waiting for 112 steps from HBM one after the other, where eight waves share them here (whole
 // call, N = 8192, K = 28672: T = 48 39.0 us with those tiles, 31.8 here; T = 64 38.7 and 34.0).  With K = 14336 or less, or
 // half the row tiles, the tiles are as fast or faster (T = 64, N = 4096, K = 14336 13.3 us, 16.3 here).
-bool decode_takes_two_row_tiles(const TiledGemmParams& p) {
+static bool takes_two_row_tiles(const TiledGemmParams& p) {
     const int tiles = (p.N + 31) / 32;
     return p.T > 32 && p.T <= 64 && p.GP > 512 && tiles >= kNumCU && tiles < 320;
 }
 
+// Whether the kernels of this file run a call.  The others, more tokens or more than 16 against enough channels for 160 tiles of
+// 64, go to the tiles of gemm_tiled.hip that stream the
+// weights through one wave each (weights in HBM, us, K split here against those tiles: N = 14336, K = 4096, T = 32
+// 9.7 against 8.0, T = 64 12.7 against 9.1; N = 28672, K = 8192, T = 32 25.5 against 22.8).  Below that the few tiles
+// cannot keep enough requests in flight and splitting K over eight waves wins (N = 4096, K = 14336: T = 32 11.6
+// against 15.6; N = K = 4096: 5.1 against 6.2; from 33 tokens on 6.3 against 6.2 and 14.2 against 15.5 there, and
+// 13.3 against 10.3 with the weights in the last-level cache).
+bool decode_splits_k(const TiledGemmParams& p) {
+    return p.T <= 16 || (p.T <= 32 && (p.N + 31) / 32 < 320) || takes_two_row_tiles(p);
+}
+
 hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream) {
-    if (p.T > kDecodeMaxT) return hipErrorInvalidValue;
+    if (!decode_splits_k(p)) return hipErrorInvalidValue;
     const unsigned tiles = (unsigned)((p.N + 31) / 32);
-    // More tokens, or more than 16 against enough channels for 160 tiles of 64: the tiles of gemm_tiled.hip that stream the
-    // weights through one wave each (weights in HBM, us, K split here against those tiles: N = 14336, K = 4096, T = 32
-    // 9.7 against 8.0, T = 64 12.7 against 9.1; N = 28672, K = 8192, T = 32 25.5 against 22.8).  Below that the few tiles
-    // cannot keep enough requests in flight and splitting K over eight waves wins (N = 4096, K = 14336: T = 32 11.6
-    // against 15.6; N = K = 4096: 5.1 against 6.2; from 33 tokens on 6.3 against 6.2 and 14.2 against 15.5 there, and
-    // 13.3 against 10.3 with the weights in the last-level cache).
-    if (decode_takes_two_row_tiles(p)) return launch_decode_rows<32, 2>(p, tiles, stream);
-    if (p.T > 32 || (p.T > 16 && tiles >= 320)) return launch_gemm_streaming_tiles(p, stream);
+    if (takes_two_row_tiles(p)) return launch_decode_rows<32, 2>(p, tiles, stream);
     // Fewer row tiles than CUs: half tiles, twice the workgroups (whole tiles on
     // half the CUs are slower from 9 tokens on).  Quartering the tiles, 16 waves per workgroup or register rings three
     // and four steps deep all lost when they were measured.

@@ -434,13 +434,15 @@ double cost_of(const Shape& s, const TiledGemmParams& p) {
            (rest == 0 ? 0.0 : steps * (rest > kNumCU ? s.two : s.one) + s.fixed);
 }
 
+// distances within a tile's tokens are 32-bit
+bool distances_fit(const Shape& s, const TiledGemmParams& p) { return (int64_t)(s.mt - 1) * p.GP * 512 < (int64_t)0xFFFFE000; }
+
 template <typename Pred>
 const Shape* best_shape(const TiledGemmParams& p, Pred&& allowed) {
     const Shape* best = nullptr;
     double best_cost = 0.0;
     for (const Shape& s : kShapes) {
-        if (!allowed(s) || (s.w < 4 && tiles_of(s, p) > kNumCU)) continue;
-        if ((int64_t)(s.mt - 1) * p.GP * 512 >= (int64_t)0xFFFFE000) continue;   // distances within a tile's tokens are 32-bit
+        if (!allowed(s) || (s.w < 4 && tiles_of(s, p) > kNumCU) || !distances_fit(s, p)) continue;
         const double c = cost_of(s, p);
         if (!best || c < best_cost) { best = &s; best_cost = c; }
     }
@@ -451,19 +453,13 @@ bool any_shape(const Shape&) { return true; }
 bool streaming_shape(const Shape& s) { return s.mt == 1 || s.w < 4; }
 bool small_shape(const Shape& s) { return s.nt == 1; }
 bool mid_shape(const Shape& s) { return s.nt == 2 && s.mt <= 4; }
-bool large_shape(const Shape& s) { return s.nt == 2 && s.mt >= 4; }
+bool large_shape(const Shape& s) { return s.nt == 2 && s.mt > 4; }
 bool unaligned_shape(const Shape& s) { return s.mt <= 4; }
 
 // N a multiple of 8 for either output type, so that the fp32 and the bf16 result of a shape are said to come from the same kernel
 bool large_ok(const TiledGemmParams& p) { return (p.N % 8) == 0 && gemm_tiled_large_accepts(p); }
 
 const Shape* choose_shape(const TiledGemmParams& p) { return large_ok(p) ? best_shape(p, any_shape) : best_shape(p, unaligned_shape); }
-
-hipError_t run_shape(const Shape* s, const TiledGemmParams& p, hipStream_t stream) {
-    if (!s) return hipErrorInvalidValue;
-    hipError_t e = setup_gemm_tiled();
-    return e == hipSuccess ? s->run(p, stream) : e;
-}
 
 }  // namespace
 
@@ -484,33 +480,44 @@ hipError_t setup_gemm_tiled() {
     });
 }
 
-// The weight-streaming tiles, for the decode launcher's larger calls.
-hipError_t launch_gemm_streaming_tiles(const TiledGemmParams& p, hipStream_t stream) {
-    return run_shape(best_shape(p, streaming_shape), p, stream);
+int gemm_tiles() { return (int)(sizeof(kShapes) / sizeof(kShapes[0])); }
+
+// The tile that `kernel` runs a call with, null where K is split over the waves instead or the kernel cannot run the call.
+static const Shape* tile_of(const TiledGemmParams& p, int kernel) {
+    switch (kernel) {
+        case DUQPP_GEMM_KERNEL_AUTO:
+            if (decode_splits_k(p)) return nullptr;
+            return p.T <= 32 ? best_shape(p, streaming_shape) : choose_shape(p);
+        case DUQPP_GEMM_KERNEL_DECODE: return decode_splits_k(p) || p.T > kDecodeMaxT ? nullptr : best_shape(p, streaming_shape);
+        case DUQPP_GEMM_KERNEL_SMALL: return best_shape(p, small_shape);
+        case DUQPP_GEMM_KERNEL_MID: return best_shape(p, mid_shape);
+        case DUQPP_GEMM_KERNEL_LARGE: return gemm_tiled_large_accepts(p) ? best_shape(p, large_shape) : nullptr;
+    }
+    const int i = kernel - DUQPP_GEMM_KERNEL_TILE;
+    return i >= 0 && i < gemm_tiles() && distances_fit(kShapes[i], p) ? &kShapes[i] : nullptr;
+}
+
+int gemm_tile_for(const TiledGemmParams& p, int kernel, int* tokens, int* channels) {
+    const Shape* s = tile_of(p, kernel);
+    if (!s) return kernel <= DUQPP_GEMM_KERNEL_DECODE && decode_splits_k(p) ? DUQPP_GEMM_SPLIT_K : -1;
+    if (tokens) *tokens = 32 * s->mt;
+    if (channels) *channels = 32 * s->nt * s->w;
+    return (int)(s - kShapes);
 }
 
 // Which kernel runs a shape, by the names of the ABI.
 int choose_gemm_kernel(const TiledGemmParams& p) {
-    if (p.T <= 32 || decode_takes_two_row_tiles(p)) return DUQPP_GEMM_KERNEL_DECODE;
-    const Shape* s = choose_shape(p);
-    if (p.T <= 64 && streaming_shape(*s)) return DUQPP_GEMM_KERNEL_DECODE;
-    if (small_shape(*s)) return DUQPP_GEMM_KERNEL_SMALL;
-    // several rounds of 256-channel tiles over the CUs
-    if (large_ok(p) && large_shape(*s) && tiles_of(*s, p) > (int64_t)kNumCU * s->per_cu) return DUQPP_GEMM_KERNEL_LARGE;
-    return s->mt <= 4 ? DUQPP_GEMM_KERNEL_MID : DUQPP_GEMM_KERNEL_LARGE;
+    const Shape* s = tile_of(p, DUQPP_GEMM_KERNEL_AUTO);
+    if (!s || p.T <= 32 || (p.T <= 64 && streaming_shape(*s))) return DUQPP_GEMM_KERNEL_DECODE;
+    return small_shape(*s) ? DUQPP_GEMM_KERNEL_SMALL : mid_shape(*s) ? DUQPP_GEMM_KERNEL_MID : DUQPP_GEMM_KERNEL_LARGE;
 }
 
 hipError_t launch_gemm_tiled_as(const TiledGemmParams& p, int kernel, hipStream_t stream) {
-    switch (kernel) {
-        case DUQPP_GEMM_KERNEL_AUTO:
-            return p.T <= 32 || decode_takes_two_row_tiles(p) ? launch_gemm_decode(p, stream) : run_shape(choose_shape(p), p, stream);
-        case DUQPP_GEMM_KERNEL_DECODE: return p.T <= kDecodeMaxT ? launch_gemm_decode(p, stream) : hipErrorInvalidValue;
-        case DUQPP_GEMM_KERNEL_SMALL: return run_shape(best_shape(p, small_shape), p, stream);
-        case DUQPP_GEMM_KERNEL_MID: return run_shape(best_shape(p, mid_shape), p, stream);
-        case DUQPP_GEMM_KERNEL_LARGE:
-            return gemm_tiled_large_accepts(p) ? run_shape(best_shape(p, large_shape), p, stream) : hipErrorInvalidValue;
-        default: return hipErrorInvalidValue;
+    if (const Shape* s = tile_of(p, kernel)) {
+        const hipError_t e = setup_gemm_tiled();
+        return e == hipSuccess ? s->run(p, stream) : e;
     }
+    return kernel <= DUQPP_GEMM_KERNEL_DECODE ? launch_gemm_decode(p, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream) {

@@ -106,8 +106,8 @@ def test_entry_points_reject_bad_arguments_before_any_launch(lib):
 
 
 def test_kernel_choice_for_the_benchmark_shapes(lib):
-    """Host-side rule that picks the GEMM kernel: weight streaming up to 64 tokens, 64 x 128 tiles when there are too
-    few 128 x 256 tiles for the chip, 256 x 256 tiles when enough of them make up whole rounds over the 256 CUs."""
+    """Host-side rule that picks the GEMM kernel: weight streaming up to 64 tokens, tiles 128 channels wide when there are too
+    few of the wider ones for the chip, tiles of 192 or 256 tokens when enough of them make up whole rounds over the 256 CUs."""
     DECODE, SMALL, MID, LARGE = 1, 2, 3, 4
     F32, BF16 = 0, 1
     k = lib.duqpp_gemm_kernel_for
@@ -119,11 +119,28 @@ def test_kernel_choice_for_the_benchmark_shapes(lib):
     assert k(2048, 4096, 14336, BF16) == MID               # 8B down_proj prefill: 256 tiles of 128 x 256, 128 of 256 x 256
     assert k(8192, 1024, 4096, BF16) == MID                # k / v projections of the layer set
     assert k(4096, 8192, 28672, F32) == LARGE              # 70B down_proj prefill: 512 tiles of 256 x 256
-    for N, K in ((4096, 4096), (14336, 4096), (4096, 14336)):
-        assert k(8192, N, K, BF16) == LARGE                # q / o, gate / up, down of the layer set
+    assert k(8192, 4096, 14336, BF16) == LARGE             # down of the layer set
+    for N in (4096, 14336):
+        assert k(8192, N, 4096, BF16) == MID               # q / o, gate / up: 128 x 256 tiles, two per CU
     assert k(8192, 4100, 4096, BF16) == MID                # bf16 rows leave in 16-byte pieces: N must be a multiple of 8
     assert k(8192, 4100, 4096, F32) == MID                 # ... and the fp32 result comes from the same kernel as the bf16 one
     assert k(0, 16, 64, F32) == SHAPE and k(8, 16, 48, F32) == SHAPE and k(8, 16, 64, 7) == DTYPE
+    # the tile behind a kernel's name
+    dims = [ctypes.c_int(0), ctypes.c_int(0)]
+
+    def tile(kernel, T, N, K, dtype=F32):
+        i = lib.duqpp_gemm_tile_for(kernel, T, N, K, dtype, ctypes.byref(dims[0]), ctypes.byref(dims[1]))
+        return i if i < 0 or i == 1000 else (dims[0].value, dims[1].value)
+    assert tile(0, 1, 14336, 4096) == 1000 and tile(DECODE, 16, 4096, 14336) == 1000      # K split over the waves
+    assert tile(0, 8192, 4096, 14336) == (256, 256) and tile(0, 8192, 14336, 4096) == (128, 256)
+    for T, N, K in ((256, 256, 128), (31, 70, 2336), (4200, 4200, 32), (2100, 4200, 64), (290, 330, 14336)):
+        assert tile(LARGE, T, N, K)[0] >= 192 and tile(LARGE, T, N, K)[1] == 256
+        assert tile(MID, T, N, K) in ((96, 256), (128, 256)) and tile(SMALL, T, N, K)[1] <= 128
+    n = lib.duqpp_gemm_tiles()
+    assert [lib.duqpp_gemm_tile_for(16 + i, 8, 16, 64, F32, None, None) for i in range(n + 1)] == list(range(n)) + [SHAPE]
+    assert tile(5, 8, 16, 64) == SHAPE and tile(DECODE, 200, 16, 64) == SHAPE and tile(LARGE, 200, 20, 64, BF16) == SHAPE
+    assert tile(0, 8, 16, 48) == SHAPE and tile(0, 8, 16, 64, 7) == DTYPE
+    assert lib.duqpp_mxfp4_gemm_tiled_on(16 + n, P, P, P, P, 8, 16, 64, P, 0, 16, None) == SHAPE
     # forcing a kernel goes through the same host-side checks first
     assert lib.duqpp_mxfp4_gemm_tiled_on(9, P, P, P, P, 8, 16, 64, P, 0, 16, None) == SHAPE
     assert lib.duqpp_mxfp4_gemm_tiled_on(DECODE, P, P, P, P, 200, 16, 64, P, 0, 16, None) == SHAPE

@@ -10,7 +10,7 @@ from helpers import bf16_dev_to_bits, rel_fro, tile_np, to_dev
 pytestmark = pytest.mark.gpu
 GEMM_TOL = 1e-5
 DECODE, SMALL, MID, LARGE = 1, 2, 3, 4
-NAMES = {DECODE: "decode", SMALL: "64x128", MID: "128x256", LARGE: "256x256"}
+NAMES = {DECODE: "decode", SMALL: "up to 128 channels", MID: "96 or 128 tokens x 256", LARGE: "192 or 256 tokens x 256"}
 
 
 @pytest.fixture(scope="module")
@@ -40,18 +40,18 @@ def _run(env, kernel, ac, asc, bc, bsc, out_dtype=0, out=None):
 
 
 # shapes chosen per kernel: one tile, ragged edges in T, N and in the padded groups, one and several K steps,
-# more tiles than CUs (several tiles per persistent workgroup)
+# more tiles than CUs
 SHAPES = [
     (LARGE, 256, 256, 128),       # one tile, one pair of K steps
     (LARGE, 256, 256, 32),        # a single group: seven of the eight padded groups are padding
     (LARGE, 300, 523, 1056),      # ragged in T and N, 33 groups padded to 40
     (LARGE, 31, 70, 2336),        # far smaller than a tile
     (LARGE, 513, 1030, 288),
-    (LARGE, 4200, 4200, 32),      # 17 x 17 = 289 tiles: two tiles for some workgroups, transfers running on
+    (LARGE, 4200, 4200, 32),      # 17 x 17 = 289 tiles: a second round for some CUs
     (LARGE, 1100, 8300, 544),
     (MID, 31, 70, 2336),
     (MID, 64, 96, 512),
-    (SMALL, 2100, 4200, 32),      # 33 x 33 = 1089 tiles
+    (SMALL, 2100, 4200, 32),      # several rounds of tiles
     (SMALL, 300, 523, 1056),
     (DECODE, 128, 300, 1184),
     (DECODE, 100, 8200, 544),
@@ -145,7 +145,7 @@ def test_named_kernel_rejections(env):
 @pytest.mark.parametrize("pad", [8, 3])
 def test_named_kernel_strided_output(env, kernel, T, N, K, out_dtype, pad):
     """Rows of the result `ldy` = N + pad elements apart: the same values as into a dense result, and nothing
-    written between the rows.  pad = 3 leaves bf16 rows off the 16-byte grid: the 256 x 256 kernel refuses that
+    written between the rows.  pad = 3 leaves bf16 rows off the 16-byte grid: LARGE refuses that
     call, the others store element by element."""
     torch, duqpp = env
     rng = np.random.default_rng(kernel * 31 + out_dtype * 7 + pad)

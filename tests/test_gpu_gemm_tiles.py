@@ -1,5 +1,6 @@
-"""GPU parity of every tile shape of the tiled MXFP4 GEMM at the sizes where it can go wrong: ragged in tokens and
-channels, one K step, and numbers of K steps that leave a remainder against the steps in flight."""
+"""GPU parity of every tile of the tiled MXFP4 GEMM, run by its index, at the sizes where it can go wrong: ragged in tokens and
+channels, one K step, numbers of K steps that leave a remainder against the steps in flight, result rows on and off the
+16-byte grid; and of the shapes at which the library picks each of them, with the tile it says it picks."""
 import numpy as np
 import pytest
 
@@ -9,40 +10,83 @@ from helpers import bf16_dev_to_bits, rel_fro, tile_np, to_dev
 pytestmark = pytest.mark.gpu
 GEMM_TOL = 1e-5      # fp32 sums of at most 16416 exact products: a relative error of 2^-24 sqrt(16416) at most, here 8e-6
 AUTO, DECODE = 0, 1
-
-# smallest shapes for which the library picks each tile (tokens x channels of a workgroup), from one K step of 256 up
-TILES = [
-    (AUTO, 33, 70, 32),          # 32 x 64, one step
-    (DECODE, 128, 1000, 2336),   # 32 x 64, ten steps of which the last is mostly padding
-    (AUTO, 33, 8300, 800),       # 32 x 128, four steps
-    (AUTO, 33, 8300, 4128),      # 64 x 64, 17 steps
-    (DECODE, 77, 14400, 1184),   # 96 x 64, five steps
-    (AUTO, 200, 5000, 4128),     # 96 x 64, 17 steps
-    (AUTO, 130, 14400, 544),     # 64 x 128, three steps
-    (AUTO, 200, 20000, 288),     # 96 x 128, two steps
-    (AUTO, 700, 8300, 32),       # 128 x 128, one step
-    (AUTO, 1000, 8300, 544),     # 96 x 256, three steps
-    (AUTO, 1500, 8300, 288),     # 128 x 256, two steps
-    (AUTO, 500, 20000, 8224),    # 192 x 256, 33 steps
-    (AUTO, 1500, 8300, 8224),    # 256 x 256 (or 128 x 256 with a result off the 16-byte grid), 33 steps
-    (AUTO, 33, 8300, 16416),     # K split over eight waves, two activation row tiles, 65 steps
-    (AUTO, 64, 8192, 16416),     # the same without ragged edges
-    (AUTO, 65, 8192, 16416),     # one token more: a tile again
-]
+TILES = [(32, 64), (64, 64), (96, 64), (32, 128), (64, 128), (96, 128), (128, 128), (96, 256), (128, 256), (192, 256), (256, 256)]
+SPLIT_K = (0, 0)
 
 
-@pytest.mark.parametrize("kernel,T,N,K", TILES)
-def test_tile_against_oracle(kernel, T, N, K):
-    """fp32 against the oracle, bf16 the rounding of that fp32 result bit for bit, also into rows that are not on the
-    16-byte grid (stored element by element) with nothing written beside them."""
-    import torch
-
-    import paper_2604_17789_amd as duqpp
+def _operands(T, N, K):
     rng = np.random.default_rng(T * 1000003 + N * 1009 + K)
     ac = rng.integers(0, 256, size=(T, K // 2)).astype(np.uint8)
     bc = rng.integers(0, 256, size=(N, K // 2)).astype(np.uint8)
     asc = rng.integers(118, 137, size=(T, K // 32)).astype(np.uint8)
     bsc = rng.integers(118, 137, size=(N, K // 32)).astype(np.uint8)
+    return ac, asc, bc, bsc
+
+
+@pytest.mark.parametrize("K", [32, 544, 2048, 4128])        # 1, 3, 8 and 17 K steps of 256, the odd ones mostly padding at the end
+@pytest.mark.parametrize("tile", range(len(TILES)))
+def test_every_tile_by_index(tile, K):
+    """Two tiles each way, the second a sliver: fp32 against the oracle and bit for bit what the first tile shape gives, bf16 the
+    rounding of that fp32 result bit for bit, into rows on and off the 16-byte grid, and nothing written beside the rows."""
+    import torch
+
+    import paper_2604_17789_amd as duqpp
+    tokens, channels = TILES[tile]
+    T, N = tokens + 5, channels + 11
+    kernel = duqpp.KERNEL_TILE + tile
+    assert duqpp.gemm_tiles() == len(TILES)
+    assert duqpp.gemm_tile_for(T, N, K, kernel=kernel) == (tile, tokens, channels)
+    ac, asc, bc, bsc = _operands(T, N, K)
+    print(f"[gemm tiles] {tokens} x {channels} T={T} N={N} K={K}", flush=True)
+    ops = [to_dev(t, torch) for t in tile_np(ac, asc) + tile_np(bc, bsc)]
+    y = duqpp.mxfp4_gemm_tiled(*ops, T, N, K, kernel=kernel)
+    other = duqpp.mxfp4_gemm_tiled(*ops, T, N, K, kernel=duqpp.KERNEL_TILE)
+    wide = [torch.full((T, ld), -77.0, dtype=torch.bfloat16, device="cuda:0") for ld in ((N + 15) // 8 * 8, N + 2)]
+    for w in wide:
+        duqpp.mxfp4_gemm_tiled(*ops, T, N, K, out_dtype=duqpp.BF16, kernel=kernel, out=w[:, :N])
+    torch.cuda.synchronize()
+    y32 = y.cpu().numpy()
+    assert rel_fro(y32, linear.mxfp4_gemm(ac, asc, bc, bsc)) <= GEMM_TOL
+    assert torch.equal(y, other)
+    for w in wide:
+        np.testing.assert_array_equal(bf16_dev_to_bits(w[:, :N].contiguous()), linear.round_to_bf16_bits(y32))
+        assert torch.all(w[:, N:] == -77.0)
+
+
+# shapes for which the library picks each tile
+PICKED = [
+    (AUTO, 33, 70, 32, (32, 64)),            # one step
+    (DECODE, 128, 1000, 2336, (32, 64)),     # ten steps of which the last is mostly padding
+    (AUTO, 33, 8300, 800, (32, 128)),
+    (AUTO, 33, 8300, 4128, (64, 64)),
+    (DECODE, 77, 14400, 1184, (96, 64)),
+    (AUTO, 200, 5000, 4128, (96, 64)),
+    (AUTO, 200, 5000, 2336, (64, 128)),
+    (AUTO, 130, 14400, 544, (96, 128)),
+    (AUTO, 300, 8296, 2336, (128, 128)),
+    (AUTO, 700, 8300, 32, (128, 128)),
+    (AUTO, 200, 20000, 288, (96, 256)),
+    (AUTO, 1000, 8300, 544, (96, 256)),
+    (AUTO, 1500, 8300, 288, (128, 256)),
+    (AUTO, 500, 20000, 8224, (192, 256)),
+    (AUTO, 1500, 8296, 8224, (256, 256)),    # in both directions ragged; 33 steps
+    (AUTO, 1500, 8300, 8224, (128, 256)),    # channels that are no multiple of 8
+    (AUTO, 33, 8300, 16416, SPLIT_K),        # K split over eight waves, two activation row tiles, 65 steps
+    (AUTO, 64, 8192, 16416, SPLIT_K),        # the same without ragged edges
+    (AUTO, 65, 8192, 16416, (64, 64)),       # one token more: a tile again
+]
+
+
+@pytest.mark.parametrize("kernel,T,N,K,picked", PICKED)
+def test_tile_against_oracle(kernel, T, N, K, picked):
+    """fp32 against the oracle, bf16 the rounding of that fp32 result bit for bit, also into rows that are not on the
+    16-byte grid (stored element by element) with nothing written beside them."""
+    import torch
+
+    import paper_2604_17789_amd as duqpp
+    rng = np.random.default_rng(T + N + K)
+    assert duqpp.gemm_tile_for(T, N, K, kernel=kernel)[1:] == picked
+    ac, asc, bc, bsc = _operands(T, N, K)
     print(f"[gemm tiles] kernel={kernel} T={T} N={N} K={K}", flush=True)
     ops = [to_dev(t, torch) for t in tile_np(ac, asc) + tile_np(bc, bsc)]
     y = duqpp.mxfp4_gemm_tiled(*ops, T, N, K, kernel=kernel)
