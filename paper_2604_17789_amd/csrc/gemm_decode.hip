@@ -1,10 +1,10 @@
-// Decode-shape W4A4 MXFP4 GEMM (Eq. 5 with a handful of tokens): up to 32 tokens are one activation row tile, in some
-// calls up to 64 are two (MT), and the product is bound by streaming the weights from HBM (N * K * 17/32 bytes).  Tiled
-// operand layout, same instruction and K permutation as the prefill kernel.
+// Decode-shape W4A4 MXFP4 GEMM (Eq. 5 with a handful of tokens): the product is bound by streaming the weights from HBM
+// (N * K * 17/32 bytes).  Tiled operand layout, same instruction and K permutation as the prefill kernel.
 //
-// One workgroup of 8 waves per ROWS = 32 or 16 output channels of a weight row tile: the streaming rate
-// a single CU sustains is a small fraction of the chip's, so the launch wants at least one workgroup per
-// CU, and with fewer row tiles than CUs each tile is cut into 2 workgroups.  With more than 16 tokens such a
+// One workgroup of 8 waves per ROWS = 32 or 16 output channels of a weight row tile and MT = 1 or 2 activation row tiles
+// of 32 tokens (blockIdx.y): the streaming rate
+// a single CU sustains is a small fraction of the chip's, so the launch wants one workgroup per
+// CU, and where there are few tiles each weight row tile is cut into 2 workgroups.  With more than 16 tokens such a
 // workgroup still issues the 32-row instruction; its lanes r >= ROWS re-read rows 0..15 and their results are dropped
 // (up to 16 tokens: gemm_decode16_kernel below, on the 16-row instruction).  The waves split K: each owns a
 // contiguous range of K steps, loads its weight fragments straight from global memory into registers
@@ -73,8 +73,8 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmPa
     const uint8_t* b_codes = p.b_codes + (int64_t)rt * p.GP * 512;
     const uint8_t* b_scales = p.b_scales + (int64_t)rt * NI * 256;
     const int64_t a_tile_bytes = (int64_t)p.GP * 512, a_tile_sbytes = (int64_t)NI * 256;
-    // this workgroup's activation row tiles: MT of them from m0; one past the last tile is all zeros
-    // (its results fall on tokens >= T and are dropped)
+    // this workgroup's activation row tiles: MT of them from m0 (the results of one past the last fall on tokens >= T and
+    // are dropped)
     const int RTa = (p.T + 31) / 32;
     const int m0 = blockIdx.y * MT;
     // A operand (activations): group 4 g + i of row r sits at (4 g + i) * 512 + r * 16, its scale word at
@@ -265,47 +265,60 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode16_kernel(TiledGemm
 }
 
 template <int ROWS, int MT>
-static hipError_t launch_decode_rows(const TiledGemmParams& p, unsigned tiles, hipStream_t stream) {
-    dim3 grid(tiles * (32 / ROWS)), block(kDecWaves * 64);
+static hipError_t launch_decode_rows(const TiledGemmParams& p, hipStream_t stream) {
+    dim3 grid((unsigned)((p.N + 31) / 32 * (32 / ROWS)), (unsigned)((p.T + 32 * MT - 1) / (32 * MT))), block(kDecWaves * 64);
     return p.out_bf16 ? launch(gemm_decode_kernel<true, ROWS, MT>, grid, block, 0, stream, p)
                       : launch(gemm_decode_kernel<false, ROWS, MT>, grid, block, 0, stream, p);
 }
 
-// 33 to 64 tokens against a long K and about one weight row tile per CU: the tiles of gemm_tiled.hip would be one small
-// workgroup per CU or fewer, waiting for 112 steps from HBM one after the other, where eight waves share them here (whole
-// call, N = 8192, K = 28672: T = 48 39.0 us with those tiles, 31.8 here; T = 64 38.7 and 34.0).  With K = 14336 or less, or
-// half the row tiles, the tiles are as fast or faster (T = 64, N = 4096, K = 14336 13.3 us, 16.3 here).
-static bool takes_two_row_tiles(const TiledGemmParams& p) {
-    const int tiles = (p.N + 31) / 32;
-    return p.T > 32 && p.T <= 64 && p.GP > 512 && tiles >= kNumCU && tiles < 320;
-}
-
-// Whether the kernels of this file run a call.  The others, more tokens or more than 16 against enough channels for 160 tiles of
-// 64, go to the tiles of gemm_tiled.hip that stream the
-// weights through one wave each (weights in HBM, us, K split here against those tiles: N = 14336, K = 4096, T = 32
-// 9.7 against 8.0, T = 64 12.7 against 9.1; N = 28672, K = 8192, T = 32 25.5 against 22.8).  Below that the few tiles
-// cannot keep enough requests in flight and splitting K over eight waves wins (N = 4096, K = 14336: T = 32 11.6
-// against 15.6; N = K = 4096: 5.1 against 6.2; from 33 tokens on 6.3 against 6.2 and 14.2 against 15.5 there, and
-// 13.3 against 10.3 with the weights in the last-level cache).
-bool decode_splits_k(const TiledGemmParams& p) {
-    return p.T <= 16 || (p.T <= 32 && (p.N + 31) / 32 < 320) || takes_two_row_tiles(p);
-}
-
-hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream) {
-    if (!decode_splits_k(p)) return hipErrorInvalidValue;
-    const unsigned tiles = (unsigned)((p.N + 31) / 32);
-    if (takes_two_row_tiles(p)) return launch_decode_rows<32, 2>(p, tiles, stream);
-    // Fewer row tiles than CUs: half tiles, twice the workgroups (whole tiles on
-    // half the CUs are slower from 9 tokens on).  Quartering the tiles, 16 waves per workgroup or register rings three
-    // and four steps deep all lost when they were measured.
+// Which of this file's kernels runs a call, kNone: none of them, the tiles of gemm_tiled.hip that stream the weights do.
+// From 17 tokens on, a workgroup per (weight row tile, token row tile) as long as that is one round over the CUs, in half row
+// tiles where those still are: the more CUs fetch, the more of HBM's rate is reached, and with 64 tokens the second token row tile
+// finds its weights in the L2 of the XCD that the first one runs on.  Workgroups that hold both token row tiles of 33 to 64
+// tokens only where N needs more than half of the CUs by itself and K is long.  Weights in HBM (sets of 640 MB in turn), us,
+// these kernels against the tiles:
+//   half tiles   1024 x 4096, T = 33 4.2 / 5.9, T = 128 4.3 / 5.8; 2048 x 8192, T = 64 6.5 / 9.2; 1024 x 28672, T = 128 14.2 / 25.6
+//   whole tiles  4096 x 4096, T = 33 4.8 / 6.1, T = 64 5.1 / 6.1; 4096 x 14336, T = 33 10.9 / 15.4, T = 64 11.2 / 15.3;
+//                2048 x 8192, T = 96 6.8 / 9.2; in two rounds instead of one: 4096 x 14336, T = 65 18.4 / 15.3, 6144 x 14336,
+//                T = 33 19.6 / 16.2; with three token row tiles against more than 64 row tiles it comes out even (2720 x 8192, T = 65
+//                9.0 / 9.4, cached 8.3 / 6.9)
+//   both         6144 x 14336, T = 33 13.8 / 16.2, T = 64 15.1 / 16.2; 8192 x 8192, T = 33 10.1 / 11.3, T = 64 10.7 / 11.4;
+//                8192 x 28672, T = 64 28.6 / 31.3; K short: 6144 x 4096, T = 33 6.0 / 6.4, T = 64 6.6 / 6.4, 8192 x 4096, T = 64
+//                6.9 / 6.7; in two rounds: 10240 x 14336, T = 64 27.3 / 22.0
+// and with the weights in the last-level cache (three sets in turn) 4096 x 14336, T = 64 10.9 / 10.7 and 8192 x 8192, T = 64 10.3 / 7.9:
+// the line is drawn for weights in HBM, which is where those of a whole model are.
+// 17 to 32 tokens against more channels than one round takes go to the tiles from 320 row tiles on (14336 x 4096, T = 32 8.5 / 7.9;
+// 28672 x 8192 25.6 / 24.3; 8192 x 8192 9.0 / 11.3).
+namespace {
+enum Split { kNone, kHalf16, kHalf, kWhole, kWholeBoth };
+Split split_of(const TiledGemmParams& p) {
+    const int64_t tiles = (p.N + 31) / 32, rt = (p.T + 31) / 32;
     // Up to 16 tokens and fewer row tiles than CUs: half tiles on the 16 x 16 x 128 instruction, whose loads are whole
     // (N = 4096, K = 14336: T = 1 9.0 -> 7.1 us, T = 16 9.1 -> 7.9 us; N = K = 4096: 4.3 -> 3.7 us).
-    if (p.T <= 16 && tiles < (unsigned)kNumCU) {
-        dim3 grid(tiles * 2), block(kDecWaves * 64);
-        return p.out_bf16 ? launch(gemm_decode16_kernel<true>, grid, block, 0, stream, p)
-                          : launch(gemm_decode16_kernel<false>, grid, block, 0, stream, p);
+    if (p.T <= 16) return tiles < kNumCU ? kHalf16 : kWhole;
+    if (p.T > kDecodeMaxT) return kNone;
+    if (2 * tiles * rt <= kNumCU) return kHalf;
+    if (tiles * (rt > 2 ? 4 : rt) <= kNumCU) return kWhole;
+    if (p.T <= 32) return tiles < 320 ? kWhole : kNone;
+    return p.T <= 64 && tiles <= kNumCU && p.GP >= 256 ? kWholeBoth : kNone;
+}
+}  // namespace
+
+bool decode_splits_k(const TiledGemmParams& p) { return split_of(p) != kNone; }
+
+// (Quartering the row tiles, 16 waves per workgroup or register rings three and four steps deep all lost when they were measured.)
+hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream) {
+    switch (split_of(p)) {
+        case kHalf16: {
+            dim3 grid((unsigned)((p.N + 31) / 32 * 2)), block(kDecWaves * 64);
+            return p.out_bf16 ? launch(gemm_decode16_kernel<true>, grid, block, 0, stream, p)
+                              : launch(gemm_decode16_kernel<false>, grid, block, 0, stream, p);
+        }
+        case kHalf: return launch_decode_rows<16, 1>(p, stream);
+        case kWhole: return launch_decode_rows<32, 1>(p, stream);
+        case kWholeBoth: return launch_decode_rows<32, 2>(p, stream);
+        default: return hipErrorInvalidValue;
     }
-    return tiles < (unsigned)kNumCU ? launch_decode_rows<16, 1>(p, tiles, stream) : launch_decode_rows<32, 1>(p, tiles, stream);
 }
 
 }  // namespace duqpp

@@ -55,8 +55,8 @@ def test_every_tile_by_index(tile, K):
 
 # shapes for which the library picks each tile
 PICKED = [
-    (AUTO, 33, 70, 32, (32, 64)),            # one step
-    (DECODE, 128, 1000, 2336, (32, 64)),     # ten steps of which the last is mostly padding
+    (AUTO, 33, 4200, 32, (32, 64)),          # one step
+    (AUTO, 200, 72, 2336, (32, 64)),         # ten steps of which the last is mostly padding
     (AUTO, 33, 8300, 800, (32, 128)),
     (AUTO, 33, 8300, 4128, (64, 64)),
     (DECODE, 77, 14400, 1184, (96, 64)),
@@ -71,9 +71,21 @@ PICKED = [
     (AUTO, 500, 20000, 8224, (192, 256)),
     (AUTO, 1500, 8296, 8224, (256, 256)),    # in both directions ragged; 33 steps
     (AUTO, 1500, 8300, 8224, (128, 256)),    # channels that are no multiple of 8
-    (AUTO, 33, 8300, 16416, SPLIT_K),        # K split over eight waves, two activation row tiles, 65 steps
-    (AUTO, 64, 8192, 16416, SPLIT_K),        # the same without ragged edges
-    (AUTO, 65, 8192, 16416, (64, 64)),       # one token more: a tile again
+    # K split over eight waves
+    (AUTO, 17, 4097, 288, SPLIT_K),          # whole row tiles, one more than there are pairs of CUs
+    (AUTO, 33, 70, 32, SPLIT_K),             # half row tiles, a second token row tile of one token, seven waves without a step
+    (AUTO, 65, 1000, 2336, SPLIT_K),         # half row tiles, three token row tiles
+    (DECODE, 128, 1024, 2336, SPLIT_K),      # four, the last of the round
+    (AUTO, 64, 4070, 2336, SPLIT_K),         # whole row tiles, two token row tiles
+    (AUTO, 97, 2040, 544, SPLIT_K),          # four
+    (AUTO, 33, 4100, 8000, SPLIT_K),         # both token row tiles in a workgroup
+    (AUTO, 64, 8192, 16416, SPLIT_K),
+    # their edges
+    (AUTO, 65, 4096, 544, (32, 64)),
+    (DECODE, 65, 2049, 544, (32, 64)),
+    (AUTO, 64, 4100, 7904, (32, 64)),
+    (AUTO, 64, 8193, 16416, (64, 64)),
+    (AUTO, 65, 8192, 16416, (64, 64)),
 ]
 
 
