@@ -280,10 +280,10 @@ _MOST = 1 << 30                                              # rows and K the li
 
 def tiled_bytes(rows, K):
     """(codes bytes, scales bytes) of the tiled form of a [rows, K] operand."""
-    if 1 <= rows <= _MOST and 32 <= K <= _MOST and K % 32 == 0:
+    if type(rows) is int and type(K) is int and 1 <= rows <= _MOST and 32 <= K <= _MOST and K % 32 == 0:
         n = (rows + 31) // 32 * ((K + 255) // 256)           # row tiles x runs of 8 groups: 4096 code and 256 scale bytes each
         return n * 4096, n * 256
-    cb, sb = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    cb, sb = ctypes.c_size_t(0), ctypes.c_size_t(0)          # everything else, other types of integer too, is the C call's to judge
     _check(lib.duqpp_tiled_bytes(rows, K, ctypes.byref(cb), ctypes.byref(sb)), "duqpp_tiled_bytes")
     return int(cb.value), int(sb.value)
 
