@@ -112,12 +112,14 @@ def _check(status, what):
 # What a call costs on the host counts: two launches take 4.4 us there, and everything below has to stay small beside them
 # (rotq_gemm_tiled_packed with its buffers given: 13.0 us per call with a torch.cuda.Stream object built for every call and
 # the layout's sizes fetched through the C call, 9.1 us without).
-_current_device = torch._C._cuda_getDevice
-_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
     """The current stream of the current device as the integer the C calls take."""
+    if _raw_stream is None or _current_device is None:       # names of torch's own use: a torch without them has the public way
+        return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_current_device())
 
 

@@ -1,5 +1,8 @@
-"""CPU-only checks of the binding's short cuts: they answer as the C calls they stand in for."""
+"""CPU-only checks of the binding's short cuts: they answer as the calls they stand in for, and it works without them."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -29,3 +32,18 @@ def test_tiled_bytes_is_the_library_s_answer(rows, K):
     else:
         with pytest.raises(want if isinstance(want, type) else duqpp.DuqppError):
             duqpp.tiled_bytes(rows, K)
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getDevice", "_cuda_getCurrentRawStream"])
+def test_the_stream_without_torch_s_private_names(missing):
+    """The package imports where torch lacks them and asks for the stream the public way."""
+    code = f"""
+import torch
+if hasattr(torch._C, {missing!r}):
+    delattr(torch._C, {missing!r})
+from paper_2604_17789_amd import binding
+torch.cuda.current_stream = lambda: type("Stream", (), {{"cuda_stream": 4711}})
+assert binding._stream() == 4711
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=300,
+                   cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
