@@ -11,6 +11,10 @@ namespace duqpp {
 namespace {
 
 constexpr int kErrWaves = 4;            // waves per workgroup, two groups each
+// Up to this many (token tile, group) pairs a wave of its own for each: no more than a wave per SIMD, and half the arithmetic in
+// the one chain that such a call is (64 x 512, ratios alone: 4.2 us with two groups per wave, 3.7 with one; 2048 x 512, 1024 pairs,
+// 4.3 and 4.1; 511 x 4096, 2048 pairs, 4.8 and 5.0).
+constexpr int64_t kOneGroupTo = 1024;
 constexpr int kErrWorkgroups = 512;     // aimed at: two per CU (1024: 11.1 us at 2048 x 4096, 512: 9.3, 256: 10.0)
 // From this many ratios on the mean is formed from the partial sums of the workgroups that compute them.
 constexpr int64_t kPartialsFrom = 65536;
@@ -78,26 +82,27 @@ __device__ __forceinline__ double pair_sums(double v0, double v1) {
            __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
 }
 
-// A wave takes two adjacent groups (one 128-byte line per token row) and walks its run of 32-token tiles with their
-// rotation blocks in registers and the next tile's line requested ahead.  Lane (c, h) computes half of token c's values
-// of both groups, then the ratio of group h: one division and square root per lane.
+// A wave takes GROUPS = 2 adjacent groups (one 128-byte line per token row) and walks its run of 32-token tiles with their
+// rotation blocks in registers and the next tile's line requested ahead, or one group and one tile.  Lane (c, h) computes half
+// of token c's values of each group, then of two groups the ratio of group h: one division and square root per lane.
 // Bound by the fp64 sums and the start (rotation blocks, first tiles), a third of it by reading x.  2048 x 4096 on one
 // MI355X: 13.2 -> 9.3 us against a wave per (tile, group) that formed the codes' values in fp64; the mean 86 -> 6.3 us (2.4 from
 // the partial sums, 3.9 to compute the first ratios again) against one workgroup with one load in flight per thread.
-template <bool ROTATED>
-__global__ __launch_bounds__(64 * kErrWaves) void group_error_kernel(GroupErrorParams p, ErrPlan e) {
-    __shared__ double sums[kErrWaves][2];
+template <bool ROTATED, int GROUPS>
+__global__ __launch_bounds__(64 * (GROUPS == 2 ? kErrWaves : 1)) void group_error_kernel(GroupErrorParams p, ErrPlan e) {
+    constexpr int kWaves = GROUPS == 2 ? kErrWaves : 1;
+    __shared__ double sums[kWaves][2];
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int chunk = blockIdx.x % e.chunks, run = blockIdx.x / e.chunks;
-    const int j0 = (chunk * kErrWaves + wave) * 2;
+    const int j0 = (chunk * kWaves + wave) * GROUPS;
     double sum = 0.0, count = 0.0;
     if (j0 < p.G) {
-        const int j1 = j0 + 1 < p.G ? j0 + 1 : j0;           // an odd last group: computed twice, stored once
+        const int j1 = GROUPS == 2 && j0 + 1 < p.G ? j0 + 1 : j0;   // an odd last group: computed twice, stored once
         RotOperand op0, op1;
         if constexpr (ROTATED) {
             load_rot_operand(p.R + (int64_t)j0 * p.r_stride, c, h, op0);
-            load_rot_operand(p.R + (int64_t)j1 * p.r_stride, c, h, op1);
+            if constexpr (GROUPS == 2) load_rot_operand(p.R + (int64_t)j1 * p.r_stride, c, h, op1);
         }
         const int step1 = 32 * (j1 - j0);
         auto load = [&](u32x4 (&v)[4], int tile) {
@@ -106,17 +111,20 @@ __global__ __launch_bounds__(64 * kErrWaves) void group_error_kernel(GroupErrorP
             if constexpr (ROTATED) {
                 v[0] = *(const u32x4*)(xr + 8 * h);
                 v[1] = *(const u32x4*)(xr + 8 * h + 16);
-                v[2] = *(const u32x4*)(xr + step1 + 8 * h);
-                v[3] = *(const u32x4*)(xr + step1 + 8 * h + 16);
+                if constexpr (GROUPS == 2) {
+                    v[2] = *(const u32x4*)(xr + step1 + 8 * h);
+                    v[3] = *(const u32x4*)(xr + step1 + 8 * h + 16);
+                }
             } else {
                 // channels 8 q + 4 h .. + 3 of each group, the layout rotate_tile would give
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const uint2 a = *(const uint2*)(xr + 8 * q + 4 * h), b = *(const uint2*)(xr + step1 + 8 * q + 4 * h);
-                    v[q / 2][2 * (q & 1)] = a.x;
-                    v[q / 2][2 * (q & 1) + 1] = a.y;
-                    v[2 + q / 2][2 * (q & 1)] = b.x;
-                    v[2 + q / 2][2 * (q & 1) + 1] = b.y;
+#pragma unroll
+                    for (int k = 0; k < GROUPS; ++k) {
+                        const uint2 a = *(const uint2*)(xr + k * step1 + 8 * q + 4 * h);
+                        v[2 * k + q / 2][2 * (q & 1)] = a.x;
+                        v[2 * k + q / 2][2 * (q & 1) + 1] = a.y;
+                    }
                 }
             }
         };
@@ -138,21 +146,23 @@ __global__ __launch_bounds__(64 * kErrWaves) void group_error_kernel(GroupErrorP
         u32x4 x[4], nx[4];
         if (run < e.ntiles) load(x, run);
         for (int tile = run; tile < e.ntiles; tile += e.runs) {
-            const int ahead = tile + e.runs < e.ntiles ? tile + e.runs : tile;
-            load(nx, ahead);
-            double n0, d0, n1, d1;
+            if constexpr (GROUPS == 2) load(nx, tile + e.runs < e.ntiles ? tile + e.runs : tile);
+            double n0, d0;
             error_sums(values(x, op0), n0, d0);
-            error_sums(values(x + 2, op1), n1, d1);
+            double n1 = n0, d1 = d0;
+            if constexpr (GROUPS == 2) error_sums(values(x + 2, op1), n1, d1);
             const double num = pair_sums(n0, n1), den = pair_sums(d0, d1);
             const int token = tile * 32 + c;
-            if (token < p.rows && j0 + h < p.G) {
+            if (token < p.rows && (GROUPS == 2 ? j0 + h < p.G : h == 0)) {
                 const float r = den > 0.0 ? (float)sqrt(num / den) : -1.0f;
                 const int64_t at = (int64_t)token * p.G + j0 + h;
                 if (at >= e.keep_from && at < e.keep_to) p.err[at] = r;
                 if (r >= 0.f) { sum += (double)r; count += 1.0; }
             }
+            if constexpr (GROUPS == 2) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x[k] = nx[k];
+                for (int k = 0; k < 4; ++k) x[k] = nx[k];
+            }
         }
     }
     if (!e.partials) return;
@@ -164,7 +174,7 @@ __global__ __launch_bounds__(64 * kErrWaves) void group_error_kernel(GroupErrorP
     __syncthreads();
     if (threadIdx.x < 2) {
         double t = 0.0;
-        for (int k = 0; k < kErrWaves; ++k) t += sums[k][threadIdx.x];
+        for (int k = 0; k < kWaves; ++k) t += sums[k][threadIdx.x];
         const unsigned long long bits = (unsigned long long)__double_as_longlong(t);
         uint32_t* out = (uint32_t*)p.err + (int64_t)blockIdx.x * 4 + 2 * threadIdx.x;      // err is aligned to a float only
         out[0] = (uint32_t)bits;
@@ -174,7 +184,7 @@ __global__ __launch_bounds__(64 * kErrWaves) void group_error_kernel(GroupErrorP
 
 // Mean of the ratios over the groups that have one (err >= 0), summed in a fixed order: each thread its elements or partial
 // sums in order, then a tree over the 1024 threads.
-template <bool PARTIALS>
+template <bool PARTIALS, int AHEAD>
 __global__ __launch_bounds__(1024) void group_error_mean_kernel(GroupErrorMeanParams p) {
     __shared__ double ssum[1024];
     __shared__ double scnt[1024];
@@ -187,13 +197,17 @@ __global__ __launch_bounds__(1024) void group_error_mean_kernel(GroupErrorMeanPa
             cnt += __longlong_as_double((long long)(((unsigned long long)q[3] << 32) | q[2]));
         }
     } else {
-        // eight elements in flight per thread: one workgroup reads at what a CU takes in
-        for (int64_t i = threadIdx.x; i < p.n; i += 8 * 1024) {
-            float e[8];
+        // AHEAD elements in flight per thread: one workgroup reads at what a CU takes in
+        for (int64_t i = threadIdx.x; i < p.n; i += AHEAD * 1024) {
+            float e[AHEAD];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) e[k] = i + k * 1024 < p.n ? p.err[i + k * 1024] : -1.f;
+            for (int k = 0; k < AHEAD; ++k) {                // no branch around a load: they would be waited for one by one
+                const int64_t at = i + k * 1024;
+                const float v = p.err[at < p.n ? at : p.n - 1];
+                e[k] = at < p.n ? v : -1.f;
+            }
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
+            for (int k = 0; k < AHEAD; ++k)
                 if (e[k] >= 0.f) { s += (double)e[k]; cnt += 1.0; }
         }
     }
@@ -228,15 +242,32 @@ hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream) {
     };
     auto run = [&](const ErrPlan& e) {
         const dim3 grid((unsigned)(e.chunks * e.runs)), block(64 * kErrWaves);
-        return p.R ? launch(group_error_kernel<true>, grid, block, 0, stream, p, e)
-                   : launch(group_error_kernel<false>, grid, block, 0, stream, p, e);
+        return p.R ? launch(group_error_kernel<true, 2>, grid, block, 0, stream, p, e)
+                   : launch(group_error_kernel<false, 2>, grid, block, 0, stream, p, e);
     };
+    auto run_one_group = [&](const ErrPlan& e) {
+        const dim3 grid((unsigned)(e.chunks * e.runs)), block(64);
+        return p.R ? launch(group_error_kernel<true, 1>, grid, block, 0, stream, p, e)
+                   : launch(group_error_kernel<false, 1>, grid, block, 0, stream, p, e);
+    };
+    auto mean_of_ratios = [&] {
+        const GroupErrorMeanParams m{p.err, n, p.mean};
+        // few ratios: seven loads too many cost more than a second round trip (2048 ratios, the whole call 6.9 and 6.5 us)
+        return n <= 2048 ? launch(group_error_mean_kernel<false, 1>, dim3(1), dim3(1024), 0, stream, m)
+                         : launch(group_error_mean_kernel<false, 8>, dim3(1), dim3(1024), 0, stream, m);
+    };
+    if (tiles * p.G <= kOneGroupTo) {                        // at most 32768 ratios
+        ErrPlan one = plan((int)tiles);
+        one.chunks = p.G;
+        one.runs = (int)tiles;
+        const hipError_t st = run_one_group(one);
+        return st != hipSuccess || !p.mean ? st : mean_of_ratios();
+    }
     ErrPlan e = plan((int)tiles);
     const int64_t workgroups = (int64_t)e.chunks * e.runs, held = 4 * workgroups;   // floats the partial sums take
     if (!p.mean || n < kPartialsFrom || held > n) {
         const hipError_t st = run(e);
-        if (st != hipSuccess || !p.mean) return st;
-        return launch(group_error_mean_kernel<false>, dim3(1), dim3(1024), 0, stream, GroupErrorMeanParams{p.err, n, p.mean});
+        return st != hipSuccess || !p.mean ? st : mean_of_ratios();
     }
     // The partial sums need a place until the mean is formed, and the call has no scratch: they take the first floats of err,
     // whose ratios (at most a few token tiles) are computed once more afterwards.
@@ -244,7 +275,7 @@ hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream) {
     e.keep_from = held;
     hipError_t st = run(e);
     if (st != hipSuccess) return st;
-    st = launch(group_error_mean_kernel<true>, dim3(1), dim3(1024), 0, stream, GroupErrorMeanParams{p.err, workgroups, p.mean});
+    st = launch(group_error_mean_kernel<true, 1>, dim3(1), dim3(1024), 0, stream, GroupErrorMeanParams{p.err, workgroups, p.mean});
     if (st != hipSuccess) return st;
     ErrPlan again = plan((int)(((held + p.G - 1) / p.G + 31) / 32));
     again.keep_to = held;

@@ -1,5 +1,6 @@
 """GPU parity of duqpp_group_error where the mean comes from partial sums that use the first ratios' places until it is
-formed: sizes either side of the switch, an odd number of groups, one group per token, more token tiles than runs."""
+formed: sizes either side of the switch, an odd number of groups, one group per token, more token tiles than runs; and either
+side of the sizes from which a wave takes two groups and the mean reads ahead."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,8 @@ from helpers import to_dev, to_dev_bf16
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,K,rotated", [(511, 4096, 1), (512, 4096, 1), (513, 4128, 1), (2100, 1024, 0), (70000, 32, 1), (5, 14368 * 32, 0)])
+@pytest.mark.parametrize("T,K,rotated", [(511, 4096, 1), (512, 4096, 1), (513, 4128, 1), (2100, 1024, 0), (70000, 32, 1), (5, 14368 * 32, 0),
+                                         (256, 4096, 1), (257, 4096, 0), (64, 1024, 0), (65, 1024, 1), (10, 32, 0)])
 def test_ratios_and_mean(T, K, rotated):
     """Every ratio within one rounding to fp32 of the oracle's on the device's own rotated values (2e-7), groups of zeros
     marked also among the first ratios, the mean within the fp64 sum's rounding."""
