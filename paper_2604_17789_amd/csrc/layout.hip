@@ -8,9 +8,10 @@ namespace duqpp {
 constexpr int kTileWaves = 4;
 
 // Row-major -> tiled, a wave per unit; the units of a second operand (none if it has no rows) follow the first's.
-__global__ __launch_bounds__(64 * kTileWaves) void tile_kernel(LayoutParams a, LayoutParams b) {
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void tile_kernel(LayoutParams a, LayoutParams b) {
     const int lane = threadIdx.x & 63;
-    const int64_t unit = (int64_t)blockIdx.x * kTileWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t unit = (int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t of_a = tile_units(a);
     if (unit < of_a) tile_unit(a, unit, lane);
     else if (unit < of_a + tile_units(b)) tile_unit(b, unit - of_a, lane);
@@ -29,7 +30,8 @@ __global__ __launch_bounds__(256) void untile_kernel(LayoutParams p) {
 
 hipError_t launch_tile(const LayoutParams& a, const LayoutParams& b, hipStream_t stream) {
     const int64_t units = tile_units(a) + tile_units(b);
-    return launch(tile_kernel, dim3((unsigned)((units + kTileWaves - 1) / kTileWaves)), dim3(64 * kTileWaves), 0, stream, a, b);
+    if (units <= kTileWaves * kNumCU) return launch(tile_kernel<1>, dim3((unsigned)units), dim3(64), 0, stream, a, b);
+    return launch(tile_kernel<kTileWaves>, dim3((unsigned)((units + kTileWaves - 1) / kTileWaves)), dim3(64 * kTileWaves), 0, stream, a, b);
 }
 hipError_t launch_tile(const LayoutParams& p, hipStream_t stream) {
     LayoutParams none = p;

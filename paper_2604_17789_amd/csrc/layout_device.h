@@ -14,9 +14,9 @@ __host__ __device__ inline int64_t tile_units(const LayoutParams& p) { return (i
 // thread per (group, row) in the order of the tiled layout the reads were 16 bytes out of every row's line.)  Rows and
 // groups of the padding read a valid place and are replaced, so that no branch stands between the loads.
 __device__ __forceinline__ void tile_unit(const LayoutParams& p, int64_t unit, int lane) {
-    const int NI = p.GP / 8;
-    const int64_t rt = unit / NI;
-    const int q8 = (int)(unit % NI);
+    const uint32_t NI = p.GP / 8, u = (uint32_t)unit;         // (2^32 units would be 17 TB)
+    const int64_t rt = u / NI;
+    const int q8 = (int)(u % NI);
     const int ch = lane & 7, r8 = lane >> 3;
     const int j = 8 * q8 + ch, jl = j < p.G ? j : p.G - 1;
     uint4 v[4];
@@ -33,11 +33,14 @@ __device__ __forceinline__ void tile_unit(const LayoutParams& p, int64_t unit, i
         s = *(const uint32_t*)(sr + (j0 < p.G ? j0 : 0));
         if (j0 >= p.G || srow >= p.rows) s = 0x7F7F7F7Fu;
     } else {
+        uint32_t one[4];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t one = sr[j0 + b < p.G ? j0 + b : 0];
-            s |= (j0 + b < p.G && srow < p.rows ? one : 127u) << (8 * b);
-        }
+        for (int b = 0; b < 4; ++b) one[b] = sr[j0 + b < p.G ? j0 + b : 0];
+        // used as loaded: or the compiler moves each load into the branch that needs it and waits there, four round trips
+        // instead of one (1030 x 1056: 2.7 -> 2.2 us)
+        asm("" : "+v"(one[0]), "+v"(one[1]), "+v"(one[2]), "+v"(one[3]));
+#pragma unroll
+        for (int b = 0; b < 4; ++b) s |= (j0 + b < p.G && srow < p.rows ? one[b] : 127u) << (8 * b);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

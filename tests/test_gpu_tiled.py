@@ -43,7 +43,8 @@ def test_numpy_layout_helpers_are_inverse():
         assert st[(((rt * (GP // 8) + j // 8) * 2 + (j % 8) // 4) * 32 + r) * 4 + j % 4] == s[row, j]
 
 
-@pytest.mark.parametrize("rows,K", [(64, 4096), (45, 352), (1, 32), (300, 1184)])
+@pytest.mark.parametrize("rows,K", [(64, 4096), (45, 352), (1, 32), (300, 1184),
+                                    (4090, 2048), (4097, 2016)])      # either side of the 1024 units that get a workgroup each
 def test_tile_and_untile_kernels(env, rows, K):
     torch, duqpp = env
     rng = np.random.default_rng(rows + K)
