@@ -12,8 +12,10 @@ namespace {
 
 constexpr int kErrWaves = 4;            // waves per workgroup, two groups each
 // Up to this many (token tile, group) pairs a wave of its own for each: no more than a wave per SIMD, and half the arithmetic in
-// the one chain that such a call is (64 x 512, ratios alone: 4.2 us with two groups per wave, 3.7 with one; 2048 x 512, 1024 pairs,
-// 4.3 and 4.1; 511 x 4096, 2048 pairs, 4.8 and 5.0).
+// the one chain that such a call is (ratios alone, one against two groups per wave: 64 x 512 2.6 / 3.2 us, 256 x 4096, 1024 pairs,
+// 3.0 / 3.3, 288 x 4096 3.3 / 3.5, 511 x 4096, 2048 pairs, 3.7 / 3.6).  Four times as many without rotation, where a wave has
+// nothing to keep from tile to tile, as long as the mean needs no partial sums (511 x 4096 3.5 / 3.4, 1500 x 2048, 3008 pairs, 4.1 / 5.4,
+// 1024 x 4096, 4096 pairs, 4.8 / 5.5).
 constexpr int64_t kOneGroupTo = 1024;
 constexpr int kErrWorkgroups = 512;     // aimed at: two per CU (1024: 11.1 us at 2048 x 4096, 512: 9.3, 256: 10.0)
 // From this many ratios on the mean is formed from the partial sums of the workgroups that compute them.
@@ -256,7 +258,7 @@ hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream) {
         return n <= 2048 ? launch(group_error_mean_kernel<false, 1>, dim3(1), dim3(1024), 0, stream, m)
                          : launch(group_error_mean_kernel<false, 8>, dim3(1), dim3(1024), 0, stream, m);
     };
-    if (tiles * p.G <= kOneGroupTo) {                        // at most 32768 ratios
+    if (tiles * p.G <= (p.R ? kOneGroupTo : 4 * kOneGroupTo) && (!p.mean || n < kPartialsFrom)) {
         ErrPlan one = plan((int)tiles);
         one.chunks = p.G;
         one.runs = (int)tiles;
@@ -270,7 +272,7 @@ hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream) {
         return st != hipSuccess || !p.mean ? st : mean_of_ratios();
     }
     // The partial sums need a place until the mean is formed, and the call has no scratch: they take the first floats of err,
-    // whose ratios (at most a few token tiles) are computed once more afterwards.
+    // whose ratios (at most 64 token tiles, with one group per token) are computed once more afterwards.
     e.partials = 1;
     e.keep_from = held;
     hipError_t st = run(e);

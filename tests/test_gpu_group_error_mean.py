@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,K,rotated", [(511, 4096, 1), (512, 4096, 1), (513, 4128, 1), (2100, 1024, 0), (70000, 32, 1), (5, 14368 * 32, 0),
-                                         (256, 4096, 1), (257, 4096, 0), (64, 1024, 0), (65, 1024, 1), (10, 32, 0)])
+                                         (256, 4096, 1), (257, 4096, 0), (64, 1024, 0), (65, 1024, 1), (10, 32, 0),
+                                         (500, 4096, 0), (1030, 4096, 0)])
 def test_ratios_and_mean(T, K, rotated):
     """Every ratio within one rounding to fp32 of the oracle's on the device's own rotated values (2e-7), groups of zeros
     marked also among the first ratios, the mean within the fp64 sum's rounding."""
