@@ -102,7 +102,7 @@ struct GroupErrorParams {
 struct GroupErrorMeanParams {
     const float* err; int64_t n; double* mean;
 };
-constexpr int64_t kGroupErrorMaxTiles = 65535;   // token tiles along blockIdx.y
+constexpr int64_t kGroupErrorMaxTiles = 65535;   // tiles of 32 tokens a call takes (DUQPP_ERR_TOO_LARGE beyond)
 hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream);
 
 struct QuantDbgParams {

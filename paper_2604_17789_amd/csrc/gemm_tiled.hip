@@ -22,11 +22,14 @@
 // keeps the weights out of LDS (per step of 128 x 256 outputs 17 KiB written to and 64 KiB read from LDS; with both
 // operands staged and the waves as 2 x 2 it was 52 and 96) and takes the tile that covers the output with the fewest
 // tiles per CU.  A tile of few MFMAs is bound by the path from L2 into the CU (about 44 bytes per cycle).
-// Measured against the kernels it replaces (both operands through LDS, 64 x 128, 128 x 256 and persistent 256 x 256 tiles;
-// us per launch on one MI355X, T x N x K): 160 x 4096 x 4096 11.4 -> 6.1, 512 x 4096 x 4096 12.3 -> 8.5,
-// 333 x 14336 x 4096 19.8 -> 14.9, 777 x 4096 x 14336 46.8 -> 30.0, 2048 x 4096 x 14336 61.0 -> 56.4,
-// 3001 x 14336 x 4096 97.1 -> 87.3, 8192 x 4096 x 4096 71.0 -> 65.3, 8192 x 14336 x 4096 239.5 -> 219.5,
-// 4096 x 8192 x 28672 412.6 -> 393.7.
+// Measured against the kernels it replaced (both operands through LDS, 64 x 128, 128 x 256 and persistent 256 x 256 tiles),
+// both in turn on one MI355X, us per launch, T x N x K, weights in HBM (sets of 640 MB in turn) and in brackets cached:
+//   160 x 4096 x 4096 11.7 -> 8.1 (10.4 -> 5.1), 512 x 4096 x 4096 12.4 -> 9.7 (11.2 -> 7.3), 333 x 14336 x 4096 21.0 -> 17.4 (18.8 -> 14.4),
+//   777 x 4096 x 14336 49.8 -> 38.0 (43.8 -> 29.9), 2048 x 4096 x 14336 61.1 -> 56.8 (60.4 -> 55.8), 3001 x 14336 x 4096 102.6 -> 93.9
+//   (100.0 -> 89.2), 8192 x 4096 x 4096 69.4 -> 68.6 (69.1 -> 65.8), 8192 x 14336 x 4096 239.9 -> 229.4 (231.8 -> 227.2),
+//   4096 x 8192 x 28672 413.7 -> 390.4 (400.6 -> 387.6).  Of 176 products (33 to 8192 tokens, eleven linears) one is slower by more
+//   than 2 % in either state of the weights, 1024 x 14336 x 4096 with 34.4 -> 36.0 (33.2 -> 32.0): constants that pick 256 x 256 tiles
+//   there (33.6, cached 32.8) lose as much at five others.
 //
 // Requests and LDS-DMA transfers are builtins, so that the compiler knows which registers are still being written and counts
 // every transfer in its waits for them.  Its waits for the transfers themselves would drain the whole queue before every LDS
@@ -392,7 +395,8 @@ hipError_t run(const TiledGemmParams& p, hipStream_t stream) {
 // waits for its first operands or stores its tile, the other has the matrix cores.  one / two: microseconds per K step of
 // 256 while a CU holds one or two tiles; fixed: per round of tiles, what the pipeline's start and the store take.  Fitted
 // to the time of every shape at 400 products (33 to 8192 tokens, seven linears of the 8B and 70B models and four generic
-// ones, weights in the last-level cache and in HBM): the shape chosen is on average 0.3 % slower than the fastest, 13 % at worst.
+// ones, weights in the last-level cache and in HBM).  Over 170 products the shape chosen takes on average 1.3 % longer than
+// the fastest of the eleven with the weights in HBM (18 % at worst) and 1.2 % with them cached (21 %).
 struct Shape {
     int mt, nt, w, per_cu;
     double one, two, fixed;
@@ -456,7 +460,7 @@ bool mid_shape(const Shape& s) { return s.nt == 2 && s.mt <= 4; }
 bool large_shape(const Shape& s) { return s.nt == 2 && s.mt > 4; }
 bool unaligned_shape(const Shape& s) { return s.mt <= 4; }
 
-// N a multiple of 8 for either output type, so that the fp32 and the bf16 result of a shape are said to come from the same kernel
+// N a multiple of 8 for either output type: the fp32 and the bf16 result of a shape come from the same tile
 bool large_ok(const TiledGemmParams& p) { return (p.N % 8) == 0 && gemm_tiled_large_accepts(p); }
 
 const Shape* choose_shape(const TiledGemmParams& p) { return large_ok(p) ? best_shape(p, any_shape) : best_shape(p, unaligned_shape); }
