@@ -136,6 +136,9 @@ def test_kernel_choice_for_the_benchmark_shapes(lib):
     for T, N, K in ((256, 256, 128), (31, 70, 2336), (4200, 4200, 32), (2100, 4200, 64), (290, 330, 14336)):
         assert tile(LARGE, T, N, K)[0] >= 192 and tile(LARGE, T, N, K)[1] == 256
         assert tile(MID, T, N, K) in ((96, 256), (128, 256)) and tile(SMALL, T, N, K)[1] <= 128
+    # row tiles of one output tile are at most 4 GiB apart
+    assert tile(16 + 10, 300, 512, 1 << 25) == (256, 256) and tile(LARGE, 300, 512, 1 << 26) == SHAPE
+    assert tile(MID, 300, 512, 1 << 26)[1] == 256 and tile(0, 300, 20000, 1 << 30)[0] == 32
     n = lib.duqpp_gemm_tiles()
     assert [lib.duqpp_gemm_tile_for(16 + i, 8, 16, 64, F32, None, None) for i in range(n + 1)] == list(range(n)) + [SHAPE]
     assert tile(5, 8, 16, 64) == SHAPE and tile(DECODE, 200, 16, 64) == SHAPE and tile(LARGE, 200, 20, 64, BF16) == SHAPE

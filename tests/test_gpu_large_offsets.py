@@ -103,3 +103,26 @@ def test_rows_beyond_4_gib():
     assert torch.equal(y_f, y16)
     del y_f, y16, x, c_rm, s_rm, act, ast
     torch.cuda.empty_cache()
+
+
+def test_distances_between_the_row_tiles_of_one_output_tile_beyond_2_31():
+    """256 tokens with 2^25 channels: the last row tile's codes start 3.5 GiB behind the first's, a distance the 256 x 256 tile
+    holds in 32 bits.  The same bits as from 32-token tiles, which hold none."""
+    import torch
+
+    import paper_2604_17789_amd as duqpp
+    T, N, K = 256, 32, 1 << 25
+    tile = duqpp.KERNEL_TILE + 10
+    assert duqpp.gemm_tile_for(T, N, K, kernel=tile) == (10, 256, 256)
+    assert duqpp.gemm_tile_for(T, N, K, kernel=duqpp.KERNEL_TILE) == (0, 32, 64)
+    print(f"[large offsets] T={T} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    ops = []
+    for rows in (T, N):
+        codes, scales = duqpp.tiled_bytes(rows, K)
+        ops.append(torch.randint(0, 256, (codes,), dtype=torch.uint8, device="cuda:0", generator=gen))
+        ops.append(torch.randint(118, 137, (scales,), dtype=torch.uint8, device="cuda:0", generator=gen))
+    y = duqpp.mxfp4_gemm_tiled(*ops, T, N, K, kernel=tile)
+    want = duqpp.mxfp4_gemm_tiled(*ops, T, N, K, kernel=duqpp.KERNEL_TILE)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(y).all()) and torch.equal(y, want)
