@@ -184,9 +184,11 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
     // No branch: the K loop has to stay one straight piece of code, or the compiler moves products out from between the
     // requests and copies registers whose contents are still on their way (waiting for them first).
     int left = NI - 1;                                     // steps after the one the sources point at
+    uint64_t zero_addr = (uint64_t)zero_codes;
+    asm volatile("" : "+s"(zero_addr));                    // one register pair: or it is computed again in every step
     auto advance = [&]() {
         const uint32_t more = left > 0 ? 1u : 0u;
-        const uint64_t keep = 0ull - more, zeros = (uint64_t)zero_codes & ~keep;
+        const uint64_t keep = 0ull - more, zeros = zero_addr & ~keep;
         --left;
         a_src += more * kTileStepBytes;
         as_src += more * 256;
@@ -244,15 +246,15 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
         sa[0][m] = *(LdsU32)(ps0 + m * 256);
     }
 
-    int stage = 0;
+    uint32_t stage = 0, spare = (TL::kStages - 1) * TL::kStageBytes;   // offsets of the stage in use and of the one before it
     // One K step; P: its register set.  MORE: it requests the step D ahead; the last D steps (MORE = false) request nothing,
     // and the wait of step P of them leaves the D - 2 - P steps behind the next one outstanding.
     auto step = [&](auto pc, auto more_c) {
         constexpr bool MORE = decltype(more_c)::value;
         constexpr int P = decltype(pc)::value, P1 = (P + 1) % D;
-        const int stage1 = stage + 1 == TL::kStages ? 0 : stage + 1;
-        const uint32_t so = (stage == 0 ? TL::kStages - 1 : stage - 1) * TL::kStageBytes;   // consumed in the previous step
-        const LdsBytes pa = pa0 + stage * TL::kStageBytes;
+        const uint32_t stage1 = stage == (TL::kStages - 1) * TL::kStageBytes ? 0 : stage + TL::kStageBytes;
+        const uint32_t so = spare;                                 // consumed in the previous step
+        const LdsBytes pa = pa0 + stage;
 #define DUQPP_PIN __builtin_amdgcn_sched_barrier(0)
         constexpr int kSlots = 3 * MT * NT;   // transfers spread over the first three quarters
         unroll<3>([&](auto qc) {
@@ -279,8 +281,8 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
         if constexpr (MORE) arrive<(D - 2) * TL::kOps + TL::kOps - TL::kLate>();
         else if constexpr (P < D - 1) arrive<(D - 2 - P) * TL::kOps>();
         DUQPP_PIN;
-        const LdsBytes na = pa0 + stage1 * TL::kStageBytes;
-        const LdsBytes ns = ps0 + stage1 * TL::kStageBytes;
+        const LdsBytes na = pa0 + stage1;
+        const LdsBytes ns = ps0 + stage1;
         unroll<NT>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
             unroll<MT>([&](auto mc) {
@@ -301,6 +303,7 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
         });
 #undef DUQPP_PIN
         if constexpr (MORE) advance();
+        spare = stage;
         stage = stage1;
     };
     for (int it = (NI + D - 1) / D; it > 1; --it) unroll<D>([&](auto dc) { step(dc, std::true_type{}); });
