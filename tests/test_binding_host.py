@@ -30,7 +30,7 @@ def test_tiled_bytes_is_the_library_s_answer(rows, K):
         got = duqpp.tiled_bytes(rows, K)
         assert got == want and all(type(v) is int for v in got)
     else:
-        with pytest.raises(want if isinstance(want, type) else duqpp.DuqppError):
+        with pytest.raises(want if isinstance(want, type) else duqpp.binding.DuqppError):
             duqpp.tiled_bytes(rows, K)
 
 
