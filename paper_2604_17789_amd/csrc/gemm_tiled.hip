@@ -28,8 +28,8 @@
 //   777 x 4096 x 14336 49.8 -> 38.0 (43.8 -> 29.9), 2048 x 4096 x 14336 61.1 -> 56.8 (60.4 -> 55.8), 3001 x 14336 x 4096 102.6 -> 93.9
 //   (100.0 -> 89.2), 8192 x 4096 x 4096 69.4 -> 68.6 (69.1 -> 65.8), 8192 x 14336 x 4096 239.9 -> 229.4 (231.8 -> 227.2),
 //   4096 x 8192 x 28672 413.7 -> 390.4 (400.6 -> 387.6).  Of 176 products (33 to 8192 tokens, eleven linears) one is slower by more
-//   than 2 % in either state of the weights, 1024 x 14336 x 4096 with 34.4 -> 36.0 (33.2 -> 32.0): constants that pick 256 x 256 tiles
-//   there (33.6, cached 32.8) lose as much at five others.
+//   than 2 %, 1024 x 14336 x 4096 with its weights in HBM, 34.4 -> 36.0 (33.2 -> 32.0): constants that pick 256 x 256 tiles there (33.6
+//   and 32.8) lose as much at five others.
 //
 // Requests and LDS-DMA transfers are builtins, so that the compiler knows which registers are still being written and counts
 // every transfer in its waits for them.  Its waits for the transfers themselves would drain the whole queue before every LDS
