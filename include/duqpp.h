@@ -326,13 +326,30 @@ int duqpp_fold_smoothing(const float* R, int64_t n_rblocks, const float* lambda,
  *   info       out  2 x int32 on the device: index of the block the matrix was built from, steps kept
  *   peaks      out  nullable, [max_steps + 1] fp64 on the device: peak |value| after 0, 1, ... steps
  *   workspace       at least duqpp_construct_rotation_workspace_bytes(T, max_steps) bytes, 256-byte aligned
- * Enqueues max_steps + 4 kernels on the stream.  Errors as for the other calls.
+ * Enqueues up to max_steps + 4 kernels on the stream.  Errors as for the other calls.
  */
 size_t duqpp_construct_rotation_workspace_bytes(int64_t T, int max_steps);   /* host, pure; 0 for invalid arguments */
 int duqpp_construct_rotation(const void* x_bf16, int64_t T, int64_t K, int64_t ldx,
                              const double* q_steps, int max_steps,
                              float* R_out, int32_t* info, double* peaks,
                              void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * NOT PART OF THE CONTRACT -- a hook for tests and measurements that may change with the kernels: duqpp_construct_rotation in one
+ * of the forms the library chooses from.  Same arguments, checks and result, bit for bit.  A form that cannot run the call returns
+ * DUQPP_ERR_SHAPE.
+ */
+enum {
+    DUQPP_CONSTRUCT_AUTO = 0,
+    DUQPP_CONSTRUCT_ONE_16 = 1,      /* one launch for all steps, workgroups of 16 or 32 rows */
+    DUQPP_CONSTRUCT_ONE_32 = 2,
+    DUQPP_CONSTRUCT_STEPS = 3,       /* a launch per step */
+    DUQPP_CONSTRUCT_IMPATIENT = 8    /* + one of ONE_*: its workgroups give up where they would have to wait for each other */
+};
+int duqpp_construct_rotation_on(int how, const void* x_bf16, int64_t T, int64_t K, int64_t ldx,
+                                const double* q_steps, int max_steps,
+                                float* R_out, int32_t* info, double* peaks,
+                                void* workspace, size_t workspace_bytes, void* stream);
 
 /* Host, pure: scratch bytes duqpp_mxfp4_gemm (fused = 0) can use or duqpp_rotq_gemm (fused = 1) needs:
  * room for both operands in the tiled layout.  0 for invalid shapes. */

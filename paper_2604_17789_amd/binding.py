@@ -64,6 +64,8 @@ def _load():
     L.duqpp_construct_rotation_workspace_bytes.restype = sz
     L.duqpp_construct_rotation.argtypes = [vp, i64, i64, i64, vp, ci, fp, vp, vp, vp, sz, vp]
     L.duqpp_construct_rotation.restype = ci
+    L.duqpp_construct_rotation_on.argtypes = [ci, vp, i64, i64, i64, vp, ci, fp, vp, vp, vp, sz, vp]
+    L.duqpp_construct_rotation_on.restype = ci
     L.duqpp_init.argtypes = []
     L.duqpp_init.restype = ci
     L.duqpp_packed_rotation_bytes.argtypes = [i64]

@@ -492,10 +492,20 @@ size_t duqpp_construct_rotation_workspace_bytes(int64_t T, int max_steps) {
 int duqpp_construct_rotation(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const double* q_steps,
                              int max_steps, float* R_out, int32_t* info, double* peaks, void* workspace,
                              size_t workspace_bytes, void* stream) {
+    return duqpp_construct_rotation_on(DUQPP_CONSTRUCT_AUTO, x_bf16, T, K, ldx, q_steps, max_steps, R_out, info, peaks, workspace,
+                                       workspace_bytes, stream);
+}
+
+int duqpp_construct_rotation_on(int how, const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const double* q_steps,
+                                int max_steps, float* R_out, int32_t* info, double* peaks, void* workspace,
+                                size_t workspace_bytes, void* stream) {
     if (!x_bf16 || !R_out || !info || (max_steps > 0 && !q_steps)) return DUQPP_ERR_NULL;
     int st = validate_rows_K(T, K, ldx, 1);
     if (st != DUQPP_OK) return st;
     if (max_steps < 0 || max_steps > 4096) return DUQPP_ERR_SHAPE;
+    const int form = how & ~DUQPP_CONSTRUCT_IMPATIENT;
+    if (form < DUQPP_CONSTRUCT_AUTO || form > DUQPP_CONSTRUCT_STEPS) return DUQPP_ERR_SHAPE;
+    if (how != form && (form < DUQPP_CONSTRUCT_ONE_16 || form > DUQPP_CONSTRUCT_ONE_32)) return DUQPP_ERR_SHAPE;
     if (!aligned_to(x_bf16, 16) || (ldx % 8) != 0 || !aligned_to(q_steps, 8) || !aligned_to(R_out, 4) ||
         !aligned_to(info, 4) || !aligned_to(peaks, 8))
         return DUQPP_ERR_ALIGN;
@@ -504,7 +514,8 @@ int duqpp_construct_rotation(const void* x_bf16, int64_t T, int64_t K, int64_t l
     st = check_device();
     if (st != DUQPP_OK) return st;
     ConstructParams p{static_cast<const uint16_t*>(x_bf16), ldx, T, K, q_steps, max_steps, R_out, info, peaks, workspace};
-    return launch_construct_rotation(p, static_cast<hipStream_t>(stream)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
+    if (!construct_runs(p, form)) return DUQPP_ERR_SHAPE;
+    return launch_construct_rotation(p, how, static_cast<hipStream_t>(stream)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
 }
 
 const char* duqpp_status_string(int status) {

@@ -13,15 +13,25 @@
 // and the result do not depend on how the work is spread over the chip.  Maxima are taken with integer atomics on
 // the bit patterns of |z| (order-independent).
 //
-// One kernel launch per step: the step needs the column maxima of the whole previous state, and all CUs wait for each other at
-// a launch (1.3 us of a step's 4.7).  What a step's result does not depend on is done ahead of the steps, for all
-// of them at once: the matrices H . diag(1, Q'_t) by construct_matrices_kernel, one workgroup per step.  A step is bound by
-// its chain of latencies (launch, column maxima, state, sums, atomics), so everything in it is spread wide: a workgroup
-// takes 32 rows, each of its eight waves 4 of the 32 columns, a lane two of them for one row.  The state is kept in tiles
-// of 32 rows with the rows adjacent, so that a wave reads and writes whole lines.
-// The call is offline.  2048 x 4096 activations, 128 steps on one MI355X: 2310 -> 667 us against a step kernel that
-// rebuilt M_t in every workgroup (a step 15.7 -> 4.7 us, of which an empty launch takes 1.3; the search for the block
-// 97 -> 5.6 us with one key per workgroup instead of one atomic per wave; the last kernel 142 -> 7 us).
+// Every step needs the largest magnitude of the whole state before it, so the steps are a chain of exchanges between all
+// workgroups.  Two forms:
+//   search kernel   (construct_search_kernel) one launch for all steps: a workgroup keeps its 16 or 32 rows of the state in LDS and
+//                   registers, publishes the largest magnitude among them after every step, waits for everybody's, and goes on.
+//                   For as many rows as workgroups that run at once hold: 16 rows each and one workgroup per CU, or 32 rows
+//                   and two per CU (T <= 16352).  Should they not come to run together, because other work holds the CUs for
+//                   longer than they wait (20 ms and more), they give up, and a launch of one workgroup does the whole
+//                   search: nothing ever waits without a limit.
+//   launch per step (construct_step_kernel) for more rows, and for one or two: the state in memory, the maxima by atomics, all
+//                   CUs waiting for each other at the launch.
+// What a step's result does not depend on is done ahead of the steps, for all of them at once: the matrices H . diag(1, Q'_t).
+// What a step of the search kernel takes (2048 rows, 130 workgroups, 2.0 us = 4900 cycles): 560 the workgroup's own maximum, 2100
+// the exchange, 500 the maximum of what came, 800 to 1250 the products (768 of them fp64 and its operands' moves, two waves
+// taking turns on a SIMD), 300 their maxima, the rest barriers.  128 steps on one MI355X, us, a launch per step / 16 rows / 32 rows
+// per workgroup (K = 4096): T = 64 554 / 244 / 337, 512 559 / 235 / 329, 1024 565 / 266 / -, 2048 601 / 262 / 325, 4096 705 / - / 333,
+// 8192 1048 / - / 457, 16000 1550 / - / 562.  The call is offline.
+#include <type_traits>
+#include <utility>
+
 #include "duqpp_internal.h"
 
 #pragma clang fp contract(off)
@@ -34,15 +44,20 @@ constexpr double kHadamardEntry = 0.17677669529663687;   // 1 / sqrt(32)
 constexpr int kTileRows = 32;                            // rows of the state per workgroup of a step
 constexpr int kStepWaves = 8;                            // waves of that workgroup; 4 columns each
 constexpr int kMaxPartials = 1024;                       // workgroups of the block search (their keys fill one slot of 8 KiB)
+constexpr int kExchangeCopies = 8;                       // copies of what the workgroups of the search kernel publish
+constexpr int kExchangeWords = 2;                        // 64-bit words between one workgroup's and the next one's (two are used)
+constexpr uint32_t kPatience = 40000;                    // looks for what the others publish, half a microsecond or more each
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ double hadamard_entry(int i, int k) { return (__popc(i & k) & 1) ? -kHadamardEntry : kHadamardEntry; }
 
-// workspace: [header 64 B: u64 block key][colmax (S + 1) x 32 u64][slots (S + 1) x 1024 f64][Z T x 32 f64]
+// workspace: [header 64 B: u64 block key, u64 search given up][colmax (S + 1) x 32 u64][slots (S + 1) x 1024 f64][Z T x 32 f64]
 // Slot 0 holds the block search's partial keys, then the maxima below; slot t >= 1 holds M_t = H . diag(1, Q'_t), then R^(t).
+// The search kernel keeps the state on the chip; the place of Z holds what its workgroups publish.
 struct Workspace {
     unsigned long long* key;
+    unsigned long long* given_up;
     unsigned long long* colmax;
     double* slots;
     double* z;
@@ -51,6 +66,7 @@ __host__ __device__ inline Workspace carve(void* ws, int steps) {
     Workspace w;
     uint8_t* p = static_cast<uint8_t*>(ws);
     w.key = reinterpret_cast<unsigned long long*>(p);
+    w.given_up = w.key + 1;
     w.colmax = reinterpret_cast<unsigned long long*>(p + 64);
     w.slots = reinterpret_cast<double*>(p + 64 + (size_t)(steps + 1) * 256);
     w.z = reinterpret_cast<double*>(p + 64 + (size_t)(steps + 1) * 256 + (size_t)(steps + 1) * 8192);
@@ -84,36 +100,46 @@ __device__ __forceinline__ int tile_rows(int64_t tile, int64_t T) {
     return (int)(left < kTileRows ? left : kTileRows);
 }
 
-// One step of a maximum over the wave: with the value of another lane, moved by the ALU (quad permutation 0xB1 = lane ^ 1,
-// 0x4E = lane ^ 2, 0x141 and 0x140 = mirrored within 8 and 16 lanes; lanes that hold the same maximum may stand in for
-// each other, so the mirrors do what lane ^ 4 and lane ^ 8 would).
+// Maxima over lanes, moved by the ALU.  A step takes the maximum with the value of another lane: quad permutation 0xB1 = lane ^ 1,
+// 0x4E = lane ^ 2, 0x141 and 0x140 = mirrored within 8 and 16 lanes (lanes that hold the same maximum may stand in for each other,
+// so the mirrors do what lane ^ 4 and lane ^ 8 would), 0x142 and 0x143 = lane 15 of a row of 16 into the next row, lane 31 into the
+// upper half.  Of 64-bit values the upper words first, then the lower words of the lanes that have the largest upper one: a step
+// is one instruction then, a comparison and selection of pairs would be five.
 template <int CTRL>
-__device__ __forceinline__ unsigned long long dpp_max(unsigned long long v) {
-    const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)v, CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), CTRL, 0xF, 0xF, true);
-    return max_u64(v, ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
+__device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+    return v > o ? v : o;
+}
+template <typename Steps>
+__device__ __forceinline__ unsigned long long words_max(unsigned long long v, Steps&& steps) {
+    const uint32_t hi = steps((uint32_t)(v >> 32));
+    const uint32_t lo = steps((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0u);
+    return ((unsigned long long)hi << 32) | lo;
+}
+// maximum over each 8 or 16 lanes, in every one of them
+__device__ __forceinline__ unsigned long long row8_max(unsigned long long v) {
+    return words_max(v, [](uint32_t m) { return dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m))); });
+}
+__device__ __forceinline__ unsigned long long row16_max(unsigned long long v) {
+    return words_max(v, [](uint32_t m) { return dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m)))); });
 }
 // maximum over each half of the wave, in every lane of the half
 __device__ __forceinline__ unsigned long long half_max(unsigned long long v) {
-    v = dpp_max<0xB1>(v);
-    v = dpp_max<0x4E>(v);
-    v = dpp_max<0x141>(v);
-    v = dpp_max<0x140>(v);
+    v = row16_max(v);
     return max_u64(v, __shfl_xor(v, 16));
 }
-// maximum over the 64 lanes, in every lane
+// maximum over the 64 lanes, uniform
 __device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
-    v = half_max(v);
-    return max_u64(v, __shfl_xor(v, 32));
+    return words_max(v, [](uint32_t m) {
+        m = dpp_max<0x143>(dpp_max<0x142>(dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m))))));
+        return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+    });
 }
 
-// Clears the first column maxima, and the largest |x| per block of 32 channels -> one 64-bit key per workgroup: magnitude bits
-// above, inverted block index below, so that the integer maximum is the largest magnitude in the smallest block.
-__global__ __launch_bounds__(256) void construct_blockmax_kernel(ConstructParams p) {
-    __shared__ unsigned long long red[4];
-    Workspace w = carve(p.workspace, p.steps);
-    const int64_t stride = (int64_t)gridDim.x * 256, at = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (at < 32) w.colmax[at] = 0ull;
+// The largest |x| per block of 32 channels -> one 64-bit key per workgroup of 256 threads: magnitude bits above, inverted block
+// index below, so that the integer maximum is the largest magnitude in the smallest block.
+__device__ __forceinline__ void block_key(const ConstructParams& p, const Workspace& w, int workgroups, unsigned long long* red) {
+    const int64_t stride = (int64_t)workgroups * 256, at = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t chunks = p.K / 8;                          // 16-byte pieces of 8 bf16 in a row; 4 per block
     const int64_t dr = stride / chunks, dc = stride % chunks;
     int64_t row = at / chunks, ch = at % chunks;
@@ -156,11 +182,16 @@ __global__ __launch_bounds__(256) void construct_blockmax_kernel(ConstructParams
         reinterpret_cast<unsigned long long*>(w.slots)[blockIdx.x] = max_u64(max_u64(red[0], red[1]), max_u64(red[2], red[3]));
 }
 
-// Z_0 = the chosen block's columns as doubles, and their column maxima.  Every workgroup finds the block again from the
-// partial keys.
-__global__ __launch_bounds__(64 * kStepWaves) void construct_extract_kernel(ConstructParams p, int partials) {
-    __shared__ unsigned long long red[kStepWaves];
+// Clears the first column maxima, and the keys.
+__global__ __launch_bounds__(256) void construct_blockmax_kernel(ConstructParams p) {
+    __shared__ unsigned long long red[4];
     Workspace w = carve(p.workspace, p.steps);
+    if (blockIdx.x == 0 && threadIdx.x < 32) w.colmax[threadIdx.x] = 0ull;
+    block_key(p, w, gridDim.x, red);
+}
+
+// The chosen block from the partial keys, in every thread of a workgroup of kStepWaves waves.
+__device__ __forceinline__ unsigned long long chosen_key(const Workspace& w, int partials, unsigned long long* red) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned long long key = 0ull;
     for (int i = threadIdx.x; i < partials; i += 64 * kStepWaves) key = max_u64(key, reinterpret_cast<const unsigned long long*>(w.slots)[i]);
@@ -169,8 +200,19 @@ __global__ __launch_bounds__(64 * kStepWaves) void construct_extract_kernel(Cons
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kStepWaves; ++k) key = max_u64(key, red[k]);
+    return key;
+}
+__device__ __forceinline__ int64_t block_of(unsigned long long key) { return 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull); }
+
+// Z_0 = the chosen block's columns as doubles, and their column maxima.  Every workgroup finds the block again from the
+// partial keys.
+__global__ __launch_bounds__(64 * kStepWaves) void construct_extract_kernel(ConstructParams p, int partials) {
+    __shared__ unsigned long long red[kStepWaves];
+    Workspace w = carve(p.workspace, p.steps);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned long long key = chosen_key(w, partials, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) *w.key = key;
-    const int64_t b = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
+    const int64_t b = block_of(key);
 
     const int n = tile_rows(blockIdx.x, p.T);
     double* z = state_tile(w, blockIdx.x);
@@ -188,10 +230,7 @@ __global__ __launch_bounds__(64 * kStepWaves) void construct_extract_kernel(Cons
 }
 
 // Slot 0: no maxima yet; slot t = M_t = H . diag(1, Q'_t): column 0 passes through, the others sum terms k = 1 .. 31 in order.
-__global__ __launch_bounds__(256) void construct_matrices_kernel(ConstructParams p) {
-    __shared__ double q[31 * 31];
-    Workspace w = carve(p.workspace, p.steps);
-    const int t = blockIdx.x;
+__device__ __forceinline__ void step_matrix(const ConstructParams& p, const Workspace& w, int t, double* q /* 31 * 31 */) {
     double* out = w.slots + (size_t)t * 1024;
     if (t > 0)
         for (int e = threadIdx.x; e < 31 * 31; e += 256) q[e] = p.q_steps[(size_t)(t - 1) * 31 * 31 + e];
@@ -210,11 +249,34 @@ __global__ __launch_bounds__(256) void construct_matrices_kernel(ConstructParams
         out[e] = acc;
     }
 }
+__global__ __launch_bounds__(256) void construct_matrices_kernel(ConstructParams p) {
+    __shared__ double q[31 * 31];
+    step_matrix(p, carve(p.workspace, p.steps), blockIdx.x, q);
+}
+
+// The largest of the lanes' values, uniform, and the lanes that hold it.
+__device__ __forceinline__ unsigned long long lanes_of_max(unsigned long long v, unsigned long long& top) {
+    auto most = [](uint32_t m) {
+        m = dpp_max<0x143>(dpp_max<0x142>(dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m))))));
+        return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+    };
+    const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v, most_hi = most(hi);
+    unsigned long long lanes = __ballot(hi == most_hi);
+    uint32_t most_lo;
+    if (lanes & (lanes - 1)) {                               // the lower words decide
+        most_lo = most(hi == most_hi ? lo : 0u);
+        lanes = __ballot(hi == most_hi && lo == most_lo);
+    } else {
+        most_lo = (uint32_t)__builtin_amdgcn_readlane((int)lo, __ffsll(lanes) - 1);
+    }
+    top = ((unsigned long long)most_hi << 32) | most_lo;
+    return lanes;
+}
 
 // The channel that step t exchanges with channel 0: largest magnitude in the state before it, smallest index among equals.
 // The same in every lane of every wave (lanes 32 .. 63 repeat lanes 0 .. 31).
 __device__ __forceinline__ int exchanged_channel(unsigned long long colmax_of_lane) {
-    const unsigned long long best = half_max(colmax_of_lane);
+    const unsigned long long best = wave_max(colmax_of_lane);
     return __builtin_amdgcn_readfirstlane(__ffsll(__ballot(colmax_of_lane == best)) - 1);
 }
 
@@ -329,15 +391,335 @@ __global__ __launch_bounds__(64 * kStepWaves) void construct_final_kernel(Constr
     for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) p.R_out[e] = bt > 0 ? (float)r[e] : (e / 32 == e % 32 ? 1.0f : 0.0f);
 }
 
+// ---- All steps in one launch ---------------------------------------------------------------------------------------
+struct SearchPlan {
+    int partials;                        // keys of the block search
+    int tiles;                           // workgroups that hold rows of the state; those behind them hold the product R^(t)
+    int participants;                    // all of them
+    uint32_t patience;                   // looks at what the others have published before one gives up
+};
+
+// What the workgroups tell each other after step t: two words each, the largest magnitude among their rows and the smallest
+// channel it stands in, into set t % 2.  Bit 63 of a word (a magnitude's sign, so free) changes with every use of a set and says
+// that the word is there: (t / 2) % 2, opposite to what was there before.  Nobody writes set t % 2 again before everybody has read
+// it: a workgroup publishes step t + 2 after it has seen all of step t + 1, which they publish after reading step t.  The words
+// are relaxed atomics of device scope, which the eight L2s do not keep to themselves; nothing else passes between workgroups, so no
+// cache has to be written back or invalidated (with an acquire per exchange instead the exchange alone takes longer than a step).
+// Requests to one line are served one after the other: eight copies of everyone's words.  (Side by side: with 64 bytes for each and
+// two copies an exchange alone is faster, but the steps slower, 2048 rows 375 against 338 us for 128: more requests per look.)
+__device__ __forceinline__ uint32_t exchange_at(int participants, int copy, int who) {
+    return (uint32_t)(copy * participants + who) * kExchangeWords;
+}
+inline size_t exchange_bytes(int participants) { return (size_t)2 * kExchangeCopies * participants * kExchangeWords * 8; }
+
+// Keys of the block search, the matrices of all steps, and nothing published yet.
+__global__ __launch_bounds__(256) void construct_prepare_kernel(ConstructParams p, SearchPlan s) {
+    __shared__ double q[31 * 31];
+    Workspace w = carve(p.workspace, p.steps);
+    const int words = 2 * kExchangeCopies * kExchangeWords * s.participants;
+    const int at = blockIdx.x * 256 + threadIdx.x;
+    if (at == 0) *w.given_up = 0ull;
+    for (int i = at; i < words; i += gridDim.x * 256) reinterpret_cast<unsigned long long*>(w.z)[i] = ~0ull;
+    if ((int)blockIdx.x < s.partials) block_key(p, w, s.partials, reinterpret_cast<unsigned long long*>(q));
+    else step_matrix(p, w, (int)blockIdx.x - s.partials + 1, q);
+}
+
+// value of lane N of each 16 lanes, in all 16
+template <int N>
+__device__ __forceinline__ double row16_broadcast(double v) {
+    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + N, 0xF, 0xF, true));
+}
+
+template <typename F, int... I>
+__device__ __forceinline__ void each_row(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// Every LDS access this wave has issued has completed, then workgroup barrier (loads from memory stay in flight).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// A workgroup holds 16 RH rows.  Lane (i, q) = (lane % 16, lane / 16) of wave (rh, cs) computes RH columns of row 16 rh + i: the
+// row is in its registers, read from LDS while the exchange is under way, and the entries of M_t are in the registers of the 16
+// lanes that need the same ones, from where an ALU move hands them round: read from LDS by every lane they cost more than the
+// products (32 rows: 2048 cycles of LDS against 1024 of fp64).
+template <int RH, int LOOKS, int PER_CU>
+__global__ __launch_bounds__(64 * kStepWaves, 2 * PER_CU) void construct_search_kernel(ConstructParams p, SearchPlan s) {
+    constexpr int kRows = 16 * RH, kPitch = 34, kMPitch = 33;
+    __shared__ __attribute__((aligned(16))) double z[2][kRows * kPitch];   // the state after even and odd steps
+    __shared__ double mt[2][32 * kMPitch];                   // M_t by columns, likewise
+    __shared__ unsigned long long colmax[32], seen[64], red[kStepWaves];
+    __shared__ int seen_channel[64];
+    const Workspace w = carve(p.workspace, p.steps);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = lane & 15, q = lane >> 4;
+    const int row = (wave % RH) * 16 + i, col0 = ((wave / RH) * 4 + q) * RH;
+    const bool product = (int)blockIdx.x >= s.tiles;         // the rows of R^(t), updated like rows of the state
+    const int64_t grow = ((int64_t)blockIdx.x - (product ? s.tiles : 0)) * kRows + row;
+    const bool counts = !product && grow < p.T;
+    const int mr = threadIdx.x >> 4, mc = 2 * (threadIdx.x & 15);   // this thread's two entries of a matrix on its way to LDS
+    auto matrix = [&](int t) {                               // (a uniform address and a 32-bit offset, here and below: registers)
+        return reinterpret_cast<const f64x2*>(w.slots + (size_t)(t < p.steps ? t : p.steps) * 1024)[threadIdx.x];
+    };
+    auto stage = [&](int t, const f64x2& e) {
+        mt[t & 1][mc * kMPitch + mr] = e[0];
+        mt[t & 1][(mc + 1) * kMPitch + mr] = e[1];
+    };
+    double acc[RH], kept[RH];
+    int at[RH], kept_at[RH];                                 // channels of acc and kept
+    auto take = [&](int t) {                                 // the new values of this lane's row
+#pragma unroll
+        for (int k = 0; k < RH; ++k) {
+            z[t & 1][row * kPitch + at[k]] = acc[k];
+            const unsigned long long top = row16_max(counts ? abs_bits(acc[k]) : 0ull);
+            if (i == 0 && top) atomicMax(&colmax[at[k]], top);
+        }
+    };
+
+    if (threadIdx.x < 32) colmax[threadIdx.x] = 0ull;
+    const unsigned long long key = chosen_key(w, s.partials, red);   // (holds a barrier: colmax is cleared)
+    const int64_t block = block_of(key);
+    f64x2 next = {0.0, 0.0};
+    if (p.steps > 0) {
+        stage(1, matrix(1));
+        next = matrix(2);
+    }
+#pragma unroll
+    for (int k = 0; k < RH; ++k) {
+        at[k] = col0 + k;
+        kept_at[k] = at[k];
+        acc[k] = 0.0;
+        if (product) acc[k] = grow == at[k] ? 1.0 : 0.0;
+        else if (counts) acc[k] = (double)__uint_as_float((uint32_t)p.x[grow * p.ldx + 32 * block + at[k]] << 16);
+        kept[k] = acc[k];
+    }
+    take(0);
+    lds_barrier();
+
+    unsigned long long* const words = reinterpret_cast<unsigned long long*>(w.z);
+    const uint32_t set_words = exchange_at(s.participants, kExchangeCopies, 0);
+    unsigned long long lowest = ~0ull;
+    int steps_kept = 0;
+    for (int t = 0;; ++t) {
+        const unsigned long long there = (unsigned long long)((t >> 1) & 1) << 63;
+        unsigned long long* const set = words + ((t & 1) ? set_words : 0u);
+        if (wave == 0) {
+            const unsigned long long cm = lane < 32 ? colmax[lane] : 0ull;
+            unsigned long long top;
+            const int d = __ffsll(lanes_of_max(cm, top)) - 1;
+            if (lane < kExchangeCopies) {
+                unsigned long long* const mine = set + exchange_at(s.participants, lane, blockIdx.x);
+                __hip_atomic_store(mine, top | there, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(mine + 1, (unsigned long long)d | there, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (lane < 32) colmax[lane] = 0ull;
+        }
+        const double* zr = &z[t & 1][row * kPitch];
+        double x[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) x[k] = zr[k];           // while the exchange is under way
+        if (wave == 0) {                                     // this wave waits, lane l for l, l + 64, ...
+            const unsigned long long* const copy = set + exchange_at(s.participants, blockIdx.x % kExchangeCopies, 0);
+            // Whoever looks too early is in the way of those still publishing (128 steps, 2048 rows, 130 workgroups, in an earlier
+            // form of this loop: 374 us without the pause, 323 with 8 here, 293 with 12, 282 with 16, 313 with 24; 6 workgroups: 241
+            // without, 243 with 12, 256 with 16)
+            __builtin_amdgcn_s_sleep(LOOKS > 1 ? 12 : 10);
+            unsigned long long best = 0ull;
+            int channel = 32;
+            bool here = true;
+            for (int first = 0; first < s.participants; first += 64 * LOOKS) {
+                unsigned long long v[LOOKS], d[LOOKS], all;  // bit 63 of all: not everyone's words are there
+                uint32_t looks = 0;
+                do {
+                    all = 0ull;
+#pragma unroll
+                    for (int k = 0; k < LOOKS; ++k) {
+                        const int l = first + 64 * k + lane, who = l < s.participants ? l : s.participants - 1;   // lanes without one: the last
+                        const unsigned long long* const theirs = copy + (uint32_t)who * kExchangeWords;
+                        v[k] = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ^ there;
+                        d[k] = __hip_atomic_load(theirs + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ^ there;
+                    }
+#pragma unroll
+                    for (int k = 0; k < LOOKS; ++k) all |= v[k] | d[k];
+                } while (__any((all >> 63) != 0) && ++looks < s.patience);
+                here = here & ((all >> 63) == 0);
+#pragma unroll
+                for (int k = 0; k < LOOKS; ++k) {            // no branch: & and | of the comparisons
+                    const bool more = (v[k] > best) | ((v[k] == best) & ((int)d[k] < channel));
+                    best = more ? v[k] : best;
+                    channel = more ? (int)d[k] : channel;
+                }
+            }
+            seen[lane] = best;
+            seen_channel[lane] = here ? channel : -1;
+        }
+        lds_barrier();
+        // largest magnitude of all, in the smallest channel
+        const unsigned long long v = seen[lane];
+        const int c = seen_channel[lane];
+        const bool missing = c < 0;
+        const bool given_up = __any(missing);
+        unsigned long long peak, tops = lanes_of_max(v, peak);
+        int d = __builtin_amdgcn_readlane(c, __ffsll(tops) - 1);
+        while (tops &= tops - 1) {                           // almost always one
+            const int other = __builtin_amdgcn_readlane(c, __ffsll(tops) - 1);
+            d = other < d ? other : d;
+        }
+        if (given_up) {                                      // the same for every thread of the workgroup
+            if (threadIdx.x == 0) __hip_atomic_store(w.given_up, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        if (product) {
+            if (peak < lowest) {
+                lowest = peak;
+                steps_kept = t;
+#pragma unroll
+                for (int k = 0; k < RH; ++k) { kept[k] = acc[k]; kept_at[k] = at[k]; }
+            }
+            if (p.peaks && (int)blockIdx.x == s.tiles && threadIdx.x == 0) p.peaks[t] = __longlong_as_double((long long)peak);
+        }
+        if (t == p.steps) break;
+
+        // step t + 1: row . M with the rows of M in the order sigma(0), sigma(1), ..., sigma exchanging 0 and d
+        auto sigma = [&](int r) { return r == 0 ? d : (r == d ? 0 : r); };
+        double lo[RH], hi[RH];
+        const int r0 = sigma(i), r1 = sigma(16 + i);
+#pragma unroll
+        for (int k = 0; k < RH; ++k) {
+            const double* m = &mt[(t + 1) & 1][(col0 + k) * kMPitch];
+            lo[k] = m[r0];
+            hi[k] = m[r1];
+            acc[k] = 0.0;
+            at[k] = sigma(col0 + k);
+        }
+        if (t + 2 <= p.steps) {
+            stage(t + 2, next);                              // its last reader was step t
+            next = matrix(t + 3);
+        }
+        auto term = [&](auto rc) {
+            constexpr int R = decltype(rc)::value;
+#pragma unroll
+            for (int k = 0; k < RH; ++k) acc[k] = acc[k] + x[R] * row16_broadcast<R % 16>(R < 16 ? lo[k] : hi[k]);
+            if constexpr (R % 4 == 3) {                      // the compiler gathers the moves of all rows ahead of the products otherwise
+#pragma unroll
+                for (int k = 0; k < RH; ++k) asm volatile("" : "+v"(acc[k]), "+v"(lo[k]), "+v"(hi[k]));
+            }
+        };
+        each_row(term, std::make_integer_sequence<int, 32>{});
+        take(t + 1);
+        lds_barrier();
+    }
+    if (product) {
+        if (grow < 32) {
+#pragma unroll
+            for (int k = 0; k < RH; ++k) p.R_out[grow * 32 + kept_at[k]] = (float)kept[k];
+        }
+        if ((int)blockIdx.x == s.tiles && threadIdx.x == 0) {
+            p.info[0] = (int)block;
+            p.info[1] = steps_kept;
+        }
+    }
+}
+
+// The whole search in one workgroup, which waits for nobody, if one of the search kernel's gave up waiting: where not all of them
+// came to run together.  Slow, and the same result.
+__global__ __launch_bounds__(64 * kStepWaves) void construct_given_up_kernel(ConstructParams p, SearchPlan s) {
+    __shared__ double m[1024], product[1024], best[1024];
+    __shared__ unsigned long long colmax[32], red[kStepWaves];
+    const Workspace w = carve(p.workspace, p.steps);
+    if (*w.given_up == 0ull) return;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x < 32) colmax[threadIdx.x] = 0ull;
+    const int64_t block = block_of(chosen_key(w, s.partials, red));
+    const int64_t rows = p.T + 32;                           // the state's, then the product's
+    auto column_top = [&](int c, double v, bool there) {
+        const unsigned long long top = wave_max(there ? abs_bits(v) : 0ull);
+        if (lane == 0 && top) atomicMax(&colmax[c], top);
+    };
+    for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) product[e] = best[e] = e / 32 == e % 32 ? 1.0 : 0.0;
+    for (int64_t r0 = 0; r0 < p.T; r0 += 64 * kStepWaves) {
+        const int64_t r = r0 + threadIdx.x;
+        for (int c = 0; c < 32; ++c) {
+            double v = 0.0;
+            if (r < p.T) {
+                v = (double)__uint_as_float((uint32_t)p.x[r * p.ldx + 32 * block + c] << 16);
+                w.z[r * 32 + c] = v;
+            }
+            column_top(c, v, r < p.T);
+        }
+    }
+    unsigned long long lowest = ~0ull;
+    int steps_kept = 0;
+    for (int t = 0;; ++t) {
+        __syncthreads();
+        const unsigned long long cm = colmax[lane & 31], peak = wave_max(cm);
+        const int d = exchanged_channel(cm);
+        auto sigma = [&](int r) { return r == 0 ? d : (r == d ? 0 : r); };
+        if (p.peaks && threadIdx.x == 0) p.peaks[t] = __longlong_as_double((long long)peak);
+        if (peak < lowest) {
+            lowest = peak;
+            steps_kept = t;
+            for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) best[e] = product[e];
+        }
+        if (t == p.steps) break;
+        for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) m[sigma(e >> 5) * 32 + (e & 31)] = w.slots[(size_t)(t + 1) * 1024 + e];
+        __syncthreads();                                     // the maxima have been read, too
+        if (threadIdx.x < 32) colmax[threadIdx.x] = 0ull;
+        __syncthreads();
+        for (int64_t r0 = 0; r0 < rows; r0 += 64 * kStepWaves) {
+            const int64_t r = r0 + threadIdx.x;
+            double* z = r < p.T ? w.z + r * 32 : product + (r < rows ? r - p.T : 0) * 32;
+            double x[32];
+#pragma unroll
+            for (int k = 0; k < 32; ++k) x[k] = z[k];
+            for (int c = 0; c < 32; ++c) {
+                double v = 0.0;
+#pragma unroll
+                for (int k = 0; k < 32; ++k) v = v + x[k] * m[k * 32 + c];
+                if (r < rows) z[sigma(c)] = v;
+                column_top(sigma(c), v, r < p.T);
+            }
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) p.R_out[e] = (float)best[e];
+    if (threadIdx.x == 0) {
+        p.info[0] = (int)block;
+        p.info[1] = steps_kept;
+    }
+}
+
 }  // namespace
 
 size_t construct_workspace_bytes(int64_t T, int steps) {
     return 64 + (size_t)(steps + 1) * 256 + (size_t)(steps + 1) * 8192 + (size_t)T * 256;
 }
 
-hipError_t launch_construct_rotation(const ConstructParams& p, hipStream_t stream) {
-    const int64_t chunks = (int64_t)p.T * (p.K / 8);
-    const int partials = (int)((chunks + 1023) / 1024 < kMaxPartials ? (chunks + 1023) / 1024 : kMaxPartials);
+namespace {
+
+// One launch for all steps (form: DUQPP_CONSTRUCT_ONE_*); false: the workspace has no room for what they publish, or there
+// would be more workgroups than run at once.
+bool plan_search(const ConstructParams& p, int form, int partials, SearchPlan& s) {
+    const int64_t rows = 16 << (form - DUQPP_CONSTRUCT_ONE_16), tiles = (p.T + rows - 1) / rows, all = tiles + (rows < 32 ? 2 : 1);
+    if (all > (form == DUQPP_CONSTRUCT_ONE_16 ? kNumCU : 2 * kNumCU) || (int64_t)exchange_bytes((int)all) > p.T * 256) return false;
+    s = SearchPlan{partials, (int)tiles, (int)all, kPatience};
+    return true;
+}
+
+hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form, hipStream_t stream) {
+    hipError_t e = launch(construct_prepare_kernel, dim3((unsigned)(s.partials + p.steps)), dim3(256), 0, stream, p, s);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)s.participants), block(64 * kStepWaves);
+    if (form == DUQPP_CONSTRUCT_ONE_16)
+        e = s.participants <= 64 ? launch(construct_search_kernel<1, 1, 1>, grid, block, 0, stream, p, s)
+                                 : launch(construct_search_kernel<1, 4, 1>, grid, block, 0, stream, p, s);
+    else
+        e = s.participants <= kNumCU ? launch(construct_search_kernel<2, 4, 1>, grid, block, 0, stream, p, s)
+                                     : launch(construct_search_kernel<2, 2, 2>, grid, block, 0, stream, p, s);
+    if (e != hipSuccess) return e;
+    return launch(construct_given_up_kernel, dim3(1), block, 0, stream, p, s);
+}
+
+hipError_t launch_steps(const ConstructParams& p, int partials, hipStream_t stream) {
     hipError_t e = launch(construct_blockmax_kernel, dim3(partials), dim3(256), 0, stream, p);
     if (e != hipSuccess) return e;
     const unsigned tiles = (unsigned)((p.T + kTileRows - 1) / kTileRows);
@@ -350,6 +732,28 @@ hipError_t launch_construct_rotation(const ConstructParams& p, hipStream_t strea
         if (e != hipSuccess) return e;
     }
     return launch(construct_final_kernel, dim3(1), dim3(64 * kStepWaves), 0, stream, p);
+}
+
+}  // namespace
+
+bool construct_runs(const ConstructParams& p, int form) {
+    SearchPlan s{};
+    return form == DUQPP_CONSTRUCT_AUTO || form == DUQPP_CONSTRUCT_STEPS || plan_search(p, form, 0, s);
+}
+
+hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStream_t stream) {
+    const int64_t chunks = (int64_t)p.T * (p.K / 8);
+    const int partials = (int)((chunks + 1023) / 1024 < kMaxPartials ? (chunks + 1023) / 1024 : kMaxPartials);
+    int form = how & ~DUQPP_CONSTRUCT_IMPATIENT;
+    SearchPlan s{};
+    if (form == DUQPP_CONSTRUCT_AUTO) {
+        form = DUQPP_CONSTRUCT_ONE_16;
+        while (form < DUQPP_CONSTRUCT_STEPS && !plan_search(p, form, partials, s)) ++form;
+    }
+    if (form == DUQPP_CONSTRUCT_STEPS) return launch_steps(p, partials, stream);
+    if (!plan_search(p, form, partials, s)) return hipErrorInvalidValue;
+    if (how & DUQPP_CONSTRUCT_IMPATIENT) s.patience = 0;
+    return launch_search(p, s, form, stream);
 }
 
 }  // namespace duqpp
