@@ -158,6 +158,15 @@ int duqpp_group_error(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, con
                       float* err, double* mean, void* stream);
 
 /*
+ * The same, bit for bit, with a place for the partial sums of the mean: without one they take the place of ratios, which are then
+ * computed twice in a third launch (2048 x 4096 from Python on one MI355X, with the wait for the mean: 30.6 us, with one 29.1).
+ *   workspace  nullable; at least duqpp_group_error_workspace_bytes(T, K) bytes of device memory, 8-byte aligned
+ */
+size_t duqpp_group_error_workspace_bytes(int64_t T, int64_t K);   /* host, pure; 0: none is used, or invalid arguments */
+int duqpp_group_error_ws(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const float* R, int64_t n_rblocks,
+                         float* err, double* mean, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * TEST ONLY: runs the quantiser stage of duqpp_rotate_quantize (group amax, E8M0 scale,
  * E2M1 rounding, packing -- Eq. 2) on caller-supplied fp32 values, so that every fp32 bit
  * pattern can be swept through the device code.

@@ -39,6 +39,10 @@ def _load():
     L.duqpp_rotq_gemm.argtypes = [vp, i64, fp, i64, u8p, u8p, i64, i64, i64, vp, ci, i64, vp, sz, vp]
     L.duqpp_quantize_f32_dbg.argtypes = [fp, i64, i64, i64, u8p, u8p, vp]
     L.duqpp_group_error.argtypes = [vp, i64, i64, i64, fp, i64, fp, vp, vp]
+    L.duqpp_group_error_ws.argtypes = [vp, i64, i64, i64, fp, i64, fp, vp, vp, sz, vp]
+    L.duqpp_group_error_ws.restype = ci
+    L.duqpp_group_error_workspace_bytes.argtypes = [i64, i64]
+    L.duqpp_group_error_workspace_bytes.restype = sz
     L.duqpp_gemm_workspace_bytes.argtypes = [i64, i64, i64, ci]
     L.duqpp_gemm_workspace_bytes.restype = sz
     L.duqpp_validate_rotate_quantize.argtypes = [vp, i64, i64, i64, fp, i64, u8p, u8p]
@@ -272,8 +276,11 @@ def group_error(x, R=None, return_mean=True):
         nrb = R.shape[0]
     err = torch.empty((T, K // 32), dtype=torch.float32, device=x.device)
     mean = torch.empty(1, dtype=torch.float64, device=x.device) if return_mean else None
-    st = lib.duqpp_group_error(x.data_ptr(), T, K, x.stride(0), R.data_ptr() if R is not None else None, nrb,
-                               err.data_ptr(), mean.data_ptr() if mean is not None else None, _stream())
+    nbytes = lib.duqpp_group_error_workspace_bytes(T, K) if return_mean else 0
+    ws, _ = _workspace(nbytes, x.device)
+    st = lib.duqpp_group_error_ws(x.data_ptr(), T, K, x.stride(0), R.data_ptr() if R is not None else None, nrb,
+                                  err.data_ptr(), mean.data_ptr() if mean is not None else None,
+                                  ws.data_ptr() if ws is not None else None, nbytes, _stream())
     _check(st, "duqpp_group_error")
     return err, (float(mean.item()) if mean is not None else None)
 

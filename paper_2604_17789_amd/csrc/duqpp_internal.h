@@ -98,11 +98,13 @@ struct GroupErrorParams {
     int r_stride;        // floats between consecutive blocks (0 when one block is shared)
     float* err;          // [rows, G]
     double* mean;        // nullable
+    float* partials;     // nullable: group_error_workspace_bytes of scratch for the mean
 };
 struct GroupErrorMeanParams {
     const float* err; int64_t n; double* mean;
 };
 constexpr int64_t kGroupErrorMaxTiles = 65535;   // tiles of 32 tokens a call takes (DUQPP_ERR_TOO_LARGE beyond)
+size_t group_error_workspace_bytes(int64_t rows, int64_t G);
 hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream);
 
 struct QuantDbgParams {

@@ -25,7 +25,7 @@ struct ErrPlan {
     int chunks, runs;                   // workgroups: column chunks x token runs
     int ntiles;                         // token tiles of 32 in play
     int64_t keep_from, keep_to;         // ratios stored: their place in err, in floats
-    int partials;                       // err's first floats receive each workgroup's partial sum and count
+    int partials;                       // each workgroup's partial sum and count are kept, four words each
 };
 
 // value of an E2M1 code (sign, two exponent bits, one mantissa bit): 0, 0.5, 1, 1.5, 2, 3, 4, 6
@@ -89,7 +89,8 @@ __device__ __forceinline__ double pair_sums(double v0, double v1) {
 // of token c's values of each group, then of two groups the ratio of group h: one division and square root per lane.
 // Bound by the fp64 sums and the start (rotation blocks, first tiles), a third of it by reading x.  2048 x 4096 on one
 // MI355X: 13.2 -> 9.3 us against a wave per (tile, group) that formed the codes' values in fp64; the mean 86 -> 6.3 us (2.4 from
-// the partial sums, 3.9 to compute the first ratios again) against one workgroup with one load in flight per thread.
+// the partial sums, 3.9 to compute the first ratios again) against one workgroup with one load in flight per thread, and 2.4
+// where the caller has a place for the partial sums.  (Both in one launch of one workgroup: 15.3 us.)
 template <bool ROTATED, int GROUPS>
 __global__ __launch_bounds__(64 * (GROUPS == 2 ? kErrWaves : 1)) void group_error_kernel(GroupErrorParams p, ErrPlan e) {
     constexpr int kWaves = GROUPS == 2 ? kErrWaves : 1;
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(64 * (GROUPS == 2 ? kErrWaves : 1)) void group_erro
         double t = 0.0;
         for (int k = 0; k < kWaves; ++k) t += sums[k][threadIdx.x];
         const unsigned long long bits = (unsigned long long)__double_as_longlong(t);
-        uint32_t* out = (uint32_t*)p.err + (int64_t)blockIdx.x * 4 + 2 * threadIdx.x;      // err is aligned to a float only
+        uint32_t* out = (uint32_t*)p.partials + (int64_t)blockIdx.x * 4 + 2 * threadIdx.x; // may be err, aligned to a float only
         out[0] = (uint32_t)bits;
         out[1] = (uint32_t)(bits >> 32);
     }
@@ -228,16 +229,30 @@ __global__ __launch_bounds__(1024) void group_error_mean_kernel(GroupErrorMeanPa
 
 }  // namespace
 
-hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream) {
+// partial sums of a call with a mean; 0: it takes none
+static int64_t error_workgroups(int64_t tiles, int64_t G, int64_t& chunks, int64_t& runs) {
+    chunks = (G + 2 * kErrWaves - 1) / (2 * kErrWaves);
+    runs = kErrWorkgroups / chunks;
+    runs = runs < 1 ? 1 : (runs > tiles ? tiles : runs);
+    return chunks * runs;
+}
+
+size_t group_error_workspace_bytes(int64_t rows, int64_t G) {
+    int64_t chunks, runs;
+    return rows * G < kPartialsFrom ? 0 : (size_t)error_workgroups((rows + 31) / 32, G, chunks, runs) * 16;
+}
+
+hipError_t launch_group_error(const GroupErrorParams& call, hipStream_t stream) {
+    GroupErrorParams p = call;
     const int64_t tiles = ((int64_t)p.rows + 31) / 32;
     if (p.G < 1 || p.rows < 1 || tiles > kGroupErrorMaxTiles) return hipErrorInvalidValue;
     const int64_t n = (int64_t)p.rows * p.G;
-    const int per_chunk = 2 * kErrWaves;
     auto plan = [&](int ntiles) {
         ErrPlan e{};
-        e.chunks = (p.G + per_chunk - 1) / per_chunk;
-        e.runs = kErrWorkgroups / e.chunks;
-        e.runs = e.runs < 1 ? 1 : (e.runs > ntiles ? ntiles : e.runs);
+        int64_t chunks, runs;
+        error_workgroups(ntiles, p.G, chunks, runs);
+        e.chunks = (int)chunks;
+        e.runs = (int)runs;
         e.ntiles = ntiles;
         e.keep_to = n;
         return e;
@@ -271,14 +286,16 @@ hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream) {
         const hipError_t st = run(e);
         return st != hipSuccess || !p.mean ? st : mean_of_ratios();
     }
-    // The partial sums need a place until the mean is formed, and the call has no scratch: they take the first floats of err,
+    // The partial sums need a place until the mean is formed.  Where the call brings none they take the first floats of err,
     // whose ratios (at most 64 token tiles, with one group per token) are computed once more afterwards.
+    const bool scratch = p.partials != nullptr;
+    if (!scratch) p.partials = p.err;
     e.partials = 1;
-    e.keep_from = held;
+    e.keep_from = scratch ? 0 : held;
     hipError_t st = run(e);
     if (st != hipSuccess) return st;
-    st = launch(group_error_mean_kernel<true, 1>, dim3(1), dim3(1024), 0, stream, GroupErrorMeanParams{p.err, workgroups, p.mean});
-    if (st != hipSuccess) return st;
+    st = launch(group_error_mean_kernel<true, 1>, dim3(1), dim3(1024), 0, stream, GroupErrorMeanParams{p.partials, workgroups, p.mean});
+    if (st != hipSuccess || scratch) return st;
     ErrPlan again = plan((int)(((held + p.G - 1) / p.G + 31) / 32));
     again.keep_to = held;
     return run(again);
