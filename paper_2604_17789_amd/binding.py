@@ -1,4 +1,5 @@
-"""ctypes binding with the same names as the C ABI (include/duqpp.h).  Argument marshalling only."""
+"""Binding with the same names as the C ABI (include/duqpp.h).  Argument marshalling only: the calls of serving and analysis
+through the native module _calls (csrc/calls.cpp) where their arguments are plain, everything else through ctypes."""
 import ctypes
 import os
 
@@ -117,7 +118,7 @@ def _check(status, what):
 
 # What a call costs on the host counts: two launches take 4.4 us there, and everything below has to stay small beside them
 # (rotq_gemm_tiled_packed with its buffers given: 13.0 us per call with a torch.cuda.Stream object built for every call and
-# the layout's sizes fetched through the C call, 9.1 us without).
+# the layout's sizes fetched through the C call, 9.1 us without, 5.5 us through _calls).
 _current_device = getattr(torch._C, "_cuda_getDevice", None)
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
@@ -127,6 +128,29 @@ def _stream():
     if _raw_stream is None or _current_device is None:       # names of torch's own use: a torch without them has the public way
         return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_current_device())
+
+
+def _load_calls():
+    try:
+        from . import _calls
+    except ImportError as e:
+        raise ImportError(f"{os.path.join(_HERE, '_calls.so')} is missing or was built for another torch or Python: build it first "
+                          "(python -c 'import __graft_entry__ as g; g.build()'); there is no fallback path") from e
+    names = ("duqpp_rotq_gemm_tiled_packed", "duqpp_rotq_gemm_tiled", "duqpp_rotq_gemm", "duqpp_gemm_workspace_bytes",
+             "duqpp_rotate_quantize_tiled_packed", "duqpp_rotate_quantize_tiled", "duqpp_quantize_weights_tiled",
+             "duqpp_mxfp4_gemm_tiled", "duqpp_group_error_ws", "duqpp_group_error_workspace_bytes")
+    _calls.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names}, _stream)
+    return _calls
+
+
+_calls = _load_calls()
+
+
+def _done(result, what):
+    """What a function of _calls answered, where that is not None: the result, or the status of the C call."""
+    if result.__class__ is int:
+        _check(result, what)
+    return result
 
 
 def _dev(t, dtype, what):
@@ -227,6 +251,9 @@ def mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, out_dtype=F32, out=None, wo
 
 
 def rotq_gemm(x, R, b_codes, b_scales, out_dtype=F32, out=None, workspace=None):
+    y = _calls.linear(2, x, R, b_codes, b_scales, None, out_dtype, out, workspace)
+    if y is not None:
+        return _done(y, "duqpp_rotq_gemm")
     _dev(x, torch.bfloat16, "x")
     _dev(R, torch.float32, "R")
     _dev(b_codes, torch.uint8, "b_codes")
@@ -264,6 +291,10 @@ def group_error(x, R=None, return_mean=True):
     """x bf16 [T, K], R fp32 [K/32 or 1, 32, 32] or None (no rotation) -> (err fp32 [T, K/32], mean): the per-group
     normalised quantisation error of Sec. 4.1 (Fig. 1), -1 where a group is all zero, and its mean over the other
     groups (a Python float; None with return_mean=False)."""
+    if return_mean:
+        both = _calls.error(x, R)
+        if both is not None:
+            return _done(both, "duqpp_group_error")
     _dev(x, torch.bfloat16, "x")
     T, K = x.shape
     if x.stride(1) != 1:
@@ -337,6 +368,9 @@ def untile_operand(codes_t, scales_t, rows, K):
 
 
 def _rows_op_tiled(fn, name, x, R, out):
+    both = _calls.rows(2 if name == "duqpp_quantize_weights_tiled" else 1, x, R, out)
+    if both is not None:
+        return _done(both, name)
     _dev(x, torch.bfloat16, "x")
     _dev(R, torch.float32, "R")
     if x.dim() != 2 or x.stride(1) != 1:
@@ -379,6 +413,9 @@ def _n_packed(Rp):
 
 def rotate_quantize_tiled_packed(x, R_packed, out=None):
     """rotate_quantize_tiled on packed rotation blocks: same bytes out."""
+    both = _calls.rows(0, x, R_packed, out)
+    if both is not None:
+        return _done(both, "duqpp_rotate_quantize_tiled_packed")
     _dev(x, torch.bfloat16, "x")
     if x.dim() != 2 or x.stride(1) != 1:
         raise ValueError("x must be [rows, K] with unit stride along K")
@@ -390,6 +427,9 @@ def rotate_quantize_tiled_packed(x, R_packed, out=None):
 
 
 def rotq_gemm_tiled_packed(x, R_packed, b_codes_t, b_scales_t, N, out_dtype=F32, out=None, workspace=None):
+    y = _calls.linear(0, x, R_packed, b_codes_t, b_scales_t, N, out_dtype, out, workspace)
+    if y is not None:
+        return _done(y, "duqpp_rotq_gemm_tiled_packed")
     _dev(x, torch.bfloat16, "x")
     _dev(b_codes_t, torch.uint8, "b_codes_t")
     _dev(b_scales_t, torch.uint8, "b_scales_t")
@@ -449,6 +489,10 @@ def gemm_tile_for(T, N, K, out_dtype=F32, kernel=KERNEL_AUTO):
 
 
 def mxfp4_gemm_tiled(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, out_dtype=F32, out=None, kernel=KERNEL_AUTO):
+    if kernel == KERNEL_AUTO:
+        y = _calls.product(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, out_dtype, out)
+        if y is not None:
+            return _done(y, "duqpp_mxfp4_gemm_tiled")
     for t, n in ((a_codes_t, "a_codes_t"), (a_scales_t, "a_scales_t"), (b_codes_t, "b_codes_t"), (b_scales_t, "b_scales_t")):
         _dev(t, torch.uint8, n)
     if (a_codes_t.numel(), a_scales_t.numel()) != tiled_bytes(T, K) or (b_codes_t.numel(), b_scales_t.numel()) != tiled_bytes(N, K):
@@ -465,6 +509,9 @@ def mxfp4_gemm_tiled(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, out_
 
 
 def rotq_gemm_tiled(x, R, b_codes_t, b_scales_t, N, out_dtype=F32, out=None, workspace=None):
+    y = _calls.linear(1, x, R, b_codes_t, b_scales_t, N, out_dtype, out, workspace)
+    if y is not None:
+        return _done(y, "duqpp_rotq_gemm_tiled")
     _dev(x, torch.bfloat16, "x")
     _dev(R, torch.float32, "R")
     _dev(b_codes_t, torch.uint8, "b_codes_t")

@@ -2,12 +2,12 @@
 //
 // A call through ctypes costs the host about 5 us beside its launches (2.3 us each): attributes of half a dozen tensors read one
 // by one from Python and sixteen arguments converted.  Here they are read from the tensors themselves.
-// Per call with its buffers given, two launches: 9.1 -> @@ us.
+// Per call with its buffers given, two launches: 9.1 -> 5.5 us.
 //
 // Each function does the plain case and nothing else: tensors of the expected types, layouts and sizes, Python integers, no
-// torch function or dispatch mode in force.  For everything else, and for whatever throws, it answers None ahead of any launch, and
-// the Python code that called it goes on with its own checks, which refuse and accept as they always have.
-// Otherwise the result, or the C call's status as an int where that is not 0.
+// torch function or dispatch mode in force.  For everything else, and for whatever throws, it answers None, and the Python code
+// that called it goes on with its own checks, which refuse and accept as they always have.  Nothing has been launched then, but
+// where the wait in error() throws.  Otherwise the result, or the C call's status as an int where that is not 0.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -31,7 +31,9 @@ decltype(&duqpp_rotate_quantize_tiled_packed) rotate_quantize_tiled_packed;
 decltype(&duqpp_rotate_quantize_tiled) rotate_quantize_tiled;
 decltype(&duqpp_quantize_weights_tiled) quantize_weights_tiled;
 decltype(&duqpp_mxfp4_gemm_tiled) mxfp4_gemm_tiled;
-decltype(&duqpp_group_error) group_error;
+decltype(&duqpp_group_error_ws) group_error_ws;
+decltype(&duqpp_group_error_workspace_bytes) group_error_workspace_bytes;
+PyObject* current_stream;                                // the binding's function that answers it as an integer
 
 // The Python threads run while the object lives.
 struct WithoutGil {
@@ -75,11 +77,14 @@ bool result_type(PyObject* o, long long& code, at::ScalarType& type) {
     type = code == DUQPP_F32 ? at::kFloat : at::kBFloat16;
     return true;
 }
-bool stream_of(PyObject* o, void*& stream) {
-    long long v;
-    if (!integer(o, v)) return false;
-    stream = reinterpret_cast<void*>(static_cast<intptr_t>(v));
-    return true;
+// the current stream of the current device; false: the binding's function threw
+bool stream_of_call(void*& stream) {
+    PyObject* o = PyObject_CallNoArgs(current_stream);
+    stream = o ? PyLong_AsVoidPtr(o) : nullptr;
+    Py_XDECREF(o);
+    if (!PyErr_Occurred()) return true;
+    PyErr_Clear();
+    return false;
 }
 
 bool sizes_ok(int64_t rows, int64_t K) { return rows >= 1 && rows <= kMost && K >= 32 && K <= kMost && K % 32 == 0; }
@@ -111,13 +116,13 @@ PyObject* guarded(F&& f) {
 
 enum Linear { kPacked = 0, kBlocks = 1, kRowMajor = 2 };
 
-// linear(form, x, R, b_codes, b_scales, N, out_dtype, out, workspace, stream) -> y
+// linear(form, x, R, b_codes, b_scales, N, out_dtype, out, workspace) -> y
 PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         long long form, N = 0, code;
         at::ScalarType type;
         void* stream;
-        if (n != 10 || !integer(a[0], form) || !result_type(a[6], code, type) || !stream_of(a[9], stream)) Py_RETURN_NONE;
+        if (n != 9 || !integer(a[0], form) || !result_type(a[6], code, type)) Py_RETURN_NONE;
         const at::Tensor* x = matrix(a[1], at::kBFloat16);
         const at::Tensor* R = form == kPacked ? packed_blocks(a[2]) : blocks(a[2]);
         const at::Tensor *bc = tensor(a[3], at::kByte), *bs = tensor(a[4], at::kByte);
@@ -139,6 +144,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (!t) Py_RETURN_NONE;
             ws = *t;
         }
+        if (!stream_of_call(stream)) Py_RETURN_NONE;
         int status;
         {
             WithoutGil threads;
@@ -169,12 +175,12 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 enum Rows { kRotatePacked = 0, kRotate = 1, kWeights = 2 };
 
-// rows(form, x, R, out, stream) -> (codes_t, scales_t)
+// rows(form, x, R, out) -> (codes_t, scales_t)
 PyObject* rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         long long form;
         void* stream;
-        if (n != 5 || !integer(a[0], form) || !stream_of(a[4], stream)) Py_RETURN_NONE;
+        if (n != 4 || !integer(a[0], form)) Py_RETURN_NONE;
         const at::Tensor* x = matrix(a[1], at::kBFloat16);
         const at::Tensor* R = form == kRotatePacked ? packed_blocks(a[2]) : blocks(a[2]);
         if (!x || !R || !sizes_ok(x->size(0), x->size(1))) Py_RETURN_NONE;
@@ -189,6 +195,7 @@ PyObject* rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
             c = *gc;
             s = *gs;
         }
+        if (!stream_of_call(stream)) Py_RETURN_NONE;
         int status;
         {
             WithoutGil threads;
@@ -213,14 +220,14 @@ PyObject* rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// product(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, out_dtype, out, stream) -> y
+// product(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, out_dtype, out) -> y
 PyObject* product(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         long long T, N, K, code;
         at::ScalarType type;
         void* stream;
-        if (n != 10 || !integer(a[4], T) || !integer(a[5], N) || !integer(a[6], K) || !result_type(a[7], code, type) ||
-            !stream_of(a[9], stream) || !sizes_ok(T, K) || !sizes_ok(N, K))
+        if (n != 9 || !integer(a[4], T) || !integer(a[5], N) || !integer(a[6], K) || !result_type(a[7], code, type) || !sizes_ok(T, K) ||
+            !sizes_ok(N, K))
             Py_RETURN_NONE;
         const at::Tensor* t[4];
         for (int i = 0; i < 4; ++i) {
@@ -228,7 +235,7 @@ PyObject* product(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (!t[i] || t[i]->numel() != tiled_units(i < 2 ? T : N, K) * (i % 2 ? 256 : 4096)) Py_RETURN_NONE;
         }
         at::Tensor y;
-        if (!given_result(a[8], T, N, type, y)) Py_RETURN_NONE;
+        if (!given_result(a[8], T, N, type, y) || !stream_of_call(stream)) Py_RETURN_NONE;
         int status;
         {
             WithoutGil threads;
@@ -246,15 +253,16 @@ PyObject* product(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// error(x, R or None, stream) -> (err, mean): the mean comes by host memory that the kernel writes, one wait for the stream instead
+// error(x, R or None) -> (err, mean): the mean comes by host memory that the kernel writes, one wait for the stream instead
 // of a copy back and its own.
 PyObject* error(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         void* stream;
-        if (n != 3 || !stream_of(a[2], stream)) Py_RETURN_NONE;
+        if (n != 2) Py_RETURN_NONE;
         const at::Tensor *x = matrix(a[0], at::kBFloat16), *R = nullptr;
         if (!x || !sizes_ok(x->size(0), x->size(1))) Py_RETURN_NONE;
         if (a[1] != Py_None && !(R = blocks(a[1]))) Py_RETURN_NONE;
+        if (!stream_of_call(stream)) Py_RETURN_NONE;
         const int64_t T = x->size(0), K = x->size(1);
         at::Tensor err;
         double mean = 0.0;
@@ -263,8 +271,12 @@ PyObject* error(PyObject*, PyObject* const* a, Py_ssize_t n) {
             WithoutGil threads;
             err = device_empty({T, K / 32}, at::kFloat, *x);
             const at::Tensor m = at::empty({1}, at::TensorOptions().dtype(at::kDouble).pinned_memory(true));
-            status = group_error(x->data_ptr(), T, K, x->stride(0), R ? static_cast<const float*>(R->data_ptr()) : nullptr,
-                                 R ? R->size(0) : 1, static_cast<float*>(err.data_ptr()), static_cast<double*>(m.data_ptr()), stream);
+            const size_t bytes = group_error_workspace_bytes(T, K);
+            at::Tensor ws;
+            if (bytes) ws = device_empty({(int64_t)bytes}, at::kByte, *x);
+            status = group_error_ws(x->data_ptr(), T, K, x->stride(0), R ? static_cast<const float*>(R->data_ptr()) : nullptr, R ? R->size(0) : 1,
+                                    static_cast<float*>(err.data_ptr()), static_cast<double*>(m.data_ptr()), bytes ? ws.data_ptr() : nullptr,
+                                    bytes, stream);
             if (status == DUQPP_OK) {
                 const c10::impl::VirtualGuardImpl device(c10::DeviceType::CUDA);
                 device.synchronizeStream(device.getStream(device.getDevice()));
@@ -281,27 +293,31 @@ PyObject* error(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// bind({name: address}): the C ABI's functions, from the library that the binding has loaded.
-PyObject* bind(PyObject*, PyObject* names) {
+// bind({name: address}, current stream): the C ABI's functions, from the library that the binding has loaded.
+PyObject* bind(PyObject*, PyObject* args) {
+    PyObject *names, *stream;
+    if (!PyArg_ParseTuple(args, "O!O", &PyDict_Type, &names, &stream)) return nullptr;
     auto take = [&](const char* name, auto& f) {
-        PyObject* o = PyDict_Check(names) ? PyDict_GetItemString(names, name) : nullptr;
+        PyObject* o = PyDict_GetItemString(names, name);
         void* p = o ? PyLong_AsVoidPtr(o) : nullptr;
         if (!p && !PyErr_Occurred()) PyErr_Format(PyExc_ImportError, "no address of %s", name);
         f = reinterpret_cast<std::remove_reference_t<decltype(f)>>(p);
         return p != nullptr;
     };
-    if (take("duqpp_rotq_gemm_tiled_packed", rotq_gemm_tiled_packed) && take("duqpp_rotq_gemm_tiled", rotq_gemm_tiled) &&
-        take("duqpp_rotq_gemm", rotq_gemm) && take("duqpp_gemm_workspace_bytes", gemm_workspace_bytes) &&
-        take("duqpp_rotate_quantize_tiled_packed", rotate_quantize_tiled_packed) &&
-        take("duqpp_rotate_quantize_tiled", rotate_quantize_tiled) && take("duqpp_quantize_weights_tiled", quantize_weights_tiled) &&
-        take("duqpp_mxfp4_gemm_tiled", mxfp4_gemm_tiled) && take("duqpp_group_error", group_error))
-        Py_RETURN_NONE;
-    return nullptr;
+    if (!take("duqpp_rotq_gemm_tiled_packed", rotq_gemm_tiled_packed) || !take("duqpp_rotq_gemm_tiled", rotq_gemm_tiled) ||
+        !take("duqpp_rotq_gemm", rotq_gemm) || !take("duqpp_gemm_workspace_bytes", gemm_workspace_bytes) ||
+        !take("duqpp_rotate_quantize_tiled_packed", rotate_quantize_tiled_packed) ||
+        !take("duqpp_rotate_quantize_tiled", rotate_quantize_tiled) || !take("duqpp_quantize_weights_tiled", quantize_weights_tiled) ||
+        !take("duqpp_mxfp4_gemm_tiled", mxfp4_gemm_tiled) || !take("duqpp_group_error_ws", group_error_ws) ||
+        !take("duqpp_group_error_workspace_bytes", group_error_workspace_bytes))
+        return nullptr;
+    Py_INCREF(stream);
+    Py_XSETREF(current_stream, stream);
+    Py_RETURN_NONE;
 }
 
-
 PyMethodDef methods[] = {
-    {"bind", bind, METH_O, nullptr},
+    {"bind", bind, METH_VARARGS, nullptr},
     {"linear", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(linear)), METH_FASTCALL, nullptr},
     {"rows", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(rows)), METH_FASTCALL, nullptr},
     {"product", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(product)), METH_FASTCALL, nullptr},
