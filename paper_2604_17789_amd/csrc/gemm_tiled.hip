@@ -121,14 +121,9 @@ constexpr int kGroupM = 8;
 // the weight codes of the steps that pad a run of K steps to a multiple of D: their products are exact zeros
 static __device__ __align__(1024) const uint8_t zero_codes[kTileStepBytes] = {};
 
-template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
-__device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged, LdsBytes __restrict__ lds) {
-    using TL = Tile<MT, NT, D, W>;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r = lane & 31, g = lane >> 5;
-
-    const int tiles_m = (p.T + TL::kBM - 1) / TL::kBM, tiles_n = (p.N + TL::kBN - 1) / TL::kBN;
+// The tile of this workgroup, among tiles_m x tiles_n.
+template <int OCC>
+__device__ __forceinline__ void tile_of_workgroup(int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
     // Workgroups are dealt to the XCDs in turn.  Within each round of as many as the chip holds at once they are renumbered
     // so that an XCD owns a contiguous range, and tile numbers run through groups of kGroupM M-tiles swept along N: the
     // workgroups sharing an L2 cover a compact block of the output, and the blocks of one round lie side by side (with
@@ -145,8 +140,18 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
     const int group_sz = kGroupM * tiles_n;
     const int first_m = (pid / group_sz) * kGroupM;
     const int gm = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
-    const int tile_m = first_m + (pid % group_sz) % gm;
-    const int tile_n = (pid % group_sz) / gm;
+    tile_m = first_m + (pid % group_sz) % gm;
+    tile_n = (pid % group_sz) / gm;
+}
+
+// The tile of MT token row tiles from row_tile and of channels tile_n.
+template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
+__device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile, int tile_n, LdsBytes __restrict__ staged,
+                                          LdsBytes __restrict__ lds) {
+    using TL = Tile<MT, NT, D, W>;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 31, g = lane >> 5;
 
     const int RTa = (p.T + 31) / 32, RTb = (p.N + 31) / 32;
     const int NI = p.GP / 8;                               // K steps
@@ -158,9 +163,9 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
     const uint8_t* b_src[NT];
     const uint8_t* bs_src[NT];
     // tokens: the tile's first row tile, and the others' distance from it (below 4 GiB: best_shape)
-    const uint8_t* a_src = p.a_codes + (int64_t)(tile_m * MT) * tile_bytes;
-    const uint8_t* as_src = p.a_scales + (int64_t)(tile_m * MT) * tile_sbytes;
-    auto valid = [&](int m) { return (uint32_t)(tile_m * MT + m < RTa ? m : RTa - 1 - tile_m * MT); };
+    const uint8_t* a_src = p.a_codes + (int64_t)row_tile * tile_bytes;
+    const uint8_t* as_src = p.a_scales + (int64_t)row_tile * tile_sbytes;
+    auto valid = [&](int m) { return (uint32_t)(row_tile + m < RTa ? m : RTa - 1 - row_tile); };
     uint32_t a_off[MT], as_off[TL::kSOps];
 #pragma unroll
     for (int m = 0; m < MT; ++m) a_off[m] = valid(m) * (uint32_t)tile_bytes;
@@ -319,7 +324,7 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
     workgroup_barrier();                                   // the stages become the scratch of the transpose below
 
     // ---- epilogue: acc[m][n][e] of lane (r, g) is row 32 m + 8 (e / 4) + 4 g + e % 4, column 32 n + r of the wave's tile
-    const int m0 = tile_m * TL::kBM, n0 = tile_n * TL::kBN + wave * 32 * NT;
+    const int m0 = row_tile * 32, n0 = tile_n * TL::kBN + wave * 32 * NT;
     if constexpr (OUT_BF16) {
         if ((reinterpret_cast<uintptr_t>(p.y) & 15) == 0 && (p.ldy % 8) == 0) {
             constexpr int kChunks = 4 * NT, kRows = 64 / kChunks;      // 16-byte pieces of a row; rows per store instruction
@@ -376,20 +381,64 @@ __device__ void gemm_tile(const TiledGemmParams& p, LdsBytes __restrict__ staged
 template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
 __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams p) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    gemm_tile<OUT_BF16, MT, NT, D, W, OCC>(p, (LdsBytes)lds, (LdsBytes)lds);
+    using TL = Tile<MT, NT, D, W>;
+    int tile_m, tile_n;
+    tile_of_workgroup<OCC>((p.T + TL::kBM - 1) / TL::kBM, (p.N + TL::kBN - 1) / TL::kBN, tile_m, tile_n);
+    gemm_tile<OUT_BF16, MT, NT, D, W, OCC>(p, tile_m * MT, tile_n, (LdsBytes)lds, (LdsBytes)lds);
+}
+
+// The same tiles where the token row tiles do not fill them: spread evenly, so that some hold MT of them and the others MT - 1 and
+// do a row tile less, instead of all but the last holding MT and the last doing the work of MT for what is left.  At the power
+// limit the products saved let the others run faster.
+template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
+__global__ __launch_bounds__(64 * W, OCC) void gemm_spread_kernel(TiledGemmParams p) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    using TL = Tile<MT, NT, D, W>;
+    const int row_tiles = (p.T + 31) / 32, tiles_m = (row_tiles + MT - 1) / MT;
+    int tile_m, tile_n;
+    tile_of_workgroup<OCC>(tiles_m, (p.N + TL::kBN - 1) / TL::kBN, tile_m, tile_n);
+    const int each = row_tiles / tiles_m, more = row_tiles % tiles_m;      // `more` tiles hold each + 1
+    const int row_tile = tile_m * each + (tile_m < more ? tile_m : more);
+    if (each + (tile_m < more ? 1 : 0) < MT) gemm_tile<OUT_BF16, MT - 1, NT, D, W, OCC>(p, row_tile, tile_n, (LdsBytes)lds, (LdsBytes)lds);
+    else gemm_tile<OUT_BF16, MT, NT, D, W, OCC>(p, row_tile, tile_n, (LdsBytes)lds, (LdsBytes)lds);
+}
+
+// Whether a call's row tiles are spread: every tile can hold MT or MT - 1 of them, and not all MT.  Long reductions only: with few
+// K steps what both bodies' code costs to fetch outweighs the products (T x N x K in us on one MI355X, weights cached: 1200 x 4096 x 4096
+// 12.7 -> 13.1, in HBM 390 x 14336 x 4096 19.3 -> 20.0).  From K = 8192 on, over 60 ragged products of the tiles below, 1.1 % faster
+// on average (cached 777 x 4096 x 14336 29.7 -> 28.5, 390 x 14336 x 8192 29.6 -> 28.2; in HBM 1800 x 8192 x 8192 61.2 -> 58.9, at worst
+// 390 x 8192 x 8192 23.9 -> 24.2, cached 19.0 -> 18.1).  96 x 128 tiles lost there (in HBM 700 x 4096 x 14336 28.9 -> 30.1, 300 x 8192 x 8192
+// 18.7 -> 19.5) what they gained cached, those of fewer tokens or two waves gain and lose alike.
+constexpr int spread_from(int mt, int nt, int w) { return w == 4 && (mt >= 4 || nt == 2) ? 256 : 0; }   // groups of K; 0: never
+template <int MT, int NT, int W>
+bool spreads(const TiledGemmParams& p) {
+    const int64_t row_tiles = ((int64_t)p.T + 31) / 32, tiles_m = (row_tiles + MT - 1) / MT;
+    return row_tiles % MT != 0 && (MT - 1) * tiles_m <= row_tiles && p.GP >= spread_from(MT, NT, W);
 }
 
 template <int MT, int NT, int D, int W, int OCC>
 hipError_t allow() {
     hipError_t e = allow_dynamic_lds((const void*)gemm_tiled_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
     if (e != hipSuccess) return e;
-    return allow_dynamic_lds((const void*)gemm_tiled_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+    e = allow_dynamic_lds((const void*)gemm_tiled_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+    if constexpr (spread_from(MT, NT, W) > 0) {
+        if (e != hipSuccess) return e;
+        e = allow_dynamic_lds((const void*)gemm_spread_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+        if (e != hipSuccess) return e;
+        e = allow_dynamic_lds((const void*)gemm_spread_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+    }
+    return e;
 }
 template <int MT, int NT, int D, int W, int OCC>
 hipError_t run(const TiledGemmParams& p, hipStream_t stream) {
     using TL = Tile<MT, NT, D, W>;
     const int64_t tiles = (int64_t)((p.T + TL::kBM - 1) / TL::kBM) * ((p.N + TL::kBN - 1) / TL::kBN);
     const dim3 grid((unsigned)tiles), block(64 * W);
+    if constexpr (spread_from(MT, NT, W) > 0) {
+        if (spreads<MT, NT, W>(p))
+            return p.out_bf16 ? launch(gemm_spread_kernel<true, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p)
+                              : launch(gemm_spread_kernel<false, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p);
+    }
     return p.out_bf16 ? launch(gemm_tiled_kernel<true, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p)
                       : launch(gemm_tiled_kernel<false, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p);
 }
