@@ -78,6 +78,7 @@ struct RotqParams {
     int waves;           // wavefronts per workgroup
     int by_columns;      // tiled-output kernel: an XCD owns column chunks (1) or token runs (0)
     int stages;          // tiled-output kernel: depth of a wave's ring of token tiles (2 or 3)
+    int few;             // tiled output: the kernel for few tokens
 };
 hipError_t launch_rotq(const RotqParams& p, hipStream_t stream);
 void plan_rotq(RotqParams& p);    // fills ntiles / tiles_per_wg / ngroups / nchunks / waves / by_columns / stages

@@ -428,13 +428,47 @@ __global__ __launch_bounds__(512) void rotq_wave_and_tile_kernel(RotqParams p, L
     for (int64_t unit = (int64_t)((int)blockIdx.x - rotating) * p.waves + wave; unit < units; unit += stride) tile_unit(w, unit, lane);
 }
 
+// Few tokens: a wave per (block, token tile), which asks for everything it needs at once and holds it in registers.  Such a call
+// is one chain of latencies, and this is what is left of it: no ring of tiles in LDS, one block's operands instead of two, no
+// division ahead of the first load.
+template <bool PACKED>
+__global__ __launch_bounds__(64) void rotq_few_kernel(RotqParams p) {
+    const int lane = threadIdx.x, c = lane & 31, h = lane >> 5;
+    const int jt = blockIdx.x, tile = blockIdx.y;
+    const int j = jt < p.G ? jt : p.G - 1;                   // padding groups: any valid block, output is masked
+    const int row = tile * 32 + c;
+    const uint16_t* x = p.x + (int64_t)(row < p.rows ? row : p.rows - 1) * p.ldx + 32 * j + 8 * h;
+    u32x4 xv[2];
+    xv[0] = *(const u32x4*)x;
+    xv[1] = *(const u32x4*)(x + 16);
+    RotOperand op;
+    if constexpr (PACKED) load_rot_operand_packed((const uint8_t*)p.R + (int64_t)j * p.r_stride, lane, op);
+    else load_rot_operand(p.R + (int64_t)j * p.r_stride, c, h, op);
+    uint2 o;
+    uint32_t byte = quantize_group(rotate_tile(op, xv), o);
+    if (row >= p.rows || jt >= p.G) {                        // padding of the tiled layout: code 0, scale 127
+        o = make_uint2(0, 0);
+        byte = 127;
+    }
+    *(uint2*)(p.codes + (((int64_t)tile * p.GP + jt) * 32 + c) * 16 + 8 * h) = o;
+    if (h == 0) p.scales[((((int64_t)tile * (p.GP / 8) + jt / 8) * 2 + (jt % 8) / 4) * 32 + c) * 4 + jt % 4] = (uint8_t)byte;
+}
+
 constexpr int kRotqStages = 4;             // 3 tiles in flight, one in use
 
 constexpr int kWaveStages = 2;             // per-wave ring of the tiled-output kernel: 2 tiles of 4 KiB in flight, or
 constexpr int kWaveStagesDeep = 3;         // 3 where a workgroup has only four waves to keep the CU's requests going
 
+// Up to how many waves, one per (block, token tile), rotq_few_kernel takes a call: beyond, fetching the blocks again for every
+// token tile costs more than the other kernel's longer chain.  T x K, us launch to launch on one MI355X, the other kernel / this one:
+//   packed blocks  1 x 4096, 128 waves, 2.51 / 1.94; 16 x 4096 2.71 / 1.99; 16 x 14336, 448, 3.19 / 2.68; 128 x 4096, 512, 3.19 / 2.58;
+//                  256 x 4096, 1024, 3.44 / 3.00; 512 x 4096, 2048, 4.00 / 3.87; 256 x 14336, 3584, 5.38 / 5.37; 512 x 8192, 4096, 5.33 / 5.68
+//   fp32 blocks    64 x 4096, 256, 3.52 / 2.30; 512 x 4096, 2048, 4.44 / 3.78; 512 x 8192, 4096, 5.73 / 5.52; 512 x 14336, 7168, 7.84 / 9.68
+constexpr int64_t kFewWavesPacked = 2048, kFewWaves = 4096;
+
 void plan_rotq(RotqParams& p) {
     p.ntiles = (p.rows + 31) / 32;
+    p.few = p.tiled && (int64_t)p.ntiles * p.GP <= (p.r_packed ? kFewWavesPacked : kFewWaves);
     p.stages = kWaveStages;
     bool one_per_cu = true;                                 // one workgroup resident per CU, or 8 / waves of them
     if (p.tiled) {
@@ -519,6 +553,11 @@ hipError_t launch_rotq(const RotqParams& p, hipStream_t stream) {
     hipError_t e = setup_rotq();
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)((int64_t)p.nchunks * p.ngroups));
+    if (p.tiled && p.few) {
+        const dim3 waves((unsigned)p.GP, (unsigned)p.ntiles);
+        return p.r_packed ? launch(rotq_few_kernel<true>, waves, dim3(64), 0, stream, p)
+                          : launch(rotq_few_kernel<false>, waves, dim3(64), 0, stream, p);
+    }
     if (p.tiled) {
         if (p.waves < 1 || p.waves > 8) return hipErrorInvalidValue;
         if (p.stages != kWaveStages && p.stages != kWaveStagesDeep) return hipErrorInvalidValue;

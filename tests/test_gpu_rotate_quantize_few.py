@@ -1,0 +1,37 @@
+"""GPU: the tiled rotate + quantise of few tokens (a wave per block and token tile) gives the bytes of the row-major kernel in their
+tiled places: ragged token tiles, groups that the layout pads, strided rows, a shared block, and either side of the numbers of
+waves up to which it is taken."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from helpers import to_dev, untile_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,K,shared", [(1, 32, 0), (1, 4096, 0), (31, 96, 1), (32, 288, 0), (33, 14336, 0), (65, 8224, 1),
+                                        (512, 4096, 0), (513, 4096, 0),          # 2048 and 2176 waves: packed blocks
+                                        (1024, 4096, 1), (1025, 4096, 0)])       # 4096 and 4224: fp32 blocks
+def test_same_bytes_as_the_row_major_kernel(T, K, shared):
+    import torch
+
+    import paper_2604_17789_amd as duqpp
+    name = f"gpu-few-{T}-{K}"
+    g = torch.Generator(device="cuda").manual_seed(T * 31 + K)
+    x = torch.randn((T, K + 16), generator=g, device="cuda").to(torch.bfloat16)[:, :K]
+    x[T // 2, :32] = 0                                       # a group without a magnitude
+    x[:, K - 1] *= 900
+    R = to_dev(wl.make_rotation_blocks(name, 1 if shared else K // 32), torch)
+    print(f"[rotate few] T={T} K={K} shared={shared}", flush=True)
+    codes, scales = duqpp.rotate_quantize(x, R)
+    n = duqpp.tiled_bytes(T, K)
+    for blocks, call in ((R, duqpp.rotate_quantize_tiled), (duqpp.pack_rotation(R), duqpp.rotate_quantize_tiled_packed)):
+        out = [torch.full((m + 256,), 0xA5, dtype=torch.uint8, device="cuda") for m in n]
+        ct, st = call(x, blocks, out=tuple(o[:m] for o, m in zip(out, n)))
+        torch.cuda.synchronize()
+        c, s, pad_c, pad_s = untile_np(ct.cpu().numpy(), st.cpu().numpy(), T, K)
+        np.testing.assert_array_equal(c, codes.cpu().numpy())
+        np.testing.assert_array_equal(s, scales.cpu().numpy())
+        assert np.all(pad_c == 0) and np.all(pad_s == 127)   # every byte of the padding, too
+        assert all(torch.all(o[m:] == 0xA5) for o, m in zip(out, n))
