@@ -432,9 +432,8 @@ __global__ __launch_bounds__(512) void rotq_wave_and_tile_kernel(RotqParams p, L
 // is one chain of latencies, and this is what is left of it: no ring of tiles in LDS, one block's operands instead of two, no
 // division ahead of the first load.
 template <bool PACKED>
-__global__ __launch_bounds__(64) void rotq_few_kernel(RotqParams p) {
-    const int lane = threadIdx.x, c = lane & 31, h = lane >> 5;
-    const int jt = blockIdx.x, tile = blockIdx.y;
+__device__ __forceinline__ void rotq_few(const RotqParams& p, int jt, int tile, int lane) {
+    const int c = lane & 31, h = lane >> 5;
     const int j = jt < p.G ? jt : p.G - 1;                   // padding groups: any valid block, output is masked
     const int row = tile * 32 + c;
     const uint16_t* x = p.x + (int64_t)(row < p.rows ? row : p.rows - 1) * p.ldx + 32 * j + 8 * h;
@@ -453,6 +452,20 @@ __global__ __launch_bounds__(64) void rotq_few_kernel(RotqParams p) {
     *(uint2*)(p.codes + (((int64_t)tile * p.GP + jt) * 32 + c) * 16 + 8 * h) = o;
     if (h == 0) p.scales[((((int64_t)tile * (p.GP / 8) + jt / 8) * 2 + (jt % 8) / 4) * 32 + c) * 4 + jt % 4] = (uint8_t)byte;
 }
+template <bool PACKED>
+__global__ __launch_bounds__(64) void rotq_few_kernel(RotqParams p) {
+    rotq_few<PACKED>(p, blockIdx.x, blockIdx.y, threadIdx.x);
+}
+// With the re-tiling of an operand in the workgroups behind it, as below.
+__global__ __launch_bounds__(64) void rotq_few_and_tile_kernel(RotqParams p, LayoutParams w) {
+    const int rotating = p.GP * p.ntiles, tiling = (int)gridDim.x - rotating;
+    if ((int)blockIdx.x < rotating) {
+        rotq_few<false>(p, (int)blockIdx.x % p.GP, (int)blockIdx.x / p.GP, threadIdx.x);
+        return;
+    }
+    const int64_t units = tile_units(w);
+    for (int64_t unit = (int)blockIdx.x - rotating; unit < units; unit += tiling) tile_unit(w, unit, threadIdx.x);
+}
 
 constexpr int kRotqStages = 4;             // 3 tiles in flight, one in use
 
@@ -464,7 +477,7 @@ constexpr int kWaveStagesDeep = 3;         // 3 where a workgroup has only four 
 //   packed blocks  1 x 4096, 128 waves, 2.51 / 1.94; 16 x 4096 2.71 / 1.99; 16 x 14336, 448, 3.19 / 2.68; 128 x 4096, 512, 3.19 / 2.58;
 //                  256 x 4096, 1024, 3.44 / 3.00; 512 x 4096, 2048, 4.00 / 3.87; 256 x 14336, 3584, 5.38 / 5.37; 512 x 8192, 4096, 5.33 / 5.68
 //   fp32 blocks    64 x 4096, 256, 3.52 / 2.30; 512 x 4096, 2048, 4.44 / 3.78; 512 x 8192, 4096, 5.73 / 5.52; 512 x 14336, 7168, 7.84 / 9.68
-constexpr int64_t kFewWavesPacked = 2048, kFewWaves = 4096;
+constexpr int64_t kFewWavesPacked = 2048, kFewWaves = 4096;   // packed, or beside a re-tiling; fp32 blocks
 
 void plan_rotq(RotqParams& p) {
     p.ntiles = (p.rows + 31) / 32;
@@ -579,6 +592,14 @@ hipError_t launch_rotq_and_tile(const RotqParams& p, const LayoutParams& w, hipS
     hipError_t e = setup_rotq();
     if (e != hipSuccess) return e;
     if (!p.tiled || p.r_packed || p.waves < 1 || p.waves > 8) return hipErrorInvalidValue;
+    // Beside an operand being re-tiled the line lies at fewer waves than alone (whole row-major calls, T x K x N, us on one MI355X:
+    // 16 x 4096 x 1024 7.53 -> 6.56, 64 x 4096 x 4096 11.81 -> 11.05, 512 x 4096 x 4096, 2048 waves, 19.5 -> 18.9; 512 x 8192 x 8192, 4096
+    // waves, 39.5 against 40.7)
+    if ((int64_t)p.GP * p.ntiles <= kFewWavesPacked) {
+        const int64_t units = tile_units(w);
+        const dim3 waves((unsigned)((int64_t)p.GP * p.ntiles + (units < kTileWorkgroups ? units : kTileWorkgroups)));
+        return launch(rotq_few_and_tile_kernel, waves, dim3(64), 0, stream, p, w);
+    }
     if (p.stages != kWaveStages && p.stages != kWaveStagesDeep) return hipErrorInvalidValue;
     const int64_t need = (tile_units(w) + p.waves - 1) / p.waves;
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.ngroups + (need < kTileWorkgroups ? need : kTileWorkgroups)));

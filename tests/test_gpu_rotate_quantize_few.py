@@ -35,3 +35,22 @@ def test_same_bytes_as_the_row_major_kernel(T, K, shared):
         np.testing.assert_array_equal(s, scales.cpu().numpy())
         assert np.all(pad_c == 0) and np.all(pad_s == 127)   # every byte of the padding, too
         assert all(torch.all(o[m:] == 0xA5) for o, m in zip(out, n))
+
+
+@pytest.mark.parametrize("T,K,N", [(1, 32, 8), (33, 288, 70), (64, 1024, 9000), (512, 4096, 100), (513, 4096, 33)])
+def test_beside_the_retiling_of_the_weights(T, K, N):
+    """The row-major call, which rotates in the launch that re-tiles its weights: bit for bit the tiled call, either side of 2048
+    waves, with a row tile of weights that is mostly padding and with more of them than tokens."""
+    import torch
+
+    import paper_2604_17789_amd as duqpp
+    g = torch.Generator(device="cuda").manual_seed(T + K + N)
+    x = torch.randn((T, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+    R = to_dev(wl.make_rotation_blocks(f"gpu-few-row-{K}", K // 32), torch)
+    print(f"[rotate few] row-major T={T} K={K} N={N}", flush=True)
+    ws = torch.full((duqpp.gemm_workspace_bytes(T, N, K, True),), 0xA5, dtype=torch.uint8, device="cuda")
+    y = duqpp.rotq_gemm(x, R, *duqpp.quantize_weights(w, R), workspace=ws)
+    want = duqpp.rotq_gemm_tiled(x, R, *duqpp.quantize_weights_tiled(w, R), N)
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
