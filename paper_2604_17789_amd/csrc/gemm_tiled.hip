@@ -137,11 +137,26 @@ __device__ __forceinline__ void tile_of_workgroup(int tiles_m, int tiles_n, int&
         const int xcd = id % kNumXCD, slot = id / kNumXCD;
         pid = first + xcd * per + (xcd < rem ? xcd : rem) + slot;
     }
-    const int group_sz = kGroupM * tiles_n;
-    const int first_m = (pid / group_sz) * kGroupM;
+    // No division by a runtime number where there is one group, and within a group a multiplication: floor(rem / gm) is the upper
+    // word of rem * ceil(2^32 / gm) while rem * (gm - 1) < 2^32.  Three divisions ahead of the first request took 0.1 us of every launch
+    // (512 x 4096 x 4096 6.88 -> 6.82, 130 x 14336 x 4096 9.11 -> 9.00; 80 products 0.5 % faster on average).
+    int first_m = 0, rem = pid;
+    if (tiles_m > kGroupM) {
+        const int group_sz = kGroupM * tiles_n, group = pid / group_sz;
+        first_m = group * kGroupM;
+        rem = pid - group * group_sz;
+    }
+    static_assert(kGroupM == 8, "reciprocals of 2 to 8");
     const int gm = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
-    tile_m = first_m + (pid % group_sz) % gm;
-    tile_n = (pid % group_sz) / gm;
+    const uint32_t reciprocal = gm == 8   ? 0x20000000u
+                                : gm == 7 ? 0x24924925u
+                                : gm == 6 ? 0x2AAAAAABu
+                                : gm == 5 ? 0x33333334u
+                                : gm == 4 ? 0x40000000u
+                                : gm == 3 ? 0x55555556u
+                                          : 0x80000000u;
+    tile_n = gm == 1 ? rem : (int)__umulhi((uint32_t)rem, reciprocal);
+    tile_m = first_m + rem - tile_n * gm;
 }
 
 // The tile of MT token row tiles from row_tile and of channels tile_n.
@@ -397,9 +412,9 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_spread_kernel(TiledGemmParam
     const int row_tiles = (p.T + 31) / 32, tiles_m = (row_tiles + MT - 1) / MT;
     int tile_m, tile_n;
     tile_of_workgroup<OCC>(tiles_m, (p.N + TL::kBN - 1) / TL::kBN, tile_m, tile_n);
-    const int each = row_tiles / tiles_m, more = row_tiles % tiles_m;      // `more` tiles hold each + 1
-    const int row_tile = tile_m * each + (tile_m < more ? tile_m : more);
-    if (each + (tile_m < more ? 1 : 0) < MT) gemm_tile<OUT_BF16, MT - 1, NT, D, W, OCC>(p, row_tile, tile_n, (LdsBytes)lds, (LdsBytes)lds);
+    const int more = row_tiles - (MT - 1) * tiles_m;         // so many tiles hold MT, the others MT - 1
+    const int row_tile = tile_m * (MT - 1) + (tile_m < more ? tile_m : more);
+    if (tile_m >= more) gemm_tile<OUT_BF16, MT - 1, NT, D, W, OCC>(p, row_tile, tile_n, (LdsBytes)lds, (LdsBytes)lds);
     else gemm_tile<OUT_BF16, MT, NT, D, W, OCC>(p, row_tile, tile_n, (LdsBytes)lds, (LdsBytes)lds);
 }
 
