@@ -97,16 +97,12 @@ __global__ __launch_bounds__(64 * (GROUPS == 2 ? kErrWaves : 1)) void group_erro
     __shared__ double sums[kWaves][2];
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int chunk = blockIdx.x % e.chunks, run = blockIdx.x / e.chunks;
+    const int chunk = blockIdx.x, run = blockIdx.y;          // (a division ahead of the first load: 2048 x 4096 7.60 -> 7.48 us without)
     const int j0 = (chunk * kWaves + wave) * GROUPS;
     double sum = 0.0, count = 0.0;
     if (j0 < p.G) {
         const int j1 = GROUPS == 2 && j0 + 1 < p.G ? j0 + 1 : j0;   // an odd last group: computed twice, stored once
         RotOperand op0, op1;
-        if constexpr (ROTATED) {
-            load_rot_operand(p.R + (int64_t)j0 * p.r_stride, c, h, op0);
-            if constexpr (GROUPS == 2) load_rot_operand(p.R + (int64_t)j1 * p.r_stride, c, h, op1);
-        }
         const int step1 = 32 * (j1 - j0);
         auto load = [&](u32x4 (&v)[4], int tile) {
             const int token = tile * 32 + c;
@@ -147,6 +143,10 @@ __global__ __launch_bounds__(64 * (GROUPS == 2 ? kErrWaves : 1)) void group_erro
             }
         };
         u32x4 x[4], nx[4];
+        if constexpr (ROTATED) {
+            load_rot_operand(p.R + (int64_t)j0 * p.r_stride, c, h, op0);
+            if constexpr (GROUPS == 2) load_rot_operand(p.R + (int64_t)j1 * p.r_stride, c, h, op1);
+        }
         if (run < e.ntiles) load(x, run);
         for (int tile = run; tile < e.ntiles; tile += e.runs) {
             if constexpr (GROUPS == 2) load(nx, tile + e.runs < e.ntiles ? tile + e.runs : tile);
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64 * (GROUPS == 2 ? kErrWaves : 1)) void group_erro
         double t = 0.0;
         for (int k = 0; k < kWaves; ++k) t += sums[k][threadIdx.x];
         const unsigned long long bits = (unsigned long long)__double_as_longlong(t);
-        uint32_t* out = (uint32_t*)p.partials + (int64_t)blockIdx.x * 4 + 2 * threadIdx.x; // may be err, aligned to a float only
+        uint32_t* out = (uint32_t*)p.partials + ((int64_t)run * e.chunks + chunk) * 4 + 2 * threadIdx.x; // may be err, aligned to a float only
         out[0] = (uint32_t)bits;
         out[1] = (uint32_t)(bits >> 32);
     }
@@ -258,12 +258,12 @@ hipError_t launch_group_error(const GroupErrorParams& call, hipStream_t stream) 
         return e;
     };
     auto run = [&](const ErrPlan& e) {
-        const dim3 grid((unsigned)(e.chunks * e.runs)), block(64 * kErrWaves);
+        const dim3 grid((unsigned)e.chunks, (unsigned)e.runs), block(64 * kErrWaves);
         return p.R ? launch(group_error_kernel<true, 2>, grid, block, 0, stream, p, e)
                    : launch(group_error_kernel<false, 2>, grid, block, 0, stream, p, e);
     };
     auto run_one_group = [&](const ErrPlan& e) {
-        const dim3 grid((unsigned)(e.chunks * e.runs)), block(64);
+        const dim3 grid((unsigned)e.chunks, (unsigned)e.runs), block(64);
         return p.R ? launch(group_error_kernel<true, 1>, grid, block, 0, stream, p, e)
                    : launch(group_error_kernel<false, 1>, grid, block, 0, stream, p, e);
     };
