@@ -21,7 +21,7 @@
 //                   and two per CU (T <= 16352).  Should they not come to run together, because other work holds the CUs for
 //                   longer than they wait (20 ms and more), they give up, and a launch of one workgroup does the whole
 //                   search: nothing ever waits without a limit.
-//   launch per step (construct_step_kernel) for more rows, and for one or two: the state in memory, the maxima by atomics, all
+//   launch per step (construct_step_kernel) for more rows, and for a single one: the state in memory, the maxima by atomics, all
 //                   CUs waiting for each other at the launch.
 // What a step's result does not depend on is done ahead of the steps, for all of them at once: the matrices H . diag(1, Q'_t).
 // What a step of the search kernel takes (2048 rows, 130 workgroups, 2.0 us = 4900 cycles): 560 the workgroup's own maximum, 2100

@@ -35,9 +35,9 @@ def check(o, ref):
     np.testing.assert_array_equal(o["R"].cpu().numpy(), ref["R"])
 
 
-# 3: the fewest rows whose workspace holds what two workgroups publish; 992 / 993: 64 / 65 workgroups of 16 rows, i.e. one or more
+# 1, 2, 3: the workspace holds what none, two and three workgroups publish; 992 / 993: 64 / 65 workgroups of 16 rows, i.e. one or more
 # looks of 64 lanes; 4064 / 4065: 256 workgroups, the most of 16 rows; 8160 / 8161: 256 / 257 workgroups of 32; 16352: the most
-CASES = [(3, 64, 4, (ONE_16, ONE_32)), (17, 32, 3, (ONE_16, ONE_32)), (33, 96, 5, (ONE_16, ONE_32)), (992, 64, 3, (ONE_16, ONE_32)),
+CASES = [(1, 64, 3, ()), (2, 64, 3, (ONE_32,)), (3, 64, 4, (ONE_16, ONE_32)), (17, 32, 3, (ONE_16, ONE_32)), (33, 96, 5, (ONE_16, ONE_32)), (992, 64, 3, (ONE_16, ONE_32)),
          (993, 32, 3, (ONE_16,)), (4064, 32, 2, (ONE_16, ONE_32)), (4065, 32, 2, (ONE_32,)), (8160, 32, 2, (ONE_32,)),
          (8161, 32, 3, (ONE_32,)), (16352, 32, 2, (ONE_32,)), (16353, 32, 2, ()), (777, 64, 0, (ONE_16, ONE_32)), (300, 512, 40, (ONE_16, ONE_32))]
 
@@ -58,7 +58,7 @@ def test_every_form_matches_the_oracle(T, K, steps, one):
         assert call(torch, duqpp, how, x, qd, o) == 0
         torch.cuda.synchronize()
         check(o, ref)
-    for how in {ONE_16, ONE_32} - set(one) if T > 4064 else ():
+    for how in {ONE_16, ONE_32} - set(one) if T > 4064 or T < 3 else ():
         assert call(torch, duqpp, how, x, qd, buffers(torch, T, steps)) == ERR_SHAPE
 
 
