@@ -159,6 +159,17 @@ def _dev(t, dtype, what):
     return t
 
 
+def _dense(t, what):
+    """The library reads and writes codes, scales and scratch as one run of bytes."""
+    if not t.is_contiguous():
+        raise ValueError(f"{what} must be contiguous")
+    return t
+
+
+def _bytes(t, what):
+    return _dense(_dev(t, torch.uint8, what), what)
+
+
 def _n_rblocks(R):
     if R.dim() != 3 or tuple(R.shape[1:]) != (32, 32) or not R.is_contiguous():
         raise ValueError("R must be a contiguous [n_rblocks, 32, 32] fp32 tensor")
@@ -229,9 +240,7 @@ def mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, out_dtype=F32, out=None, wo
     """Row-major operands -> Y [T, N].  workspace: None = allocate the scratch of the fast path, False = none
     (direct kernel), or a uint8 tensor of at least gemm_workspace_bytes(T, N, K)."""
     for t, n in ((a_codes, "a_codes"), (a_scales, "a_scales"), (b_codes, "b_codes"), (b_scales, "b_scales")):
-        _dev(t, torch.uint8, n)
-        if not t.is_contiguous():
-            raise ValueError(f"{n} must be contiguous")
+        _bytes(t, n)
     T, K = a_codes.shape[0], a_codes.shape[1] * 2
     N = b_codes.shape[0]
     if b_codes.shape[1] * 2 != K or tuple(a_scales.shape) != (T, K // 32) or tuple(b_scales.shape) != (N, K // 32):
@@ -242,7 +251,7 @@ def mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, out_dtype=F32, out=None, wo
     elif workspace is False:                                # no scratch: the direct row-major kernel
         workspace, nbytes = None, 0
     else:
-        nbytes = workspace.numel()
+        nbytes = _dense(workspace, "workspace").numel()
     st = lib.duqpp_mxfp4_gemm(a_codes.data_ptr(), a_scales.data_ptr(), b_codes.data_ptr(), b_scales.data_ptr(),
                               T, N, K, y.data_ptr(), out_dtype, y.stride(0),
                               workspace.data_ptr() if workspace is not None else None, nbytes, _stream())
@@ -256,8 +265,8 @@ def rotq_gemm(x, R, b_codes, b_scales, out_dtype=F32, out=None, workspace=None):
         return _done(y, "duqpp_rotq_gemm")
     _dev(x, torch.bfloat16, "x")
     _dev(R, torch.float32, "R")
-    _dev(b_codes, torch.uint8, "b_codes")
-    _dev(b_scales, torch.uint8, "b_scales")
+    _bytes(b_codes, "b_codes")
+    _bytes(b_scales, "b_scales")
     if x.dim() != 2 or x.stride(1) != 1:
         raise ValueError("x must be [T, K] with unit stride along K")
     T, K = x.shape
@@ -268,7 +277,7 @@ def rotq_gemm(x, R, b_codes, b_scales, out_dtype=F32, out=None, workspace=None):
     if workspace is None:
         workspace, nbytes = _workspace(gemm_workspace_bytes(T, N, K, True), x.device)
     else:
-        nbytes = workspace.numel()
+        nbytes = _dense(workspace, "workspace").numel()
     st = lib.duqpp_rotq_gemm(x.data_ptr(), x.stride(0), R.data_ptr(), _n_rblocks(R), b_codes.data_ptr(),
                              b_scales.data_ptr(), T, N, K, y.data_ptr(), out_dtype, y.stride(0),
                              workspace.data_ptr() if workspace is not None else None, nbytes, _stream())
@@ -279,6 +288,8 @@ def rotq_gemm(x, R, b_codes, b_scales, out_dtype=F32, out=None, workspace=None):
 def quantize_f32_dbg(y):
     """Test only: the device quantiser stage on fp32 [rows, K]."""
     _dev(y, torch.float32, "y")
+    if y.dim() != 2 or y.stride(1) != 1:
+        raise ValueError("y must be [rows, K] with unit stride along K")
     rows, K = y.shape
     codes = torch.empty((rows, K // 2), dtype=torch.uint8, device=y.device)
     scales = torch.empty((rows, K // 32), dtype=torch.uint8, device=y.device)
@@ -348,9 +359,11 @@ def _tiled_buffers(rows, K, device, out=None):
 
 
 def tile_operand(codes, scales):
-    _dev(codes, torch.uint8, "codes")
-    _dev(scales, torch.uint8, "scales")
+    _bytes(codes, "codes")
+    _bytes(scales, "scales")
     rows, K = codes.shape[0], codes.shape[1] * 2
+    if scales.numel() < rows * (K // 32):
+        raise ValueError("operand shapes disagree")
     ct, st_ = _tiled_buffers(rows, K, codes.device)
     _check(lib.duqpp_tile_operand(codes.data_ptr(), scales.data_ptr(), rows, K, ct.data_ptr(), st_.data_ptr(), _stream()),
            "duqpp_tile_operand")
@@ -358,8 +371,11 @@ def tile_operand(codes, scales):
 
 
 def untile_operand(codes_t, scales_t, rows, K):
-    _dev(codes_t, torch.uint8, "codes_t")
-    _dev(scales_t, torch.uint8, "scales_t")
+    _bytes(codes_t, "codes_t")
+    _bytes(scales_t, "scales_t")
+    cb, sb = tiled_bytes(rows, K)
+    if codes_t.numel() < cb or scales_t.numel() < sb:
+        raise ValueError("operand sizes disagree with rows, K")
     codes = torch.empty((rows, K // 2), dtype=torch.uint8, device=codes_t.device)
     scales = torch.empty((rows, K // 32), dtype=torch.uint8, device=codes_t.device)
     _check(lib.duqpp_untile_operand(codes_t.data_ptr(), scales_t.data_ptr(), rows, K, codes.data_ptr(), scales.data_ptr(),
@@ -431,8 +447,8 @@ def rotq_gemm_tiled_packed(x, R_packed, b_codes_t, b_scales_t, N, out_dtype=F32,
     if y is not None:
         return _done(y, "duqpp_rotq_gemm_tiled_packed")
     _dev(x, torch.bfloat16, "x")
-    _dev(b_codes_t, torch.uint8, "b_codes_t")
-    _dev(b_scales_t, torch.uint8, "b_scales_t")
+    _bytes(b_codes_t, "b_codes_t")
+    _bytes(b_scales_t, "b_scales_t")
     if x.dim() != 2 or x.stride(1) != 1:
         raise ValueError("x must be [T, K] with unit stride along K")
     T, K = x.shape
@@ -443,7 +459,7 @@ def rotq_gemm_tiled_packed(x, R_packed, b_codes_t, b_scales_t, N, out_dtype=F32,
         workspace = _tiled_workspace(T, K, x.device)
     _check(lib.duqpp_rotq_gemm_tiled_packed(x.data_ptr(), x.stride(0), R_packed.data_ptr(), _n_packed(R_packed),
                                             b_codes_t.data_ptr(), b_scales_t.data_ptr(), T, N, K, y.data_ptr(), out_dtype,
-                                            y.stride(0), workspace.data_ptr(), workspace.numel(), _stream()),
+                                            y.stride(0), workspace.data_ptr(), _dense(workspace, "workspace").numel(), _stream()),
            "duqpp_rotq_gemm_tiled_packed")
     return y
 
@@ -451,8 +467,8 @@ def rotq_gemm_tiled_packed(x, R_packed, b_codes_t, b_scales_t, N, out_dtype=F32,
 def rotq_gemm_fused_decode(x, R_packed, b_codes_t, b_scales_t, N, out_dtype=F32, out=None, return_operand=False):
     """The one-kernel form (T <= 32).  return_operand: also the activation codes / scales (tiled) it was formed from."""
     _dev(x, torch.bfloat16, "x")
-    _dev(b_codes_t, torch.uint8, "b_codes_t")
-    _dev(b_scales_t, torch.uint8, "b_scales_t")
+    _bytes(b_codes_t, "b_codes_t")
+    _bytes(b_scales_t, "b_scales_t")
     if x.dim() != 2 or x.stride(1) != 1:
         raise ValueError("x must be [T, K] with unit stride along K")
     T, K = x.shape
@@ -494,7 +510,7 @@ def mxfp4_gemm_tiled(a_codes_t, a_scales_t, b_codes_t, b_scales_t, T, N, K, out_
         if y is not None:
             return _done(y, "duqpp_mxfp4_gemm_tiled")
     for t, n in ((a_codes_t, "a_codes_t"), (a_scales_t, "a_scales_t"), (b_codes_t, "b_codes_t"), (b_scales_t, "b_scales_t")):
-        _dev(t, torch.uint8, n)
+        _bytes(t, n)
     if (a_codes_t.numel(), a_scales_t.numel()) != tiled_bytes(T, K) or (b_codes_t.numel(), b_scales_t.numel()) != tiled_bytes(N, K):
         raise ValueError("operand sizes disagree with T, N, K")
     y = _out(T, N, out_dtype, a_codes_t.device, out)
@@ -514,8 +530,8 @@ def rotq_gemm_tiled(x, R, b_codes_t, b_scales_t, N, out_dtype=F32, out=None, wor
         return _done(y, "duqpp_rotq_gemm_tiled")
     _dev(x, torch.bfloat16, "x")
     _dev(R, torch.float32, "R")
-    _dev(b_codes_t, torch.uint8, "b_codes_t")
-    _dev(b_scales_t, torch.uint8, "b_scales_t")
+    _bytes(b_codes_t, "b_codes_t")
+    _bytes(b_scales_t, "b_scales_t")
     if x.dim() != 2 or x.stride(1) != 1:
         raise ValueError("x must be [T, K] with unit stride along K")
     T, K = x.shape
@@ -526,7 +542,7 @@ def rotq_gemm_tiled(x, R, b_codes_t, b_scales_t, N, out_dtype=F32, out=None, wor
         workspace = _tiled_workspace(T, K, x.device)
     _check(lib.duqpp_rotq_gemm_tiled(x.data_ptr(), x.stride(0), R.data_ptr(), _n_rblocks(R), b_codes_t.data_ptr(),
                                      b_scales_t.data_ptr(), T, N, K, y.data_ptr(), out_dtype, y.stride(0),
-                                     workspace.data_ptr(), workspace.numel(), _stream()), "duqpp_rotq_gemm_tiled")
+                                     workspace.data_ptr(), _dense(workspace, "workspace").numel(), _stream()), "duqpp_rotq_gemm_tiled")
     return y
 
 
@@ -539,8 +555,8 @@ def rotq_gemm_tiled_noalloc(x, R, b_codes_t, b_scales_t, N, out_dtype=F32, out=N
     from allocating the result."""
     _dev(x, torch.bfloat16, "x")
     _dev(R, torch.float32, "R")
-    _dev(b_codes_t, torch.uint8, "b_codes_t")
-    _dev(b_scales_t, torch.uint8, "b_scales_t")
+    _bytes(b_codes_t, "b_codes_t")
+    _bytes(b_scales_t, "b_scales_t")
     if x.dim() != 2 or x.stride(1) != 1:
         raise ValueError("x must be [T, K] with unit stride along K")
     T, K = x.shape
@@ -575,12 +591,14 @@ def construct_rotation(x, q_steps, return_peaks=False, workspace=None):
     _dev(q_steps, torch.float64, "q_steps")
     if q_steps.dim() != 3 or tuple(q_steps.shape[1:]) != (31, 31) or not q_steps.is_contiguous():
         raise ValueError("q_steps must be contiguous [steps, 31, 31]")
+    if x.dim() != 2 or x.stride(1) != 1:
+        raise ValueError("x must be [T, K] with unit stride along K")
     T, K = x.shape
     steps = q_steps.shape[0]
     nbytes = lib.duqpp_construct_rotation_workspace_bytes(T, steps)
     if nbytes == 0:
         raise ValueError("bad T or number of steps")
-    ws = workspace if workspace is not None else _workspace(nbytes, x.device)[0]
+    ws = _dense(workspace, "workspace") if workspace is not None else _workspace(nbytes, x.device)[0]
     R = torch.empty((1, 32, 32), dtype=torch.float32, device=x.device)
     info = torch.empty(2, dtype=torch.int32, device=x.device)
     peaks = torch.empty(steps + 1, dtype=torch.float64, device=x.device) if return_peaks else None

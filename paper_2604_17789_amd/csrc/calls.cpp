@@ -52,6 +52,11 @@ const at::Tensor* tensor(PyObject* o, at::ScalarType type) {
     const at::Tensor& t = THPVariable_Unpack(o);
     return t.defined() && t.is_cuda() && t.scalar_type() == type && t.layout() == at::kStrided ? &t : nullptr;
 }
+// bytes that the library reads or writes as one run
+const at::Tensor* bytes(PyObject* o) {
+    const at::Tensor* t = tensor(o, at::kByte);
+    return t && t->is_contiguous() ? t : nullptr;
+}
 const at::Tensor* matrix(PyObject* o, at::ScalarType type) {
     const at::Tensor* t = tensor(o, type);
     return t && t->dim() == 2 && t->stride(1) == 1 ? t : nullptr;
@@ -62,8 +67,8 @@ const at::Tensor* blocks(PyObject* o) {
 }
 constexpr int64_t kPackedBlock = 6144;
 const at::Tensor* packed_blocks(PyObject* o) {
-    const at::Tensor* t = tensor(o, at::kByte);
-    return t && t->dim() == 1 && t->is_contiguous() && t->numel() > 0 && t->numel() % kPackedBlock == 0 ? t : nullptr;
+    const at::Tensor* t = bytes(o);
+    return t && t->dim() == 1 && t->numel() > 0 && t->numel() % kPackedBlock == 0 ? t : nullptr;
 }
 bool integer(PyObject* o, long long& v) {
     if (!PyLong_CheckExact(o)) return false;
@@ -125,7 +130,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (n != 9 || !integer(a[0], form) || !result_type(a[6], code, type)) Py_RETURN_NONE;
         const at::Tensor* x = matrix(a[1], at::kBFloat16);
         const at::Tensor* R = form == kPacked ? packed_blocks(a[2]) : blocks(a[2]);
-        const at::Tensor *bc = tensor(a[3], at::kByte), *bs = tensor(a[4], at::kByte);
+        const at::Tensor *bc = bytes(a[3]), *bs = bytes(a[4]);
         if (!x || !R || !bc || !bs) Py_RETURN_NONE;
         const int64_t T = x->size(0), K = x->size(1);
         if (form == kRowMajor) {
@@ -140,7 +145,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor y, ws;
         if (!given_result(a[7], T, N, type, y)) Py_RETURN_NONE;
         if (a[8] != Py_None) {
-            const at::Tensor* t = tensor(a[8], at::kByte);
+            const at::Tensor* t = bytes(a[8]);
             if (!t) Py_RETURN_NONE;
             ws = *t;
         }
@@ -189,9 +194,8 @@ PyObject* rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor c, s;
         if (a[3] != Py_None) {
             if (!PyTuple_CheckExact(a[3]) || PyTuple_GET_SIZE(a[3]) != 2) Py_RETURN_NONE;
-            const at::Tensor *gc = tensor(PyTuple_GET_ITEM(a[3], 0), at::kByte), *gs = tensor(PyTuple_GET_ITEM(a[3], 1), at::kByte);
-            if (!gc || !gs || gc->numel() != units * 4096 || gs->numel() != units * 256 || !gc->is_contiguous() || !gs->is_contiguous())
-                Py_RETURN_NONE;
+            const at::Tensor *gc = bytes(PyTuple_GET_ITEM(a[3], 0)), *gs = bytes(PyTuple_GET_ITEM(a[3], 1));
+            if (!gc || !gs || gc->numel() != units * 4096 || gs->numel() != units * 256) Py_RETURN_NONE;
             c = *gc;
             s = *gs;
         }
@@ -231,7 +235,7 @@ PyObject* product(PyObject*, PyObject* const* a, Py_ssize_t n) {
             Py_RETURN_NONE;
         const at::Tensor* t[4];
         for (int i = 0; i < 4; ++i) {
-            t[i] = tensor(a[i], at::kByte);
+            t[i] = bytes(a[i]);
             if (!t[i] || t[i]->numel() != tiled_units(i < 2 ? T : N, K) * (i % 2 ? 256 : 4096)) Py_RETURN_NONE;
         }
         at::Tensor y;
@@ -271,12 +275,12 @@ PyObject* error(PyObject*, PyObject* const* a, Py_ssize_t n) {
             WithoutGil threads;
             err = device_empty({T, K / 32}, at::kFloat, *x);
             const at::Tensor m = at::empty({1}, at::TensorOptions().dtype(at::kDouble).pinned_memory(true));
-            const size_t bytes = group_error_workspace_bytes(T, K);
+            const size_t scratch = group_error_workspace_bytes(T, K);
             at::Tensor ws;
-            if (bytes) ws = device_empty({(int64_t)bytes}, at::kByte, *x);
+            if (scratch) ws = device_empty({(int64_t)scratch}, at::kByte, *x);
             status = group_error_ws(x->data_ptr(), T, K, x->stride(0), R ? static_cast<const float*>(R->data_ptr()) : nullptr, R ? R->size(0) : 1,
-                                    static_cast<float*>(err.data_ptr()), static_cast<double*>(m.data_ptr()), bytes ? ws.data_ptr() : nullptr,
-                                    bytes, stream);
+                                    static_cast<float*>(err.data_ptr()), static_cast<double*>(m.data_ptr()), scratch ? ws.data_ptr() : nullptr,
+                                    scratch, stream);
             if (status == DUQPP_OK) {
                 const c10::impl::VirtualGuardImpl device(c10::DeviceType::CUDA);
                 device.synchronizeStream(device.getStream(device.getDevice()));
