@@ -430,7 +430,7 @@ __global__ __launch_bounds__(512) void rotq_wave_and_tile_kernel(RotqParams p, L
 
 // Few tokens: a wave per (block, token tile), which asks for everything it needs at once and holds it in registers.  Such a call
 // is one chain of latencies, and this is what is left of it: no ring of tiles in LDS, one block's operands instead of two, no
-// division ahead of the first load.
+// division ahead of the first load (but beside a re-tiling, where the launch has one dimension).
 template <bool PACKED>
 __device__ __forceinline__ void rotq_few(const RotqParams& p, int jt, int tile, int lane) {
     const int c = lane & 31, h = lane >> 5;
@@ -456,15 +456,17 @@ template <bool PACKED>
 __global__ __launch_bounds__(64) void rotq_few_kernel(RotqParams p) {
     rotq_few<PACKED>(p, blockIdx.x, blockIdx.y, threadIdx.x);
 }
-// With the re-tiling of an operand in the workgroups behind it, as below.
-__global__ __launch_bounds__(64) void rotq_few_and_tile_kernel(RotqParams p, LayoutParams w) {
-    const int rotating = p.GP * p.ntiles, tiling = (int)gridDim.x - rotating;
-    if ((int)blockIdx.x < rotating) {
-        rotq_few<false>(p, (int)blockIdx.x % p.GP, (int)blockIdx.x / p.GP, threadIdx.x);
+// With the re-tiling of an operand in the waves behind it (WAVES per workgroup, each on its own).
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void rotq_few_and_tile_kernel(RotqParams p, LayoutParams w) {
+    const int rotating = p.GP * p.ntiles, tiling = (int)gridDim.x * WAVES - rotating;
+    const int id = (int)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (id < rotating) {
+        rotq_few<false>(p, id % p.GP, id / p.GP, lane);
         return;
     }
     const int64_t units = tile_units(w);
-    for (int64_t unit = (int)blockIdx.x - rotating; unit < units; unit += tiling) tile_unit(w, unit, threadIdx.x);
+    for (int64_t unit = id - rotating; unit < units; unit += tiling) tile_unit(w, unit, lane);
 }
 
 constexpr int kRotqStages = 4;             // 3 tiles in flight, one in use
@@ -586,7 +588,7 @@ hipError_t launch_rotq(const RotqParams& p, hipStream_t stream) {
     return launch(rotq_kernel<kRotqWaves, kRotqStages, false>, grid, dim3(kRotqWaves * 64), TL::kLdsBytes, stream, p);
 }
 
-constexpr int64_t kTileWorkgroups = 8192;  // beyond these a wave takes several units
+constexpr int64_t kTileWorkgroups = 8192;  // that re-tile; beyond these a wave takes several units
 
 hipError_t launch_rotq_and_tile(const RotqParams& p, const LayoutParams& w, hipStream_t stream) {
     hipError_t e = setup_rotq();
@@ -595,13 +597,20 @@ hipError_t launch_rotq_and_tile(const RotqParams& p, const LayoutParams& w, hipS
     // Beside an operand being re-tiled the line lies at fewer waves than alone (whole row-major calls, T x K x N, us on one MI355X:
     // 16 x 4096 x 1024 7.53 -> 6.56, 64 x 4096 x 4096 11.81 -> 11.05, 512 x 4096 x 4096, 2048 waves, 19.5 -> 18.9; 512 x 8192 x 8192, 4096
     // waves, 39.5 against 40.7)
-    if ((int64_t)p.GP * p.ntiles <= kFewWavesPacked) {
-        const int64_t units = tile_units(w);
-        const dim3 waves((unsigned)((int64_t)p.GP * p.ntiles + (units < kTileWorkgroups ? units : kTileWorkgroups)));
-        return launch(rotq_few_and_tile_kernel, waves, dim3(64), 0, stream, p, w);
+    // Up to kTileWorkgroups units a workgroup is one wave, beyond it is four: so many workgroups of one take longer to start, and
+    // 8192 of them would share the units (us, 8192 of one wave / workgroups of four / the ring kernel: 16 x 4096 x 28672
+    // 40.1 / 36.3 / 39.4, 512 x 4096 x 28672 63.2 / 59.6 / 60.5, 256 x 8192 x 28672 87.5 / 79.7 / 81.2, 64 x 28672 x 8192 83.6 / 78.6 / 79.3;
+    // with a wave per unit in all of them: 512 x 4096 x 14336 34.4 / 33.5 / 33.8, 64 x 4096 x 4096 10.9 / 11.5 / 11.7).
+    const int64_t units = tile_units(w), rotating = (int64_t)p.GP * p.ntiles;
+    if (rotating <= kFewWavesPacked) {
+        if (units <= kTileWorkgroups)
+            return launch(rotq_few_and_tile_kernel<1>, dim3((unsigned)(rotating + units)), dim3(64), 0, stream, p, w);
+        const int64_t tiling = (units + 3) / 4;              // rotating is a multiple of 8
+        return launch(rotq_few_and_tile_kernel<4>, dim3((unsigned)(rotating / 4 + (tiling < kTileWorkgroups ? tiling : kTileWorkgroups))),
+                      dim3(256), 0, stream, p, w);
     }
     if (p.stages != kWaveStages && p.stages != kWaveStagesDeep) return hipErrorInvalidValue;
-    const int64_t need = (tile_units(w) + p.waves - 1) / p.waves;
+    const int64_t need = (units + p.waves - 1) / p.waves;
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.ngroups + (need < kTileWorkgroups ? need : kTileWorkgroups)));
     const dim3 block(p.waves * 64);
     const size_t lds = (size_t)p.waves * p.stages * kWaveTileBytes;

@@ -37,10 +37,12 @@ def test_same_bytes_as_the_row_major_kernel(T, K, shared):
         assert all(torch.all(o[m:] == 0xA5) for o, m in zip(out, n))
 
 
-@pytest.mark.parametrize("T,K,N", [(1, 32, 8), (33, 288, 70), (64, 1024, 9000), (512, 4096, 100), (513, 4096, 33)])
+@pytest.mark.parametrize("T,K,N", [(1, 32, 8), (33, 288, 70), (64, 1024, 9000), (512, 4096, 100), (513, 4096, 33),
+                                   (1, 32, 32 * 8192), (40, 32, 32 * 8192 + 1), (3, 64, 32 * 32768 + 70)])
 def test_beside_the_retiling_of_the_weights(T, K, N):
     """The row-major call, which rotates in the launch that re-tiles its weights: bit for bit the tiled call, either side of 2048
-    waves, with a row tile of weights that is mostly padding and with more of them than tokens."""
+    waves, with a row tile of weights that is mostly padding and with more of them than tokens, and either side of 8192 units of weights
+    (workgroups of one wave and of four) and of 32768 (a wave per unit and several units)."""
     import torch
 
     import paper_2604_17789_amd as duqpp
@@ -51,6 +53,11 @@ def test_beside_the_retiling_of_the_weights(T, K, N):
     print(f"[rotate few] row-major T={T} K={K} N={N}", flush=True)
     ws = torch.full((duqpp.gemm_workspace_bytes(T, N, K, True),), 0xA5, dtype=torch.uint8, device="cuda")
     y = duqpp.rotq_gemm(x, R, *duqpp.quantize_weights(w, R), workspace=ws)
-    want = duqpp.rotq_gemm_tiled(x, R, *duqpp.quantize_weights_tiled(w, R), N)
+    wt = duqpp.quantize_weights_tiled(w, R)
+    want = duqpp.rotq_gemm_tiled(x, R, *wt, N)
     torch.cuda.synchronize()
     assert torch.equal(y, want)
+    at = 0                                                   # every byte of both operands, the padding's too
+    for part in duqpp.rotate_quantize_tiled(x, R) + wt:
+        assert torch.equal(ws[at:at + part.numel()], part)
+        at += part.numel()
