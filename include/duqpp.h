@@ -353,7 +353,7 @@ enum {
     DUQPP_CONSTRUCT_ONE_16 = 1,      /* one launch for all steps, workgroups of 16 or 32 rows */
     DUQPP_CONSTRUCT_ONE_32 = 2,
     DUQPP_CONSTRUCT_STEPS = 3,       /* a launch per step */
-    DUQPP_CONSTRUCT_IMPATIENT = 8    /* + one of ONE_*: its workgroups give up where they would have to wait for each other */
+    DUQPP_CONSTRUCT_IMPATIENT = 8    /* + one of ONE_*: its workgroups give up at the first exchange, whatever they find there */
 };
 int duqpp_construct_rotation_on(int how, const void* x_bf16, int64_t T, int64_t K, int64_t ldx,
                                 const double* q_steps, int max_steps,

@@ -396,7 +396,7 @@ struct SearchPlan {
     int partials;                        // keys of the block search
     int tiles;                           // workgroups that hold rows of the state; those behind them hold the product R^(t)
     int participants;                    // all of them
-    uint32_t patience;                   // looks at what the others have published before one gives up
+    uint32_t patience;                   // looks at what the others have published before one gives up; 0: gives up in any case
 };
 
 // What the workgroups tell each other after step t: two words each, the largest magnitude among their rows and the smallest
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(64 * kStepWaves, 2 * PER_CU) void construct_search_
             __builtin_amdgcn_s_sleep(LOOKS > 1 ? 12 : 10);
             unsigned long long best = 0ull;
             int channel = 32;
-            bool here = true;
+            bool here = s.patience > 0;
             for (int first = 0; first < s.participants; first += 64 * LOOKS) {
                 unsigned long long v[LOOKS], d[LOOKS], all;  // bit 63 of all: not everyone's words are there
                 uint32_t looks = 0;

@@ -28,6 +28,12 @@ def buffers(torch, T, steps):
                 ws=torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda"))
 
 
+def given_up(torch, o):
+    """What the search kernel's workgroups leave in the second word of the workspace: 1 where one of them gave up, and then the launch
+    behind them did the work; 0 where it found nothing to do."""
+    return int(o["ws"][8:16].view(torch.int64).item())
+
+
 def check(o, ref):
     """fp64 in the oracle's operation order: block, steps kept, peaks and matrix bit for bit."""
     assert o["info"].tolist() == [ref["block"], ref["steps"]]
@@ -58,6 +64,8 @@ def test_every_form_matches_the_oracle(T, K, steps, one):
         assert call(torch, duqpp, how, x, qd, o) == 0
         torch.cuda.synchronize()
         check(o, ref)
+        if how in (ONE_16, ONE_32) or how & IMPATIENT:
+            assert given_up(torch, o) == (1 if how & IMPATIENT else 0)
     for how in {ONE_16, ONE_32} - set(one) if T > 4064 or T < 3 else ():
         assert call(torch, duqpp, how, x, qd, buffers(torch, T, steps)) == ERR_SHAPE
 
