@@ -19,8 +19,12 @@
 //                   registers, publishes the largest magnitude among them after every step, waits for everybody's, and goes on.
 //                   For as many rows as workgroups that run at once hold: 16 rows each and one workgroup per CU, or 32 rows
 //                   and two per CU (T <= 16352).  Should they not come to run together, because other work holds the CUs for
-//                   longer than they wait (20 ms and more), they give up, and a launch of one workgroup does the whole
-//                   search: nothing ever waits without a limit.
+//                   longer than they wait (1 to 2 ms), they give up, and up to 64 workgroups with the state in memory do the
+//                   search (construct_again_kernel); should not even these come to run together (within 20 ms and more), one
+//                   does it, which waits for nobody: nothing ever waits without a limit.  128 steps, with what is waited ahead
+//                   of it left out: 64 workgroups 2.7 ms at T = 512, 2.8 at 4064, 3.1 at 16000; one 5.2, 24, 82 ms.  Two calls of
+//                   16000 rows on two streams at once: 4.0 to 5.1 ms each (with one workgroup behind 20 ms of waiting 140 to 160;
+//                   a launch per step, alone, 1.5); three of 8160: one 0.4, the others 4.2.
 //   launch per step (construct_step_kernel) for more rows, and for a single one: the state in memory, the maxima by atomics, all
 //                   CUs waiting for each other at the launch.
 // What a step's result does not depend on is done ahead of the steps, for all of them at once: the matrices H . diag(1, Q'_t).
@@ -46,18 +50,22 @@ constexpr int kStepWaves = 8;                            // waves of that workgr
 constexpr int kMaxPartials = 1024;                       // workgroups of the block search (their keys fill one slot of 8 KiB)
 constexpr int kExchangeCopies = 8;                       // copies of what the workgroups of the search kernel publish
 constexpr int kExchangeWords = 2;                        // 64-bit words between one workgroup's and the next one's (two are used)
-constexpr uint32_t kPatience = 40000;                    // looks for what the others publish, half a microsecond or more each
+constexpr uint32_t kPatience = 2000;                     // looks for what the others publish, half a microsecond or more each: about what
+                                                         // doing it in a few workgroups takes
+constexpr int kFewWorkgroups = 64;                       // these (a wave looks at all of them at once)
+constexpr uint32_t kPatienceAgain = 40000;               // and what doing it in one takes
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ double hadamard_entry(int i, int k) { return (__popc(i & k) & 1) ? -kHadamardEntry : kHadamardEntry; }
 
-// workspace: [header 64 B: u64 block key, u64 search given up][colmax (S + 1) x 32 u64][slots (S + 1) x 1024 f64][Z T x 32 f64]
+// workspace: [header 64 B: u64 block key, u64 search given up, u64 given up again][colmax (S + 1) x 32 u64][slots (S + 1) x 1024 f64][Z T x 32 f64]
 // Slot 0 holds the block search's partial keys, then the maxima below; slot t >= 1 holds M_t = H . diag(1, Q'_t), then R^(t).
-// The search kernel keeps the state on the chip; the place of Z holds what its workgroups publish.
+// The search kernel keeps the state on the chip; the place of Z holds what its workgroups publish, that of colmax what those of the
+// kernel behind it do.
 struct Workspace {
     unsigned long long* key;
-    unsigned long long* given_up;
+    unsigned long long* given_up;        // two words
     unsigned long long* colmax;
     double* slots;
     double* z;
@@ -397,6 +405,8 @@ struct SearchPlan {
     int tiles;                           // workgroups that hold rows of the state; those behind them hold the product R^(t)
     int participants;                    // all of them
     uint32_t patience;                   // looks at what the others have published before one gives up; 0: gives up in any case
+    int few;                             // workgroups of the search behind it
+    int asked;                           // for those: the word of given_up that asks for them; the next one is theirs
 };
 
 // What the workgroups tell each other after step t: two words each, the largest magnitude among their rows and the smallest
@@ -418,7 +428,8 @@ __global__ __launch_bounds__(256) void construct_prepare_kernel(ConstructParams 
     Workspace w = carve(p.workspace, p.steps);
     const int words = 2 * kExchangeCopies * kExchangeWords * s.participants;
     const int at = blockIdx.x * 256 + threadIdx.x;
-    if (at == 0) *w.given_up = 0ull;
+    if (at < 2) w.given_up[at] = 0ull;
+    if (at < 4 * s.few) w.colmax[at] = ~0ull;
     for (int i = at; i < words; i += gridDim.x * 256) reinterpret_cast<unsigned long long*>(w.z)[i] = ~0ull;
     if ((int)blockIdx.x < s.partials) block_key(p, w, s.partials, reinterpret_cast<unsigned long long*>(q));
     else step_matrix(p, w, (int)blockIdx.x - s.partials + 1, q);
@@ -526,9 +537,9 @@ __global__ __launch_bounds__(64 * kStepWaves, 2 * PER_CU) void construct_search_
             unsigned long long best = 0ull;
             int channel = 32;
             bool here = s.patience > 0;
+            uint32_t looks = 0;
             for (int first = 0; first < s.participants; first += 64 * LOOKS) {
                 unsigned long long v[LOOKS], d[LOOKS], all;  // bit 63 of all: not everyone's words are there
-                uint32_t looks = 0;
                 do {
                     all = 0ull;
 #pragma unroll
@@ -620,67 +631,114 @@ __global__ __launch_bounds__(64 * kStepWaves, 2 * PER_CU) void construct_search_
     }
 }
 
-// The whole search in one workgroup, which waits for nobody, if one of the search kernel's gave up waiting: where not all of them
-// came to run together.  Slow, and the same result.
-__global__ __launch_bounds__(64 * kStepWaves) void construct_given_up_kernel(ConstructParams p, SearchPlan s) {
-    __shared__ double m[1024], product[1024], best[1024];
-    __shared__ unsigned long long colmax[32], red[kStepWaves];
+// The search again where the search kernel's workgroups did not come to run together: in a few workgroups, which find room where
+// hundreds do not, and if not even these did, in one, which waits for nobody.  The rows are in memory, a lane has a row at a time,
+// 64 rows going to the first wave of each workgroup in turn, then to the second.  The same result; bound by the reads of M_t from LDS.
+__global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(ConstructParams p, SearchPlan s) {
+    __shared__ __attribute__((aligned(16))) double m[1024];
+    __shared__ double product[1024], best[1024];
+    __shared__ unsigned long long red[kStepWaves], peak_of_all;
+    __shared__ int red_channel[kStepWaves], channel_of_all;
     const Workspace w = carve(p.workspace, p.steps);
-    if (*w.given_up == 0ull) return;
-    const int lane = threadIdx.x & 63;
-    if (threadIdx.x < 32) colmax[threadIdx.x] = 0ull;
+    if (w.given_up[s.asked] == 0ull) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t first = ((int64_t)wave * gridDim.x + blockIdx.x) * 64, stride = (int64_t)64 * kStepWaves * gridDim.x;
     const int64_t block = block_of(chosen_key(w, s.partials, red));
-    const int64_t rows = p.T + 32;                           // the state's, then the product's
-    auto column_top = [&](int c, double v, bool there) {
-        const unsigned long long top = wave_max(there ? abs_bits(v) : 0ull);
-        if (lane == 0 && top) atomicMax(&colmax[c], top);
+    const bool writes = blockIdx.x == 0;                     // this workgroup has the product R^(t) and the results
+    unsigned long long top = 0ull;                           // the largest magnitude this lane has seen, and its smallest channel
+    int channel = 32;
+    auto seen = [&](double v, int c) {
+        const unsigned long long a = abs_bits(v);
+        const bool more = (a > top) | ((a == top) & (c < channel));
+        top = more ? a : top;
+        channel = more ? c : channel;
     };
     for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) product[e] = best[e] = e / 32 == e % 32 ? 1.0 : 0.0;
-    for (int64_t r0 = 0; r0 < p.T; r0 += 64 * kStepWaves) {
-        const int64_t r = r0 + threadIdx.x;
+    for (int64_t r = first + lane; r < p.T; r += stride)
         for (int c = 0; c < 32; ++c) {
-            double v = 0.0;
-            if (r < p.T) {
-                v = (double)__uint_as_float((uint32_t)p.x[r * p.ldx + 32 * block + c] << 16);
-                w.z[r * 32 + c] = v;
-            }
-            column_top(c, v, r < p.T);
+            const double v = (double)__uint_as_float((uint32_t)p.x[r * p.ldx + 32 * block + c] << 16);
+            w.z[r * 32 + c] = v;
+            seen(v, c);
         }
-    }
     unsigned long long lowest = ~0ull;
     int steps_kept = 0;
     for (int t = 0;; ++t) {
+        // the workgroup's largest magnitude and the smallest channel it stands in
+        auto smallest_channel = [&](unsigned long long v, int c, unsigned long long of) { return 32 - (int)wave_max(v == of ? 32 - c : 0); };
+        const unsigned long long wave_top = wave_max(top);
+        const int wave_channel = smallest_channel(top, channel, wave_top);
+        __syncthreads();                                     // the last reader of red was the exchange before, or chosen_key
+        if (lane == 0) { red[wave] = wave_top; red_channel[wave] = wave_channel; }
         __syncthreads();
-        const unsigned long long cm = colmax[lane & 31], peak = wave_max(cm);
-        const int d = exchanged_channel(cm);
-        auto sigma = [&](int r) { return r == 0 ? d : (r == d ? 0 : r); };
-        if (p.peaks && threadIdx.x == 0) p.peaks[t] = __longlong_as_double((long long)peak);
+        if (wave == 0) {
+            unsigned long long v = lane < kStepWaves ? red[lane] : 0ull;
+            int c = lane < kStepWaves ? red_channel[lane] : 32;
+            unsigned long long peak = wave_max(v);
+            int d = smallest_channel(v, c, peak);
+            if (gridDim.x > 1) {                             // among all, by the rules of the search kernel's exchange
+                const unsigned long long there = (unsigned long long)((t >> 1) & 1) << 63;
+                unsigned long long* const set = w.colmax + (t & 1) * 2 * gridDim.x;
+                if (lane == 0) {
+                    __hip_atomic_store(set + 2 * blockIdx.x, peak | there, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(set + 2 * blockIdx.x + 1, (unsigned long long)d | there, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                const unsigned long long* const theirs = set + 2 * (lane < (int)gridDim.x ? lane : (int)gridDim.x - 1);
+                unsigned long long dd;
+                uint32_t looks = 0;
+                bool missing;
+                do {
+                    __builtin_amdgcn_s_sleep(8);
+                    v = __hip_atomic_load(theirs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ^ there;
+                    dd = __hip_atomic_load(theirs + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ^ there;
+                    missing = __any(((v | dd) >> 63) != 0);
+                } while (missing && ++looks < s.patience);
+                peak = wave_max(v);
+                d = missing || s.patience == 0 ? -1 : smallest_channel(v, (int)dd, peak);
+            }
+            if (lane == 0) { peak_of_all = peak; channel_of_all = d; }
+        }
+        __syncthreads();
+        const unsigned long long peak = peak_of_all;
+        const int d = channel_of_all;
+        if (d < 0) {                                         // the same for every thread of the workgroup
+            if (threadIdx.x == 0) __hip_atomic_store(w.given_up + s.asked + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        if (writes && p.peaks && threadIdx.x == 0) p.peaks[t] = __longlong_as_double((long long)peak);
         if (peak < lowest) {
             lowest = peak;
             steps_kept = t;
             for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) best[e] = product[e];
         }
         if (t == p.steps) break;
+        auto sigma = [&](int r) { return r == 0 ? d : (r == d ? 0 : r); };
         for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) m[sigma(e >> 5) * 32 + (e & 31)] = w.slots[(size_t)(t + 1) * 1024 + e];
-        __syncthreads();                                     // the maxima have been read, too
-        if (threadIdx.x < 32) colmax[threadIdx.x] = 0ull;
         __syncthreads();
-        for (int64_t r0 = 0; r0 < rows; r0 += 64 * kStepWaves) {
-            const int64_t r = r0 + threadIdx.x;
-            double* z = r < p.T ? w.z + r * 32 : product + (r < rows ? r - p.T : 0) * 32;
+        top = 0ull;
+        channel = 32;
+        auto multiply = [&](double* z, bool counts) {
             double x[32];
 #pragma unroll
             for (int k = 0; k < 32; ++k) x[k] = z[k];
-            for (int c = 0; c < 32; ++c) {
-                double v = 0.0;
+#pragma unroll 1
+            for (int c = 0; c < 32; c += 2) {
+                double v0 = 0.0, v1 = 0.0;
 #pragma unroll
-                for (int k = 0; k < 32; ++k) v = v + x[k] * m[k * 32 + c];
-                if (r < rows) z[sigma(c)] = v;
-                column_top(sigma(c), v, r < p.T);
+                for (int k = 0; k < 32; ++k) {
+                    const f64x2 e = *reinterpret_cast<const f64x2*>(m + k * 32 + c);
+                    v0 = v0 + x[k] * e[0];
+                    v1 = v1 + x[k] * e[1];
+                }
+                z[sigma(c)] = v0;
+                z[sigma(c + 1)] = v1;
+                if (counts) { seen(v0, sigma(c)); seen(v1, sigma(c + 1)); }
             }
-        }
+        };
+        for (int64_t r = first + lane; r < p.T; r += stride) multiply(w.z + r * 32, true);
+        if (writes && wave == kStepWaves - 1 && lane < 32) multiply(product + lane * 32, false);
     }
     __syncthreads();
+    if (!writes) return;
     for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) p.R_out[e] = (float)best[e];
     if (threadIdx.x == 0) {
         p.info[0] = (int)block;
@@ -701,11 +759,15 @@ namespace {
 bool plan_search(const ConstructParams& p, int form, int partials, SearchPlan& s) {
     const int64_t rows = 16 << (form - DUQPP_CONSTRUCT_ONE_16), tiles = (p.T + rows - 1) / rows, all = tiles + (rows < 32 ? 2 : 1);
     if (all > (form == DUQPP_CONSTRUCT_ONE_16 ? kNumCU : 2 * kNumCU) || (int64_t)exchange_bytes((int)all) > p.T * 256) return false;
-    s = SearchPlan{partials, (int)tiles, (int)all, kPatience};
+    // of the search behind it: not more than have rows, nor than the place of their words holds
+    const int64_t waves = (p.T + 63) / 64, room = 8 * ((int64_t)p.steps + 1);
+    int64_t few = waves < kFewWorkgroups ? waves : kFewWorkgroups;
+    few = few < room ? few : room;
+    s = SearchPlan{partials, (int)tiles, (int)all, kPatience, (int)few, 0};
     return true;
 }
 
-hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form, hipStream_t stream) {
+hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form, uint32_t patience_again, hipStream_t stream) {
     hipError_t e = launch(construct_prepare_kernel, dim3((unsigned)(s.partials + p.steps)), dim3(256), 0, stream, p, s);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)s.participants), block(64 * kStepWaves);
@@ -716,7 +778,14 @@ hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form
         e = s.participants <= kNumCU ? launch(construct_search_kernel<2, 4, 1>, grid, block, 0, stream, p, s)
                                      : launch(construct_search_kernel<2, 2, 2>, grid, block, 0, stream, p, s);
     if (e != hipSuccess) return e;
-    return launch(construct_given_up_kernel, dim3(1), block, 0, stream, p, s);
+    SearchPlan again = s;
+    again.patience = patience_again;
+    if (s.few > 1) {
+        e = launch(construct_again_kernel, dim3((unsigned)s.few), block, 0, stream, p, again);
+        if (e != hipSuccess) return e;
+        again.asked = 1;
+    }
+    return launch(construct_again_kernel, dim3(1), block, 0, stream, p, again);
 }
 
 hipError_t launch_steps(const ConstructParams& p, int partials, hipStream_t stream) {
@@ -744,7 +813,7 @@ bool construct_runs(const ConstructParams& p, int form) {
 hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStream_t stream) {
     const int64_t chunks = (int64_t)p.T * (p.K / 8);
     const int partials = (int)((chunks + 1023) / 1024 < kMaxPartials ? (chunks + 1023) / 1024 : kMaxPartials);
-    int form = how & ~DUQPP_CONSTRUCT_IMPATIENT;
+    int form = how & ~DUQPP_CONSTRUCT_ALONE;
     SearchPlan s{};
     if (form == DUQPP_CONSTRUCT_AUTO) {
         form = DUQPP_CONSTRUCT_ONE_16;
@@ -753,7 +822,7 @@ hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStrea
     if (form == DUQPP_CONSTRUCT_STEPS) return launch_steps(p, partials, stream);
     if (!plan_search(p, form, partials, s)) return hipErrorInvalidValue;
     if (how & DUQPP_CONSTRUCT_IMPATIENT) s.patience = 0;
-    return launch_search(p, s, form, stream);
+    return launch_search(p, s, form, (how & DUQPP_CONSTRUCT_ALONE) == DUQPP_CONSTRUCT_ALONE ? 0 : kPatienceAgain, stream);
 }
 
 }  // namespace duqpp
