@@ -364,6 +364,9 @@ int duqpp_construct_rotation_on(int how, const void* x_bf16, int64_t T, int64_t 
                                 const double* q_steps, int max_steps,
                                 float* R_out, int32_t* info, double* peaks,
                                 void* workspace, size_t workspace_bytes, void* stream);
+/* Host, pure: the form that runs such a call where the stream has `cus` CUs (the device's, or those of its mask), DUQPP_ERR_SHAPE where
+ * the one asked for cannot. */
+int duqpp_construct_form_for(int how, int64_t T, int max_steps, int cus);
 
 /* Host, pure: scratch bytes duqpp_mxfp4_gemm (fused = 0) can use or duqpp_rotq_gemm (fused = 1) needs:
  * room for both operands in the tiled layout.  0 for invalid shapes. */

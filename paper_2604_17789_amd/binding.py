@@ -71,6 +71,8 @@ def _load():
     L.duqpp_construct_rotation.restype = ci
     L.duqpp_construct_rotation_on.argtypes = [ci, vp, i64, i64, i64, vp, ci, fp, vp, vp, vp, sz, vp]
     L.duqpp_construct_rotation_on.restype = ci
+    L.duqpp_construct_form_for.argtypes = [ci, i64, ci, ci]
+    L.duqpp_construct_form_for.restype = ci
     L.duqpp_init.argtypes = []
     L.duqpp_init.restype = ci
     L.duqpp_packed_rotation_bytes.argtypes = [i64]

@@ -528,8 +528,16 @@ int duqpp_construct_rotation_on(int how, const void* x_bf16, int64_t T, int64_t 
     st = check_device();
     if (st != DUQPP_OK) return st;
     ConstructParams p{static_cast<const uint16_t*>(x_bf16), ldx, T, K, q_steps, max_steps, R_out, info, peaks, workspace};
-    if (!construct_runs(p, form)) return DUQPP_ERR_SHAPE;
-    return launch_construct_rotation(p, how, static_cast<hipStream_t>(stream)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
+    bool runs = false;
+    if (launch_construct_rotation(p, how, static_cast<hipStream_t>(stream), runs) != hipSuccess) return DUQPP_ERR_HIP;
+    return runs ? DUQPP_OK : DUQPP_ERR_SHAPE;
+}
+
+int duqpp_construct_form_for(int how, int64_t T, int max_steps, int cus) {
+    if (T < 1 || T > (int64_t)1 << 30 || max_steps < 0 || max_steps > 4096 || cus < 0) return DUQPP_ERR_SHAPE;
+    if (how < DUQPP_CONSTRUCT_AUTO || how > DUQPP_CONSTRUCT_STEPS) return DUQPP_ERR_SHAPE;
+    const int form = construct_form(T, max_steps, how, cus);
+    return form < 0 ? DUQPP_ERR_SHAPE : form;
 }
 
 const char* duqpp_status_string(int status) {

@@ -18,7 +18,7 @@
 //   search kernel   (construct_search_kernel) one launch for all steps: a workgroup keeps its 16 or 32 rows of the state in LDS and
 //                   registers, publishes the largest magnitude among them after every step, waits for everybody's, and goes on.
 //                   For as many rows as workgroups that run at once hold: 16 rows each and one workgroup per CU, or 32 rows
-//                   and two per CU (T <= 16352).  Should they not come to run together, because other work holds the CUs for
+//                   and two per CU (T <= 16352 on 256 CUs).  Should they not come to run together, because other work holds the CUs for
 //                   longer than they wait (1 to 2 ms), they give up, and up to 64 workgroups with the state in memory do the
 //                   search (construct_again_kernel); should not even these come to run together (within 20 ms and more), one
 //                   does it, which waits for nobody: nothing ever waits without a limit.  128 steps, with what is waited ahead
@@ -405,6 +405,7 @@ struct SearchPlan {
     int tiles;                           // workgroups that hold rows of the state; those behind them hold the product R^(t)
     int participants;                    // all of them
     uint32_t patience;                   // looks at what the others have published before one gives up; 0: gives up in any case
+    int cus;                             // CUs they have
     int few;                             // workgroups of the search behind it
     int asked;                           // for those: the word of given_up that asks for them; the next one is theirs
 };
@@ -754,16 +755,28 @@ size_t construct_workspace_bytes(int64_t T, int steps) {
 
 namespace {
 
+// CUs that a kernel on the stream can be given: the device's (fewer than a whole chip's where it is partitioned), or those of the
+// stream's mask.
+int cus_of(hipStream_t stream) {
+    int dev = 0, n = 0;
+    uint32_t mask[32] = {};
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    if (hipExtStreamGetCUMask(stream, 32, mask) != hipSuccess) return n;
+    int masked = 0;
+    for (uint32_t word : mask) masked += __builtin_popcount(word);
+    return masked > 0 && masked < n ? masked : n;
+}
+
 // One launch for all steps (form: DUQPP_CONSTRUCT_ONE_*); false: the workspace has no room for what they publish, or there
-// would be more workgroups than run at once.
-bool plan_search(const ConstructParams& p, int form, int partials, SearchPlan& s) {
-    const int64_t rows = 16 << (form - DUQPP_CONSTRUCT_ONE_16), tiles = (p.T + rows - 1) / rows, all = tiles + (rows < 32 ? 2 : 1);
-    if (all > (form == DUQPP_CONSTRUCT_ONE_16 ? kNumCU : 2 * kNumCU) || (int64_t)exchange_bytes((int)all) > p.T * 256) return false;
+// would be more workgroups than run at once on so many CUs.
+bool plan_search(int64_t T, int steps, int form, int cus, SearchPlan& s) {
+    const int64_t rows = 16 << (form - DUQPP_CONSTRUCT_ONE_16), tiles = (T + rows - 1) / rows, all = tiles + (rows < 32 ? 2 : 1);
+    if (all > (form == DUQPP_CONSTRUCT_ONE_16 ? cus : 2 * (int64_t)cus) || (int64_t)exchange_bytes((int)all) > T * 256) return false;
     // of the search behind it: not more than have rows, nor than the place of their words holds
-    const int64_t waves = (p.T + 63) / 64, room = 8 * ((int64_t)p.steps + 1);
+    const int64_t waves = (T + 63) / 64, room = 8 * ((int64_t)steps + 1);
     int64_t few = waves < kFewWorkgroups ? waves : kFewWorkgroups;
     few = few < room ? few : room;
-    s = SearchPlan{partials, (int)tiles, (int)all, kPatience, (int)few, 0};
+    s = SearchPlan{0, (int)tiles, (int)all, kPatience, cus, (int)few, 0};
     return true;
 }
 
@@ -775,7 +788,7 @@ hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form
         e = s.participants <= 64 ? launch(construct_search_kernel<1, 1, 1>, grid, block, 0, stream, p, s)
                                  : launch(construct_search_kernel<1, 4, 1>, grid, block, 0, stream, p, s);
     else
-        e = s.participants <= kNumCU ? launch(construct_search_kernel<2, 4, 1>, grid, block, 0, stream, p, s)
+        e = s.participants <= s.cus ? launch(construct_search_kernel<2, 4, 1>, grid, block, 0, stream, p, s)
                                      : launch(construct_search_kernel<2, 2, 2>, grid, block, 0, stream, p, s);
     if (e != hipSuccess) return e;
     SearchPlan again = s;
@@ -805,22 +818,25 @@ hipError_t launch_steps(const ConstructParams& p, int partials, hipStream_t stre
 
 }  // namespace
 
-bool construct_runs(const ConstructParams& p, int form) {
-    SearchPlan s{};
-    return form == DUQPP_CONSTRUCT_AUTO || form == DUQPP_CONSTRUCT_STEPS || plan_search(p, form, 0, s);
-}
-
-hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStream_t stream) {
-    const int64_t chunks = (int64_t)p.T * (p.K / 8);
-    const int partials = (int)((chunks + 1023) / 1024 < kMaxPartials ? (chunks + 1023) / 1024 : kMaxPartials);
-    int form = how & ~DUQPP_CONSTRUCT_ALONE;
+int construct_form(int64_t T, int steps, int form, int cus) {
     SearchPlan s{};
     if (form == DUQPP_CONSTRUCT_AUTO) {
         form = DUQPP_CONSTRUCT_ONE_16;
-        while (form < DUQPP_CONSTRUCT_STEPS && !plan_search(p, form, partials, s)) ++form;
+        while (form < DUQPP_CONSTRUCT_STEPS && !plan_search(T, steps, form, cus, s)) ++form;
     }
+    return form == DUQPP_CONSTRUCT_STEPS || plan_search(T, steps, form, cus, s) ? form : -1;
+}
+
+hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStream_t stream, bool& runs) {
+    const int64_t chunks = (int64_t)p.T * (p.K / 8);
+    const int partials = (int)((chunks + 1023) / 1024 < kMaxPartials ? (chunks + 1023) / 1024 : kMaxPartials);
+    const int cus = cus_of(stream), form = construct_form(p.T, p.steps, how & ~DUQPP_CONSTRUCT_ALONE, cus);
+    runs = form >= 0;
+    if (!runs) return hipSuccess;
     if (form == DUQPP_CONSTRUCT_STEPS) return launch_steps(p, partials, stream);
-    if (!plan_search(p, form, partials, s)) return hipErrorInvalidValue;
+    SearchPlan s{};
+    plan_search(p.T, p.steps, form, cus, s);
+    s.partials = partials;
     if (how & DUQPP_CONSTRUCT_IMPATIENT) s.patience = 0;
     return launch_search(p, s, form, (how & DUQPP_CONSTRUCT_ALONE) == DUQPP_CONSTRUCT_ALONE ? 0 : kPatienceAgain, stream);
 }

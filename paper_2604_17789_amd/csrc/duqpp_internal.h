@@ -166,8 +166,8 @@ struct ConstructParams {
     void* workspace;
 };
 size_t construct_workspace_bytes(int64_t T, int steps);
-bool construct_runs(const ConstructParams& p, int form);        // the form can run the call
-hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStream_t stream);   // how: DUQPP_CONSTRUCT_*
+int construct_form(int64_t T, int steps, int form, int cus);   // the form that runs it on so many CUs, -1: `form` cannot
+hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStream_t stream, bool& runs);   // how: DUQPP_CONSTRUCT_*
 
 struct TiledGemmParams {
     const uint8_t* a_codes; const uint8_t* a_scales;   // tiled, T rows

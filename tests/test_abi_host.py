@@ -151,6 +151,24 @@ def test_kernel_choice_for_the_benchmark_shapes(lib):
     assert lib.duqpp_mxfp4_gemm_tiled_on(MID, None, P, P, P, 200, 16, 64, P, 0, 16, None) == NULL
 
 
+def test_construction_takes_the_workgroups_that_run_at_once(lib):
+    """One launch for all steps: 16 rows each and one workgroup per CU (two more hold the product), else 32 rows and two per CU (one
+    more), else a launch per step; of the CUs there are, not of a whole chip's."""
+    f = lib.duqpp_construct_form_for
+    auto, one16, one32, steps = range(4)
+    for cus in (256, 128, 64, 38, 16, 4, 3, 2, 1, 0):
+        most16, most32 = 16 * (cus - 2), 32 * (2 * cus - 1)
+        for T in sorted({1, 2, 3, 17, 64, 1000, most16, most16 + 1, most32, most32 + 1, 1 << 20}):
+            if T < 1:
+                continue
+            fits16, fits32 = 3 <= T <= most16, 2 <= T <= most32
+            assert f(auto, T, 8, cus) == (one16 if fits16 else one32 if fits32 else steps), (T, cus)
+            assert f(one16, T, 8, cus) == (one16 if fits16 else SHAPE)
+            assert f(one32, T, 8, cus) == (one32 if fits32 else SHAPE)
+            assert f(steps, T, 8, cus) == steps
+    assert [f(*a) for a in ((4, 64, 8, 256), (-1, 64, 8, 256), (0, 0, 8, 256), (0, 64, 4097, 256), (0, 64, -1, 256), (0, 64, 8, -1))] == [SHAPE] * 6
+
+
 def test_construct_rotation_host_checks(lib):
     ws = lib.duqpp_construct_rotation_workspace_bytes
     assert ws(0, 4) == 0 and ws(8, -1) == 0 and ws(8, 5000) == 0
