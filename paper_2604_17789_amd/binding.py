@@ -2,6 +2,8 @@
 through the native module _calls (csrc/calls.cpp) where their arguments are plain, everything else through ctypes."""
 import ctypes
 import os
+import sys
+import warnings
 
 import torch
 
@@ -132,12 +134,23 @@ def _stream():
     return _raw_stream(_current_device())
 
 
+class _NoCalls:
+    """In the place of the native module: it takes none of the calls."""
+    linear = rows = product = error = staticmethod(lambda *args: None)
+
+
 def _load_calls():
+    running = f"torch {torch.__version__}, Python {sys.version_info[0]}.{sys.version_info[1]}"
     try:
         from . import _calls
+        built_for = getattr(_calls, "built_for", "something else")
+        why = None if built_for == running else f"was built for {built_for}, this is {running}"
     except ImportError as e:
-        raise ImportError(f"{os.path.join(_HERE, '_calls.so')} is missing or was built for another torch or Python: build it first "
-                          "(python -c 'import __graft_entry__ as g; g.build()'); there is no fallback path") from e
+        why = f"does not load ({e})"
+    if why:
+        warnings.warn(f"{os.path.join(_HERE, '_calls.so')} {why}: calls go through ctypes, some microseconds each; "
+                      "python -c 'import __graft_entry__ as g; g.build()' builds it", RuntimeWarning, stacklevel=2)
+        return _NoCalls
     names = ("duqpp_rotq_gemm_tiled_packed", "duqpp_rotq_gemm_tiled", "duqpp_rotq_gemm", "duqpp_gemm_workspace_bytes",
              "duqpp_rotate_quantize_tiled_packed", "duqpp_rotate_quantize_tiled", "duqpp_quantize_weights_tiled",
              "duqpp_mxfp4_gemm_tiled", "duqpp_group_error_ws", "duqpp_group_error_workspace_bytes")

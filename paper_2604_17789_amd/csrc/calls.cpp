@@ -332,4 +332,15 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module); }
+#define TEXT_OF(x) #x
+#define TEXT(x) TEXT_OF(x)
+
+// built_for: what the binding compares with what runs, since torch's classes are read here by the layout they were compiled with.
+PyMODINIT_FUNC PyInit__calls() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", "torch " DUQPP_BUILT_WITH_TORCH ", Python " TEXT(PY_MAJOR_VERSION) "." TEXT(PY_MINOR_VERSION)) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
