@@ -151,8 +151,9 @@ int duqpp_pack_rotation(const float* R, int64_t n_rblocks, void* R_packed, void*
  *   R       in   [n_rblocks, 32, 32] fp32 with n_rblocks == K/32 or 1, or NULL: no rotation (y = x, the figure's
  *                unrotated setting; n_rblocks is then ignored)
  *   err     out  [T, K/32] fp32; -1 for a group whose 32 values are all zero (it has no ratio)
- *   mean    out  nullable; one double in device memory, 8-byte aligned: the mean of err over the groups that have a
- *                ratio (what the figure plots), summed in a fixed order; 0 when no group has one
+ *   mean    out  nullable; one double, 8-byte aligned, in device memory or in pinned host memory that the device can write: the
+ *                mean of err over the groups that have a ratio (what the figure plots), summed in a fixed order; 0 when no group
+ *                has one.  One plain store writes it and nothing reads it back; it is there once the stream has been waited for.
  */
 int duqpp_group_error(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const float* R, int64_t n_rblocks,
                       float* err, double* mean, void* stream);

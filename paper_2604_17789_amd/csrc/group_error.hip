@@ -224,6 +224,7 @@ __global__ __launch_bounds__(1024) void group_error_mean_kernel(GroupErrorMeanPa
         }
         __syncthreads();
     }
+    // the caller may have it in pinned host memory: stored once, read nowhere
     if (threadIdx.x == 0) *p.mean = scnt[0] > 0.0 ? ssum[0] / scnt[0] : 0.0;
 }
 

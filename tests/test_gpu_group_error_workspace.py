@@ -1,5 +1,6 @@
 """GPU: duqpp_group_error with a place for the partial sums of its mean gives the bits of the call without one, either side of the
-size from which there are partial sums, with an odd number of groups and more workgroups than tokens."""
+size from which there are partial sums, with an odd number of groups and more workgroups than tokens, and the mean in pinned host memory
+is the one in device memory."""
 import pytest
 
 import workloads as wl
@@ -24,9 +25,9 @@ def test_same_bits_with_and_without(T, K, rotated):
     ws = torch.randint(0, 256, (n + 24,), dtype=torch.uint8, device="cuda")
     tail = ws[n + 8:].clone()
 
-    def call(workspace, nbytes):
+    def call(workspace, nbytes, pinned=False):
         err = torch.full((T, K // 32), 9.0, device="cuda")
-        mean = torch.full((1,), 9.0, dtype=torch.float64, device="cuda")
+        mean = torch.full((1,), 9.0, dtype=torch.float64, **(dict(pin_memory=True) if pinned else dict(device="cuda")))
         st = lib.duqpp_group_error_ws(x.data_ptr(), T, K, K, R.data_ptr() if rotated else None, K // 32, err.data_ptr(), mean.data_ptr(),
                                       workspace, nbytes, _stream())
         torch.cuda.synchronize()
@@ -38,6 +39,8 @@ def test_same_bits_with_and_without(T, K, rotated):
     assert want[0] == got[0] == 0
     assert torch.equal(want[1], got[1]) and torch.equal(want[2], got[2])
     assert torch.equal(ws[n + 8:], tail)                     # nothing behind the bytes it was told of
+    for args in ((None, 0), (ws.data_ptr() + 8, n)):
+        assert torch.equal(call(*args, pinned=True)[2], want[2].cpu())
     assert call(ws.data_ptr() + 4, n)[0] == ERR_ALIGN
     if n:
         assert call(ws.data_ptr(), n - 1)[0] == ERR_WORKSPACE
