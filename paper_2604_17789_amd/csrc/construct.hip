@@ -124,10 +124,7 @@ __device__ __forceinline__ unsigned long long words_max(unsigned long long v, St
     const uint32_t lo = steps((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0u);
     return ((unsigned long long)hi << 32) | lo;
 }
-// maximum over each 8 or 16 lanes, in every one of them
-__device__ __forceinline__ unsigned long long row8_max(unsigned long long v) {
-    return words_max(v, [](uint32_t m) { return dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m))); });
-}
+// maximum over each 16 lanes, in every one of them
 __device__ __forceinline__ unsigned long long row16_max(unsigned long long v) {
     return words_max(v, [](uint32_t m) { return dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m)))); });
 }

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(1024) void group_error_mean_kernel(GroupErrorMeanPa
 
 }  // namespace
 
-// partial sums of a call with a mean; 0: it takes none
+// column chunks x token runs
 static int64_t error_workgroups(int64_t tiles, int64_t G, int64_t& chunks, int64_t& runs) {
     chunks = (G + 2 * kErrWaves - 1) / (2 * kErrWaves);
     runs = kErrWorkgroups / chunks;
@@ -238,6 +238,7 @@ static int64_t error_workgroups(int64_t tiles, int64_t G, int64_t& chunks, int64
     return chunks * runs;
 }
 
+// of the partial sums of a call with a mean; 0: it takes none
 size_t group_error_workspace_bytes(int64_t rows, int64_t G) {
     int64_t chunks, runs;
     return rows * G < kPartialsFrom ? 0 : (size_t)error_workgroups((rows + 31) / 32, G, chunks, runs) * 16;

@@ -488,10 +488,11 @@ void plan_rotq(RotqParams& p) {
     bool one_per_cu = true;                                 // one workgroup resident per CU, or 8 / waves of them
     if (p.tiled) {
         // wave-private pipelines: a workgroup is `waves` independent waves on adjacent block pairs.
-        // Fewer waves per workgroup when the problem is too small to give every CU a full one.
+        // Four waves per workgroup when the problem is too small to give every CU a full one.  (What is planned here has more
+        // than kFewWavesPacked blocks x token tiles, so that four always do.)
         const int npairs = p.GP / 2;
-        p.waves = 8;
-        while (p.waves > 1 && (int64_t)((npairs + p.waves - 1) / p.waves) * p.ntiles < kNumCU) p.waves /= 2;
+        static_assert(kFewWavesPacked >= 2 * 4 * kNumCU, "four waves per workgroup give every CU one");
+        p.waves = (int64_t)((npairs + 7) / 8) * p.ntiles < kNumCU ? 4 : 8;
         one_per_cu = p.waves >= 5;
         if (p.waves == 8 && (p.G & (p.G - 1)) == 0) {
             // Enough work for every CU, and a row length that is a power of two (K = 4096, 8192, ...).  With
