@@ -169,3 +169,102 @@ def test_modes_and_subclasses_take_the_python_path(monkeypatch, data):
     p = torch.nn.Parameter(Rp, requires_grad=False)          # what a module's weights are
     a, b = both_ways(monkeypatch, lambda: duqpp.rotq_gemm_tiled_packed(x, p, *wt, N))
     assert torch.equal(a, plain) and torch.equal(b, plain)
+
+
+@pytest.mark.gpu
+def test_function_transforms_end_as_on_the_python_path(monkeypatch, data):
+    """Under vmap, grad and functionalization tensors have no memory to pass on; a tensor from outside still has, with the result's not."""
+    x, w, R, Rp = data
+    wt = duqpp.quantize_weights_tiled(w, R)
+    calls = [lambda v: duqpp.rotq_gemm_tiled_packed(v, Rp, *wt, N), lambda v: duqpp.rotate_quantize_tiled(v, R)[0], lambda v: duqpp.group_error(v, R)[0],
+             lambda v: duqpp.rotq_gemm_tiled_packed(x, Rp, *wt, N) + v.sum(), lambda v: duqpp.group_error(x, R)[0].sum() + v.sum()]
+    transforms = [lambda f: torch.func.vmap(f)(x.expand(2, T, K)), lambda f: torch.func.grad(lambda v: f(v).sum().float())(x),
+                  lambda f: torch.func.functionalize(f)(x), lambda f: torch.func.jvp(f, (x,), (x,))]
+
+    def ends(f):
+        try:
+            r = f()
+            return r if isinstance(r, torch.Tensor) else [v for v in r]
+        except Exception as e:
+            return type(e), str(e).split("\n")[0]
+
+    for transform in transforms:
+        for call in calls:
+            native = ends(lambda: transform(call))
+            with monkeypatch.context() as m:
+                m.setattr(binding, "_calls", Never)
+                python = ends(lambda: transform(call))
+            assert type(native) is type(python), (native, python)
+            assert native == python if isinstance(native, tuple) else same(native, python)
+
+
+@pytest.mark.gpu
+def test_two_threads_on_two_streams(data):
+    """Each thread its own stream, tensors and results, with the interpreter let go during the launches."""
+    import threading
+    x, w, R, Rp = data
+    wt, wr = duqpp.quantize_weights_tiled(w, R), duqpp.quantize_weights(w, R)
+    inputs = [x * (i + 1) for i in range(4)]
+    want = [(duqpp.rotq_gemm_tiled_packed(v, Rp, *wt, N), duqpp.rotq_gemm(v, R, *wr), duqpp.group_error(v, R)) for v in inputs]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        try:
+            side = torch.cuda.Stream()
+            with torch.cuda.stream(side):
+                for _ in range(50):
+                    y, z, e = duqpp.rotq_gemm_tiled_packed(inputs[i], Rp, *wt, N), duqpp.rotq_gemm(inputs[i], R, *wr), duqpp.group_error(inputs[i], R)
+                    side.synchronize()
+                    if not (torch.equal(y, want[i][0]) and torch.equal(z, want[i][1]) and same(e, want[i][2])):
+                        wrong.append(i)
+        except BaseException as e:
+            wrong.append((i, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
+@pytest.mark.gpu
+def test_captured_once_and_replayed(data):
+    """Calls through the native path in a graph, results and workspaces from the graph's pool: every replay, between other work, gives what
+    eager calls do."""
+    x, w, R, Rp = data
+    wt, wr = duqpp.quantize_weights_tiled(w, R), duqpp.quantize_weights(w, R)
+    held = x.clone(memory_format=torch.contiguous_format)
+
+    def f():
+        a = duqpp.rotate_quantize_tiled_packed(held, Rp)
+        return (duqpp.rotq_gemm_tiled_packed(held, Rp, *wt, N, duqpp.BF16), duqpp.rotq_gemm(held, R, *wr), duqpp.mxfp4_gemm_tiled(*a, *wt, T, N, K),
+                duqpp.group_error(held, R, return_mean=False)[0], *a)
+
+    f()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        outs = f()
+    for i in range(4):
+        held.copy_(x * (i + 1))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, f()))
+        torch.ones(1 << 16, device="cuda").sum().item()
+
+
+@pytest.mark.gpu
+def test_compiled_callers(data):
+    """A function that dynamo traces: it breaks its graph at the call, as it did at the Python path's, and the result is the eager one."""
+    x, w, R, Rp = data
+    wt = duqpp.quantize_weights_tiled(w, R)
+
+    def f(v):
+        return duqpp.rotq_gemm_tiled_packed(v * 2, Rp, *wt, N) + 1
+
+    want = f(x)
+    torch._dynamo.reset()
+    got = torch.compile(f, backend="eager")(x)
+    assert torch.equal(got, want)

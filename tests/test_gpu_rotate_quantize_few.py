@@ -1,6 +1,6 @@
 """GPU: the tiled rotate + quantise of few tokens (a wave per block and token tile) gives the bytes of the row-major kernel in their
 tiled places: ragged token tiles, groups that the layout pads, strided rows, a shared block, and either side of the numbers of
-waves up to which it is taken."""
+waves up to which it is taken.  Likewise the kernel beyond them where rows are short."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,K,shared", [(1, 32, 0), (1, 4096, 0), (31, 96, 1), (32, 288, 0), (33, 14336, 0), (65, 8224, 1),
                                         (512, 4096, 0), (513, 4096, 0),          # 2048 and 2176 waves: packed blocks
-                                        (1024, 4096, 1), (1025, 4096, 0)])       # 4096 and 4224: fp32 blocks
+                                        (1024, 4096, 1), (1025, 4096, 0),        # 4096 and 4224: fp32 blocks
+                                        # rows below 2048 channels, where an XCD has token runs: 4 waves per workgroup, 5 and groups that
+                                        # the layout pads, 4 and a ring of three tiles for one group
+                                        (8200, 1024, 0), (8200, 1120, 1), (70000, 32, 0)])
 def test_same_bytes_as_the_row_major_kernel(T, K, shared):
     import torch
 

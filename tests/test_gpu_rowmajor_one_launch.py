@@ -1,6 +1,6 @@
 """The row-major fused call prepares both operands in one launch: every byte it leaves in the workspace, at the edges of the
-units (32 rows x 8 groups), for each number of waves and ring depth the rotation is planned with, and with more units
-than workgroups."""
+units (32 rows x 8 groups), with a wave per block and token tile and beyond 2048 of these with rings of both depths, four and more
+waves per workgroup and both orders of the workgroups, and with more units than waves."""
 import numpy as np
 import pytest
 
@@ -15,9 +15,12 @@ pytestmark = pytest.mark.gpu
     (45, 100, 352, 0),          # 11 groups: scale rows that are not whole words
     (64, 64, 1024, 1),          # scales that do not start on a word
     (33, 31, 288, 3),
-    (300, 200, 14336, 0),       # several waves per workgroup
-    (2048, 40, 4096, 0),        # the deeper ring
-    (1, 12000, 8192, 0),        # one wave per workgroup, several units per wave
+    (300, 200, 14336, 0),       # 4480 blocks and token tiles: the ring, five waves per workgroup
+    (2048, 40, 4096, 0),        # four waves per workgroup
+    (4100, 40, 4096, 0),        # the deeper ring
+    (2100, 70, 1120, 2),        # rows below 2048 channels
+    (1, 12000, 8192, 0),        # a wave per block and token tile, 12000 units in workgroups of four waves
+    (513, 65573, 4096, 0),      # the ring, four waves per workgroup, 32800 units: several per wave
 ])
 def test_workspace_of_the_rowmajor_call(T, N, K, shift):
     import torch
