@@ -758,7 +758,10 @@ int cus_of(hipStream_t stream) {
     int dev = 0, n = 0;
     uint32_t mask[32] = {};
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipExtStreamGetCUMask(stream, 32, mask) != hipSuccess) return n;
+    if (hipExtStreamGetCUMask(stream, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();                             // not the caller's to find
+        return n;
+    }
     int masked = 0;
     for (uint32_t word : mask) masked += __builtin_popcount(word);
     return masked > 0 && masked < n ? masked : n;
