@@ -337,10 +337,12 @@ int duqpp_fold_smoothing(const float* R, int64_t n_rblocks, const float* lambda,
  *   peaks      out  nullable, [max_steps + 1] fp64 on the device: peak |value| after 0, 1, ... steps
  *   workspace       at least duqpp_construct_rotation_workspace_bytes(T, max_steps) bytes, 256-byte aligned
  * Enqueues up to max_steps + 4 kernels on the stream.  Errors as for the other calls.
- * Up to some thousand tokens all steps are one kernel, whose workgroups exchange their maxima and are therefore to run at the same
- * time.  Where they do not, because other work holds the device (a second construction on another stream, for one), they give up
- * after 1 to 2 ms and fewer workgroups do the search, at last one: the result is the same, the time is longer (128 steps on one
- * MI355X, T = 2048 / 16000: 0.28 / 0.59 ms, with fewer workgroups 2.8 / 3.1, with one 13 / 82).  No wait is without a limit.
+ * Where massive values leave only a few tokens that can ever hold the largest magnitude (up to 28, of up to 16352), only those are followed: 128
+ * steps on one MI355X, T = 2048 / 16000: 0.13 / 0.18 ms.
+ * Otherwise, up to some thousand tokens, all steps are one kernel, whose workgroups exchange their maxima and are therefore to run at the
+ * same time.  Where they do not, because other work holds the device (a second construction on another stream, for one), they give up
+ * after 1 to 2 ms and fewer workgroups do the search, at last one: the result is the same, the time is longer (T = 2048 / 16000: 0.30 /
+ * 0.60 ms, with fewer workgroups 2.8 / 3.1, with one 13 / 82).  No wait is without a limit.
  */
 size_t duqpp_construct_rotation_workspace_bytes(int64_t T, int max_steps);   /* host, pure; 0 for invalid arguments */
 int duqpp_construct_rotation(const void* x_bf16, int64_t T, int64_t K, int64_t ldx,

@@ -14,13 +14,15 @@
 // the bit patterns of |z| (order-independent).
 //
 // Every step needs the largest magnitude of the whole state before it, so the steps are a chain of exchanges between all
-// workgroups.  Two forms:
+// workgroups, unless only a few rows can hold it.  Three forms:
+//   rows that count (construct_rows_kernel) where massive values leave at most 28 rows that can ever hold the largest magnitude, every one
+//                   of sixteen workgroups follows just those, without an exchange.  Tried first by calls of up to 16352 rows.
 //   search kernel   (construct_search_kernel) one launch for all steps: a workgroup keeps its 16 or 32 rows of the state in LDS and
 //                   registers, publishes the largest magnitude among them after every step, waits for everybody's, and goes on.
 //                   For as many rows as workgroups that run at once hold: 16 rows each and one workgroup per CU, or 32 rows
 //                   and two per CU (T <= 16352 on 256 CUs).  Should they not come to run together, because other work holds the CUs for
 //                   longer than they wait (1 to 2 ms), they give up, and up to 64 workgroups with the state in memory do the
-//                   search (construct_again_kernel); should not even these come to run together (within 20 ms and more), one
+//                   search (construct_again_kernel); should not even these come to run together (within 20 ms and more), the first
 //                   does it, which waits for nobody: nothing ever waits without a limit.  128 steps, with what is waited ahead
 //                   of it left out: 64 workgroups 2.7 ms at T = 512, 2.8 at 4064, 3.1 at 16000; one 5.2, 24, 82 ms.  Two calls of
 //                   16000 rows on two streams at once: 4.0 to 5.1 ms each (with one workgroup behind 20 ms of waiting 140 to 160;
@@ -59,13 +61,14 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ double hadamard_entry(int i, int k) { return (__popc(i & k) & 1) ? -kHadamardEntry : kHadamardEntry; }
 
-// workspace: [header 64 B: u64 block key, u64 search given up, u64 given up again][colmax (S + 1) x 32 u64][slots (S + 1) x 1024 f64][Z T x 32 f64]
+// workspace: [header 64 B: u64 block key, u64 search given up, u64 given up again, u64 done by the rows that count][colmax (S + 1) x 32 u64][slots (S + 1) x 1024 f64][Z T x 32 f64]
 // Slot 0 holds the block search's partial keys, then the maxima below; slot t >= 1 holds M_t = H . diag(1, Q'_t), then R^(t).
 // The search kernel keeps the state on the chip; the place of Z holds what its workgroups publish, that of colmax what those of the
-// kernel behind it do.
+// kernel behind it do, and at its end, a word per step, how far the step's draw is from orthogonal.
 struct Workspace {
     unsigned long long* key;
     unsigned long long* given_up;        // two words
+    unsigned long long* done;
     unsigned long long* colmax;
     double* slots;
     double* z;
@@ -75,6 +78,7 @@ __host__ __device__ inline Workspace carve(void* ws, int steps) {
     uint8_t* p = static_cast<uint8_t*>(ws);
     w.key = reinterpret_cast<unsigned long long*>(p);
     w.given_up = w.key + 1;
+    w.done = w.key + 3;
     w.colmax = reinterpret_cast<unsigned long long*>(p + 64);
     w.slots = reinterpret_cast<double*>(p + 64 + (size_t)(steps + 1) * 256);
     w.z = reinterpret_cast<double*>(p + 64 + (size_t)(steps + 1) * 256 + (size_t)(steps + 1) * 8192);
@@ -143,8 +147,8 @@ __device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
 
 // The largest |x| per block of 32 channels -> one 64-bit key per workgroup of 256 threads: magnitude bits above, inverted block
 // index below, so that the integer maximum is the largest magnitude in the smallest block.
-__device__ __forceinline__ void block_key(const ConstructParams& p, const Workspace& w, int workgroups, unsigned long long* red) {
-    const int64_t stride = (int64_t)workgroups * 256, at = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void block_key(const ConstructParams& p, const Workspace& w, int index, int workgroups, unsigned long long* red) {
+    const int64_t stride = (int64_t)workgroups * 256, at = (int64_t)index * 256 + threadIdx.x;
     const int64_t chunks = p.K / 8;                          // 16-byte pieces of 8 bf16 in a row; 4 per block
     const int64_t dr = stride / chunks, dc = stride % chunks;
     int64_t row = at / chunks, ch = at % chunks;
@@ -184,7 +188,7 @@ __device__ __forceinline__ void block_key(const ConstructParams& p, const Worksp
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
     __syncthreads();
     if (threadIdx.x == 0)
-        reinterpret_cast<unsigned long long*>(w.slots)[blockIdx.x] = max_u64(max_u64(red[0], red[1]), max_u64(red[2], red[3]));
+        reinterpret_cast<unsigned long long*>(w.slots)[index] = max_u64(max_u64(red[0], red[1]), max_u64(red[2], red[3]));
 }
 
 // Clears the first column maxima, and the keys.
@@ -192,19 +196,20 @@ __global__ __launch_bounds__(256) void construct_blockmax_kernel(ConstructParams
     __shared__ unsigned long long red[4];
     Workspace w = carve(p.workspace, p.steps);
     if (blockIdx.x == 0 && threadIdx.x < 32) w.colmax[threadIdx.x] = 0ull;
-    block_key(p, w, gridDim.x, red);
+    block_key(p, w, blockIdx.x, gridDim.x, red);
 }
 
-// The chosen block from the partial keys, in every thread of a workgroup of kStepWaves waves.
+// The chosen block from the partial keys, in every thread of a workgroup.
+template <int WAVES = kStepWaves>
 __device__ __forceinline__ unsigned long long chosen_key(const Workspace& w, int partials, unsigned long long* red) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned long long key = 0ull;
-    for (int i = threadIdx.x; i < partials; i += 64 * kStepWaves) key = max_u64(key, reinterpret_cast<const unsigned long long*>(w.slots)[i]);
+    for (int i = threadIdx.x; i < partials; i += 64 * WAVES) key = max_u64(key, reinterpret_cast<const unsigned long long*>(w.slots)[i]);
     key = wave_max(key);
     if (lane == 0) red[wave] = key;
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kStepWaves; ++k) key = max_u64(key, red[k]);
+    for (int k = 0; k < WAVES; ++k) key = max_u64(key, red[k]);
     return key;
 }
 __device__ __forceinline__ int64_t block_of(unsigned long long key) { return 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull); }
@@ -240,30 +245,30 @@ __device__ __forceinline__ void step_matrix(const ConstructParams& p, const Work
     if (t > 0)
         for (int e = threadIdx.x; e < 31 * 31; e += 256) q[e] = p.q_steps[(size_t)(t - 1) * 31 * 31 + e];
     __syncthreads();
-    for (int e = threadIdx.x; e < 1024; e += 256) {
-        const int i = e >> 5, j = e & 31;
-        double acc;
-        if (t == 0) {
-            acc = 0.0;
-        } else if (j == 0) {
-            acc = hadamard_entry(i, 0);
-        } else {
-            acc = 0.0;
-            for (int k = 1; k < 32; ++k) acc = acc + hadamard_entry(i, k) * q[(k - 1) * 31 + (j - 1)];
+    // a thread's four entries stand in one column, rows 8 apart
+    const int i = threadIdx.x >> 5, j = threadIdx.x & 31;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (t > 0 && j > 0)
+        for (int k = 1; k < 32; ++k) {
+            const double v = q[(k - 1) * 31 + (j - 1)];
+#pragma unroll
+            for (int n = 0; n < 4; ++n) acc[n] = acc[n] + hadamard_entry(i + 8 * n, k) * v;
         }
-        out[e] = acc;
-    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) out[threadIdx.x + 256 * n] = t > 0 && j == 0 ? hadamard_entry(i + 8 * n, 0) : acc[n];
 }
 __global__ __launch_bounds__(256) void construct_matrices_kernel(ConstructParams p) {
     __shared__ double q[31 * 31];
     step_matrix(p, carve(p.workspace, p.steps), blockIdx.x, q);
 }
 
-// The largest of the lanes' values, uniform, and the lanes that hold it.
+// The largest of the first LANES lanes' values (the others hold 0), uniform, and the lanes that hold it.
+template <int LANES = 64>
 __device__ __forceinline__ unsigned long long lanes_of_max(unsigned long long v, unsigned long long& top) {
     auto most = [](uint32_t m) {
-        m = dpp_max<0x143>(dpp_max<0x142>(dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m))))));
-        return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+        m = dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(m))));
+        if constexpr (LANES > 16) m = dpp_max<0x143>(dpp_max<0x142>(m));
+        return (uint32_t)__builtin_amdgcn_readlane((int)m, LANES - 1);
     };
     const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v, most_hi = most(hi);
     unsigned long long lanes = __ballot(hi == most_hi);
@@ -404,7 +409,6 @@ struct SearchPlan {
     uint32_t patience;                   // looks at what the others have published before one gives up; 0: gives up in any case
     int cus;                             // CUs they have
     int few;                             // workgroups of the search behind it
-    int asked;                           // for those: the word of given_up that asks for them; the next one is theirs
 };
 
 // What the workgroups tell each other after step t: two words each, the largest magnitude among their rows and the smallest
@@ -420,17 +424,49 @@ __device__ __forceinline__ uint32_t exchange_at(int participants, int copy, int 
 }
 inline size_t exchange_bytes(int participants) { return (size_t)2 * kExchangeCopies * participants * kExchangeWords * 8; }
 
-// Keys of the block search, the matrices of all steps, and nothing published yet.
+// How far step t's draw is from orthogonal: the largest entry of |Q'.Q'^T - 1|, as the bits of a double (a NaN is larger than all).
+__device__ __forceinline__ unsigned long long* deviation(const Workspace& w, int steps, int t) { return w.colmax + (size_t)(steps + 1) * 32 - t; }
+__device__ __forceinline__ void step_deviation(const ConstructParams& p, const Workspace& w, int t, const double* q, unsigned long long* red) {
+    unsigned long long most = 0ull;
+    // the upper triangle: rows a and 30 - a of it have 32 entries together (row 15 comes twice)
+    const int b = threadIdx.x & 31;
+    int i[2], j[2];
+    double acc[2] = {0.0, 0.0};
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int a = (threadIdx.x >> 5) + 8 * n;
+        i[n] = b < 31 - a ? a : 30 - a;
+        j[n] = b < 31 - a ? a + b : b - 1;
+    }
+    for (int k = 0; k < 31; ++k) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n) acc[n] = acc[n] + q[31 * i[n] + k] * q[31 * j[n] + k];
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) most = max_u64(most, abs_bits(i[n] == j[n] ? acc[n] - 1.0 : acc[n]));
+    most = wave_max(most);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = most;
+    __syncthreads();
+    if (threadIdx.x == 0) *deviation(w, p.steps, t) = max_u64(max_u64(red[0], red[1]), max_u64(red[2], red[3]));
+}
+
+// The matrices of all steps, keys of the block search, and nothing published yet.
 __global__ __launch_bounds__(256) void construct_prepare_kernel(ConstructParams p, SearchPlan s) {
     __shared__ double q[31 * 31];
+    __shared__ unsigned long long red[4];
     Workspace w = carve(p.workspace, p.steps);
     const int words = 2 * kExchangeCopies * kExchangeWords * s.participants;
     const int at = blockIdx.x * 256 + threadIdx.x;
     if (at < 2) w.given_up[at] = 0ull;
-    if (at < 4 * s.few) w.colmax[at] = ~0ull;
+    if (at == 2) *w.done = 0ull;
+    if (at < 5 * s.few) w.colmax[at] = at < 4 * s.few ? ~0ull : 0ull;
     for (int i = at; i < words; i += gridDim.x * 256) reinterpret_cast<unsigned long long*>(w.z)[i] = ~0ull;
-    if ((int)blockIdx.x < s.partials) block_key(p, w, s.partials, reinterpret_cast<unsigned long long*>(q));
-    else step_matrix(p, w, (int)blockIdx.x - s.partials + 1, q);
+    if ((int)blockIdx.x < p.steps) {
+        step_matrix(p, w, (int)blockIdx.x + 1, q);
+        step_deviation(p, w, (int)blockIdx.x + 1, q, red);
+    } else {
+        block_key(p, w, (int)blockIdx.x - p.steps, s.partials, red);
+    }
 }
 
 // value of lane N of each 16 lanes, in all 16
@@ -485,7 +521,9 @@ __global__ __launch_bounds__(64 * kStepWaves, 2 * PER_CU) void construct_search_
     };
 
     if (threadIdx.x < 32) colmax[threadIdx.x] = 0ull;
+    const unsigned long long done = *w.done;
     const unsigned long long key = chosen_key(w, s.partials, red);   // (holds a barrier: colmax is cleared)
+    if (done != 0ull) return;
     const int64_t block = block_of(key);
     f64x2 next = {0.0, 0.0};
     if (p.steps > 0) {
@@ -629,18 +667,291 @@ __global__ __launch_bounds__(64 * kStepWaves, 2 * PER_CU) void construct_search_
     }
 }
 
+// The search on the rows that count.  A step keeps a row's 2-norm, so that no entry of a row ever exceeds the norm the row begins
+// with, while the row of the largest norm N always has an entry of N / sqrt(32) or more: rows with less than that never hold the
+// largest magnitude, and the search need not follow them.  Activations with massive values leave few: of 2048 or 8192 tokens with a
+// value of 900 and a channel at 50 times the others in the block 4 to 15, without such a channel one.  Up to kRowsKept of them, every
+// workgroup does the whole search by itself, waits for nobody, and carries two rows of the product R^(t) along.
+// Norms are kept as far as the draws are orthogonal, which the kernel ahead has measured: a singular value of Q' lies within
+// sqrt(1 -+ 31 d), d the largest entry of |Q'.Q'^T - 1|.  With 31 d times the steps up to 0.02 norms stay within a factor of 0.9898
+// to 1.0101, which the 0.95 below leaves room for (0.960 would do).  Otherwise, with more rows than that or with infinities or NaN
+// the kernel leaves the search to the one behind it.
+// A step is a chain of latencies of one workgroup, about 1700 cycles: 350 until the row is back from LDS, from where every lane needs all
+// of it, 400 for the products that do not depend on the exchanged channel d, 230 for the largest magnitude, 250 for the two that do,
+// 400 for the 32 additions in order and the next matrix column's way to registers.  The whole call, 128 steps on one MI355X, K = 4096,
+// massive values, us, search kernel / this: T = 64 265 / 127, 2048 289 / 131, 8160 370 / 150, 16000 593 / 177.  Without massive
+// values, where it only finds that out: 2048 289 / 295, 16000 593 / 596.
+constexpr int kRowsWaves = 8;
+constexpr int kRowsOnce = 2 * (kRowsWaves - 1);          // the first wave has two rows of the product, the others two rows each,
+constexpr int kRowsKept = 2 * kRowsOnce;                 // and two more each where there are more
+constexpr int kRowsBring = 4;                            // the last waves bring the matrices, whether they have rows or not
+constexpr int kRowsWorkgroups = kBlock / 2;              // two rows of the product each
+constexpr int64_t kRowsScanned = 16384;                  // rows whose norms fit beside each other
+typedef double f64x16 __attribute__((ext_vector_type(16)));
+
+// max(top, |v|) of finite values (the compiler's own first makes quiet NaN of signalling ones, an instruction more per operand)
+__device__ __forceinline__ double larger(double top, double v) {
+    asm("v_max_f64 %0, %0, |%1|" : "+v"(top) : "v"(v));
+    return top;
+}
+
+__global__ __launch_bounds__(64 * kRowsWaves) void construct_rows_kernel(ConstructParams p, SearchPlan s) {
+    constexpr int kPitch = 34, kThreads = 64 * kRowsWaves;
+    constexpr int kRowsLds = 4 * kRowsWaves * kPitch;
+    __shared__ __attribute__((aligned(16))) double lds[3 * 1024 + 2 * kRowsLds];
+    __shared__ unsigned long long red[2][kRowsWaves];
+    __shared__ int kept_rows[kRowsKept], count, many;
+    double* const mt = lds;                                  // M_t in place t % 3
+    double* const z = lds + 3 * 1024;                        // four rows of the state per wave, after even and odd steps
+    uint16_t* const norms = reinterpret_cast<uint16_t*>(lds);    // before that: upper words of the squared norms
+    static_assert(kRowsScanned * 2 <= (int64_t)sizeof(lds), "norms");
+    const Workspace w = carve(p.workspace, p.steps);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    if (threadIdx.x == 0) count = many = 0;
+    unsigned long long most = 0ull;
+    for (int t = 1 + threadIdx.x; t <= p.steps; t += kThreads) most = max_u64(most, *deviation(w, p.steps, t));
+    const unsigned long long key = chosen_key<kRowsWaves>(w, s.partials, red[0]);
+    const int64_t block = block_of(key);
+    most = wave_max(most);
+    if (lane == 0) red[1][wave] = most;
+
+    // squared norms: four lanes to a row, 16 rows of every wave in flight eight times
+    const uint16_t* const xb = p.x + 32 * block + 8 * (threadIdx.x & 3);
+    unsigned long long top = 0ull;
+    const double largest = (double)__uint_as_float((uint32_t)(key >> 32) << 16);
+    for (int64_t first = 0; first < p.T; first += 8 * (kThreads / 4)) {
+        const int64_t r0 = first + (threadIdx.x >> 2);
+        bool large = false;
+        uint4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {                        // (no branch around the loads: past the end the last row)
+            const int64_t r = r0 + k * (kThreads / 4);
+            v[k] = *reinterpret_cast<const uint4*>(xb + (r < p.T ? r : p.T - 1) * p.ldx);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t words[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+            double n = 0.0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double lo = (double)__uint_as_float(words[j] << 16), hi = (double)__uint_as_float(words[j] & 0xFFFF0000u);
+                n = n + lo * lo;
+                n = n + hi * hi;
+            }
+            n = n + __shfl_xor(n, 1);
+            n = n + __shfl_xor(n, 2);
+            const unsigned long long bits = abs_bits(n);
+            top = max_u64(top, bits);
+            const int64_t r = r0 + k * (kThreads / 4);
+            if ((threadIdx.x & 3) == 0 && r < p.T) {
+                norms[r] = (uint16_t)(bits >> 48);
+                large |= n >= 0.25 * largest * largest;
+            }
+        }
+        // Where many of the first 1024 rows are not far below the largest magnitude there is no point in looking at the others
+        if (first == 0 && p.T > kRowsKept) {
+            const int here = __popcll(__ballot(large));
+            if (lane == 0 && here) atomicAdd(&many, here);
+            __syncthreads();
+            if (many > kRowsKept) return;                    // here and below the same for every thread of the launch
+        }
+    }
+    __syncthreads();                                         // red[0] has been read
+    top = wave_max(top);
+    if (lane == 0) red[0][wave] = top;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRowsWaves; ++k) {
+        top = max_u64(top, red[0][k]);
+        most = max_u64(most, red[1][k]);
+    }
+    if ((top >> 52) == 0x7FF) return;                        // infinities or NaN
+    const bool orthogonal = __longlong_as_double((long long)most) * 31.0 * p.steps <= 0.02;   // (false for a NaN)
+    if (!orthogonal) return;                                 // (also with few rows: nothing becomes infinite below)
+    const unsigned long long least = (unsigned long long)__double_as_longlong(__longlong_as_double((long long)top) * (0.95 / 32.0)) >> 48;
+    for (int64_t r = threadIdx.x; r < p.T; r += kThreads)
+        if (p.T <= kRowsKept || norms[r] >= least) {         // (upper words: less is less of the whole, equal stays)
+            const int i = atomicAdd(&count, 1);
+            if (i < kRowsKept) kept_rows[i] = (int)r;
+        }
+    __syncthreads();
+    const int kept = __builtin_amdgcn_readfirstlane(count);
+    if (kept > kRowsKept) return;
+    for (int e = threadIdx.x; e < 2 * kRowsLds; e += kThreads) z[e] = 0.0;   // rows that nobody has
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) *w.done = 1ull;
+    const bool product = wave == 0, works = product || 2 * (wave - 1) < kept, brings = wave >= kRowsWaves - kRowsBring;
+    const bool twice = !product && kRowsOnce + 2 * (wave - 1) < kept;
+    if (!works && !brings) return;                           // (a wave that has ended no longer counts for the barriers)
+
+    // Lane (h, c) has a row, and column c of the matrices: of the first wave row h of the workgroup's two of the product, of the others
+    // row h of two of those that count, and perhaps of two more
+    const int h = lane >> 5, c = lane & 31;
+    const int prow = 2 * (int)blockIdx.x + h;
+    double* const mine = z + (4 * wave + h) * kPitch;
+    auto state = [&](int i) {
+        return i < kept ? (double)__uint_as_float((uint32_t)p.x[kept_rows[i] * p.ldx + 32 * block + c] << 16) : 0.0;
+    };
+    double acc = product ? (prow == c ? 1.0 : 0.0) : state(2 * (wave - 1) + h), more = twice ? state(kRowsOnce + 2 * (wave - 1) + h) : 0.0;
+    double best = acc;
+    int at = c, best_at = c;                                 // the channels of acc and more, and of best
+    unsigned long long lowest = ~0ull;
+    int steps_kept = 0;
+    // A matrix comes from memory a step ahead of its way to LDS, four entries a thread
+    const int bringer = threadIdx.x - 64 * (kRowsWaves - kRowsBring);
+    auto matrix = [&](int t, int k) {
+        return reinterpret_cast<const f64x2*>(w.slots + (size_t)(t < p.steps ? t : p.steps) * 1024)[bringer + 64 * kRowsBring * k];
+    };
+    auto stage = [&](int place, const f64x2* e) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) reinterpret_cast<f64x2*>(mt + place)[bringer + 64 * kRowsBring * k] = e[k];
+    };
+    f64x2 next[2] = {};
+    if (brings && p.steps > 0) {
+        const f64x2 first[2] = {matrix(1, 0), matrix(1, 1)};
+        stage(0, first);
+        next[0] = matrix(2, 0);
+        next[1] = matrix(2, 1);
+    }
+    lds_barrier();
+    // places of M_{t+1}, M_{t+2} and M_{t+3}; the last was read in step t - 1, a barrier before M_{t+3} comes
+    int m1 = 0, m2 = 1024, m3 = 2048;
+    auto bring = [&](int t) {
+        if (brings && t + 2 <= p.steps) {
+            stage(m2, next);
+            next[0] = matrix(t + 3, 0);
+            next[1] = matrix(t + 3, 1);
+        }
+    };
+    auto turn = [&] {
+        const int m0 = m1;
+        m1 = m2;
+        m2 = m3;
+        m3 = m0;
+    };
+    if (!works) {
+        for (int t = 0; t <= p.steps; ++t) {
+            bring(t);
+            turn();
+            lds_barrier();
+        }
+        return;
+    }
+    double m[32];                                            // column c of M_{t+1}
+    auto column = [&](int place) {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) m[r] = mt[place + r * 32 + c];
+    };
+    column(m1);
+    for (int t = 0;; ++t) {
+        double* const z0 = mine + (t & 1) * kRowsLds;
+        double* const z1 = z0 + 2 * kPitch;
+        z0[at] = acc;
+        if (twice) z1[at] = more;
+        bring(t);
+        __builtin_amdgcn_sched_barrier(0);
+        f64x2 x[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) x[k] = *reinterpret_cast<const f64x2*>(z0 + 2 * k);
+        __builtin_amdgcn_sched_barrier(0);
+        // What has been written is there (accesses complete in order, at most 12 are left and 16 reads stand behind the writes), the rest
+        // of the reads is on its way
+        asm volatile("s_waitcnt lgkmcnt(12)\n\ts_barrier" ::: "memory");
+        // the largest magnitude of each channel, lane (h, c) among rows h and 2 + h of all waves
+        const double* const column_c = z + (t & 1) * kRowsLds + h * kPitch + c;
+        double top = 0.0, of[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) of[k] = column_c[4 * (k + 1) * kPitch];
+        __builtin_amdgcn_sched_barrier(0);
+        f64x16 lo, hi;                                       // x_r . M[r][c], right for all r but 0 and d
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            lo[r] = x[r / 2][r % 2] * m[r];
+            hi[r] = x[8 + r / 2][r % 2] * m[16 + r];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) asm volatile("" ::"v"(lo[r]), "v"(hi[r]));   // made here, not behind d
+#pragma unroll
+        for (int k = 0; k < 3; ++k) top = larger(top, of[k]);
+        if (kept > 6) {
+#pragma unroll
+            for (int k = 4; k < kRowsWaves; ++k) top = larger(top, column_c[4 * k * kPitch]);
+        }
+        if (kept > kRowsOnce) {
+#pragma unroll
+            for (int k = 1; k < kRowsWaves; ++k) top = larger(top, column_c[(4 * k + 2) * kPitch]);
+        }
+        unsigned long long peak;
+        const unsigned long long lanes = lanes_of_max(abs_bits(top), peak);
+        const int d = __builtin_amdgcn_readfirstlane(__ffs((uint32_t)lanes | (uint32_t)(lanes >> 32)) - 1);
+        if (product) {
+            if (peak < lowest) {
+                lowest = peak;
+                steps_kept = t;
+                best = acc;
+                best_at = at;
+            }
+            if (p.peaks && blockIdx.x == 0 && threadIdx.x == 0) p.peaks[t] = __longlong_as_double((long long)peak);
+        }
+        if (t == p.steps) break;
+        // row . M with the rows of M in the order sigma(0), sigma(1), ..., sigma exchanging 0 and d
+        const double md = mt[m1 + d * 32 + c], first = z0[0] * md, other = z0[d] * m[0];
+        if (twice) {
+            const double other1 = z1[d] * m[0];
+            more = 0.0 + z1[0] * md;
+#pragma unroll
+            for (int r = 1; r < 32; ++r) {
+                const double term = z1[r] * m[r];
+                more = more + (r == d ? other1 : term);
+            }
+        }
+        lo[d < 16 ? d : 0] = other;                          // (term 0 is `first`)
+        hi[d < 16 ? 0 : d - 16] = d < 16 ? hi[0] : other;    // (no branch: the compiler copies the whole vector around one)
+        __builtin_amdgcn_sched_barrier(0);
+        column(m2);                                          // while the additions run (past the last step whatever stands there)
+        __builtin_amdgcn_sched_barrier(0);
+        acc = 0.0 + first;
+#pragma unroll
+        for (int r = 1; r < 16; ++r) acc = acc + lo[r];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc = acc + hi[r];
+        at = c == 0 ? d : (c == d ? 0 : c);
+        turn();
+    }
+    if (product) {
+        p.R_out[prow * 32 + best_at] = (float)best;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            p.info[0] = (int)block;
+            p.info[1] = steps_kept;
+        }
+    }
+}
+
 // The search again where the search kernel's workgroups did not come to run together: in a few workgroups, which find room where
-// hundreds do not, and if not even these did, in one, which waits for nobody.  The rows are in memory, a lane has a row at a time,
+// hundreds do not, and if not even these did, in the first of them, which waits for nobody then.  The rows are in memory, a lane has a row at a time,
 // 64 rows going to the first wave of each workgroup in turn, then to the second.  The same result; bound by the reads of M_t from LDS.
+constexpr unsigned long long kNotBegun = 0, kBegun = 1, kLeft = 2;
+
 __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(ConstructParams p, SearchPlan s) {
     __shared__ __attribute__((aligned(16))) double m[1024];
     __shared__ double product[1024], best[1024];
     __shared__ unsigned long long red[kStepWaves], peak_of_all;
     __shared__ int red_channel[kStepWaves], channel_of_all;
     const Workspace w = carve(p.workspace, p.steps);
-    if (w.given_up[s.asked] == 0ull) return;
+    __shared__ int goes;
+    if (w.given_up[0] == 0ull) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t first = ((int64_t)wave * gridDim.x + blockIdx.x) * 64, stride = (int64_t)64 * kStepWaves * gridDim.x;
+    // A workgroup that begins says so, unless the first has given up by then; that goes on alone when those that began have left: they
+    // wait for nobody for longer than it did, and what they wrote must not come after what it writes.
+    unsigned long long* const state = w.colmax + 4 * s.few;
+    if (blockIdx.x > 0) {
+        if (threadIdx.x == 0) goes = atomicCAS(state + blockIdx.x, kNotBegun, kBegun) == kNotBegun;
+        __syncthreads();
+        if (!goes) return;
+    }
+    int workgroups = gridDim.x;
+    int64_t first = ((int64_t)wave * workgroups + blockIdx.x) * 64, stride = (int64_t)64 * kStepWaves * workgroups;
     const int64_t block = block_of(chosen_key(w, s.partials, red));
     const bool writes = blockIdx.x == 0;                     // this workgroup has the product R^(t) and the results
     unsigned long long top = 0ull;                           // the largest magnitude this lane has seen, and its smallest channel
@@ -651,15 +962,24 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(Con
         top = more ? a : top;
         channel = more ? c : channel;
     };
-    for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) product[e] = best[e] = e / 32 == e % 32 ? 1.0 : 0.0;
-    for (int64_t r = first + lane; r < p.T; r += stride)
-        for (int c = 0; c < 32; ++c) {
-            const double v = (double)__uint_as_float((uint32_t)p.x[r * p.ldx + 32 * block + c] << 16);
-            w.z[r * 32 + c] = v;
-            seen(v, c);
-        }
     unsigned long long lowest = ~0ull;
     int steps_kept = 0;
+    auto begin = [&]() {
+        top = 0ull;
+        channel = 32;
+        lowest = ~0ull;
+        steps_kept = 0;
+        for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) product[e] = best[e] = e / 32 == e % 32 ? 1.0 : 0.0;
+#pragma unroll 1
+        for (int64_t r = first + lane; r < p.T; r += stride)
+#pragma unroll 1
+            for (int c = 0; c < 32; ++c) {
+                const double v = (double)__uint_as_float((uint32_t)p.x[r * p.ldx + 32 * block + c] << 16);
+                w.z[r * 32 + c] = v;
+                seen(v, c);
+            }
+    };
+    begin();
     for (int t = 0;; ++t) {
         // the workgroup's largest magnitude and the smallest channel it stands in
         auto smallest_channel = [&](unsigned long long v, int c, unsigned long long of) { return 32 - (int)wave_max(v == of ? 32 - c : 0); };
@@ -673,14 +993,14 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(Con
             int c = lane < kStepWaves ? red_channel[lane] : 32;
             unsigned long long peak = wave_max(v);
             int d = smallest_channel(v, c, peak);
-            if (gridDim.x > 1) {                             // among all, by the rules of the search kernel's exchange
+            if (workgroups > 1) {                            // among all, by the rules of the search kernel's exchange
                 const unsigned long long there = (unsigned long long)((t >> 1) & 1) << 63;
-                unsigned long long* const set = w.colmax + (t & 1) * 2 * gridDim.x;
+                unsigned long long* const set = w.colmax + (t & 1) * 2 * workgroups;
                 if (lane == 0) {
                     __hip_atomic_store(set + 2 * blockIdx.x, peak | there, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     __hip_atomic_store(set + 2 * blockIdx.x + 1, (unsigned long long)d | there, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                const unsigned long long* const theirs = set + 2 * (lane < (int)gridDim.x ? lane : (int)gridDim.x - 1);
+                const unsigned long long* const theirs = set + 2 * (lane < workgroups ? lane : workgroups - 1);
                 unsigned long long dd;
                 uint32_t looks = 0;
                 bool missing;
@@ -699,8 +1019,23 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(Con
         const unsigned long long peak = peak_of_all;
         const int d = channel_of_all;
         if (d < 0) {                                         // the same for every thread of the workgroup
-            if (threadIdx.x == 0) __hip_atomic_store(w.given_up + s.asked + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __syncthreads();
+            if (!writes) {
+                if (threadIdx.x == 0) __hip_atomic_store(state + blockIdx.x, kLeft, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+            if (threadIdx.x == 0) w.given_up[1] = 1ull;
+            if (threadIdx.x > 0 && (int)threadIdx.x < workgroups && atomicCAS(state + threadIdx.x, kNotBegun, kLeft) == kBegun)
+                while (__hip_atomic_load(state + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kLeft) __builtin_amdgcn_s_sleep(64);
+            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            workgroups = 1;
+            first = wave * 64;
+            stride = 64 * kStepWaves;
+            begin();
+            t = -1;
+            continue;
         }
         if (writes && p.peaks && threadIdx.x == 0) p.peaks[t] = __longlong_as_double((long long)peak);
         if (peak < lowest) {
@@ -773,15 +1108,16 @@ bool plan_search(int64_t T, int steps, int form, int cus, SearchPlan& s) {
     const int64_t rows = 16 << (form - DUQPP_CONSTRUCT_ONE_16), tiles = (T + rows - 1) / rows, all = tiles + (rows < 32 ? 2 : 1);
     if (all > (form == DUQPP_CONSTRUCT_ONE_16 ? cus : 2 * (int64_t)cus) || (int64_t)exchange_bytes((int)all) > T * 256) return false;
     // of the search behind it: not more than have rows, nor than the place of their words holds
-    const int64_t waves = (T + 63) / 64, room = 8 * ((int64_t)steps + 1);
+    const int64_t waves = (T + 63) / 64, room = 31 * ((int64_t)steps + 1) / 5;
     int64_t few = waves < kFewWorkgroups ? waves : kFewWorkgroups;
     few = few < room ? few : room;
-    s = SearchPlan{0, (int)tiles, (int)all, kPatience, cus, (int)few, 0};
+    s = SearchPlan{0, (int)tiles, (int)all, kPatience, cus, (int)few};
     return true;
 }
 
-hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form, uint32_t patience_again, hipStream_t stream) {
+hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form, bool rows, uint32_t patience_again, hipStream_t stream) {
     hipError_t e = launch(construct_prepare_kernel, dim3((unsigned)(s.partials + p.steps)), dim3(256), 0, stream, p, s);
+    if (e == hipSuccess && rows) e = launch(construct_rows_kernel, dim3(kRowsWorkgroups), dim3(64 * kRowsWaves), 0, stream, p, s);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)s.participants), block(64 * kStepWaves);
     if (form == DUQPP_CONSTRUCT_ONE_16)
@@ -793,12 +1129,7 @@ hipError_t launch_search(const ConstructParams& p, const SearchPlan& s, int form
     if (e != hipSuccess) return e;
     SearchPlan again = s;
     again.patience = patience_again;
-    if (s.few > 1) {
-        e = launch(construct_again_kernel, dim3((unsigned)s.few), block, 0, stream, p, again);
-        if (e != hipSuccess) return e;
-        again.asked = 1;
-    }
-    return launch(construct_again_kernel, dim3(1), block, 0, stream, p, again);
+    return launch(construct_again_kernel, dim3((unsigned)s.few), block, 0, stream, p, again);
 }
 
 hipError_t launch_steps(const ConstructParams& p, int partials, hipStream_t stream) {
@@ -838,7 +1169,8 @@ hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStrea
     plan_search(p.T, p.steps, form, cus, s);
     s.partials = partials;
     if (how & DUQPP_CONSTRUCT_IMPATIENT) s.patience = 0;
-    return launch_search(p, s, form, (how & DUQPP_CONSTRUCT_ALONE) == DUQPP_CONSTRUCT_ALONE ? 0 : kPatienceAgain, stream);
+    const bool rows = how == DUQPP_CONSTRUCT_AUTO && p.T <= kRowsScanned;
+    return launch_search(p, s, form, rows, (how & DUQPP_CONSTRUCT_ALONE) == DUQPP_CONSTRUCT_ALONE ? 0 : kPatienceAgain, stream);
 }
 
 }  // namespace duqpp
