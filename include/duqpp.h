@@ -168,6 +168,17 @@ int duqpp_group_error_ws(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, 
                          float* err, double* mean, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * The ratios, and instead of their mean what it is formed from: a sum and a count of every workgroup, in memory that the caller may have
+ * on the host (pinned, that the device can write).  One launch; duqpp_group_error_mean forms the mean of them there, in a fixed order, once
+ * the stream has been waited for.  It is duqpp_group_error's but for the order of the additions in fp64, from 65536 ratios on bit for bit.
+ *   partials   at least duqpp_group_error_partials_bytes(T, K) bytes (those that are used), 8-byte aligned
+ */
+size_t duqpp_group_error_partials_bytes(int64_t T, int64_t K);   /* host, pure; 0 for invalid arguments */
+int duqpp_group_error_partials(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const float* R, int64_t n_rblocks,
+                               float* err, double* partials, size_t partials_bytes, void* stream);
+double duqpp_group_error_mean(const double* partials, size_t partials_bytes);   /* host, pure; the bytes that are used */
+
+/*
  * TEST ONLY: runs the quantiser stage of duqpp_rotate_quantize (group amax, E8M0 scale,
  * E2M1 rounding, packing -- Eq. 2) on caller-supplied fp32 values, so that every fp32 bit
  * pattern can be swept through the device code.

@@ -46,6 +46,12 @@ def _load():
     L.duqpp_group_error_ws.restype = ci
     L.duqpp_group_error_workspace_bytes.argtypes = [i64, i64]
     L.duqpp_group_error_workspace_bytes.restype = sz
+    L.duqpp_group_error_partials.argtypes = [vp, i64, i64, i64, fp, i64, fp, vp, sz, vp]
+    L.duqpp_group_error_partials.restype = ci
+    L.duqpp_group_error_partials_bytes.argtypes = [i64, i64]
+    L.duqpp_group_error_partials_bytes.restype = sz
+    L.duqpp_group_error_mean.argtypes = [vp, sz]
+    L.duqpp_group_error_mean.restype = ctypes.c_double
     L.duqpp_gemm_workspace_bytes.argtypes = [i64, i64, i64, ci]
     L.duqpp_gemm_workspace_bytes.restype = sz
     L.duqpp_validate_rotate_quantize.argtypes = [vp, i64, i64, i64, fp, i64, u8p, u8p]
@@ -153,7 +159,7 @@ def _load_calls():
         return _NoCalls
     names = ("duqpp_rotq_gemm_tiled_packed", "duqpp_rotq_gemm_tiled", "duqpp_rotq_gemm", "duqpp_gemm_workspace_bytes",
              "duqpp_rotate_quantize_tiled_packed", "duqpp_rotate_quantize_tiled", "duqpp_quantize_weights_tiled",
-             "duqpp_mxfp4_gemm_tiled", "duqpp_group_error_ws", "duqpp_group_error_workspace_bytes")
+             "duqpp_mxfp4_gemm_tiled", "duqpp_group_error_partials", "duqpp_group_error_partials_bytes", "duqpp_group_error_mean")
     _calls.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names}, _stream)
     return _calls
 
@@ -332,14 +338,21 @@ def group_error(x, R=None, return_mean=True):
             raise ValueError("R must be a contiguous [n, 32, 32] tensor")
         nrb = R.shape[0]
     err = torch.empty((T, K // 32), dtype=torch.float32, device=x.device)
-    mean = torch.empty(1, dtype=torch.float64, device=x.device) if return_mean else None
-    nbytes = lib.duqpp_group_error_workspace_bytes(T, K) if return_mean else 0
-    ws, _ = _workspace(nbytes, x.device)
-    st = lib.duqpp_group_error_ws(x.data_ptr(), T, K, x.stride(0), R.data_ptr() if R is not None else None, nrb,
-                                  err.data_ptr(), mean.data_ptr() if mean is not None else None,
-                                  ws.data_ptr() if ws is not None else None, nbytes, _stream())
-    _check(st, "duqpp_group_error")
-    return err, (float(mean.item()) if mean is not None else None)
+    args = (x.data_ptr(), T, K, x.stride(0), R.data_ptr() if R is not None else None, nrb, err.data_ptr())
+    if not return_mean:
+        _check(lib.duqpp_group_error(*args, None, _stream()), "duqpp_group_error")
+        return err, None
+    nbytes = lib.duqpp_group_error_partials_bytes(T, K)
+    if nbytes > 65536:                                       # more sums than the host should add: rows of a million channels
+        nbytes = lib.duqpp_group_error_workspace_bytes(T, K)
+        ws, _ = _workspace(nbytes, x.device)
+        mean = torch.empty(1, dtype=torch.float64, device=x.device)
+        _check(lib.duqpp_group_error_ws(*args, mean.data_ptr(), ws.data_ptr() if ws is not None else None, nbytes, _stream()), "duqpp_group_error")
+        return err, float(mean.item())
+    partials = torch.empty(max(nbytes, 8) // 8, dtype=torch.float64, device=x.device)
+    _check(lib.duqpp_group_error_partials(*args, partials.data_ptr(), nbytes, _stream()), "duqpp_group_error")
+    partials = partials.cpu()
+    return err, lib.duqpp_group_error_mean(partials.data_ptr(), nbytes)
 
 
 # ---------------------------------------------------------------- tiled operand layout

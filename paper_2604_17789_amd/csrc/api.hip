@@ -275,16 +275,17 @@ int duqpp_group_error(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, con
     return duqpp_group_error_ws(x_bf16, T, K, ldx, R, n_rblocks, err, mean, nullptr, 0, stream);
 }
 
-int duqpp_group_error_ws(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const float* R, int64_t n_rblocks,
-                         float* err, double* mean, void* workspace, size_t workspace_bytes, void* stream) {
-    if (!x_bf16 || !err) return DUQPP_ERR_NULL;
+static int group_error_impl(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const float* R, int64_t n_rblocks,
+                            float* err, double* mean, void* partials, size_t partials_bytes, bool mean_by_caller, void* stream) {
+    if (!x_bf16 || !err || (mean_by_caller && !partials)) return DUQPP_ERR_NULL;
     int st = validate_rows_K(T, K, ldx, R ? n_rblocks : 1);
     if (st != DUQPP_OK) return st;
     if ((T + 31) / 32 > kGroupErrorMaxTiles) return DUQPP_ERR_TOO_LARGE;
     if (!aligned_to(x_bf16, 16) || (ldx % 8) != 0) return DUQPP_ERR_ALIGN;
     if ((R && !aligned_to(R, 4)) || !aligned_to(err, 4) || (mean && !aligned_to(mean, 8))) return DUQPP_ERR_ALIGN;
-    if (workspace && !aligned_to(workspace, 8)) return DUQPP_ERR_ALIGN;
-    if (workspace && workspace_bytes < group_error_workspace_bytes(T, K / 32)) return DUQPP_ERR_WORKSPACE;
+    if (partials && !aligned_to(partials, 8)) return DUQPP_ERR_ALIGN;
+    const size_t needed = mean_by_caller ? group_error_partials_bytes(T, K / 32) : group_error_workspace_bytes(T, K / 32);
+    if (partials && partials_bytes < needed) return DUQPP_ERR_WORKSPACE;
     st = check_device();
     if (st != DUQPP_OK) return st;
     GroupErrorParams p{};
@@ -296,9 +297,26 @@ int duqpp_group_error_ws(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, 
     p.r_stride = (n_rblocks == 1) ? 0 : 32 * 32;
     p.err = err;
     p.mean = mean;
-    p.partials = static_cast<float*>(workspace);
-    return launch_group_error(p, static_cast<hipStream_t>(stream)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
+    p.partials = static_cast<float*>(partials);
+    return launch_group_error(p, mean_by_caller, static_cast<hipStream_t>(stream)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
 }
+
+int duqpp_group_error_ws(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const float* R, int64_t n_rblocks,
+                         float* err, double* mean, void* workspace, size_t workspace_bytes, void* stream) {
+    return group_error_impl(x_bf16, T, K, ldx, R, n_rblocks, err, mean, workspace, workspace_bytes, false, stream);
+}
+
+size_t duqpp_group_error_partials_bytes(int64_t T, int64_t K) {
+    if (validate_rows_K(T, K, K, 1) != DUQPP_OK || (T + 31) / 32 > kGroupErrorMaxTiles) return 0;
+    return group_error_partials_bytes(T, K / 32);
+}
+
+int duqpp_group_error_partials(const void* x_bf16, int64_t T, int64_t K, int64_t ldx, const float* R, int64_t n_rblocks,
+                               float* err, double* partials, size_t partials_bytes, void* stream) {
+    return group_error_impl(x_bf16, T, K, ldx, R, n_rblocks, err, nullptr, partials, partials_bytes, true, stream);
+}
+
+double duqpp_group_error_mean(const double* partials, size_t partials_bytes) { return group_error_mean(partials, partials_bytes); }
 
 int duqpp_quantize_f32_dbg(const float* y, int64_t rows, int64_t K, int64_t ldy, uint8_t* codes,
                            uint8_t* scales, void* stream) {

@@ -31,8 +31,9 @@ decltype(&duqpp_rotate_quantize_tiled_packed) rotate_quantize_tiled_packed;
 decltype(&duqpp_rotate_quantize_tiled) rotate_quantize_tiled;
 decltype(&duqpp_quantize_weights_tiled) quantize_weights_tiled;
 decltype(&duqpp_mxfp4_gemm_tiled) mxfp4_gemm_tiled;
-decltype(&duqpp_group_error_ws) group_error_ws;
-decltype(&duqpp_group_error_workspace_bytes) group_error_workspace_bytes;
+decltype(&duqpp_group_error_partials) group_error_partials;
+decltype(&duqpp_group_error_partials_bytes) group_error_partials_bytes;
+decltype(&duqpp_group_error_mean) group_error_mean;
 PyObject* current_stream;                                // the binding's function that answers it as an integer
 
 // The Python threads run while the object lives.
@@ -257,8 +258,8 @@ PyObject* product(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// error(x, R or None) -> (err, mean): the mean comes by host memory that the kernel writes, one wait for the stream instead
-// of a copy back and its own.
+// error(x, R or None) -> (err, mean): what the mean is formed from comes by host memory that the kernel writes, one wait for the
+// stream instead of another launch, a copy back and its own.
 PyObject* error(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         void* stream;
@@ -266,25 +267,23 @@ PyObject* error(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor *x = matrix(a[0], at::kBFloat16), *R = nullptr;
         if (!x || !sizes_ok(x->size(0), x->size(1))) Py_RETURN_NONE;
         if (a[1] != Py_None && !(R = blocks(a[1]))) Py_RETURN_NONE;
-        if (!stream_of_call(stream)) Py_RETURN_NONE;
         const int64_t T = x->size(0), K = x->size(1);
+        const size_t bytes = group_error_partials_bytes(T, K);
+        if (bytes == 0 || bytes > 65536 || !stream_of_call(stream)) Py_RETURN_NONE;
         at::Tensor err;
         double mean = 0.0;
         int status;
         {
             WithoutGil threads;
             err = device_empty({T, K / 32}, at::kFloat, *x);
-            const at::Tensor m = at::empty({1}, at::TensorOptions().dtype(at::kDouble).pinned_memory(true));
-            const size_t scratch = group_error_workspace_bytes(T, K);
-            at::Tensor ws;
-            if (scratch) ws = device_empty({(int64_t)scratch}, at::kByte, *x);
-            status = group_error_ws(x->data_ptr(), T, K, x->stride(0), R ? static_cast<const float*>(R->data_ptr()) : nullptr, R ? R->size(0) : 1,
-                                    static_cast<float*>(err.data_ptr()), static_cast<double*>(m.data_ptr()), scratch ? ws.data_ptr() : nullptr,
-                                    scratch, stream);
+            const at::Tensor m = at::empty({(int64_t)bytes / 8}, at::TensorOptions().dtype(at::kDouble).pinned_memory(true));
+            double* const partials = static_cast<double*>(m.data_ptr());
+            status = group_error_partials(x->data_ptr(), T, K, x->stride(0), R ? static_cast<const float*>(R->data_ptr()) : nullptr,
+                                          R ? R->size(0) : 1, static_cast<float*>(err.data_ptr()), partials, bytes, stream);
             if (status == DUQPP_OK) {
                 const c10::impl::VirtualGuardImpl device(c10::DeviceType::CUDA);
                 device.synchronizeStream(device.getStream(device.getDevice()));
-                mean = *static_cast<const double*>(m.data_ptr());
+                mean = group_error_mean(partials, bytes);
             }
         }
         if (status != DUQPP_OK) return PyLong_FromLong(status);
@@ -312,8 +311,8 @@ PyObject* bind(PyObject*, PyObject* args) {
         !take("duqpp_rotq_gemm", rotq_gemm) || !take("duqpp_gemm_workspace_bytes", gemm_workspace_bytes) ||
         !take("duqpp_rotate_quantize_tiled_packed", rotate_quantize_tiled_packed) ||
         !take("duqpp_rotate_quantize_tiled", rotate_quantize_tiled) || !take("duqpp_quantize_weights_tiled", quantize_weights_tiled) ||
-        !take("duqpp_mxfp4_gemm_tiled", mxfp4_gemm_tiled) || !take("duqpp_group_error_ws", group_error_ws) ||
-        !take("duqpp_group_error_workspace_bytes", group_error_workspace_bytes))
+        !take("duqpp_mxfp4_gemm_tiled", mxfp4_gemm_tiled) || !take("duqpp_group_error_partials", group_error_partials) ||
+        !take("duqpp_group_error_partials_bytes", group_error_partials_bytes) || !take("duqpp_group_error_mean", group_error_mean))
         return nullptr;
     Py_INCREF(stream);
     Py_XSETREF(current_stream, stream);

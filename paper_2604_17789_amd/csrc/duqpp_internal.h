@@ -106,7 +106,9 @@ struct GroupErrorMeanParams {
 };
 constexpr int64_t kGroupErrorMaxTiles = 65535;   // tiles of 32 tokens a call takes (DUQPP_ERR_TOO_LARGE beyond)
 size_t group_error_workspace_bytes(int64_t rows, int64_t G);
-hipError_t launch_group_error(const GroupErrorParams& p, hipStream_t stream);
+size_t group_error_partials_bytes(int64_t rows, int64_t G);
+double group_error_mean(const double* partials, size_t bytes);
+hipError_t launch_group_error(const GroupErrorParams& p, bool mean_by_caller, hipStream_t stream);   // true: partials are all that is left
 
 struct QuantDbgParams {
     const float* y; int64_t ldy; int rows; int G; uint8_t* codes; uint8_t* scales;

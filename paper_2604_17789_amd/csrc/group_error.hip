@@ -25,8 +25,9 @@ struct ErrPlan {
     int chunks, runs;                   // workgroups: column chunks x token runs
     int ntiles;                         // token tiles of 32 in play
     int64_t keep_from, keep_to;         // ratios stored: their place in err, in floats
-    int partials;                       // each workgroup's partial sum and count are kept, four words each
+    int partials;                       // each workgroup's partial sum and count are kept: as four words, or (kPairs) as two doubles
 };
+constexpr int kWords = 1, kPairs = 2;
 
 // value of an E2M1 code (sign, two exponent bits, one mantissa bit): 0, 0.5, 1, 1.5, 2, 3, 4, 6
 __device__ __forceinline__ double e2m1_value(uint32_t nib) {
@@ -179,6 +180,10 @@ __global__ __launch_bounds__(64 * (GROUPS == 2 ? kErrWaves : 1)) void group_erro
         double t = 0.0;
         for (int k = 0; k < kWaves; ++k) t += sums[k][threadIdx.x];
         const unsigned long long bits = (unsigned long long)__double_as_longlong(t);
+        if (e.partials == kPairs) {                          // may be host memory: one store each
+            ((double*)p.partials)[((int64_t)run * e.chunks + chunk) * 2 + threadIdx.x] = t;
+            return;
+        }
         uint32_t* out = (uint32_t*)p.partials + ((int64_t)run * e.chunks + chunk) * 4 + 2 * threadIdx.x; // may be err, aligned to a float only
         out[0] = (uint32_t)bits;
         out[1] = (uint32_t)(bits >> 32);
@@ -244,7 +249,30 @@ size_t group_error_workspace_bytes(int64_t rows, int64_t G) {
     return rows * G < kPartialsFrom ? 0 : (size_t)error_workgroups((rows + 31) / 32, G, chunks, runs) * 16;
 }
 
-hipError_t launch_group_error(const GroupErrorParams& call, hipStream_t stream) {
+static bool one_group_each(int64_t tiles, int64_t G) { return tiles * G <= kOneGroupTo; }
+
+size_t group_error_partials_bytes(int64_t rows, int64_t G) {
+    int64_t chunks, runs;
+    const int64_t tiles = (rows + 31) / 32;
+    return (size_t)(one_group_each(tiles, G) ? tiles * G : error_workgroups(tiles, G, chunks, runs)) * 16;
+}
+
+double group_error_mean(const double* partials, size_t bytes) {
+    const int64_t n = (int64_t)(bytes / 16);
+    double sum[1024] = {}, count[1024] = {};                 // in the order of group_error_mean_kernel
+    for (int64_t i = 0; i < n; ++i) {
+        sum[i & 1023] += partials[2 * i];
+        count[i & 1023] += partials[2 * i + 1];
+    }
+    for (int w = 512; w > 0; w >>= 1)
+        for (int i = 0; i < w; ++i) {
+            sum[i] += sum[i + w];
+            count[i] += count[i + w];
+        }
+    return count[0] > 0.0 ? sum[0] / count[0] : 0.0;
+}
+
+hipError_t launch_group_error(const GroupErrorParams& call, bool mean_by_caller, hipStream_t stream) {
     GroupErrorParams p = call;
     const int64_t tiles = ((int64_t)p.rows + 31) / 32;
     if (p.G < 1 || p.rows < 1 || tiles > kGroupErrorMaxTiles) return hipErrorInvalidValue;
@@ -275,6 +303,14 @@ hipError_t launch_group_error(const GroupErrorParams& call, hipStream_t stream) 
         return n <= 2048 ? launch(group_error_mean_kernel<false, 1>, dim3(1), dim3(1024), 0, stream, m)
                          : launch(group_error_mean_kernel<false, 8>, dim3(1), dim3(1024), 0, stream, m);
     };
+    if (mean_by_caller) {                                    // a launch less; the sums of 512 workgroups take the host a microsecond
+        ErrPlan e = plan((int)tiles);
+        e.partials = kPairs;
+        if (!one_group_each(tiles, p.G)) return run(e);
+        e.chunks = p.G;
+        e.runs = (int)tiles;
+        return run_one_group(e);
+    }
     if (tiles * p.G <= (p.R ? kOneGroupTo : 4 * kOneGroupTo) && (!p.mean || n < kPartialsFrom)) {
         ErrPlan one = plan((int)tiles);
         one.chunks = p.G;
@@ -292,7 +328,7 @@ hipError_t launch_group_error(const GroupErrorParams& call, hipStream_t stream) 
     // whose ratios (at most 64 token tiles, with one group per token) are computed once more afterwards.
     const bool scratch = p.partials != nullptr;
     if (!scratch) p.partials = p.err;
-    e.partials = 1;
+    e.partials = kWords;
     e.keep_from = scratch ? 0 : held;
     hipError_t st = run(e);
     if (st != hipSuccess) return st;
