@@ -252,17 +252,19 @@ int duqpp_rotq_gemm(const void* x_bf16, int64_t ldx, const float* R, int64_t n_r
     if (st != DUQPP_OK) return st;
     st = check_device();
     if (st != DUQPP_OK) return st;
-    // one launch rotates and quantises the activations straight into the tiled layout and re-tiles the row-major weights
+    // one launch rotates and quantises the activations straight into the tiled layout and, unless the product takes them as they
+    // are, re-tiles the row-major weights
     hipStream_t hs = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     const TiledScratch w = tiled_scratch(T, N, K);
     const int G = (int)(K / 32), GP = (int)tiled_groups(G);
     const LayoutParams lb{b_codes, b_scales, ws + w.b_codes, ws + w.b_scales, (int)N, G, GP};
-    st = rotate_quantize_impl(x_bf16, T, K, ldx, R, n_rblocks, ws + w.a_codes, ws + w.a_scales, nullptr, stream, true, false, &lb);
+    const bool rows = rows_fit(T, N, K, b_scales);
+    st = rotate_quantize_impl(x_bf16, T, K, ldx, R, n_rblocks, ws + w.a_codes, ws + w.a_scales, nullptr, stream, true, false, rows ? nullptr : &lb);
     if (st != DUQPP_OK) return st;
-    TiledGemmParams p{ws + w.a_codes, ws + w.a_scales, ws + w.b_codes, ws + w.b_scales, (int)T, (int)N, GP,
+    TiledGemmParams p{ws + w.a_codes, ws + w.a_scales, rows ? b_codes : ws + w.b_codes, rows ? b_scales : ws + w.b_scales, (int)T, (int)N, GP,
                       y, ldy, out_dtype == DUQPP_BF16};
-    return launch_gemm_tiled(p, hs) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
+    return (rows ? launch_gemm_rows(p, hs) : launch_gemm_tiled(p, hs)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
 }
 
 size_t duqpp_group_error_workspace_bytes(int64_t T, int64_t K) {

@@ -176,7 +176,10 @@ struct TiledGemmParams {
     const uint8_t* b_codes; const uint8_t* b_scales;   // tiled, N rows
     int T, N, GP;
     void* y; int64_t ldy; int out_bf16;
+    int b_rows;                                        // the weights are in the row-major layout (launch_gemm_rows)
 };
+bool rows_fit(int64_t T, int64_t N, int64_t K, const uint8_t* scales);        // launch_gemm_rows takes such weights, and is the faster way
+hipError_t launch_gemm_rows(const TiledGemmParams& p, hipStream_t stream);
 hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream);     // picks the kernel by shape
 int choose_gemm_kernel(const TiledGemmParams& p);                              // the DUQPP_GEMM_KERNEL_* it picks
 hipError_t launch_gemm_tiled_as(const TiledGemmParams& p, int kernel, hipStream_t stream);   // a named kernel

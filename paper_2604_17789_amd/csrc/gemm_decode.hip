@@ -35,12 +35,14 @@ struct DecStep {
 // no extra traffic -- fetching all 32 rows of a tile that holds a handful of tokens would be more traffic into the CU
 // than the weights -- and their results fall on tokens >= T and are never stored.  Likewise the lanes beyond a
 // half-tile workgroup's 16 rows re-read rows 0..15 (lane_code_b is built from r % ROWS).
-template <int ROWS, int MT>
+// B_ROWS: weights in the row-major layout, where the four groups of a lane lie side by side; the loads are ordinary ones then, the four
+// of a step meeting in the lines of 32 rows.
+template <int ROWS, int MT, bool B_ROWS>
 __device__ __forceinline__ void dec_load(DecStep<MT>& d, const uint8_t* a_codes, const uint8_t* a_scales,
                                          const int64_t (&a_off)[MT], const int64_t (&a_soff)[MT],
-                                         const uint8_t* b_codes, const uint8_t* b_scales, int step, int lane_code_b,
-                                         int lane4_b) {
-    const uint8_t* pb = b_codes + (int64_t)step * 4096 + lane_code_b;
+                                         const uint8_t* b_codes, const uint8_t* b_scales, int step, int64_t lane_code_b,
+                                         int64_t lane4_b) {
+    const uint8_t* pb = b_codes + (int64_t)step * (B_ROWS ? 128 : 4096) + lane_code_b;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         const uint8_t* pa = a_codes + a_off[m] + (int64_t)step * 4096;
@@ -50,8 +52,8 @@ __device__ __forceinline__ void dec_load(DecStep<MT>& d, const uint8_t* a_codes,
     }
     // weights are read once
 #pragma unroll
-    for (int i = 0; i < 4; ++i) d.b[i] = __builtin_nontemporal_load((const u32x4*)(pb + i * 512));
-    d.sb = *(const uint32_t*)(b_scales + (int64_t)step * 256 + lane4_b);
+    for (int i = 0; i < 4; ++i) d.b[i] = B_ROWS ? *(const u32x4*)(pb + i * 16) : __builtin_nontemporal_load((const u32x4*)(pb + i * 512));
+    d.sb = *(const uint32_t*)(b_scales + (int64_t)step * (B_ROWS ? 8 : 256) + lane4_b);
 }
 
 // Products behind this stay behind the requests ahead of it.  Both ways out of the loops below begin with the products of `even`, and
@@ -65,7 +67,7 @@ __device__ __forceinline__ void requested_first(V (&acc)[N]) {
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(acc[i]));
 }
 
-template <bool OUT_BF16, int ROWS, int MT>
+template <bool OUT_BF16, int ROWS, int MT, bool B_ROWS>
 __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmParams p) {
     static_assert(ROWS == 32 || ROWS == 16, "a row tile is cut into 1 or 2 workgroups");
     __shared__ float part[kDecWaves][16][64];              // [wave][accumulator register][lane]
@@ -90,8 +92,9 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmPa
     const int m0 = blockIdx.y * MT;
     // A operand (activations): group 4 g + i of row r sits at (4 g + i) * 512 + r * 16, its scale word at
     // (32 g + r) * 4; B operand (weights): the same with row rb
-    const int lane_code = g * 2048 + r * 16, lane_code_b = g * 2048 + rb * 16;
-    const int lane4 = lane * 4, lane4_b = (g * 32 + rb) * 4;
+    const int lane_code = g * 2048 + r * 16, lane4 = lane * 4;
+    const int64_t lane_code_b = B_ROWS ? (int64_t)rb * p.GP * 16 + g * 64 : g * 2048 + rb * 16;
+    const int64_t lane4_b = B_ROWS ? (int64_t)rb * p.GP + g * 4 : (g * 32 + rb) * 4;
     // per activation row tile: this lane's token row, or row 0 of the first tile when it has none
     int64_t a_off[MT], a_soff[MT];
 #pragma unroll
@@ -123,10 +126,10 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmPa
         // 1-4 % faster than the two-set form below (8192 x 8192, T = 32: 8.7 against 9.0 us).
         if (s0 < s1) {
             DecStep<MT> cur, nxt;
-            dec_load<ROWS, MT>(cur, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s0, lane_code_b, lane4_b);
+            dec_load<ROWS, MT, B_ROWS>(cur, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s0, lane_code_b, lane4_b);
             for (int s = s0; s < s1; ++s) {
                 if (s + 1 < s1)
-                    dec_load<ROWS, MT>(nxt, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
+                    dec_load<ROWS, MT, B_ROWS>(nxt, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
                 mfmas(cur);
                 cur = nxt;
             }
@@ -136,22 +139,22 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode_kernel(TiledGemmPa
         // load, or a copy from one set to the other, the compiler's wait covers the loads just issued as well and
         // only one step is ever in flight.
         DecStep<MT> even, odd;
-        dec_load<ROWS, MT>(even, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s0, lane_code_b, lane4_b);
+        dec_load<ROWS, MT, B_ROWS>(even, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s0, lane_code_b, lane4_b);
         int s = s0;
         for (; s + 2 < s1; s += 2) {
             // (the barriers keep the scheduler from gathering all loads of the round at its top, which again ends
             // every round with nothing in flight)
-            dec_load<ROWS, MT>(odd, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
+            dec_load<ROWS, MT, B_ROWS>(odd, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(even);
             __builtin_amdgcn_sched_barrier(0);
-            dec_load<ROWS, MT>(even, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 2, lane_code_b, lane4_b);
+            dec_load<ROWS, MT, B_ROWS>(even, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 2, lane_code_b, lane4_b);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(odd);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (s + 1 < s1) {
-            dec_load<ROWS, MT>(odd, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
+            dec_load<ROWS, MT, B_ROWS>(odd, p.a_codes, p.a_scales, a_off, a_soff, b_codes, b_scales, s + 1, lane_code_b, lane4_b);
             requested_first(acc);
             mfmas(even);
             mfmas(odd);
@@ -197,19 +200,25 @@ struct Dec16Step {
     uint32_t sa[2], sb[2];
 };
 
+template <bool B_ROWS>
 __device__ __forceinline__ void dec16_load(Dec16Step& d, const uint8_t* a_codes, const uint8_t* a_scales,
                                            const uint8_t* b_codes, const uint8_t* b_scales, int step, int off_a,
-                                           int soff_a, int off_b, int soff_b) {
+                                           int soff_a, int64_t off_b, int64_t soff_b) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         d.a[q] = *(const u32x4*)(a_codes + (int64_t)step * 4096 + q * 2048 + off_a);
         d.sa[q] = a_scales[(int64_t)step * 256 + q * 128 + soff_a];
-        d.b[q] = __builtin_nontemporal_load((const u32x4*)(b_codes + (int64_t)step * 4096 + q * 2048 + off_b));
-        d.sb[q] = b_scales[(int64_t)step * 256 + q * 128 + soff_b];
+        if constexpr (B_ROWS) {
+            d.b[q] = *(const u32x4*)(b_codes + (int64_t)step * 128 + q * 64 + off_b);
+            d.sb[q] = b_scales[(int64_t)step * 8 + q * 4 + soff_b];
+        } else {
+            d.b[q] = __builtin_nontemporal_load((const u32x4*)(b_codes + (int64_t)step * 4096 + q * 2048 + off_b));
+            d.sb[q] = b_scales[(int64_t)step * 256 + q * 128 + soff_b];
+        }
     }
 }
 
-template <bool OUT_BF16>
+template <bool OUT_BF16, bool B_ROWS>
 __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode16_kernel(TiledGemmParams p) {
     __shared__ float part[kDecWaves][4][64];               // [wave][accumulator register][lane]
     const int lane = threadIdx.x & 63;
@@ -228,7 +237,8 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode16_kernel(TiledGemm
     // (lanes without a token re-read token 0: no branch around a load, no extra cache line; their results are tokens >= T)
     const int ca = c < p.T ? c : 0;
     const int off_a = g * 512 + ca * 16, soff_a = ca * 4 + g;
-    const int off_b = g * 512 + rb * 16, soff_b = rb * 4 + g;
+    const int64_t off_b = B_ROWS ? (int64_t)rb * p.GP * 16 + g * 16 : g * 512 + rb * 16;
+    const int64_t soff_b = B_ROWS ? (int64_t)rb * p.GP + g : rb * 4 + g;
 
     f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     auto mfmas = [&](const Dec16Step& d) {
@@ -239,20 +249,20 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode16_kernel(TiledGemm
     };
     if (s0 < s1) {                                         // two register sets taking turns, as above
         Dec16Step even, odd;
-        dec16_load(even, p.a_codes, p.a_scales, b_codes, b_scales, s0, off_a, soff_a, off_b, soff_b);
+        dec16_load<B_ROWS>(even, p.a_codes, p.a_scales, b_codes, b_scales, s0, off_a, soff_a, off_b, soff_b);
         int s = s0;
         for (; s + 2 < s1; s += 2) {
-            dec16_load(odd, p.a_codes, p.a_scales, b_codes, b_scales, s + 1, off_a, soff_a, off_b, soff_b);
+            dec16_load<B_ROWS>(odd, p.a_codes, p.a_scales, b_codes, b_scales, s + 1, off_a, soff_a, off_b, soff_b);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(even);
             __builtin_amdgcn_sched_barrier(0);
-            dec16_load(even, p.a_codes, p.a_scales, b_codes, b_scales, s + 2, off_a, soff_a, off_b, soff_b);
+            dec16_load<B_ROWS>(even, p.a_codes, p.a_scales, b_codes, b_scales, s + 2, off_a, soff_a, off_b, soff_b);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(odd);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (s + 1 < s1) {
-            dec16_load(odd, p.a_codes, p.a_scales, b_codes, b_scales, s + 1, off_a, soff_a, off_b, soff_b);
+            dec16_load<B_ROWS>(odd, p.a_codes, p.a_scales, b_codes, b_scales, s + 1, off_a, soff_a, off_b, soff_b);
             requested_first(acc);
             mfmas(even);
             mfmas(odd);
@@ -280,8 +290,11 @@ __global__ __launch_bounds__(kDecWaves * 64) void gemm_decode16_kernel(TiledGemm
 template <int ROWS, int MT>
 static hipError_t launch_decode_rows(const TiledGemmParams& p, hipStream_t stream) {
     dim3 grid((unsigned)((p.N + 31) / 32 * (32 / ROWS)), (unsigned)((p.T + 32 * MT - 1) / (32 * MT))), block(kDecWaves * 64);
-    return p.out_bf16 ? launch(gemm_decode_kernel<true, ROWS, MT>, grid, block, 0, stream, p)
-                      : launch(gemm_decode_kernel<false, ROWS, MT>, grid, block, 0, stream, p);
+    if (p.b_rows)
+        return p.out_bf16 ? launch(gemm_decode_kernel<true, ROWS, MT, true>, grid, block, 0, stream, p)
+                          : launch(gemm_decode_kernel<false, ROWS, MT, true>, grid, block, 0, stream, p);
+    return p.out_bf16 ? launch(gemm_decode_kernel<true, ROWS, MT, false>, grid, block, 0, stream, p)
+                      : launch(gemm_decode_kernel<false, ROWS, MT, false>, grid, block, 0, stream, p);
 }
 
 // Which of this file's kernels runs a call, kNone: none of them, the tiles of gemm_tiled.hip that stream the weights do.
@@ -324,8 +337,11 @@ hipError_t launch_gemm_decode(const TiledGemmParams& p, hipStream_t stream) {
     switch (split_of(p)) {
         case kHalf16: {
             dim3 grid((unsigned)((p.N + 31) / 32 * 2)), block(kDecWaves * 64);
-            return p.out_bf16 ? launch(gemm_decode16_kernel<true>, grid, block, 0, stream, p)
-                              : launch(gemm_decode16_kernel<false>, grid, block, 0, stream, p);
+            if (p.b_rows)
+                return p.out_bf16 ? launch(gemm_decode16_kernel<true, true>, grid, block, 0, stream, p)
+                                  : launch(gemm_decode16_kernel<false, true>, grid, block, 0, stream, p);
+            return p.out_bf16 ? launch(gemm_decode16_kernel<true, false>, grid, block, 0, stream, p)
+                              : launch(gemm_decode16_kernel<false, false>, grid, block, 0, stream, p);
         }
         case kHalf: return launch_decode_rows<16, 1>(p, stream);
         case kWhole: return launch_decode_rows<32, 1>(p, stream);

@@ -97,7 +97,7 @@ __device__ __forceinline__ void arrive() {
 // Every LDS access this wave has issued has completed, then workgroup barrier.
 __device__ __forceinline__ void workgroup_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int MT, int NT, int D, int W>
+template <int MT, int NT, int D, int W, bool B_ROWS = false>
 struct Tile {
     static constexpr int kBM = 32 * MT, kBN = 32 * NT * W;
     static constexpr int kScalesOff = MT * kTileStepBytes;    // scale words follow the codes in a stage
@@ -108,7 +108,7 @@ struct Tile {
     static constexpr int kSOps = (MT + W - 1) / W;            // scale transfers per wave and step
     static constexpr int kDma = kCOps + kSOps;                // LDS-DMA transfers per wave and step
     static constexpr int kOps = kDma + 5 * NT;                // all requests per wave and step, in the order they complete
-    static constexpr int kLate = 2 * NT;                      // of them behind the step's wait
+    static constexpr int kLate = (B_ROWS ? 5 : 2) * NT;       // of them behind the step's wait
     static constexpr int kPitch = 64 * NT + 16;               // a row of the bf16 transpose
     static constexpr int kEpBytes = 32 * kPitch;
     static constexpr int kLdsBytes = kStages * kStageBytes > W * kEpBytes ? kStages * kStageBytes : W * kEpBytes;
@@ -160,10 +160,14 @@ __device__ __forceinline__ void tile_of_workgroup(int tiles_m, int tiles_n, int&
 }
 
 // The tile of MT token row tiles from row_tile and of channels tile_n.
-template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
+// B_ROWS: the weights are in the row-major layout (rows_fit), the 64 code bytes of a lane's four groups side by side and its four
+// scales a word of the row.  A request is then half of a line's sixteenth from each of 32 rows, so the four of a fragment are made one
+// behind the other at the end of the step, for the lines to be fetched from L2 once.
+template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC, bool B_ROWS = false>
 __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile, int tile_n, LdsBytes __restrict__ staged,
                                           LdsBytes __restrict__ lds) {
-    using TL = Tile<MT, NT, D, W>;
+    using TL = Tile<MT, NT, D, W, B_ROWS>;
+    constexpr int kStepB = B_ROWS ? 128 : kTileStepBytes, kStepBs = B_ROWS ? 8 : 256, kNextB = B_ROWS ? 16 : 512;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, g = lane >> 5;
@@ -198,7 +202,10 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         b_src[n] = p.b_codes + rt * tile_bytes;
         bs_src[n] = p.b_scales + rt * tile_sbytes;
     }
-    const uint32_t voff_dma = wave * (TL::kPieces * 1024) + lane * 16, voff_word = lane * 4, voff_b = g * 2048 + r * 16;
+    const uint32_t voff_dma = wave * (TL::kPieces * 1024) + lane * 16, voff_word = lane * 4;
+    const uint32_t row_bytes = (uint32_t)p.GP * 16;        // of row-major codes
+    uint32_t voff_b = B_ROWS ? r * row_bytes + g * 64 : g * 2048 + r * 16;
+    const uint32_t voff_bs = B_ROWS ? (uint32_t)r * p.GP + g * 4 : voff_word;
     const LdsBytes a_dst = staged + wave * (TL::kPieces * 1024);
 
     // No branch: the K loop has to stay one straight piece of code, or the compiler moves products out from between the
@@ -214,9 +221,10 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         as_src += more * 256;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
-            b_src[n] = (const uint8_t*)((((uint64_t)b_src[n] + kTileStepBytes) & keep) | zeros);
-            bs_src[n] += more * 256;
+            b_src[n] = (const uint8_t*)((((uint64_t)b_src[n] + kStepB) & keep) | zeros);
+            bs_src[n] += more * kStepBs;
         }
+        if constexpr (B_ROWS) voff_b = more ? voff_b : 0u; // within the zero codes
     };
 
     u32x4 b[D][NT][4];
@@ -241,10 +249,10 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         unroll<NT>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
             b[d][n][0] = request_b128<0>(voff_b, b_src[n]);
-            b[d][n][1] = request_b128<512>(voff_b, b_src[n]);
-            b[d][n][2] = request_b128<1024>(voff_b, b_src[n]);
-            b[d][n][3] = request_b128<1536>(voff_b, b_src[n]);
-            sb[d][n] = request_b32(voff_word, bs_src[n]);
+            b[d][n][1] = request_b128<kNextB>(voff_b, b_src[n]);
+            b[d][n][2] = request_b128<2 * kNextB>(voff_b, b_src[n]);
+            b[d][n][3] = request_b128<3 * kNextB>(voff_b, b_src[n]);
+            sb[d][n] = request_b32(voff_bs, bs_src[n]);
         });
         advance();
         __builtin_amdgcn_sched_barrier(0);                 // the waits count on the steps' order
@@ -293,7 +301,7 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
                     DUQPP_MFMA(acc[m][n], fa[Q & 1][m], b[P][n][Q], sa[P & 1][m], sb[P][n], Q);
                     DUQPP_PIN;
                 });
-                if constexpr (MORE) b[P][n][Q] = request_b128<Q * 512>(voff_b, b_src[n]);
+                if constexpr (MORE && !B_ROWS) b[P][n][Q] = request_b128<Q * kNextB>(voff_b, b_src[n]);
                 DUQPP_PIN;
             });
         });
@@ -316,8 +324,13 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
                 DUQPP_PIN;
             });
             if constexpr (MORE) {
-                b[P][n][3] = request_b128<1536>(voff_b, b_src[n]);
-                sb[P][n] = request_b32(voff_word, bs_src[n]);
+                if constexpr (B_ROWS) {
+                    b[P][n][0] = request_b128<0>(voff_b, b_src[n]);
+                    b[P][n][1] = request_b128<kNextB>(voff_b, b_src[n]);
+                    b[P][n][2] = request_b128<2 * kNextB>(voff_b, b_src[n]);
+                }
+                b[P][n][3] = request_b128<3 * kNextB>(voff_b, b_src[n]);
+                sb[P][n] = request_b32(voff_bs, bs_src[n]);
                 DUQPP_PIN;
             }
         });
@@ -402,6 +415,16 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
     gemm_tile<OUT_BF16, MT, NT, D, W, OCC>(p, tile_m * MT, tile_n, (LdsBytes)lds, (LdsBytes)lds);
 }
 
+// The same with row-major weights.
+template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
+__global__ __launch_bounds__(64 * W, OCC) void gemm_rows_kernel(TiledGemmParams p) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    using TL = Tile<MT, NT, D, W>;
+    int tile_m, tile_n;
+    tile_of_workgroup<OCC>((p.T + TL::kBM - 1) / TL::kBM, p.N / TL::kBN, tile_m, tile_n);
+    gemm_tile<OUT_BF16, MT, NT, D, W, OCC, true>(p, tile_m * MT, tile_n, (LdsBytes)lds, (LdsBytes)lds);
+}
+
 // The same tiles where the token row tiles do not fill them: spread evenly, so that some hold MT of them and the others MT - 1 and
 // do a row tile less, instead of all but the last holding MT and the last doing the work of MT for what is left.  At the power
 // limit the products saved let the others run faster.
@@ -436,6 +459,12 @@ hipError_t allow() {
     hipError_t e = allow_dynamic_lds((const void*)gemm_tiled_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
     if (e != hipSuccess) return e;
     e = allow_dynamic_lds((const void*)gemm_tiled_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+    if constexpr (NT == 1) {
+        if (e != hipSuccess) return e;
+        e = allow_dynamic_lds((const void*)gemm_rows_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+        if (e != hipSuccess) return e;
+        e = allow_dynamic_lds((const void*)gemm_rows_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+    }
     if constexpr (spread_from(MT, NT, W) > 0) {
         if (e != hipSuccess) return e;
         e = allow_dynamic_lds((const void*)gemm_spread_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
@@ -449,6 +478,11 @@ hipError_t run(const TiledGemmParams& p, hipStream_t stream) {
     using TL = Tile<MT, NT, D, W>;
     const int64_t tiles = (int64_t)((p.T + TL::kBM - 1) / TL::kBM) * ((p.N + TL::kBN - 1) / TL::kBN);
     const dim3 grid((unsigned)tiles), block(64 * W);
+    if constexpr (NT == 1) {
+        if (p.b_rows)
+            return p.out_bf16 ? launch(gemm_rows_kernel<true, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p)
+                              : launch(gemm_rows_kernel<false, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p);
+    }
     if constexpr (spread_from(MT, NT, W) > 0) {
         if (spreads<MT, NT, W>(p))
             return p.out_bf16 ? launch(gemm_spread_kernel<true, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p)
@@ -593,6 +627,29 @@ hipError_t launch_gemm_tiled_as(const TiledGemmParams& p, int kernel, hipStream_
 
 hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream) {
     return launch_gemm_tiled_as(p, DUQPP_GEMM_KERNEL_AUTO, stream);
+}
+
+// Row-major weights are multiplied as they are, instead of being read and written tiled first, where few tokens meet many weights: whole
+// K steps and tiles only, rows of scales that are whole words, and a row tile's rows within 32 bits of each other.  A request gathers from
+// 32 rows, which costs more than a run: with few row tiles, i.e. few CUs fetching, more than re-tiling, which all CUs do, and with
+// many tokens, whose tiles each read the weights from L2, as well.  The whole call, weights in HBM, re-tiled first / as they are, us, K x N:
+//   T = 1    4096 x 1024 5.7 / 6.3, 14336 x 1024 9.7 / 11.2, 4096 x 2048 6.4 / 6.2, 4096 x 4096 9.0 / 6.4, 4096 x 14336 21.8 / 11.9,
+//            14336 x 4096 22.0 / 13.4, 8192 x 28672 63 / 33, 28672 x 8192 67 / 35
+//   T = 64   4096 x 2048 7.2 / 7.4, 4096 x 4096 10.1 / 7.8, 4096 x 14336 22.5 / 18.2, 14336 x 4096 26.8 / 20.4, 28672 x 8192 78 / 47
+//   T = 128  4096 x 4096 10.6 / 10.2, 14336 x 4096 28.5 / 29.6, 1024 x 16384 10.1 / 8.2, 8192 x 8192 28.6 / 22.3
+//   T = 192  4096 x 4096 11.8 / 14.8, 14336 x 4096 30.7 / 36.2, 1024 x 16384 10.8 / 8.7, 8192 x 8192 31.6 / 27.5, 28672 x 8192 100 / 84
+//   T = 333  4096 x 14336 31.0 / 35.0, 8192 x 28672 98 / 118
+bool rows_fit(int64_t T, int64_t N, int64_t K, const uint8_t* scales) {
+    if (K % 256 != 0 || N % 128 != 0 || K > (int64_t)1 << 24 || (reinterpret_cast<uintptr_t>(scales) & 3) != 0) return false;
+    return N >= 4096 && N * K >= (int64_t)1 << 24 && T <= (N >= 8192 ? 192 : 64);
+}
+hipError_t launch_gemm_rows(const TiledGemmParams& call, hipStream_t stream) {
+    TiledGemmParams p = call;
+    p.b_rows = 1;
+    if (decode_splits_k(p)) return launch_gemm_decode(p, stream);
+    const Shape* s = p.T <= 32 ? best_shape(p, streaming_shape) : best_shape(p, small_shape);   // all 32 channels per wave
+    const hipError_t e = setup_gemm_tiled();
+    return e == hipSuccess ? s->run(p, stream) : e;
 }
 
 }  // namespace duqpp
