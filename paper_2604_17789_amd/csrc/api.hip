@@ -258,13 +258,17 @@ int duqpp_rotq_gemm(const void* x_bf16, int64_t ldx, const float* R, int64_t n_r
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     const TiledScratch w = tiled_scratch(T, N, K);
     const int G = (int)(K / 32), GP = (int)tiled_groups(G);
-    const LayoutParams lb{b_codes, b_scales, ws + w.b_codes, ws + w.b_scales, (int)N, G, GP};
-    const bool rows = rows_fit(T, N, K, b_scales);
-    st = rotate_quantize_impl(x_bf16, T, K, ldx, R, n_rblocks, ws + w.a_codes, ws + w.a_scales, nullptr, stream, true, false, rows ? nullptr : &lb);
-    if (st != DUQPP_OK) return st;
-    TiledGemmParams p{ws + w.a_codes, ws + w.a_scales, rows ? b_codes : ws + w.b_codes, rows ? b_scales : ws + w.b_scales, (int)T, (int)N, GP,
+    LayoutParams lb{b_codes, b_scales, ws + w.b_codes, ws + w.b_scales, (int)N, G, GP};
+    TiledGemmParams p{ws + w.a_codes, ws + w.a_scales, ws + w.b_codes, ws + w.b_scales, (int)T, (int)N, GP,
                       y, ldy, out_dtype == DUQPP_BF16};
-    return (rows ? launch_gemm_rows(p, hs) : launch_gemm_tiled(p, hs)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
+    const RowsForm form = G == GP ? rows_form(p, b_scales) : kRowsTiled;
+    lb.scales_only = form == kRowsScalesTiled;
+    st = rotate_quantize_impl(x_bf16, T, K, ldx, R, n_rblocks, ws + w.a_codes, ws + w.a_scales, nullptr, stream, true, false,
+                              form == kRowsAsTheyAre ? nullptr : &lb);
+    if (st != DUQPP_OK) return st;
+    if (form != kRowsTiled) p.b_codes = b_codes;
+    if (form == kRowsAsTheyAre) p.b_scales = b_scales;
+    return (form == kRowsTiled ? launch_gemm_tiled(p, hs) : launch_gemm_rows(p, hs)) == hipSuccess ? DUQPP_OK : DUQPP_ERR_HIP;
 }
 
 size_t duqpp_group_error_workspace_bytes(int64_t T, int64_t K) {

@@ -145,6 +145,7 @@ struct LayoutParams {
     const uint8_t* src_codes; const uint8_t* src_scales;
     uint8_t* dst_codes; uint8_t* dst_scales;
     int rows, G, GP;
+    int scales_only;     // G a multiple of 8, rows of scales on 8 bytes; with launch_rotq_and_tile
 };
 hipError_t launch_tile(const LayoutParams& p, hipStream_t stream);     // row-major -> tiled (writes the padding too)
 hipError_t launch_tile(const LayoutParams& a, const LayoutParams& b, hipStream_t stream);   // two operands in one launch
@@ -178,7 +179,8 @@ struct TiledGemmParams {
     void* y; int64_t ldy; int out_bf16;
     int b_rows;                                        // the weights are in the row-major layout (launch_gemm_rows)
 };
-bool rows_fit(int64_t T, int64_t N, int64_t K, const uint8_t* scales);        // launch_gemm_rows takes such weights, and is the faster way
+enum RowsForm { kRowsTiled, kRowsScalesTiled, kRowsAsTheyAre };
+RowsForm rows_form(const TiledGemmParams& p, const uint8_t* scales);          // in which form a call with row-major weights multiplies them
 hipError_t launch_gemm_rows(const TiledGemmParams& p, hipStream_t stream);
 hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream);     // picks the kernel by shape
 int choose_gemm_kernel(const TiledGemmParams& p);                              // the DUQPP_GEMM_KERNEL_* it picks

@@ -160,14 +160,14 @@ __device__ __forceinline__ void tile_of_workgroup(int tiles_m, int tiles_n, int&
 }
 
 // The tile of MT token row tiles from row_tile and of channels tile_n.
-// B_ROWS: the weights are in the row-major layout (rows_fit), the 64 code bytes of a lane's four groups side by side and its four
-// scales a word of the row.  A request is then half of a line's sixteenth from each of 32 rows, so the four of a fragment are made one
-// behind the other at the end of the step, for the lines to be fetched from L2 once.
+// B_ROWS: the codes of the weights are in the row-major layout (rows_form; their scales are tiled: 8 bytes of each row and step would fetch
+// as much from L2 as the codes), four requests of 64 bytes from each of 16 rows for a fragment, which the lanes put in order among them
+// (rows_to_fragments).  They are made one behind the other at the end of the step, for both halves of a line to be fetched from L2 at once.
 template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC, bool B_ROWS = false>
 __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile, int tile_n, LdsBytes __restrict__ staged,
                                           LdsBytes __restrict__ lds) {
     using TL = Tile<MT, NT, D, W, B_ROWS>;
-    constexpr int kStepB = B_ROWS ? 128 : kTileStepBytes, kStepBs = B_ROWS ? 8 : 256, kNextB = B_ROWS ? 16 : 512;
+    constexpr int kStepB = B_ROWS ? 128 : kTileStepBytes;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, g = lane >> 5;
@@ -204,8 +204,8 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
     }
     const uint32_t voff_dma = wave * (TL::kPieces * 1024) + lane * 16, voff_word = lane * 4;
     const uint32_t row_bytes = (uint32_t)p.GP * 16;        // of row-major codes
-    uint32_t voff_b = B_ROWS ? r * row_bytes + g * 64 : g * 2048 + r * 16;
-    const uint32_t voff_bs = B_ROWS ? (uint32_t)r * p.GP + g * 4 : voff_word;
+    uint32_t voff_b = B_ROWS ? (lane & 15) * row_bytes + (lane >> 4) * 16 : g * 2048 + r * 16;
+    uint32_t voff_b16 = voff_b + 16 * row_bytes;           // 16 rows on
     const LdsBytes a_dst = staged + wave * (TL::kPieces * 1024);
 
     // No branch: the K loop has to stay one straight piece of code, or the compiler moves products out from between the
@@ -222,9 +222,12 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
             b_src[n] = (const uint8_t*)((((uint64_t)b_src[n] + kStepB) & keep) | zeros);
-            bs_src[n] += more * kStepBs;
+            bs_src[n] += more * 256;
         }
-        if constexpr (B_ROWS) voff_b = more ? voff_b : 0u; // within the zero codes
+        if constexpr (B_ROWS) {                            // within the zero codes
+            voff_b = more ? voff_b : 0u;
+            voff_b16 = more ? voff_b16 : 0u;
+        }
     };
 
     u32x4 b[D][NT][4];
@@ -242,17 +245,28 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         }
     };
 
+    auto request_rows = [&](u32x4 (&v)[4], const uint8_t* src) {
+        v[0] = request_b128<0>(voff_b, src);
+        v[1] = request_b128<0>(voff_b16, src);
+        v[2] = request_b128<64>(voff_b, src);
+        v[3] = request_b128<64>(voff_b16, src);
+    };
+
     // ---- prologue: D steps in flight
     unroll<D>([&](auto dc) {
         constexpr int d = decltype(dc)::value;
         unroll<TL::kDma>([&](auto kc) { dma_op(kc, d * TL::kStageBytes); });
         unroll<NT>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
-            b[d][n][0] = request_b128<0>(voff_b, b_src[n]);
-            b[d][n][1] = request_b128<kNextB>(voff_b, b_src[n]);
-            b[d][n][2] = request_b128<2 * kNextB>(voff_b, b_src[n]);
-            b[d][n][3] = request_b128<3 * kNextB>(voff_b, b_src[n]);
-            sb[d][n] = request_b32(voff_bs, bs_src[n]);
+            if constexpr (B_ROWS) {
+                request_rows(b[d][n], b_src[n]);
+            } else {
+                b[d][n][0] = request_b128<0>(voff_b, b_src[n]);
+                b[d][n][1] = request_b128<512>(voff_b, b_src[n]);
+                b[d][n][2] = request_b128<1024>(voff_b, b_src[n]);
+                b[d][n][3] = request_b128<1536>(voff_b, b_src[n]);
+            }
+            sb[d][n] = request_b32(voff_word, bs_src[n]);
         });
         advance();
         __builtin_amdgcn_sched_barrier(0);                 // the waits count on the steps' order
@@ -285,6 +299,10 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         const LdsBytes pa = pa0 + stage;
 #define DUQPP_PIN __builtin_amdgcn_sched_barrier(0)
         constexpr int kSlots = 3 * MT * NT;   // transfers spread over the first three quarters
+        if constexpr (B_ROWS) {
+            unroll<NT>([&](auto nc) { rows_to_fragments(b[P][decltype(nc)::value]); });
+            DUQPP_PIN;
+        }
         unroll<3>([&](auto qc) {
             constexpr int Q = decltype(qc)::value;
             unroll<NT>([&](auto nc) {
@@ -301,7 +319,7 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
                     DUQPP_MFMA(acc[m][n], fa[Q & 1][m], b[P][n][Q], sa[P & 1][m], sb[P][n], Q);
                     DUQPP_PIN;
                 });
-                if constexpr (MORE && !B_ROWS) b[P][n][Q] = request_b128<Q * kNextB>(voff_b, b_src[n]);
+                if constexpr (MORE && !B_ROWS) b[P][n][Q] = request_b128<Q * 512>(voff_b, b_src[n]);
                 DUQPP_PIN;
             });
         });
@@ -324,13 +342,9 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
                 DUQPP_PIN;
             });
             if constexpr (MORE) {
-                if constexpr (B_ROWS) {
-                    b[P][n][0] = request_b128<0>(voff_b, b_src[n]);
-                    b[P][n][1] = request_b128<kNextB>(voff_b, b_src[n]);
-                    b[P][n][2] = request_b128<2 * kNextB>(voff_b, b_src[n]);
-                }
-                b[P][n][3] = request_b128<3 * kNextB>(voff_b, b_src[n]);
-                sb[P][n] = request_b32(voff_bs, bs_src[n]);
+                if constexpr (B_ROWS) request_rows(b[P][n], b_src[n]);
+                else b[P][n][3] = request_b128<1536>(voff_b, b_src[n]);
+                sb[P][n] = request_b32(voff_word, bs_src[n]);
                 DUQPP_PIN;
             }
         });
@@ -630,18 +644,24 @@ hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream) {
 }
 
 // Row-major weights are multiplied as they are, instead of being read and written tiled first, where few tokens meet many weights: whole
-// K steps and tiles only, rows of scales that are whole words, and a row tile's rows within 32 bits of each other.  A request gathers from
-// 32 rows, which costs more than a run: with few row tiles, i.e. few CUs fetching, more than re-tiling, which all CUs do, and with
-// many tokens, whose tiles each read the weights from L2, as well.  The whole call, weights in HBM, re-tiled first / as they are, us, K x N:
+// K steps and tiles only, rows of scales on 8 bytes, and a row tile's rows within 32 bits of each other.  The kernels that split K
+// over their waves take codes and scales, the tiles only the codes (the launch that rotates tiles the scales, a sixteenth of the
+// bytes; taken as they are, too, 8192 x 8192, T = 192 27.5 us against 22.9).  A request gathers from 16 or 32 rows, which costs more
+// than a run: with few row tiles, i.e. few CUs fetching, more than re-tiling, which all CUs do, and with many tokens, whose
+// tiles each read the weights from L2, as well.  The whole call, weights in HBM, re-tiled first / as they are, us, K x N:
 //   T = 1    4096 x 1024 5.7 / 6.3, 14336 x 1024 9.7 / 11.2, 4096 x 2048 6.4 / 6.2, 4096 x 4096 9.0 / 6.4, 4096 x 14336 21.8 / 11.9,
 //            14336 x 4096 22.0 / 13.4, 8192 x 28672 63 / 33, 28672 x 8192 67 / 35
-//   T = 64   4096 x 2048 7.2 / 7.4, 4096 x 4096 10.1 / 7.8, 4096 x 14336 22.5 / 18.2, 14336 x 4096 26.8 / 20.4, 28672 x 8192 78 / 47
-//   T = 128  4096 x 4096 10.6 / 10.2, 14336 x 4096 28.5 / 29.6, 1024 x 16384 10.1 / 8.2, 8192 x 8192 28.6 / 22.3
-//   T = 192  4096 x 4096 11.8 / 14.8, 14336 x 4096 30.7 / 36.2, 1024 x 16384 10.8 / 8.7, 8192 x 8192 31.6 / 27.5, 28672 x 8192 100 / 84
-//   T = 333  4096 x 14336 31.0 / 35.0, 8192 x 28672 98 / 118
-bool rows_fit(int64_t T, int64_t N, int64_t K, const uint8_t* scales) {
-    if (K % 256 != 0 || N % 128 != 0 || K > (int64_t)1 << 24 || (reinterpret_cast<uintptr_t>(scales) & 3) != 0) return false;
-    return N >= 4096 && N * K >= (int64_t)1 << 24 && T <= (N >= 8192 ? 192 : 64);
+//   T = 64   4096 x 2048 7.2 / 7.4, 4096 x 4096 10.1 / 7.8, 4096 x 14336 22.5 / 16.0, 14336 x 4096 26.8 / 20.4, 28672 x 8192 78 / 47
+//   T = 128  4096 x 4096 10.6 / 9.9, 14336 x 4096 28.1 / 24.2, 1024 x 16384 10.0 / 8.3, 8192 x 8192 28.1 / 20.5, 14336 x 2048 18.6 / 18.6
+//   T = 192  4096 x 4096 12.0 / 13.6, 14336 x 4096 30.4 / 30.1, 1024 x 16384 10.8 / 9.1, 8192 x 8192 31.3 / 22.9, 28672 x 8192 100 / 63
+//   T = 256  1024 x 16384 11.3 / 11.1, 4096 x 8192 18.4 / 16.4, 4096 x 14336 27.7 / 25.2, 14336 x 4096 32.3 / 30.4, 8192 x 28672 92 / 67
+//   T = 288  4096 x 14336 29.5 / 30.4;  T = 384 8192 x 8192 34.0 / 32.6, 28672 x 8192 120 / 91, 28672 x 4096 67 / 60
+//   T = 448  8192 x 8192 36.7 / 43.7, 28672 x 4096 67 / 77;  T = 512 4096 x 4096 15.3 / 16.4
+RowsForm rows_form(const TiledGemmParams& p, const uint8_t* scales) {
+    const int64_t K = (int64_t)p.GP * 32, N = p.N, T = p.T;
+    if (N % 128 != 0 || N < 4096 || K > (int64_t)1 << 24 || (reinterpret_cast<uintptr_t>(scales) & 7) != 0) return kRowsTiled;
+    const int64_t to = N * K >= (int64_t)1 << 26 ? 384 : N * K >= (int64_t)1 << 25 ? 256 : N * K < (int64_t)1 << 24 ? 0 : N >= 8192 ? 192 : 128;
+    return T > to ? kRowsTiled : decode_splits_k(p) ? kRowsAsTheyAre : kRowsScalesTiled;
 }
 hipError_t launch_gemm_rows(const TiledGemmParams& call, hipStream_t stream) {
     TiledGemmParams p = call;

@@ -6,14 +6,37 @@
 
 namespace duqpp {
 
-// A unit of work is one row tile x 8 groups: 4 KiB of codes and 256 bytes of scales, moved by one wave.
-__host__ __device__ inline int64_t tile_units(const LayoutParams& p) { return (int64_t)((p.rows + 31) / 32) * (p.GP / 8); }
+// A unit of work is one row tile x 8 groups: 4 KiB of codes and 256 bytes of scales, moved by one wave; of scales alone 64 groups.
+__host__ __device__ inline int64_t tile_units(const LayoutParams& p) {
+    const int steps = p.GP / 8;
+    return (int64_t)((p.rows + 31) / 32) * (p.scales_only ? (steps + 7) / 8 : steps);
+}
+
+// Scales: lane (row, h) has 32 bytes of its row's 64, which are four K steps.
+__device__ __forceinline__ void tile_scales_unit(const LayoutParams& p, int64_t unit, int lane) {
+    const uint32_t NI = p.GP / 8, across = (NI + 7) / 8, u = (uint32_t)unit;
+    const int64_t rt = u / across;
+    const int step0 = 8 * (int)(u % across) + 4 * (lane >> 5), r = lane & 31;
+    const int64_t row = 32 * rt + r;
+    const uint8_t* src = p.src_scales + (row < p.rows ? row : p.rows - 1) * p.G;
+    uint2 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *(const uint2*)(src + 8 * (step0 + i < (int)NI ? step0 + i : (int)NI - 1));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (step0 + i >= (int)NI) continue;
+        uint32_t* dst = (uint32_t*)(p.dst_scales + (rt * NI + step0 + i) * 256 + r * 4);
+        dst[0] = row < p.rows ? v[i].x : 0x7F7F7F7Fu;
+        dst[32] = row < p.rows ? v[i].y : 0x7F7F7F7Fu;
+    }
+}
 
 // Codes: lane (row % 8, group) of four loads reads 16 bytes, so that a row's 128 bytes are one run, and stores them at
 // group * 512 + row * 16, where eight rows are a run of 128 bytes again: both sides move whole lines without LDS.  (With a
 // thread per (group, row) in the order of the tiled layout the reads were 16 bytes out of every row's line.)  Rows and
 // groups of the padding read a valid place and are replaced, so that no branch stands between the loads.
 __device__ __forceinline__ void tile_unit(const LayoutParams& p, int64_t unit, int lane) {
+    if (p.scales_only) return tile_scales_unit(p, unit, lane);
     const uint32_t NI = p.GP / 8, u = (uint32_t)unit;         // (2^32 units would be 17 TB)
     const int64_t rt = u / NI;
     const int q8 = (int)(u % NI);

@@ -1,5 +1,6 @@
-"""The row-major fused call where the product takes the weights as they are: the bits of the product on tiled weights, in every kernel that
-does it, with fewer and more K steps than are in flight; and where it may not, they are re-tiled into the workspace as before."""
+"""The row-major fused call where the product takes the weights, or their codes, as they are: the bits of the product on tiled weights, in every
+kernel that does it, with fewer and more K steps than are in flight; and where it may not, they are re-tiled into the workspace as
+before."""
 import numpy as np
 import pytest
 
@@ -8,14 +9,16 @@ from helpers import to_dev, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 
-# half row tiles on the 16-row and the 32-row instruction, whole ones, two token row tiles at once, and the seven tiles of 32 channels per wave
-# (19 x 10240 x 2048, 19 x 20480 x 1024, 34 x 8704 x 8192, 34 x 20480 x 1024, 67 x 11264 x 4096, 67 x 20480 x 2048, 97 x 20480 x 2048); one K step,
-# and 9 and 17 (a wave with fewer steps than the others, steps past the end)
+# half row tiles on the 16-row and the 32-row instruction, whole ones, two token row tiles at once; 9 and 17 K steps (waves with fewer)
 AS_THEY_ARE = [(1, 4096, 4096), (16, 4096, 4352), (1, 8192, 2304), (16, 16384, 1024), (17, 4096, 4352), (32, 8192, 2304), (33, 4096, 4096), (64, 4096, 8448),
-               (40, 6144, 8192), (19, 10240, 2048), (19, 20480, 1024), (32, 65536, 256), (34, 8704, 8192), (34, 20480, 1024), (67, 11264, 4096),
-               (67, 20480, 2048), (97, 20480, 2048), (130, 8192, 2304), (192, 65536, 256)]
-# another token, row or group than that takes; scales that do not start on a word; fewer weights
-RE_TILED = [(65, 4096, 4096, 0), (193, 8192, 2048, 0), (16, 4128, 4096, 0), (16, 4096, 4128, 0), (16, 4096, 4096, 1), (16, 3968, 8192, 0), (16, 4096, 3840, 0)]
+               (40, 6144, 8192)]
+# the seven tiles of 32 channels per wave (the first five, 67 x 20480 x 2048, 97 x 20480 x 2048); one K step, 9 (steps past the end; the scales of
+# 8 steps and one); the most tokens
+CODES_AS_THEY_ARE = [(19, 10240, 2048), (19, 20480, 1024), (34, 8704, 8192), (34, 20480, 1024), (67, 11264, 4096), (67, 20480, 2048), (97, 20480, 2048),
+                     (32, 65536, 256), (130, 8192, 2304), (192, 65536, 256), (128, 4096, 4096), (256, 4096, 8448), (384, 8192, 8192)]
+# another token, row or group than that takes; scales that start elsewhere; fewer weights
+RE_TILED = [(129, 4096, 4096, 0), (193, 8192, 2048, 0), (257, 4096, 8448, 0), (385, 8192, 8192, 0), (16, 4128, 4096, 0), (16, 4096, 4128, 0),
+            (16, 4096, 4096, 1), (100, 4096, 4096, 4), (16, 3968, 8192, 0), (16, 4096, 3840, 0)]
 
 
 def weights(torch, T, N, K, shift):
@@ -27,7 +30,7 @@ def weights(torch, T, N, K, shift):
     return bc, bs
 
 
-def run(torch, T, N, K, shift, as_they_are):
+def run(torch, T, N, K, shift, codes, scales):
     import paper_2604_17789_amd as duqpp
     print(f"[row-major direct] T={T} N={N} K={K} shift={shift}", flush=True)
     bc, bs = weights(torch, T, N, K, shift)
@@ -41,7 +44,9 @@ def run(torch, T, N, K, shift, as_they_are):
         got = duqpp.rotq_gemm(x, R, bc, bs, out_dtype=code, workspace=ws)
         torch.cuda.synchronize()
         assert torch.equal(got, want)
-        assert bool((ws[cb + sb:] == 0xA5).all()) == as_they_are
+        at = cb + sb + b[0].numel()
+        assert bool((ws[cb + sb:at] == 0xA5).all()) if codes else torch.equal(ws[cb + sb:at], b[0].reshape(-1))
+        assert bool((ws[at:] == 0xA5).all()) if scales else torch.equal(ws[at:at + b[1].numel()], b[1].reshape(-1))
     # into a wider matrix: rows of their own length, nothing beside them
     wide = torch.full((T, N + 9), 3.0, dtype=torch.bfloat16, device="cuda")
     duqpp.rotq_gemm(x, R, bc, bs, out_dtype=duqpp.BF16, out=wide[:, :N], workspace=ws)
@@ -52,10 +57,16 @@ def run(torch, T, N, K, shift, as_they_are):
 @pytest.mark.parametrize("T,N,K", AS_THEY_ARE)
 def test_weights_as_they_are(T, N, K):
     import torch
-    run(torch, T, N, K, 0, True)
+    run(torch, T, N, K, 0, True, True)
+
+
+@pytest.mark.parametrize("T,N,K", CODES_AS_THEY_ARE)
+def test_codes_as_they_are(T, N, K):
+    import torch
+    run(torch, T, N, K, 0, True, False)
 
 
 @pytest.mark.parametrize("T,N,K,shift", RE_TILED)
 def test_weights_that_are_re_tiled(T, N, K, shift):
     import torch
-    run(torch, T, N, K, shift, False)
+    run(torch, T, N, K, shift, False, False)
