@@ -101,14 +101,16 @@ template <int MT, int NT, int D, int W, bool B_ROWS = false>
 struct Tile {
     static constexpr int kBM = 32 * MT, kBN = 32 * NT * W;
     static constexpr int kScalesOff = MT * kTileStepBytes;    // scale words follow the codes in a stage
-    static constexpr int kStageBytes = kScalesOff + MT * 256;
+    static constexpr int kBOff = kScalesOff + MT * 256;       // B_ROWS: behind them the weights' codes, 4 KiB of each wave and row tile
+    static constexpr int kStageBytes = kBOff + (B_ROWS ? W * NT * 4096 : 0);
     static constexpr int kStages = D + 1;
     static constexpr int kPieces = 4 / W;                     // KiB of a token row tile's step that one wave transfers
     static constexpr int kCOps = MT * kPieces;
     static constexpr int kSOps = (MT + W - 1) / W;            // scale transfers per wave and step
-    static constexpr int kDma = kCOps + kSOps;                // LDS-DMA transfers per wave and step
-    static constexpr int kOps = kDma + 5 * NT;                // all requests per wave and step, in the order they complete
-    static constexpr int kLate = (B_ROWS ? 5 : 2) * NT;       // of them behind the step's wait
+    static constexpr int kBOps = B_ROWS ? 4 * NT : 0;
+    static constexpr int kDma = kCOps + kSOps + kBOps;        // LDS-DMA transfers per wave and step
+    static constexpr int kOps = kDma + (B_ROWS ? 1 : 5) * NT; // all requests per wave and step, in the order they complete
+    static constexpr int kLate = (B_ROWS ? 1 : 2) * NT;       // of them behind the step's wait
     static constexpr int kPitch = 64 * NT + 16;               // a row of the bf16 transpose
     static constexpr int kEpBytes = 32 * kPitch;
     static constexpr int kLdsBytes = kStages * kStageBytes > W * kEpBytes ? kStages * kStageBytes : W * kEpBytes;
@@ -161,8 +163,9 @@ __device__ __forceinline__ void tile_of_workgroup(int tiles_m, int tiles_n, int&
 
 // The tile of MT token row tiles from row_tile and of channels tile_n.
 // B_ROWS: the codes of the weights are in the row-major layout (rows_form; their scales are tiled: 8 bytes of each row and step would fetch
-// as much from L2 as the codes), four requests of 64 bytes from each of 16 rows for a fragment, which the lanes put in order among them
-// (rows_to_fragments).  They are made one behind the other at the end of the step, for both halves of a line to be fetched from L2 at once.
+// as much from L2 as the codes).  They go to LDS as the tokens' do, to a part of the stage that is the wave's own: a transfer takes
+// whole lines of 8 rows, lane l the 16 bytes (l % 8) ^ (l / 8) of row l / 8, so that the 8 lanes that read the same group of
+// 8 rows meet in no bank.  (Requests into registers gathered from 16 rows: 512 x 4096 x 4096 12 us for the product, 8 on tiled weights.)
 template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC, bool B_ROWS = false>
 __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile, int tile_n, LdsBytes __restrict__ staged,
                                           LdsBytes __restrict__ lds) {
@@ -204,8 +207,9 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
     }
     const uint32_t voff_dma = wave * (TL::kPieces * 1024) + lane * 16, voff_word = lane * 4;
     const uint32_t row_bytes = (uint32_t)p.GP * 16;        // of row-major codes
-    uint32_t voff_b = B_ROWS ? (lane & 15) * row_bytes + (lane >> 4) * 16 : g * 2048 + r * 16;
-    uint32_t voff_b16 = voff_b + 16 * row_bytes;           // 16 rows on
+    uint32_t voff_b = B_ROWS ? (lane >> 3) * row_bytes + ((lane & 7) ^ (lane >> 3)) * 16 : g * 2048 + r * 16;
+    uint32_t eight_rows = 8 * row_bytes;
+    const LdsBytes b_dst = staged + TL::kBOff + wave * NT * 4096;
     const LdsBytes a_dst = staged + wave * (TL::kPieces * 1024);
 
     // No branch: the K loop has to stay one straight piece of code, or the compiler moves products out from between the
@@ -226,11 +230,12 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         }
         if constexpr (B_ROWS) {                            // within the zero codes
             voff_b = more ? voff_b : 0u;
-            voff_b16 = more ? voff_b16 : 0u;
+            eight_rows = more ? eight_rows : 0u;
         }
     };
 
-    u32x4 b[D][NT][4];
+    u32x4 b[D][NT][4];                                     // (B_ROWS: fb instead)
+    u32x4 fb[2][NT];
     uint32_t sb[D][NT];
     u32x4 fa[2][MT];
     uint32_t sa[2][MT];
@@ -241,15 +246,13 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
             constexpr int m = k / TL::kPieces, piece = k % TL::kPieces;
             dma<16, piece * 1024>(a_src, a_off[m], voff_dma, a_dst + m * kTileStepBytes + so);
         } else if constexpr (k < TL::kDma) {
-            dma<4, 0>(as_src, as_off[k - TL::kCOps], voff_word, as_dst[k - TL::kCOps] + so);
+            if constexpr (k < TL::kCOps + TL::kSOps) {
+                dma<4, 0>(as_src, as_off[k - TL::kCOps], voff_word, as_dst[k - TL::kCOps] + so);
+            } else {
+                constexpr int n = (k - TL::kCOps - TL::kSOps) / 4, piece = (k - TL::kCOps - TL::kSOps) % 4;
+                dma<16, 0>(b_src[n], piece * eight_rows, voff_b, b_dst + n * 4096 + piece * 1024 + so);
+            }
         }
-    };
-
-    auto request_rows = [&](u32x4 (&v)[4], const uint8_t* src) {
-        v[0] = request_b128<0>(voff_b, src);
-        v[1] = request_b128<0>(voff_b16, src);
-        v[2] = request_b128<64>(voff_b, src);
-        v[3] = request_b128<64>(voff_b16, src);
     };
 
     // ---- prologue: D steps in flight
@@ -258,9 +261,7 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         unroll<TL::kDma>([&](auto kc) { dma_op(kc, d * TL::kStageBytes); });
         unroll<NT>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
-            if constexpr (B_ROWS) {
-                request_rows(b[d][n], b_src[n]);
-            } else {
+            if constexpr (!B_ROWS) {
                 b[d][n][0] = request_b128<0>(voff_b, b_src[n]);
                 b[d][n][1] = request_b128<512>(voff_b, b_src[n]);
                 b[d][n][2] = request_b128<1024>(voff_b, b_src[n]);
@@ -287,6 +288,14 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         fa[0][m] = *(LdsU32x4)(pa0 + m * kTileStepBytes);
         sa[0][m] = *(LdsU32)(ps0 + m * 256);
     }
+    // B_ROWS: group 4 g + Q of row r
+    LdsBytes pb0[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) pb0[q] = lds + TL::kBOff + wave * NT * 4096 + r * 128 + (((4 * g + q) ^ (r & 7)) * 16);
+    if constexpr (B_ROWS) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n) fb[0][n] = *(LdsU32x4)(pb0[0] + n * 4096);
+    }
 
     uint32_t stage = 0, spare = (TL::kStages - 1) * TL::kStageBytes;   // offsets of the stage in use and of the one before it
     // One K step; P: its register set.  MORE: it requests the step D ahead; the last D steps (MORE = false) request nothing,
@@ -299,10 +308,6 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
         const LdsBytes pa = pa0 + stage;
 #define DUQPP_PIN __builtin_amdgcn_sched_barrier(0)
         constexpr int kSlots = 3 * MT * NT;   // transfers spread over the first three quarters
-        if constexpr (B_ROWS) {
-            unroll<NT>([&](auto nc) { rows_to_fragments(b[P][decltype(nc)::value]); });
-            DUQPP_PIN;
-        }
         unroll<3>([&](auto qc) {
             constexpr int Q = decltype(qc)::value;
             unroll<NT>([&](auto nc) {
@@ -315,8 +320,10 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
                         unroll<k1 - k0>([&](auto kc) { dma_op(std::integral_constant<int, k0 + decltype(kc)::value>{}, so); });
                     }
                     if constexpr (n == 0) fa[(Q + 1) & 1][m] = *(LdsU32x4)(pa + m * kTileStepBytes + (Q + 1) * 512);
+                    if constexpr (B_ROWS && m0 == 0) fb[(Q + 1) & 1][n] = *(LdsU32x4)(pb0[Q + 1] + n * 4096 + stage);
                     DUQPP_PIN;
-                    DUQPP_MFMA(acc[m][n], fa[Q & 1][m], b[P][n][Q], sa[P & 1][m], sb[P][n], Q);
+                    if constexpr (B_ROWS) DUQPP_MFMA(acc[m][n], fa[Q & 1][m], fb[Q & 1][n], sa[P & 1][m], sb[P][n], Q);
+                    else DUQPP_MFMA(acc[m][n], fa[Q & 1][m], b[P][n][Q], sa[P & 1][m], sb[P][n], Q);
                     DUQPP_PIN;
                 });
                 if constexpr (MORE && !B_ROWS) b[P][n][Q] = request_b128<Q * 512>(voff_b, b_src[n]);
@@ -337,13 +344,14 @@ __device__ __forceinline__ void gemm_tile(const TiledGemmParams& p, int row_tile
                     fa[0][m] = *(LdsU32x4)(na + m * kTileStepBytes);
                     sa[(P + 1) & 1][m] = *(LdsU32)(ns + m * 256);
                 }
+                if constexpr (B_ROWS && m0 == 0 && (MORE || P < D - 1)) fb[0][n] = *(LdsU32x4)(pb0[0] + n * 4096 + stage1);
                 DUQPP_PIN;
-                DUQPP_MFMA(acc[m][n], fa[1][m], b[P][n][3], sa[P & 1][m], sb[P][n], 3);
+                if constexpr (B_ROWS) DUQPP_MFMA(acc[m][n], fa[1][m], fb[1][n], sa[P & 1][m], sb[P][n], 3);
+                else DUQPP_MFMA(acc[m][n], fa[1][m], b[P][n][3], sa[P & 1][m], sb[P][n], 3);
                 DUQPP_PIN;
             });
             if constexpr (MORE) {
-                if constexpr (B_ROWS) request_rows(b[P][n], b_src[n]);
-                else b[P][n][3] = request_b128<1536>(voff_b, b_src[n]);
+                if constexpr (!B_ROWS) b[P][n][3] = request_b128<1536>(voff_b, b_src[n]);
                 sb[P][n] = request_b32(voff_word, bs_src[n]);
                 DUQPP_PIN;
             }
@@ -433,7 +441,7 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
 template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
 __global__ __launch_bounds__(64 * W, OCC) void gemm_rows_kernel(TiledGemmParams p) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    using TL = Tile<MT, NT, D, W>;
+    using TL = Tile<MT, NT, D, W, true>;
     int tile_m, tile_n;
     tile_of_workgroup<OCC>((p.T + TL::kBM - 1) / TL::kBM, p.N / TL::kBN, tile_m, tile_n);
     gemm_tile<OUT_BF16, MT, NT, D, W, OCC, true>(p, tile_m * MT, tile_n, (LdsBytes)lds, (LdsBytes)lds);
@@ -475,9 +483,9 @@ hipError_t allow() {
     e = allow_dynamic_lds((const void*)gemm_tiled_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
     if constexpr (NT == 1) {
         if (e != hipSuccess) return e;
-        e = allow_dynamic_lds((const void*)gemm_rows_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+        e = allow_dynamic_lds((const void*)gemm_rows_kernel<true, MT, NT, D, W, OCC>, Tile<MT, NT, D, W, true>::kLdsBytes);
         if (e != hipSuccess) return e;
-        e = allow_dynamic_lds((const void*)gemm_rows_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W>::kLdsBytes);
+        e = allow_dynamic_lds((const void*)gemm_rows_kernel<false, MT, NT, D, W, OCC>, Tile<MT, NT, D, W, true>::kLdsBytes);
     }
     if constexpr (spread_from(MT, NT, W) > 0) {
         if (e != hipSuccess) return e;
@@ -494,8 +502,8 @@ hipError_t run(const TiledGemmParams& p, hipStream_t stream) {
     const dim3 grid((unsigned)tiles), block(64 * W);
     if constexpr (NT == 1) {
         if (p.b_rows)
-            return p.out_bf16 ? launch(gemm_rows_kernel<true, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p)
-                              : launch(gemm_rows_kernel<false, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p);
+            return p.out_bf16 ? launch(gemm_rows_kernel<true, MT, NT, D, W, OCC>, grid, block, Tile<MT, NT, D, W, true>::kLdsBytes, stream, p)
+                              : launch(gemm_rows_kernel<false, MT, NT, D, W, OCC>, grid, block, Tile<MT, NT, D, W, true>::kLdsBytes, stream, p);
     }
     if constexpr (spread_from(MT, NT, W) > 0) {
         if (spreads<MT, NT, W>(p))
@@ -643,25 +651,25 @@ hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream) {
     return launch_gemm_tiled_as(p, DUQPP_GEMM_KERNEL_AUTO, stream);
 }
 
-// Row-major weights are multiplied as they are, instead of being read and written tiled first, where few tokens meet many weights: whole
-// K steps and tiles only, rows of scales on 8 bytes, and a row tile's rows within 32 bits of each other.  The kernels that split K
-// over their waves take codes and scales, the tiles only the codes (the launch that rotates tiles the scales, a sixteenth of the
-// bytes; taken as they are, too, 8192 x 8192, T = 192 27.5 us against 22.9).  A request gathers from 16 or 32 rows, which costs more
-// than a run: with few row tiles, i.e. few CUs fetching, more than re-tiling, which all CUs do, and with many tokens, whose
-// tiles each read the weights from L2, as well.  The whole call, weights in HBM, re-tiled first / as they are, us, K x N:
+// Row-major weights are multiplied as they are, instead of being read and written tiled first, where re-tiling is a large part of the call:
+// whole K steps and tiles only, rows of scales on 8 bytes, and a row tile's rows within 32 bits of each other.  The kernels that split K
+// over their waves take codes and scales, the tiles only the codes (the launch that rotates tiles the scales, a sixteenth of the bytes).
+// That loses with few row tiles, i.e. few CUs fetching, where all CUs re-tile, and with many tokens, when the weights' way through LDS
+// costs more than re-tiling them once: beyond 512 tokens from the second round of 128 x 128 tiles on.  The whole call, weights in HBM,
+// re-tiled first / as they are, us, K x N:
 //   T = 1    4096 x 1024 5.7 / 6.3, 14336 x 1024 9.7 / 11.2, 4096 x 2048 6.4 / 6.2, 4096 x 4096 9.0 / 6.4, 4096 x 14336 21.8 / 11.9,
 //            14336 x 4096 22.0 / 13.4, 8192 x 28672 63 / 33, 28672 x 8192 67 / 35
-//   T = 64   4096 x 2048 7.2 / 7.4, 4096 x 4096 10.1 / 7.8, 4096 x 14336 22.5 / 16.0, 14336 x 4096 26.8 / 20.4, 28672 x 8192 78 / 47
-//   T = 128  4096 x 4096 10.6 / 9.9, 14336 x 4096 28.1 / 24.2, 1024 x 16384 10.0 / 8.3, 8192 x 8192 28.1 / 20.5, 14336 x 2048 18.6 / 18.6
-//   T = 192  4096 x 4096 12.0 / 13.6, 14336 x 4096 30.4 / 30.1, 1024 x 16384 10.8 / 9.1, 8192 x 8192 31.3 / 22.9, 28672 x 8192 100 / 63
-//   T = 256  1024 x 16384 11.3 / 11.1, 4096 x 8192 18.4 / 16.4, 4096 x 14336 27.7 / 25.2, 14336 x 4096 32.3 / 30.4, 8192 x 28672 92 / 67
-//   T = 288  4096 x 14336 29.5 / 30.4;  T = 384 8192 x 8192 34.0 / 32.6, 28672 x 8192 120 / 91, 28672 x 4096 67 / 60
-//   T = 448  8192 x 8192 36.7 / 43.7, 28672 x 4096 67 / 77;  T = 512 4096 x 4096 15.3 / 16.4
+//   T = 64   4096 x 2048 7.2 / 7.4, 4096 x 4096 10.1 / 7.8, 4096 x 14336 22.5 / 14.6, 14336 x 4096 26.8 / 20.4, 28672 x 8192 78 / 47
+//   T = 128  4096 x 1024 6.6 / 7.6, 4096 x 4096 10.5 / 8.8, 14336 x 4096 27.9 / 21.2, 1024 x 16384 10.0 / 7.6, 8192 x 8192 27.6 / 19.0
+//   T = 256  4096 x 1024 8.0 / 8.4, 4096 x 4096 12.2 / 9.9, 14336 x 4096 32.4 / 27.5, 4096 x 14336 27.5 / 19.0, 8192 x 28672 92 / 61
+//   T = 512  4096 x 4096 15.2 / 13.5, 8192 x 8192 37.5 / 32.6, 4096 x 14336 34.8 / 32.0, 8192 x 28672 106 / 102, 2048 x 2048 9.0 / 9.0
+//   beyond   640 4096 x 6144 0.85 of the time, 8192 x 8192 1.05, 4096 x 14336 1.13; 777 4096 x 5120 1.05, 4096 x 6144 0.99;
+//            1024 4096 x 4096 20.8 / 18.7, 14336 x 4096 55.7 / 54.0, 8192 x 8192 54.8 / 56.4
 RowsForm rows_form(const TiledGemmParams& p, const uint8_t* scales) {
     const int64_t K = (int64_t)p.GP * 32, N = p.N, T = p.T;
-    if (N % 128 != 0 || N < 4096 || K > (int64_t)1 << 24 || (reinterpret_cast<uintptr_t>(scales) & 7) != 0) return kRowsTiled;
-    const int64_t to = N * K >= (int64_t)1 << 26 ? 384 : N * K >= (int64_t)1 << 25 ? 256 : N * K < (int64_t)1 << 24 ? 0 : N >= 8192 ? 192 : 128;
-    return T > to ? kRowsTiled : decode_splits_k(p) ? kRowsAsTheyAre : kRowsScalesTiled;
+    if (N % 128 != 0 || K > (int64_t)1 << 24 || (reinterpret_cast<uintptr_t>(scales) & 7) != 0) return kRowsTiled;
+    if (N < 4096 || N * K < (int64_t)1 << 24 || (T > 512 && (T + 127) / 128 * (N / 128) > kNumCU)) return kRowsTiled;
+    return decode_splits_k(p) ? kRowsAsTheyAre : kRowsScalesTiled;
 }
 hipError_t launch_gemm_rows(const TiledGemmParams& call, hipStream_t stream) {
     TiledGemmParams p = call;

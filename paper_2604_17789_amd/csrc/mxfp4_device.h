@@ -28,27 +28,5 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return (uint16_t)(u >> 16);
 }
 
-// Row-major codes of 32 rows x 8 groups in the registers of a wave.  A request takes 64 bytes of each of 16 rows: lane (i, c) = (lane % 16,
-// lane / 16) has group 4 (k / 2) + c of row 16 (k % 2) + i in v[k].  The matrix cores want group 4 g + q of row r in v[q] of lane (r, g):
-// two bits of the lane's number change places with the two of the register's, an instruction for a pair of words.
-__device__ __forceinline__ void rows_to_fragments(u32x4 (&v)[4]) {
-#pragma unroll
-    for (int k = 0; k < 4; k += 2)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const auto s = __builtin_amdgcn_permlane16_swap(v[k][w], v[k + 1][w], false, false);
-            v[k][w] = s[0];
-            v[k + 1][w] = s[1];
-        }
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const auto s = __builtin_amdgcn_permlane32_swap(v[k][w], v[k + 2][w], false, false);
-            v[k][w] = s[0];
-            v[k + 2][w] = s[1];
-        }
-}
-
 }  // namespace duqpp
 #endif
