@@ -117,10 +117,11 @@ int duqpp_mxfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
 
 /*
  * Fused form of the online path: Y = Q(X . R^) . Q(W^) in one call, producing exactly the
- * codes duqpp_rotate_quantize would and the product duqpp_mxfp4_gemm would (two kernels on the stream
- * plus the re-tiling of the row-major weights; callers that keep the weights tiled use
+ * codes duqpp_rotate_quantize would and the product duqpp_mxfp4_gemm would (two kernels on the stream;
+ * with many tokens, or few weights, the first also re-tiles the row-major weights; callers that keep the weights tiled use
  * duqpp_rotq_gemm_tiled and skip that).
- *   workspace  required: at least duqpp_gemm_workspace_bytes(T, N, K, 1) bytes, 256-byte aligned
+ *   workspace  required: at least duqpp_gemm_workspace_bytes(T, N, K, 1) bytes, 256-byte aligned.  What it holds afterwards is
+ *              not part of the result.
  */
 int duqpp_rotq_gemm(const void* x_bf16, int64_t ldx, const float* R, int64_t n_rblocks,
                     const uint8_t* b_codes, const uint8_t* b_scales,
