@@ -373,7 +373,9 @@ enum {
     DUQPP_CONSTRUCT_ONE_32 = 2,
     DUQPP_CONSTRUCT_STEPS = 3,       /* a launch per step */
     DUQPP_CONSTRUCT_IMPATIENT = 8,   /* + one of ONE_*: its workgroups give up at the first exchange, whatever they find there */
-    DUQPP_CONSTRUCT_ALONE = 24       /* likewise, and so do the few that do the search instead: one does it */
+    DUQPP_CONSTRUCT_ALONE = 24,      /* likewise, and so do the few that do the search instead: one does it */
+    DUQPP_CONSTRUCT_LEAVES = 32      /* + IMPATIENT, times t + 1, t <= max_steps: of the few the first gives up after the exchange behind
+                                        step t, the others by what they find there */
 };
 int duqpp_construct_rotation_on(int how, const void* x_bf16, int64_t T, int64_t K, int64_t ldx,
                                 const double* q_steps, int max_steps,

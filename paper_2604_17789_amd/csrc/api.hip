@@ -540,8 +540,10 @@ int duqpp_construct_rotation_on(int how, const void* x_bf16, int64_t T, int64_t 
     int st = validate_rows_K(T, K, ldx, 1);
     if (st != DUQPP_OK) return st;
     if (max_steps < 0 || max_steps > 4096) return DUQPP_ERR_SHAPE;
-    const int form = how & ~DUQPP_CONSTRUCT_ALONE, hurry = how & DUQPP_CONSTRUCT_ALONE;
+    if (how < 0) return DUQPP_ERR_SHAPE;
+    const int hurry = how & DUQPP_CONSTRUCT_ALONE, leaves = how / DUQPP_CONSTRUCT_LEAVES, form = how % DUQPP_CONSTRUCT_LEAVES - hurry;
     if (form < DUQPP_CONSTRUCT_AUTO || form > DUQPP_CONSTRUCT_STEPS) return DUQPP_ERR_SHAPE;
+    if (leaves && (hurry != DUQPP_CONSTRUCT_IMPATIENT || leaves - 1 > max_steps)) return DUQPP_ERR_SHAPE;
     if (hurry && hurry != DUQPP_CONSTRUCT_IMPATIENT && hurry != DUQPP_CONSTRUCT_ALONE) return DUQPP_ERR_SHAPE;
     if (hurry && (form < DUQPP_CONSTRUCT_ONE_16 || form > DUQPP_CONSTRUCT_ONE_32)) return DUQPP_ERR_SHAPE;
     if (!aligned_to(x_bf16, 16) || (ldx % 8) != 0 || !aligned_to(q_steps, 8) || !aligned_to(R_out, 4) ||

@@ -409,6 +409,7 @@ struct SearchPlan {
     uint32_t patience;                   // looks at what the others have published before one gives up; 0: gives up in any case
     int cus;                             // CUs they have
     int few;                             // workgroups of the search behind it
+    int leaves;                          // the exchange after which the first of those gives up, whatever it finds there; -1: none
 };
 
 // What the workgroups tell each other after step t: two words each, the largest magnitude among their rows and the smallest
@@ -942,8 +943,9 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(Con
     __shared__ int goes;
     if (w.given_up[0] == 0ull) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // A workgroup that begins says so, unless the first has given up by then; that goes on alone when those that began have left: they
-    // wait for nobody for longer than it did, and what they wrote must not come after what it writes.
+    // A workgroup that begins says so, unless the first has given up by then, and when it leaves, whether it has given up or done all
+    // steps (it may have seen everybody's words of the last one where the first looked too early).  The first goes on alone when those that
+    // began have left: they wait for nobody for longer than it did, and what they wrote must not come after what it writes.
     unsigned long long* const state = w.colmax + 4 * s.few;
     if (blockIdx.x > 0) {
         if (threadIdx.x == 0) goes = atomicCAS(state + blockIdx.x, kNotBegun, kBegun) == kNotBegun;
@@ -1011,7 +1013,7 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(Con
                     missing = __any(((v | dd) >> 63) != 0);
                 } while (missing && ++looks < s.patience);
                 peak = wave_max(v);
-                d = missing || s.patience == 0 ? -1 : smallest_channel(v, (int)dd, peak);
+                d = missing || s.patience == 0 || (writes && t == s.leaves) ? -1 : smallest_channel(v, (int)dd, peak);
             }
             if (lane == 0) { peak_of_all = peak; channel_of_all = d; }
         }
@@ -1019,12 +1021,7 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(Con
         const unsigned long long peak = peak_of_all;
         const int d = channel_of_all;
         if (d < 0) {                                         // the same for every thread of the workgroup
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            __syncthreads();
-            if (!writes) {
-                if (threadIdx.x == 0) __hip_atomic_store(state + blockIdx.x, kLeft, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-                return;
-            }
+            if (!writes) break;
             if (threadIdx.x == 0) w.given_up[1] = 1ull;
             if (threadIdx.x > 0 && (int)threadIdx.x < workgroups && atomicCAS(state + threadIdx.x, kNotBegun, kLeft) == kBegun)
                 while (__hip_atomic_load(state + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kLeft) __builtin_amdgcn_s_sleep(64);
@@ -1070,8 +1067,12 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void construct_again_kernel(Con
         for (int64_t r = first + lane; r < p.T; r += stride) multiply(w.z + r * 32, true);
         if (writes && wave == kStepWaves - 1 && lane < 32) multiply(product + lane * 32, false);
     }
+    if (!writes) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
-    if (!writes) return;
+    if (!writes) {                                           // the only way out once it has begun
+        if (threadIdx.x == 0) __hip_atomic_store(state + blockIdx.x, kLeft, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
     for (int e = threadIdx.x; e < 1024; e += 64 * kStepWaves) p.R_out[e] = (float)best[e];
     if (threadIdx.x == 0) {
         p.info[0] = (int)block;
@@ -1111,7 +1112,7 @@ bool plan_search(int64_t T, int steps, int form, int cus, SearchPlan& s) {
     const int64_t waves = (T + 63) / 64, room = 31 * ((int64_t)steps + 1) / 5;
     int64_t few = waves < kFewWorkgroups ? waves : kFewWorkgroups;
     few = few < room ? few : room;
-    s = SearchPlan{0, (int)tiles, (int)all, kPatience, cus, (int)few};
+    s = SearchPlan{0, (int)tiles, (int)all, kPatience, cus, (int)few, -1};
     return true;
 }
 
@@ -1161,7 +1162,7 @@ int construct_form(int64_t T, int steps, int form, int cus) {
 hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStream_t stream, bool& runs) {
     const int64_t chunks = (int64_t)p.T * (p.K / 8);
     const int partials = (int)((chunks + 1023) / 1024 < kMaxPartials ? (chunks + 1023) / 1024 : kMaxPartials);
-    const int cus = cus_of(stream), form = construct_form(p.T, p.steps, how & ~DUQPP_CONSTRUCT_ALONE, cus);
+    const int cus = cus_of(stream), form = construct_form(p.T, p.steps, how % DUQPP_CONSTRUCT_IMPATIENT, cus);
     runs = form >= 0;
     if (!runs) return hipSuccess;
     if (form == DUQPP_CONSTRUCT_STEPS) return launch_steps(p, partials, stream);
@@ -1169,6 +1170,7 @@ hipError_t launch_construct_rotation(const ConstructParams& p, int how, hipStrea
     plan_search(p.T, p.steps, form, cus, s);
     s.partials = partials;
     if (how & DUQPP_CONSTRUCT_IMPATIENT) s.patience = 0;
+    s.leaves = how / DUQPP_CONSTRUCT_LEAVES - 1;
     const bool rows = how == DUQPP_CONSTRUCT_AUTO && p.T <= kRowsScanned;
     return launch_search(p, s, form, rows, (how & DUQPP_CONSTRUCT_ALONE) == DUQPP_CONSTRUCT_ALONE ? 0 : kPatienceAgain, stream);
 }

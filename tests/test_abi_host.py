@@ -185,6 +185,14 @@ def test_construct_rotation_host_checks(lib):
     assert c(P, 8, 64, 64, P, 2, P, P, None, None, 0, None) == WORKSPACE
     assert c(P, 8, 64, 64, P, 2, P, P, None, P, 100, None) == WORKSPACE
     assert c(P, 8, 64, 64, P, 2, P, P, None, P + 16, big, None) == ALIGN
+    # the hook: forms and what may be added to them; an exchange at which the first of the few gives up is one of max_steps + 1
+    on = lambda how: lib.duqpp_construct_rotation_on(how, P, 300, 64, 64, P, 2, P, P, None, P + 16, big, None)
+    one16, steps, impatient, alone, leaves = 1, 3, 8, 24, 32
+    for how in (0, one16, steps, one16 + impatient, one16 + alone, one16 + impatient + leaves, one16 + impatient + 3 * leaves):
+        assert on(how) == ALIGN, how                                          # goes on to what is checked behind them
+    for how in (-1, -32, 4, 16, one16 + 16, impatient, steps + impatient, leaves, one16 + leaves, one16 + alone + leaves, impatient + leaves,
+                steps + impatient + leaves, one16 + impatient + 4 * leaves, 2 ** 31 - 1):
+        assert on(how) == SHAPE, how
 
 
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):

@@ -9,7 +9,7 @@ from helpers import to_dev, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 
-AUTO, ONE_16, ONE_32, STEPS, IMPATIENT, ALONE = 0, 1, 2, 3, 8, 24
+AUTO, ONE_16, ONE_32, STEPS, IMPATIENT, ALONE, LEAVES = 0, 1, 2, 3, 8, 24, 32
 ERR_SHAPE = -2
 
 
@@ -70,6 +70,26 @@ def test_every_form_matches_the_oracle(T, K, steps, one):
             assert given_up(torch, o) == [int(how & ALONE > 0), int(how & ALONE == ALONE and few > 1)]
     for how in {ONE_16, ONE_32} - set(one) if T > 4064 or T < 3 else ():
         assert call(torch, duqpp, how, x, qd, buffers(torch, T, steps)) == ERR_SHAPE
+
+
+# two, five and 49 workgroups; the first, one in the middle and the last exchange, without a step the only one
+@pytest.mark.parametrize("T,steps,at", [(300, 0, 0), (65, 1, 1), (300, 4, 0), (300, 4, 2), (300, 4, 4), (8160, 7, 7)])
+def test_the_first_of_the_few_gives_up(T, steps, at):
+    """The first workgroup goes on alone behind one exchange that the others complete: those that have seen the last one leave with all
+    steps done, the others when their patience ends."""
+    import torch
+
+    import paper_2604_17789_amd as duqpp
+    K, how = 64, ONE_32 + IMPATIENT + LEAVES * (at + 1)
+    name = f"gpu-cons-leaves-{T}-{steps}"
+    xb = wl.make_activations(name, T, K, (wl.OutlierSpec(3, 50.0),))
+    q = wl.make_orthogonal_steps(name, steps)
+    print(f"[construct] T={T} steps={steps} the first gives up at {at}", flush=True)
+    o = buffers(torch, T, steps)
+    assert call(torch, duqpp, how, to_dev_bf16(xb, torch), to_dev(q, torch), o) == 0
+    torch.cuda.synchronize()
+    check(o, construction.greedy_rotation(wl.bf16_bits_to_f32(xb), q))
+    assert given_up(torch, o) == [1, 1]
 
 
 @pytest.mark.parametrize("how", [ONE_16, ONE_32, ONE_16 + IMPATIENT, ONE_16 + ALONE, STEPS])
