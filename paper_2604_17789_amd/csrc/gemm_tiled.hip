@@ -651,31 +651,49 @@ hipError_t launch_gemm_tiled(const TiledGemmParams& p, hipStream_t stream) {
     return launch_gemm_tiled_as(p, DUQPP_GEMM_KERNEL_AUTO, stream);
 }
 
+// The tile of a call with row-major weights whose K is not split over the waves.  All of them are 32 channels per wave.
+static const Shape* rows_shape(const TiledGemmParams& p) { return p.T <= 32 ? best_shape(p, streaming_shape) : best_shape(p, small_shape); }
+
 // Row-major weights are multiplied as they are, instead of being read and written tiled first, where re-tiling is a large part of the call:
 // whole K steps and tiles only, rows of scales on 8 bytes, and a row tile's rows within 32 bits of each other.  The kernels that split K
 // over their waves take codes and scales, the tiles only the codes (the launch that rotates tiles the scales, a sixteenth of the bytes).
 // That loses with few row tiles, i.e. few CUs fetching, where all CUs re-tile, and with many tokens, when the weights' way through LDS
-// costs more than re-tiling them once: beyond 512 tokens from the second round of 128 x 128 tiles on.  The whole call, weights in HBM,
-// re-tiled first / as they are, us, K x N:
+// costs more than re-tiling them once.  The whole call, weights in HBM, re-tiled first / as they are, us, K x N:
 //   T = 1    4096 x 1024 5.7 / 6.3, 14336 x 1024 9.7 / 11.2, 4096 x 2048 6.4 / 6.2, 4096 x 4096 9.0 / 6.4, 4096 x 14336 21.8 / 11.9,
 //            14336 x 4096 22.0 / 13.4, 8192 x 28672 63 / 33, 28672 x 8192 67 / 35
 //   T = 64   4096 x 2048 7.2 / 7.4, 4096 x 4096 10.1 / 7.8, 4096 x 14336 22.5 / 14.6, 14336 x 4096 26.8 / 20.4, 28672 x 8192 78 / 47
 //   T = 128  4096 x 1024 6.6 / 7.6, 4096 x 4096 10.5 / 8.8, 14336 x 4096 27.9 / 21.2, 1024 x 16384 10.0 / 7.6, 8192 x 8192 27.6 / 19.0
 //   T = 256  4096 x 1024 8.0 / 8.4, 4096 x 4096 12.2 / 9.9, 14336 x 4096 32.4 / 27.5, 4096 x 14336 27.5 / 19.0, 8192 x 28672 92 / 61
-//   T = 512  4096 x 4096 15.2 / 13.5, 8192 x 8192 37.5 / 32.6, 4096 x 14336 34.8 / 32.0, 8192 x 28672 106 / 102, 2048 x 2048 9.0 / 9.0
-//   beyond   640 4096 x 6144 0.85 of the time, 8192 x 8192 1.05, 4096 x 14336 1.13; 777 4096 x 5120 1.05, 4096 x 6144 0.99;
-//            1024 4096 x 4096 20.8 / 18.7, 14336 x 4096 55.7 / 54.0, 8192 x 8192 54.8 / 56.4
+//   T = 512  4096 x 4096 15.2 / 13.5, 8192 x 8192 37.5 / 32.6, 4096 x 14336 34.8 / 32.0, 2048 x 2048 9.0 / 9.0
+// The codes take so much LDS that one of the 128-channel tiles fits a CU, where two of those on tiled weights do.  While the tiles are one
+// round over the CUs the calls take 0.85 of the time on average (4500 of 65 to 1024 tokens); below 5248 channels with K of 8192 and more
+// they come out level from 300 tokens on, 0.8 to 1.1 (12288 x 4224, T = 320 31.2 / 34.8, T = 512 36.0 / 34.8).  Further rounds
+// lose against the tiles of 256 channels, which need half as many: T = 480 2560 x 10240 20.0 / 22.4, 12288 x 10240 62.1 / 70.4, 6144 x 8320 1.24
+// of the time; T = 384 12288 x 11008 1.15; T = 288 4096 x 14336 29.1 / 28.3, 12288 x 14336 66.5 / 71.0.  They pay
+//   where K is short     T = 416 2048 x 10240 19.0 / 15.7, T = 448 2048 x 8320 0.80 of the time (2560 x 8320, T = 480 1.10); of three rounds and more
+//                        with few steps the starts and stores are the call (256 x 65536, T = 288 19.9 / 24.9; 1536 x 28672 0.88 of the time)
+//   where they are nearly full and there is much to re-tile or K is not long     T = 448 4096 x 14336 35.1 / 30.7, T = 416 12288 x 12288 0.93 of
+//                        the time, 12288 x 11008 1.0, T = 448 1.06, 4096 x 11520 0.90; 8192 x 28672 T = 288 86.0 / 72.5, T = 512 101.5 / 102.7;
+//                        13 / 16 leaves 384 tiles out (12288 x 12288, T = 384 65.5 / 70.2)
+// Of 1440 calls of two rounds and more these lines leave 17 that lose more than 3 % (2560 x 11520, T = 480 1.08) and 88 that would have gained as much
+// (2560 x 12288, T = 512 0.85).
+static bool rows_pay(const TiledGemmParams& p) {
+    const int64_t K = (int64_t)p.GP * 32, tiles = tiles_of(*rows_shape(p), p), rounds = (tiles + kNumCU - 1) / kNumCU;
+    if (p.T <= 128 || rounds == 1) return true;
+    if (p.T > 512) return false;
+    return (rounds == 2 && K <= 2304) || (K >= 1536 && 16 * tiles >= 13 * rounds * kNumCU && (p.N >= 12032 || K <= 4096));
+}
 RowsForm rows_form(const TiledGemmParams& p, const uint8_t* scales) {
-    const int64_t K = (int64_t)p.GP * 32, N = p.N, T = p.T;
+    const int64_t K = (int64_t)p.GP * 32, N = p.N;
     if (N % 128 != 0 || K > (int64_t)1 << 24 || (reinterpret_cast<uintptr_t>(scales) & 7) != 0) return kRowsTiled;
-    if (N < 4096 || N * K < (int64_t)1 << 24 || (T > 512 && (T + 127) / 128 * (N / 128) > kNumCU)) return kRowsTiled;
-    return decode_splits_k(p) ? kRowsAsTheyAre : kRowsScalesTiled;
+    if (N < 4096 || N * K < (int64_t)1 << 24) return kRowsTiled;
+    return decode_splits_k(p) ? kRowsAsTheyAre : rows_pay(p) ? kRowsScalesTiled : kRowsTiled;
 }
 hipError_t launch_gemm_rows(const TiledGemmParams& call, hipStream_t stream) {
     TiledGemmParams p = call;
     p.b_rows = 1;
     if (decode_splits_k(p)) return launch_gemm_decode(p, stream);
-    const Shape* s = p.T <= 32 ? best_shape(p, streaming_shape) : best_shape(p, small_shape);   // all 32 channels per wave
+    const Shape* s = rows_shape(p);
     const hipError_t e = setup_gemm_tiled();
     return e == hipSuccess ? s->run(p, stream) : e;
 }

@@ -13,12 +13,14 @@ pytestmark = pytest.mark.gpu
 AS_THEY_ARE = [(1, 4096, 4096), (16, 4096, 4352), (1, 8192, 2304), (16, 16384, 1024), (17, 4096, 4352), (32, 8192, 2304), (33, 4096, 4096), (64, 4096, 8448),
                (40, 6144, 8192)]
 # the seven tiles of 32 channels per wave (the first five, 67 x 20480 x 2048, 97 x 20480 x 2048); one K step, 9 (steps past the end; the scales of
-# 8 steps and one), 33; tokens that do not fill their tiles, the most tokens at several widths
+# 8 steps and one), 33; tokens that do not fill their tiles, the most tokens at several widths; two rounds of tiles
 CODES_AS_THEY_ARE = [(19, 10240, 2048), (19, 20480, 1024), (34, 8704, 8192), (34, 20480, 1024), (67, 11264, 4096), (67, 20480, 2048), (97, 20480, 2048),
-                     (32, 65536, 256), (130, 8192, 2304), (192, 65536, 256), (333, 4096, 8448), (512, 8192, 2048), (512, 4096, 4352), (640, 6144, 4096),
-                     (1024, 4096, 4096)]
-# another token, row or group than that takes; scales that start elsewhere; fewer weights
-RE_TILED = [(513, 8320, 2048, 0), (1025, 4096, 4096, 0), (641, 6144, 4096, 0), (16, 4128, 4096, 0), (16, 4096, 4128, 0), (16, 4096, 4096, 1),
+                     (32, 65536, 256), (130, 8192, 2304), (128, 65536, 256), (333, 4096, 8448), (512, 8192, 2048), (512, 4096, 4352), (640, 6144, 4096),
+                     (1024, 4096, 4096), (480, 8320, 2304), (320, 14336, 1280), (385, 8320, 4096), (417, 12032, 4352)]
+# another token, row or group than that takes; scales that start elsewhere; fewer weights; a second round of tiles with few of them, or against
+# fewer channels, or a third of few K steps
+RE_TILED = [(513, 8320, 2048, 0), (480, 8320, 2560, 0), (384, 12288, 2560, 0), (288, 14336, 2560, 0), (385, 8320, 4352, 0), (417, 11904, 4352, 0),
+            (192, 65536, 256, 0), (129, 65536, 256, 0), (320, 28672, 1280, 0), (1025, 4096, 4096, 0), (641, 6144, 4096, 0), (16, 4128, 4096, 0), (16, 4096, 4128, 0), (16, 4096, 4096, 1),
             (100, 4096, 4096, 4), (16, 3968, 8192, 0), (16, 4096, 3840, 0)]
 
 
