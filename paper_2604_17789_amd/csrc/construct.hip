@@ -747,10 +747,14 @@ __global__ __launch_bounds__(64 * kRowsWaves) void construct_rows_kernel(Constru
             const int64_t r = r0 + k * (kThreads / 4);
             if ((threadIdx.x & 3) == 0 && r < p.T) {
                 norms[r] = (uint16_t)(bits >> 48);
-                large |= n >= 0.25 * largest * largest;
+                large |= n >= 0.125 * largest * largest;
             }
         }
-        // Where many of the first 1024 rows are not far below the largest magnitude there is no point in looking at the others
+        // Where many of the first 1024 rows are not far below the largest magnitude there is no point in looking at the others: a row of
+        // an eighth of its square counts unless N^2 is more than four times that.  (A quarter let activations pass that have channels at 50
+        // times the others but no massive values, to find out from all rows: 128 steps, us, the search kernel by itself / behind this one with a
+        // quarter / with an eighth: T = 4064 273 / 289 / 280, 16000 564 / 608 / 571.  Asked behind every 1024 rows it costs those that go on 20 us
+        // at 16000.)
         if (first == 0 && p.T > kRowsKept) {
             const int here = __popcll(__ballot(large));
             if (lane == 0 && here) atomicAdd(&many, here);
