@@ -112,3 +112,33 @@ def test_infinities_go_to_the_other_kernels():
                 assert not done(torch, o)
                 results.append((o["info"].tolist(), o["peaks"].view(torch.int64).tolist(), o["R"].view(torch.int32).tolist()))
             assert results[0] == results[1]
+
+
+@pytest.mark.parametrize("captured", [True, False])
+def test_one_workspace_for_few_rows_and_many(captured):
+    """Replays of one graph, and calls with one workspace, whose activations leave few rows, too many, and few again: what the call before left
+    in the workspace does not decide which kernel does the work."""
+    import torch
+
+    import paper_2604_17789_amd as duqpp
+    T, K, steps = 400, 64, 10
+    q = wl.make_orthogonal_steps("gpu-cons-rows-reuse", steps)
+    inputs = [activations(f"gpu-cons-rows-reuse-{i}", T, K, large) for i, large in enumerate((3, 60, 20, 200, 1))]
+    bits = [(xf.view(np.uint32) >> 16).astype(np.uint16) for xf in inputs]
+    x, qd, o = to_dev_bf16(bits[0], torch).clone(), to_dev(q, torch), buffers(torch, T, steps)
+    duqpp.init()
+    if captured:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert call(torch, duqpp, AUTO, x, qd, o) == 0
+    for i in (0, 1, 2, 3, 4, 1, 1, 0, 0):
+        print(f"[construct rows] one workspace, captured={captured}, activations {i}", flush=True)
+        x.copy_(to_dev_bf16(bits[i], torch))
+        if captured:
+            graph.replay()
+        else:
+            assert call(torch, duqpp, AUTO, x, qd, o) == 0
+        torch.cuda.synchronize()
+        check(o, construction.greedy_rotation(wl.bf16_bits_to_f32(bits[i]), q))
+        assert done(torch, o) == (i in (0, 2, 4))
+        torch.ones(1 << 16, device="cuda").sum().item()
