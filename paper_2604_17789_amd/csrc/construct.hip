@@ -15,7 +15,7 @@
 //
 // Every step needs the largest magnitude of the whole state before it, so the steps are a chain of exchanges between all
 // workgroups, unless only a few rows can hold it.  Three forms:
-//   rows that count (construct_rows_kernel) where massive values leave at most 28 rows that can ever hold the largest magnitude, every one
+//   rows that count (construct_rows_kernel) where massive values leave at most 22 rows, beyond 992 rows 28, that can ever hold the largest magnitude, every one
 //                   of sixteen workgroups follows just those, without an exchange.  Tried first by calls of up to 16352 rows.
 //   search kernel   (construct_search_kernel) one launch for all steps: a workgroup keeps its 16 or 32 rows of the state in LDS and
 //                   registers, publishes the largest magnitude among them after every step, waits for everybody's, and goes on.
@@ -33,8 +33,8 @@
 // What a step of the search kernel takes (2048 rows, 130 workgroups, 2.0 us = 4900 cycles): 560 the workgroup's own maximum, 2100
 // the exchange, 500 the maximum of what came, 800 to 1250 the products (768 of them fp64 and its operands' moves, two waves
 // taking turns on a SIMD), 300 their maxima, the rest barriers.  128 steps on one MI355X, us, a launch per step / 16 rows / 32 rows
-// per workgroup (K = 4096): T = 64 554 / 244 / 337, 512 559 / 235 / 329, 1024 565 / 266 / -, 2048 601 / 262 / 325, 4096 705 / - / 333,
-// 8192 1048 / - / 457, 16000 1550 / - / 562.  The call is offline.
+// per workgroup (K = 4096; the kernels of the form alone, none ahead of them): T = 64 554 / 244 / 337, 512 559 / 235 / 329,
+// 1024 565 / 266 / -, 2048 601 / 262 / 325, 4096 705 / - / 333, 8192 1048 / - / 457, 16000 1550 / - / 562.  The call is offline.
 #include <type_traits>
 #include <utility>
 
@@ -679,12 +679,16 @@ __global__ __launch_bounds__(64 * kStepWaves, 2 * PER_CU) void construct_search_
 // the kernel leaves the search to the one behind it.
 // A step is a chain of latencies of one workgroup, about 1700 cycles: 350 until the row is back from LDS, from where every lane needs all
 // of it, 400 for the products that do not depend on the exchanged channel d, 230 for the largest magnitude, 250 for the two that do,
-// 400 for the 32 additions in order and the next matrix column's way to registers.  The whole call, 128 steps on one MI355X, K = 4096,
-// massive values, us, search kernel / this: T = 64 265 / 127, 2048 289 / 131, 8160 370 / 150, 16000 593 / 177.  Without massive
-// values, where it only finds that out: 2048 289 / 295, 16000 593 / 596.
+// 400 for the 32 additions in order and the next matrix column's way to registers.  128 steps on one MI355X, K = 4096, us, search kernel by itself /
+// behind this: with massive values T = 64 250 / 102, 2048 266 / 106, 8160 347 / 124, 16000 563 / 151; without, where it only finds that out,
+// 64 250 / 255, 2048 264 / 270, 8160 347 / 350, 16000 563 / 571.  (Calls from Python, which allocate: 2048 289 / 131 and 289 / 295.)
 constexpr int kRowsWaves = 8;
 constexpr int kRowsOnce = 2 * (kRowsWaves - 1);          // the first wave has two rows of the product, the others two rows each,
 constexpr int kRowsKept = 2 * kRowsOnce;                 // and two more each where there are more
+// So many pay: 1 to 6 rows take 102 to 119 us for 128 steps of 2048 rows, 7 to 14 162 to 185, 15 217, 20 228, 24 261, 28 272, the search kernel 267
+// (8160 rows: 28 289, search 347); up to 992 rows, which the search kernel looks at in one go, 20 take 225, 24 257, 28 269, that 241 to 252.
+constexpr int kRowsFew = 22;
+constexpr int64_t kRowsFewTo = 992;
 constexpr int kRowsBring = 4;                            // the last waves bring the matrices, whether they have rows or not
 constexpr int kRowsWorkgroups = kBlock / 2;              // two rows of the product each
 constexpr int64_t kRowsScanned = 16384;                  // rows whose norms fit beside each other
@@ -776,13 +780,13 @@ __global__ __launch_bounds__(64 * kRowsWaves) void construct_rows_kernel(Constru
     if (!orthogonal) return;                                 // (also with few rows: nothing becomes infinite below)
     const unsigned long long least = (unsigned long long)__double_as_longlong(__longlong_as_double((long long)top) * (0.95 / 32.0)) >> 48;
     for (int64_t r = threadIdx.x; r < p.T; r += kThreads)
-        if (p.T <= kRowsKept || norms[r] >= least) {         // (upper words: less is less of the whole, equal stays)
+        if (norms[r] >= least) {                             // (upper words: less is less of the whole, equal stays)
             const int i = atomicAdd(&count, 1);
             if (i < kRowsKept) kept_rows[i] = (int)r;
         }
     __syncthreads();
     const int kept = __builtin_amdgcn_readfirstlane(count);
-    if (kept > kRowsKept) return;
+    if (kept > (p.T <= kRowsFewTo ? kRowsFew : kRowsKept)) return;
     for (int e = threadIdx.x; e < 2 * kRowsLds; e += kThreads) z[e] = 0.0;   // rows that nobody has
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) *w.done = 1ull;
@@ -849,6 +853,10 @@ __global__ __launch_bounds__(64 * kRowsWaves) void construct_rows_kernel(Constru
         for (int r = 0; r < 32; ++r) m[r] = mt[place + r * 32 + c];
     };
     column(m1);
+    // Where the loop's code lies among the 32 bytes fetched at once is 1 to 5 % of the call, whatever ends ahead of it: of the eight places
+    // (1 / 7 / 14 rows that count, 64 rows, us: 103 / 160 / 179 here, 103 / 159 / 182, 104 / 164 / 181, 105 / 157 / 181, 105 / 161 / 183,
+    // 105 / 164 / 182, 107 / 160 / 181, 108 / 167 / 184)
+    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (int t = 0;; ++t) {
         double* const z0 = mine + (t & 1) * kRowsLds;
         double* const z1 = z0 + 2 * kPitch;
