@@ -118,8 +118,8 @@ int duqpp_mxfp4_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
 /*
  * Fused form of the online path: Y = Q(X . R^) . Q(W^) in one call, producing exactly the
  * codes duqpp_rotate_quantize would and the product duqpp_mxfp4_gemm would (two kernels on the stream;
- * with many tokens, or few weights, the first also re-tiles the row-major weights; callers that keep the weights tiled use
- * duqpp_rotq_gemm_tiled and skip that).
+ * with many tokens, few weights, or outputs of several rounds of tiles the first also re-tiles the row-major weights; callers that keep
+ * the weights tiled use duqpp_rotq_gemm_tiled and skip that).
  *   workspace  required: at least duqpp_gemm_workspace_bytes(T, N, K, 1) bytes, 256-byte aligned.  What it holds afterwards is
  *              not part of the result.
  */
@@ -349,8 +349,8 @@ int duqpp_fold_smoothing(const float* R, int64_t n_rblocks, const float* lambda,
  *   peaks      out  nullable, [max_steps + 1] fp64 on the device: peak |value| after 0, 1, ... steps
  *   workspace       at least duqpp_construct_rotation_workspace_bytes(T, max_steps) bytes, 256-byte aligned
  * Enqueues up to max_steps + 4 kernels on the stream.  Errors as for the other calls.
- * Where massive values leave only a few tokens that can ever hold the largest magnitude (up to 28, of up to 16352), only those are followed: 128
- * steps on one MI355X, T = 2048 / 16000: 0.13 / 0.18 ms.
+ * Where massive values leave only a few tokens that can ever hold the largest magnitude (up to 22 of 992, up to 28 of 16352), only those are
+ * followed: 128 steps on one MI355X, T = 2048 / 16000: 0.13 / 0.18 ms.  Other activations take up to 2.5 % longer for finding out.
  * Otherwise, up to some thousand tokens, all steps are one kernel, whose workgroups exchange their maxima and are therefore to run at the
  * same time.  Where they do not, because other work holds the device (a second construction on another stream, for one), they give up
  * after 1 to 2 ms and fewer workgroups do the search, at last one: the result is the same, the time is longer (T = 2048 / 16000: 0.30 /

@@ -437,7 +437,8 @@ __global__ __launch_bounds__(64 * W, OCC) void gemm_tiled_kernel(TiledGemmParams
     gemm_tile<OUT_BF16, MT, NT, D, W, OCC>(p, tile_m * MT, tile_n, (LdsBytes)lds, (LdsBytes)lds);
 }
 
-// The same with row-major weights.
+// The same with row-major weights.  (Renumbered in rounds of OCC workgroups per CU, too, although of four waves one fits: in rounds of one per CU
+// it comes out level, 0.999 of the time over 4400 pairs of tile and product.)
 template <bool OUT_BF16, int MT, int NT, int D, int W, int OCC>
 __global__ __launch_bounds__(64 * W, OCC) void gemm_rows_kernel(TiledGemmParams p) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -514,8 +515,9 @@ hipError_t run(const TiledGemmParams& p, hipStream_t stream) {
                       : launch(gemm_tiled_kernel<false, MT, NT, D, W, OCC>, grid, block, TL::kLdsBytes, stream, p);
 }
 
-// The tile shapes.  Two workgroups of the four-wave tiles fit a CU, but for the two largest (one): while one of them
-// waits for its first operands or stores its tile, the other has the matrix cores.  one / two: microseconds per K step of
+// The tile shapes.  Two workgroups of the four-wave tiles fit a CU, but for the two largest (one; and one of those on row-major codes, for
+// which these figures are not made, see rows_pay): while one of them waits for its first operands or stores its tile, the other has the
+// matrix cores.  one / two: microseconds per K step of
 // 256 while a CU holds one or two tiles; fixed: per round of tiles, what the pipeline's start and the store take.  Fitted
 // to the time of every shape at 400 products (33 to 8192 tokens, seven linears of the 8B and 70B models and four generic
 // ones, weights in the last-level cache and in HBM).  Over 170 products the shape chosen takes on average 1.3 % longer than

@@ -602,6 +602,8 @@ hipError_t launch_rotq_and_tile(const RotqParams& p, const LayoutParams& w, hipS
     // 8192 of them would share the units (us, 8192 of one wave / workgroups of four / the ring kernel: 16 x 4096 x 28672
     // 40.1 / 36.3 / 39.4, 512 x 4096 x 28672 63.2 / 59.6 / 60.5, 256 x 8192 x 28672 87.5 / 79.7 / 81.2, 64 x 28672 x 8192 83.6 / 78.6 / 79.3;
     // with a wave per unit in all of them: 512 x 4096 x 14336 34.4 / 33.5 / 33.8, 64 x 4096 x 4096 10.9 / 11.5 / 11.7).
+    // Both lines are from calls that re-tiled codes and scales.  Most of those named here now leave the codes, or both, as they are (rows_form);
+    // with scales alone the units are an eighth, and such calls mostly lie far below the second line.
     const int64_t units = tile_units(w), rotating = (int64_t)p.GP * p.ntiles;
     if (rotating <= kFewWavesPacked) {
         if (units <= kTileWorkgroups)
