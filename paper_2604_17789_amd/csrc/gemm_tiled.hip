@@ -667,6 +667,10 @@ static const Shape* rows_shape(const TiledGemmParams& p) { return p.T <= 32 ? be
 //   T = 128  4096 x 1024 6.6 / 7.6, 4096 x 4096 10.5 / 8.8, 14336 x 4096 27.9 / 21.2, 1024 x 16384 10.0 / 7.6, 8192 x 8192 27.6 / 19.0
 //   T = 256  4096 x 1024 8.0 / 8.4, 4096 x 4096 12.2 / 9.9, 14336 x 4096 32.4 / 27.5, 4096 x 14336 27.5 / 19.0, 8192 x 28672 92 / 61
 //   T = 512  4096 x 4096 15.2 / 13.5, 8192 x 8192 37.5 / 32.6, 4096 x 14336 34.8 / 32.0, 2048 x 2048 9.0 / 9.0
+// The lines at 4096 channels and 16 M weights are where single calls came out even (4096 x 2048 and 4096 x 1024 above).  In graphs of calls with
+// other weights each it gains below them as well, up to 256 tokens of 2048 channels and more or 4 M weights by 10 to 35 %: 4096 x 2048 T = 1 7.9 / 6.5,
+// T = 256 10.4 / 9.1, T = 512 14.6 / 10.8; 2048 x 4096 T = 256 9.9 / 7.9; 4096 x 3072 T = 64 9.9 / 7.8; 8192 x 2048 T = 512 20.3 / 18.5; but 14336 x 2048 T = 256
+// 23.4 / 23.7, T = 512 27.0 / 29.7, 28672 x 2048 T = 512 47.2 / 49.4, 8192 x 3072 T = 512 22.9 / 24.6.  They stand as they are.
 // The codes take so much LDS that one of the 128-channel tiles fits a CU, where two of those on tiled weights do.  While the tiles are one
 // round over the CUs the calls take 0.85 of the time on average (4500 of 65 to 1024 tokens); below 5248 channels with K of 8192 and more
 // they come out level from 300 tokens on, 0.8 to 1.1 (12288 x 4224, T = 320 31.2 / 34.8, T = 512 36.0 / 34.8).  Further rounds
